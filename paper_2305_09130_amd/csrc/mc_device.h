@@ -632,6 +632,16 @@ __device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
 // Records the first error of a query (later ones keep it).
 __device__ __forceinline__ void set_error(Ctrl* ctrl, unsigned int e) { atomicCAS(&ctrl->error, 0u, e); }
 
+// The host's stop request, as read by the workgroup that takes item `taken` of a queue.  The
+// word is in host memory and reads of it serialise on the link: one read per partition cost
+// the 644-partition search of matmul32_cu4_s1123 52 us of 684 (the 530-partition one of
+// reduction_g256_cu4_s1123 38 of 263).  One item in 64 reads it, and the rest see the error
+// flag that it sets.
+__device__ __forceinline__ uint32_t abort_asked(const unsigned int* abort, uint32_t taken) {
+  if (!abort || (taken & 63u)) return 0u;
+  return __hip_atomic_load(abort, __ATOMIC_RELAXED, kScopeSystem);
+}
+
 // splitmix64 (Steele, Lea, Flood 2014)
 __device__ __forceinline__ unsigned long long splitmix64(unsigned long long z) {
   z += 0x9E3779B97F4A7C15ull;

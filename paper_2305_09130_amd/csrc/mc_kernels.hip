@@ -1498,7 +1498,7 @@ __global__ __launch_bounds__(BLOCK, (HET && BLOCK == 512) ? 4 : 1) void k_supers
       // it concurrently, and every wave must take the same branch around the barriers
       // of the exploration
       bool stop = __hip_atomic_load(&sh.md.ctrl->error, __ATOMIC_RELAXED, kScopeAgent) != 0u;
-      if (!stop && a.abort && __hip_atomic_load(a.abort, __ATOMIC_RELAXED, kScopeSystem) != 0u) {
+      if (!stop && abort_asked(a.abort, part)) {
         set_error(sh.md.ctrl, kDevErrAbort);
         stop = true;
       }
