@@ -126,25 +126,31 @@ typedef struct mc_desc {
 /* ---- options ------------------------------------------------------------------- */
 #define MC_ENGINE_SUPERSTEP 0u /* persistent kernel, one configuration's subgraph per
                                   workgroup, zero-time closures and lock-step runs
-                                  expanded in one super-step */
+                                  expanded in one super-step; on units alike with one-word
+                                  keys, pieces of a configuration's rounds per workgroup,
+                                  each piece's visited states in the workgroup's LDS */
 #define MC_ENGINE_LEVEL 1u     /* plain level-synchronous BFS, one launch per level */
 
 typedef struct mc_opts {
     uint32_t engine;         /* MC_ENGINE_* */
     uint32_t block;          /* threads per workgroup: 256, 512 or 1024 (0 = automatic:
-                                512 when the query has fewer than 256 partitions, whose
-                                critical chains of inserts then decide the launch time,
-                                or when the units have unequal speeds; else 256) */
+                                256 where pieces of rounds are explored; else 512 when the
+                                query has fewer than 256 partitions, whose critical chains
+                                of inserts then decide the launch time, or when the units
+                                have unequal speeds; else 256) */
     uint32_t log2_slots;     /* visited-set capacity 2^log2_slots (0 = from load_factor) */
     float load_factor;       /* target states/slots when sizing (0 = automatic: at most
                                 0.375 after rounding the slots up to a power of two, or
                                 0.5 where that passes 2^31 slots) */
-    uint32_t grid;           /* persistent workgroups (0 = automatic) */
+    uint32_t grid;           /* persistent workgroups (0 = automatic; at most 1024 where
+                                pieces of rounds are explored) */
     uint32_t batch_items;    /* super-step engine: states generated from one frontier state
-                                before waiting for the visited set (0 = 2 x lanes) */
+                                before waiting for the visited set (0 = 2 x lanes); unused
+                                where pieces of rounds are explored */
     uint32_t lane_items;     /* keys each thread inserts per round trip: 1 or 2
                                 (else automatic: 2 for keys of up to 128 bits,
-                                1 for wider keys) */
+                                1 for wider keys); unused where pieces of rounds are
+                                explored */
     uint32_t part_states;    /* super-step engine: target states per partition when a
                                 configuration's subgraph is cut into blocks of whole
                                 rounds and its long lock-step runs into run slices (a
@@ -165,15 +171,18 @@ typedef struct mc_stats {
     uint64_t dups;           /* inserts that found the state present (engine-specific) */
     uint64_t probes;         /* hash-slot probes (engine-specific) */
     uint64_t launches;       /* kernel launches of the exploration */
-    uint64_t explore_ns;     /* GPU time of the exploration kernels (HIP events) */
+    uint64_t explore_ns;     /* GPU time of the exploration kernels (HIP events; where pieces
+                                of rounds are explored, from the first workgroup's start to
+                                the last one's end on the device clock) */
     uint64_t total_ns;       /* host wall time of the query call */
     uint64_t clear_ns;       /* GPU time clearing the visited set */
     uint64_t engine_ns;      /* GPU time of the exploration engine's own launch(es),
-                                without the seed and result copies (HIP events) */
-    uint64_t supersteps;     /* super-steps of the persistent engine */
+                                without the seed and result copies (as explore_ns) */
+    uint64_t supersteps;     /* super-steps of the persistent engine (rounds of its pieces) */
     uint64_t batches;        /* insert batches of the persistent engine */
     uint64_t max_probe;      /* longest probe sequence of one insert */
-    uint64_t critical_ns;    /* longest single-partition exploration (device clock) */
+    uint64_t critical_ns;    /* longest exploration of a single partition, or of a piece of
+                                one (device clock) */
     uint64_t critical_cfg;   /* the configuration of that partition */
     uint64_t parts;          /* partitions of the persistent launch (configurations, or
                                 blocks of whole rounds of them) */

@@ -113,13 +113,18 @@ mc_opts default_opts(const mc_opts* o) {
   return r;
 }
 
-// Partitions of a single-model query, largest expected block first.
-std::vector<Part> model_parts(const ModelHost& mh, const mc_opts& o) {
+// Partitions of a single-model query.
+std::vector<PartPlan> model_plan(const ModelHost& mh, const mc_opts& o) {
   const uint64_t target = o.part_states == 0xFFFFFFFFu ? 0u
                           : o.part_states              ? o.part_states
                                                        : auto_part_states(mh.states, mh.m);
   std::vector<PartPlan> plan;
   plan_parts(mh, target, &plan);
+  return plan;
+}
+
+// ... largest expected block first.
+std::vector<Part> sorted_parts(std::vector<PartPlan> plan) {
   std::stable_sort(plan.begin(), plan.end(),
                    [](const PartPlan& a, const PartPlan& b) { return a.states > b.states; });
   std::vector<Part> parts(plan.size());
@@ -146,6 +151,8 @@ hipError_t ev_ms(float* ms, hipEvent_t a, hipEvent_t b) {
 }
 
 }  // namespace
+
+constexpr uint32_t kRoundsGrid = 1024;  // four workgroups of 33 KiB LDS on each of 256 CUs
 
 enum { kQueryNone = 0, kQueryMin = 1, kQueryCheck = 2 };
 
@@ -208,6 +215,15 @@ struct mc_model {
   uint32_t resident_T = 0;
   std::vector<Part> parts_host;  // the load's partition plan (run_resume overwrites parts)
   bool parts_resumed = false;
+  // the round engine explores this model (units alike, one-word keys, room for a slot per
+  // generated state): its plan, in the place of `parts_host`; the terminals' slots (in the
+  // region of the seeds, which it does not use); whether the last query ran on it
+  bool rounds = false;
+  RoundPlan rplan;
+  uint32_t* tslot = nullptr;
+  bool on_rounds = false;
+  RoundRecord* records = nullptr;  // pinned, kRoundsGrid entries (pooled handles)
+  unsigned char* stage_parts = nullptr;  // pinned staging of a plan, or null
   // unpooled binding (the static scratch): host staging in ordinary memory, no events
   bool pooled = true;
   std::vector<unsigned char> host_stage;
@@ -348,15 +364,181 @@ int level_loop(mc_model* h, const QueryArgs& q, uint64_t* launches) {
 int finish_query(mc_model* h, std::chrono::steady_clock::time_point t0, bool cleared,
                  uint64_t launches, mc_stats* st);
 
+// The statistics of the query whose counters h->hctrl holds.
+void fill_stats(const mc_model* h, std::chrono::steady_clock::time_point t0, uint64_t launches,
+                uint64_t explore_ns, uint64_t engine_ns, uint64_t clear_ns, mc_stats* st) {
+  if (!st) return;
+  std::memset(st, 0, sizeof(*st));
+  st->states = h->hctrl->states;
+  st->levels = h->hctrl->max_depth + 1;
+  st->terminals = h->hctrl->terminals;
+  st->edges = h->hctrl->edges;
+  st->dups = h->hctrl->dups;
+  st->probes = h->hctrl->probes;
+  st->launches = launches;
+  st->explore_ns = explore_ns;
+  st->clear_ns = clear_ns;
+  st->engine_ns = engine_ns;
+  st->supersteps = h->hctrl->supersteps;
+  st->batches = h->hctrl->chunks;
+  st->max_probe = h->hctrl->max_probe;
+  st->critical_ns = h->hctrl->crit_ticks * 10ull;  // 100 MHz device clock
+  st->critical_cfg = h->hctrl->crit_part;
+  st->parts = h->opts.engine == MC_ENGINE_SUPERSTEP ? h->q_parts : 0u;
+  st->cas_fail = cas_fails(st->probes, st->states, st->dups);
+  st->total_ns = (uint64_t)std::chrono::duration_cast<std::chrono::nanoseconds>(
+                     std::chrono::steady_clock::now() - t0)
+                     .count();
+}
+
+// A query's counters from the workgroups' records, added to what they hold.
+void add_records(Ctrl* c, const RoundRecord* rec, uint32_t n, uint64_t* ticks) {
+  unsigned long long first = ~0ull, last = 0;
+  for (uint32_t i = 0; i < n; ++i) {
+    const RoundRecord& r = rec[i];
+    c->states += r.states;
+    c->terminals += r.terms;
+    c->edges += r.edges;
+    c->dups += r.dups;
+    c->probes += r.probes;
+    c->chunks += r.chunks;
+    c->supersteps += r.rounds;
+    c->max_depth = std::max<unsigned long long>(c->max_depth, r.depth);
+    c->max_probe = std::max(c->max_probe, r.max_probe);
+    if (r.crit > c->crit_ticks) {
+      c->crit_ticks = r.crit;
+      c->crit_part = r.crit_cfg;
+    }
+    if (!c->error) c->error = r.error;
+    if (r.terms) c->violated = 1u;
+    first = std::min(first, r.t_first);
+    last = std::max(last, r.t_last);
+  }
+  *ticks = last > first ? last - first : 0;
+}
+
+// A query on the round engine.  resume: the states with clock <= h->resident_T are in the
+// set, and the counters and clocks run on.
+int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool resume) {
+  const auto t0 = std::chrono::steady_clock::now();
+  hipStream_t s = h->stream;
+  h->trace_ready = false;
+  h->last = kQueryNone;
+  h->swarm_members = 0;  // the visited set overwrites a swarm's records
+  h->q_slots = h->plan.slots;
+  if (!resume) h->resident = false;
+  HIPCHK(join_side(h));
+  // nothing is cleared before or after it: a slot is read only where this exploration wrote
+  h->behind_lo = h->behind_hi = 0;
+  h->dirty_in = std::max<uint64_t>(h->dirty_in,
+                                   std::min<uint64_t>(8ull * h->rplan.used, h->max_need));
+  const RoundPlan* plan = &h->rplan;
+  RoundPlan own;
+  uint64_t states = h->mh.states;
+  uint32_t piece = auto_piece(states);  // of the load's plan, as uploaded
+  if (prune && T < h->mh.max_clock) {
+    trim_rounds(h->mh, h->rplan, resume ? h->resident_T + 1ull : 0, T, &own);
+    plan = &own;
+    states = count_le_bound(h->mh, T);
+    if (resume) states -= std::min(states, count_le_bound(h->mh, h->resident_T));
+    piece = auto_piece(states);
+  }
+  uint64_t n_pieces = 0;
+  if (plan == &own) {
+    n_pieces = number_pieces(&own, piece);
+    const size_t bytes = sizeof(RoundPart) * own.parts.size();
+    const void* src = own.parts.data();
+    if (h->stage_parts) src = std::memcpy(h->stage_parts, src, bytes);
+    if (bytes) HIPCHK(hipMemcpyAsync(h->parts, src, bytes, hipMemcpyHostToDevice, s));
+    h->parts_resumed = true;
+  } else {
+    n_pieces = number_pieces(&h->rplan, piece);
+    if (h->parts_resumed) {
+      const size_t bytes = sizeof(RoundPart) * h->rplan.parts.size();
+      const void* src = h->rplan.parts.data();
+      if (h->stage_parts) src = std::memcpy(h->stage_parts, src, bytes);
+      HIPCHK(hipMemcpyAsync(h->parts, src, bytes, hipMemcpyHostToDevice, s));
+      h->parts_resumed = false;
+    }
+  }
+  h->q_parts = (uint32_t)plan->parts.size();
+  ModelDev& md = *h->hmd;
+  std::memset(&md, 0, sizeof(md));
+  md.ctrl = h->ctrl;
+  md.tc = h->tc;
+  md.cfgs = h->cfgs;
+  md.table = h->table;
+  md.mask = h->plan.slots - 1;
+  md.L = h->mh.layout;
+  md.n_cfg = h->mh.n_cfg;
+  md.prune = prune ? 1u : 0u;
+  md.T = T;
+  md.max_clock = h->mh.max_clock;
+  md.n_parts = h->q_parts;
+  md.bb = bb ? 1u : 0u;
+  md.hkeep = h->opts.test_hash_bits;
+  md.refloor = resume ? h->resident_T + 1u : 0u;
+  md.tslot = h->tslot;
+  const uint32_t grid = std::min<uint32_t>(
+      {h->opts.grid ? h->opts.grid : kRoundsGrid, kRoundsGrid, (uint32_t)std::max<uint64_t>(n_pieces, 1)});
+  if (!resume)  // the host's copies run on in a continued exploration
+    for (uint32_t c = 0; c < h->mh.n_cfg; ++c) h->tc_host[c] = kNoClock;
+  HIPCHK(launch_rounds_begin(s, md, h->dmd, h->head));
+  uint64_t launches = 1;
+  if (n_pieces) {
+    RoundQueue q;
+    q.models = h->dmd;
+    q.parts = reinterpret_cast<const RoundPart*>(h->parts);
+    q.n_parts = h->q_parts;
+    q.n_pieces = (uint32_t)n_pieces;
+    q.piece = piece;
+    q.log2_set = set_log2(piece);
+    q.reverse = bb ? 1u : 0u;
+    q.head = h->head;
+    q.abort = h->habort;
+    q.records = h->records;
+    q.host_tc = h->records ? h->tc_host : nullptr;
+    HIPCHK(launch_rounds(s, grid, h->opts.block, q, h->mh.general));
+    ++launches;
+  }
+  h->on_rounds = true;
+  Ctrl* ctrl = h->hctrl;
+  uint64_t ticks = 0;
+  if (h->records) {
+    HIPCHK(hipStreamSynchronize(s));
+    if (!resume) {
+      std::memset(ctrl, 0, sizeof(Ctrl));
+      ctrl->states = ctrl->probes = 1ull + h->mh.n_cfg;
+      ctrl->edges = h->mh.n_cfg;
+      ctrl->max_depth = 1;
+      ctrl->max_probe = 1;
+    }
+    ctrl->error = ctrl->violated = 0u;
+    if (n_pieces) add_records(ctrl, h->records, grid, &ticks);
+  } else {
+    HIPCHK(hipMemcpyAsync(ctrl, h->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(h->tc_host, h->tc, 4ull * h->mh.n_cfg, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+  }
+  const int derr = dev_error_code(ctrl->error);
+  if (derr == MC_E_ABORTED && h->habort) __atomic_store_n(h->habort, 0u, __ATOMIC_RELEASE);
+  if (derr != MC_OK) return derr;
+  fill_stats(h, t0, launches, ticks * 10ull, ticks * 10ull, 0, st);
+  return MC_OK;
+}
+
 // prune: drop states with clock > T.  bb (super-step engine): branch and bound, the
 // threshold falls to the least terminal clock found so far and partitions are taken
 // smallest first.
 int run_query(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb = false,
               uint32_t T_size = 0) {
+  if (h->rounds && h->opts.engine == MC_ENGINE_SUPERSTEP)
+    return run_rounds(h, prune, T, st, bb, false);
   const auto t0 = std::chrono::steady_clock::now();
   hipStream_t s = h->stream;
   h->trace_ready = false;
   h->last = kQueryNone;
+  h->on_rounds = false;
   h->swarm_members = 0;  // the visited set overwrites a swarm's records
   // a check(T) inserts only the states with clock <= T: its visited set is the prefix of
   // the table sized for their number at the same load factor
@@ -395,7 +577,7 @@ int run_query(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb = false
       h->parts_resumed = true;  // the load's plan goes back before the next other query
     }
   }
-  if (!own_plan && h->parts_resumed) {
+  if (!own_plan && h->parts_resumed && !h->rounds) {
     HIPCHK(hipMemcpyAsync(h->parts, h->parts_host.data(), sizeof(Part) * h->parts_host.size(),
                           hipMemcpyHostToDevice, s));
     h->parts_resumed = false;
@@ -425,6 +607,7 @@ int run_query(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb = false
     md.pstate = nullptr;
     md.hkeep = h->opts.test_hash_bits;
     md.refloor = 0u;
+    md.tslot = nullptr;
     HIPCHK(hipMemcpyAsync(h->dmd, h->hmd, sizeof(ModelDev), hipMemcpyHostToDevice, s));
     HIPCHK(launch_reset_models(s, h->dmd, 1, h->head, 1));
     HIPCHK(ev_record(h->ev[2], s));
@@ -481,29 +664,8 @@ int finish_query(mc_model* h, std::chrono::steady_clock::time_point t0, bool cle
   HIPCHK(ev_ms(&ms_explore, h->ev[2], h->ev[3]));
   HIPCHK(ev_ms(&ms_engine, h->ev[4], h->ev[5]));
   if (cleared) HIPCHK(ev_ms(&ms_clear, h->ev[0], h->ev[1]));
-  if (st) {
-    std::memset(st, 0, sizeof(*st));
-    st->states = h->hctrl->states;
-    st->levels = h->hctrl->max_depth + 1;
-    st->terminals = h->hctrl->terminals;
-    st->edges = h->hctrl->edges;
-    st->dups = h->hctrl->dups;
-    st->probes = h->hctrl->probes;
-    st->launches = launches;
-    st->explore_ns = (uint64_t)(ms_explore * 1e6);
-    st->clear_ns = (uint64_t)(ms_clear * 1e6);
-    st->engine_ns = (uint64_t)(ms_engine * 1e6);
-    st->supersteps = h->hctrl->supersteps;
-    st->batches = h->hctrl->chunks;
-    st->max_probe = h->hctrl->max_probe;
-    st->critical_ns = h->hctrl->crit_ticks * 10ull;  // 100 MHz device clock
-    st->critical_cfg = h->hctrl->crit_part;
-    st->parts = h->opts.engine == MC_ENGINE_SUPERSTEP ? h->q_parts : 0u;
-    st->cas_fail = cas_fails(st->probes, st->states, st->dups);
-    st->total_ns = (uint64_t)std::chrono::duration_cast<std::chrono::nanoseconds>(
-                       std::chrono::steady_clock::now() - t0)
-                       .count();
-  }
+  fill_stats(h, t0, launches, (uint64_t)(ms_explore * 1e6), (uint64_t)(ms_engine * 1e6),
+             (uint64_t)(ms_clear * 1e6), st);
   return MC_OK;
 }
 
@@ -513,6 +675,12 @@ int finish_query(mc_model* h, std::chrono::steady_clock::time_point t0, bool cle
 // holding resident_T.  Counters and clocks accumulate, so the result is that of
 // check(T).  Super-step engine and resumable models only (the caller checks).
 int run_resume(mc_model* h, uint32_t T, mc_stats* st) {
+  if (h->rounds) {
+    const int rc = run_rounds(h, true, T, st, false, true);
+    if (rc == MC_OK) h->resident_T = T;
+    else h->resident = false;
+    return rc;
+  }
   const auto t0 = std::chrono::steady_clock::now();
   hipStream_t s = h->stream;
   h->trace_ready = false;
@@ -580,8 +748,13 @@ int trace_w(mc_model* h, uint32_t cfg, uint32_t clock) {
   fields[kFClock] = clock;
   uint64_t words[4];
   encode_key_host(h->mh.layout, fields, words);
-  const QueryArgs q = make_args(h, false, 0);
-  HIPCHK(launch_find<W>(s, q, reinterpret_cast<const unsigned long long*>(words)));
+  QueryArgs q = make_args(h, false, 0);
+  if (h->on_rounds) {
+    q.tslot = h->tslot;
+    q.target = cfg;
+  } else {
+    HIPCHK(launch_find<W>(s, q, reinterpret_cast<const unsigned long long*>(words)));
+  }
   HIPCHK(launch_chase<W>(s, q, h->trace_buf, (uint32_t)h->plan.trace_cap));
   HIPCHK(hipMemcpyAsync(h->hctrl, h->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
@@ -676,7 +849,7 @@ int mc_workspace_bytes(const mc_desc* d, const mc_opts* o, size_t* bytes) {
     if (rc) return rc;
     WsPlan p;
     const mc_opts oo = default_opts(o);
-    rc = plan_ws(mh, oo, model_parts(mh, oo).size(), &p);
+    rc = plan_ws(mh, oo, model_plan(mh, oo).size(), &p);
     if (rc) return rc;
     *bytes = p.total;
     return MC_OK;
@@ -711,25 +884,52 @@ struct Loaded {
   mc_opts opts{};
   WsPlan plan;
   std::vector<Part> parts;
+  RoundPlan rounds;
 };
+
+// The round engine's form of the load's plan, largest partitions first; empty where that
+// engine cannot explore the model or the visited set has no slot for every generated state
+// (a set given smaller than the model's states has to fill up and say so).
+void plan_rounds(const ModelHost& mh, const mc_opts& o, const std::vector<PartPlan>& plan,
+                 uint64_t slots, RoundPlan* out) {
+  if (!rounds_model(mh)) return;
+  RoundPlan p;
+  round_plan(mh, 0, plan, &p);
+  if (p.used > slots) return;
+  std::vector<uint32_t> order(p.parts.size());
+  for (uint32_t i = 0; i < (uint32_t)order.size(); ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](uint32_t a, uint32_t b) { return p.items[a] > p.items[b]; });
+  out->used = p.used;
+  for (const uint32_t i : order) {
+    out->parts.push_back(p.parts[i]);
+    out->items.push_back(p.items[i]);
+    out->end_group.push_back(p.end_group[i]);
+  }
+  number_pieces(out, auto_piece(mh.states));
+}
 
 int prepare_load(const mc_desc* d, const mc_opts& opts_in, size_t ws_bytes, Loaded* L) {
   std::string err;
   int rc = build_model(d, &L->mh, &err);
   if (rc) return rc;
   L->opts = opts_in;
-  L->parts = model_parts(L->mh, L->opts);
-  rc = plan_ws(L->mh, L->opts, L->parts.size(), &L->plan);
+  const std::vector<PartPlan> plan = model_plan(L->mh, L->opts);
+  rc = plan_ws(L->mh, L->opts, plan.size(), &L->plan);
   if (rc) return rc;
   if (ws_bytes < L->plan.total) return MC_E_NOMEM;
+  plan_rounds(L->mh, L->opts, plan, L->plan.slots, &L->rounds);
+  if (L->rounds.parts.empty()) L->parts = sorted_parts(plan);
   // automatic workgroup size: with fewer partitions than a wide launch has workgroups,
   // each runs nearly alone on its compute unit and its chain of insert round trips is
   // the launch time, which 512 threads shorten; with many, 256 keeps more of them
   // resident
   // units of unequal speed: 512 (their chain listing is block-wide; on the 1.4M-state
   // workload the launch took 0.70 ms against 0.95 with 256 and 0.83 with 1024)
-  if (!L->opts.block)
-    L->opts.block = (L->mh.hetero || L->parts.size() < kWideParts) ? 512u : 256u;
+  if (!L->opts.block) {
+    if (!L->rounds.parts.empty()) L->opts.block = 256u;
+    else L->opts.block = (L->mh.hetero || L->parts.size() < kWideParts) ? 512u : 256u;
+  }
   return MC_OK;
 }
 
@@ -745,6 +945,9 @@ int install(mc_model* h, Loaded& L) {
   h->opts = L.opts;
   h->plan = L.plan;
   h->parts_host = std::move(L.parts);
+  h->rplan = std::move(L.rounds);
+  h->rounds = !h->rplan.parts.empty();
+  h->on_rounds = false;
   h->ctrl = reinterpret_cast<Ctrl*>(h->ws + h->plan.ctrl);
   h->tc = reinterpret_cast<uint32_t*>(h->ws + h->plan.tc);
   h->cfgs = reinterpret_cast<CfgRec*>(h->ws + h->plan.cfgs);
@@ -758,8 +961,8 @@ int install(mc_model* h, Loaded& L) {
   h->table = h->ws + h->plan.table;
   h->q_slots = h->plan.slots;
   h->q_parts = 0;
-  const std::vector<Part>& parts = h->parts_host;
-  h->n_parts = (uint32_t)parts.size();
+  h->tslot = reinterpret_cast<uint32_t*>(h->ws + h->plan.seeds);
+  h->n_parts = (uint32_t)(h->rounds ? h->rplan.parts.size() : h->parts_host.size());
   h->trace_ready = false;
   h->trace_rows.clear();
   h->last = kQueryNone;
@@ -773,8 +976,9 @@ int install(mc_model* h, Loaded& L) {
   // one staging block: counters, poll words, descriptor, clocks and, when small, the
   // staging of the uploads below
   static_assert(sizeof(Ctrl) <= 256 && sizeof(ModelDev) <= 256, "staging block layout");
-  const size_t tc_off = 768, up_off = align_up(tc_off + 4ull * h->mh.n_cfg);
-  const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg, part_bytes = sizeof(Part) * parts.size();
+  const size_t rec_off = 768, tc_off = rec_off + sizeof(RoundRecord) * kRoundsGrid;
+  const size_t up_off = align_up(tc_off + 4ull * h->mh.n_cfg);
+  const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg, part_bytes = sizeof(Part) * h->n_parts;
   const bool stage = cfg_bytes + part_bytes <= (4u << 20);
   const size_t pin_bytes = stage ? up_off + cfg_bytes + part_bytes : up_off;
   unsigned char* blk = nullptr;
@@ -796,16 +1000,20 @@ int install(mc_model* h, Loaded& L) {
   // the stop request is a word the kernels read at system scope: pinned memory only
   h->habort = h->pooled ? reinterpret_cast<unsigned int*>(blk + 256 + 128) : nullptr;
   if (h->habort) __atomic_store_n(h->habort, 0u, __ATOMIC_RELEASE);
+  h->records = h->pooled ? reinterpret_cast<RoundRecord*>(blk + rec_off) : nullptr;
   h->hmd = reinterpret_cast<ModelDev*>(blk + 512);
   h->tc_host = reinterpret_cast<uint32_t*>(blk + tc_off);
   for (uint32_t c = 0; c < h->mh.n_cfg; ++c) h->tc_host[c] = kNoClock;
   const void* up_cfg = h->mh.cfgs.data();
-  const void* up_part = parts.data();
+  const void* up_part = h->rounds ? static_cast<const void*>(h->rplan.parts.data())
+                                  : static_cast<const void*>(h->parts_host.data());
+  h->stage_parts = nullptr;
   if (stage) {
     std::memcpy(blk + up_off, up_cfg, cfg_bytes);
     std::memcpy(blk + up_off + cfg_bytes, up_part, part_bytes);
     up_cfg = blk + up_off;
     up_part = blk + up_off + cfg_bytes;
+    h->stage_parts = blk + up_off + cfg_bytes;
   }
   hipStream_t s = h->stream;
   if (hipMemcpyAsync(h->cfgs, up_cfg, cfg_bytes, hipMemcpyHostToDevice, s) != hipSuccess ||

@@ -21,6 +21,9 @@ struct QueryArgs {
   uint32_t T;
   uint32_t max_clock;       // bound of the packed clock field
   uint32_t hkeep;           // bits of the key hash kept (0 = all; testing only)
+  // after the round engine: the terminal's slot per configuration, and the one asked for
+  const uint32_t* tslot = nullptr;
+  uint32_t target = 0;
 };
 
 // Keys each thread of the persistent kernel inserts per round trip: 1 or 2 as asked,
@@ -79,6 +82,8 @@ struct ModelDev {
   uint32_t refloor;   // a continued exploration: every state with clock < refloor was
                       // inserted before, and one found again is still expanded, so the
                       // walk reaches the new states past it (0 = a fresh exploration)
+  uint32_t* tslot;    // round engine: slot of each configuration's terminal (else null:
+                      // the model is not explored by the round engine)
 };
 
 // One partition of a persistent launch: rounds [r0, r1) of one configuration's subgraph
@@ -109,6 +114,48 @@ struct PartQueue {
   // every workgroup still exits normally
   const unsigned int* abort;
 };
+
+// A launch of the round engine.
+struct RoundQueue {
+  const ModelDev* models;
+  const RoundPart* parts;
+  uint32_t n_parts, n_pieces;
+  uint32_t piece;       // items per piece
+  uint32_t log2_set;    // slots of a piece's hash set, at least twice its items
+  uint32_t reverse;     // take the pieces last first
+  unsigned int* head;
+  const unsigned int* abort;  // as PartQueue::abort
+  // One model, a handle with pinned memory: every workgroup stores its sums here (grid
+  // records in host memory) and every terminal its clock in host_tc; else null, and the
+  // sums are added to the models' counters and the clocks to ModelDev::tc.
+  struct RoundRecord* records;
+  uint32_t* host_tc;
+};
+// One workgroup's sums over a launch (its pieces of one model, where counters are device's).
+struct RoundRecord {
+  unsigned long long states, terms, edges, dups, probes, chunks, rounds;
+  unsigned long long t_first, t_last;  // device clock (100 MHz): its first piece, its end
+  uint32_t pieces;
+  uint32_t depth, max_probe;
+  uint32_t crit, crit_cfg;  // its longest piece, in ticks
+  uint32_t error;
+};
+static_assert(sizeof(RoundRecord) == 96, "RoundRecord layout");
+// Least log2 of the slots of a hash set for pieces of `piece` items.
+inline uint32_t set_log2(uint32_t piece) {
+  uint32_t l = 9;
+  while ((1u << l) < 2u * piece) ++l;
+  return l;
+}
+// Counters, clocks, root and SELECT states of one model (its descriptor is written to
+// dst), or of every model of a queue that the round engine explores.
+hipError_t launch_rounds_begin(hipStream_t st, const ModelDev& md, ModelDev* dst,
+                               unsigned int* head);
+hipError_t launch_rounds_begin_models(hipStream_t st, const ModelDev* models, uint32_t n,
+                                      unsigned int* head);
+// general: some configuration has waves or two-operation periods.
+hipError_t launch_rounds(hipStream_t st, uint32_t grid, uint32_t block, const RoundQueue& q,
+                         bool general);
 
 template <int W>
 hipError_t launch_seed(hipStream_t st, const QueryArgs& q, Seed* seeds, void* front0);

@@ -802,6 +802,135 @@ uint64_t auto_part_states(uint64_t states, uint32_t m) {
   return std::min<uint64_t>(1ull << 14, std::max<uint64_t>(1, states / parts));
 }
 
+bool rounds_model(const ModelHost& h) {
+  if (h.hetero || h.W != 1 || !h.layout.shared_rem) return false;
+  const uint64_t m = h.m;
+  // pending counts that one piece can span: its rounds (a round has at least 2^m - 1 + b
+  // items, or the piece lies within two), the one before and the one after
+  for (const CfgRec& r : h.cfgs) {
+    const uint64_t span = std::min<uint64_t>(r.n, (kMaxPiece / (((1ull << m) - 1) + r.b) + 4) * m);
+    if (bit_length(span) + m + code_rem_bits(r) > 32u) return false;
+  }
+  return true;
+}
+
+void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>& plan,
+                RoundPlan* out) {
+  const uint64_t m = h.m, cl = (1ull << m) - 1;
+  uint64_t slot = 1ull + h.n_cfg;
+  uint32_t cfg = kNoClock;
+  uint64_t root = 0, leaf = 0;  // of the configuration's next round / of the head's round
+  out->parts.reserve(out->parts.size() + plan.size());
+  for (const PartPlan& q : plan) {
+    const CfgRec& r = h.cfgs[q.cfg];
+    if (q.cfg != cfg) {
+      cfg = q.cfg;
+      root = 1ull + cfg;  // its SELECT state
+    }
+    const uint64_t full = r.n / m, p = r.n % m;
+    RoundPart x{};
+    x.model = model;
+    x.cfg_flags = cfg;
+    x.slot0 = (uint32_t)slot;
+    uint64_t nfull, ja = 0, jb = r.b, extra = 0;
+    bool partial, closure = true;
+    if (q.r0 == kRunSlice) {
+      closure = false;
+      ja = q.j0;
+      jb = q.j1;
+      partial = q.r1 >= full;
+      nfull = partial ? 0 : 1;
+      x.r0 = q.r1;
+      x.a = (uint32_t)ja;
+      x.link = (uint32_t)leaf;
+    } else {
+      partial = q.r1 == kRoundsToEnd && p != 0;
+      nfull = (q.r1 == kRoundsToEnd ? full : q.r1) - q.r0;
+      if (q.j1) {
+        jb = q.j1;
+        extra = q.r1 == kRoundsToEnd ? 0 : 1;  // its round's end starts the next round
+      }
+      x.r0 = q.r0;
+      x.a = (uint32_t)nfull;
+      x.link = (uint32_t)root;
+    }
+    x.jb = (uint32_t)jb;
+    const uint64_t per = (closure ? cl : 0) + (jb - ja) + extra;
+    uint64_t items = nfull * per, group = 1;
+    if (partial) {
+      const uint64_t choices = binom((uint32_t)m, (uint32_t)p);
+      uint64_t sets = 0;
+      for (uint32_t j = 1; j <= p; ++j) sets += binom((uint32_t)m, j);
+      if (closure) {
+        leaf = slot + items + sets - choices;
+        items += sets;
+      }
+      items += choices * (jb - ja);
+      if (jb == r.b) group = choices;  // the runs end in one state
+    } else if (closure) {
+      leaf = slot + (nfull - 1) * per + cl - 1;
+      root = slot + items - 1;  // the last round's end, where it is held
+    }
+    x.cfg_flags |= (closure ? kRpClosure : 0u) | (extra ? kRpEndExtra : 0u) |
+                   (partial ? kRpPartial : 0u);
+    out->parts.push_back(x);
+    out->items.push_back(items);
+    out->end_group.push_back(group);
+    slot += items;
+  }
+  out->used = slot;
+}
+
+void trim_rounds(const ModelHost& h, const RoundPlan& plan, uint64_t floor, uint64_t T,
+                 RoundPlan* out) {
+  const uint64_t m = h.m, cl = (1ull << m) - 1;
+  out->used = plan.used;
+  for (size_t i = 0; i < plan.parts.size(); ++i) {
+    RoundPart x = plan.parts[i];
+    const CfgRec& r = h.cfgs[x.cfg_flags & kRpCfg];
+    const uint64_t d = r.d, start = (uint64_t)x.r0 * d;
+    if (start > T) continue;
+    uint64_t items = plan.items[i], group = plan.end_group[i];
+    if (!(x.cfg_flags & kRpClosure)) {  // a slice: clocks of its states ja .. jb - 1
+      if (start + end_at_host(r, x.a) > T || start + end_at_host(r, x.jb - 1) < floor) continue;
+    } else {
+      const uint64_t per = cl + x.jb + (x.cfg_flags & kRpEndExtra ? 1 : 0);
+      const bool partial = (x.cfg_flags & kRpPartial) != 0;
+      const uint64_t rest = items - x.a * per;  // the partial round's
+      const uint64_t upto = std::min<uint64_t>(x.a, T / d - x.r0 + 1);
+      // rounds that end below the floor
+      const uint64_t over = floor ? (floor - 1) / d : 0;
+      const uint64_t from = std::min<uint64_t>(upto, over > x.r0 ? over - x.r0 : 0);
+      const bool keep = partial && upto == x.a && (x.r0 + (uint64_t)x.a) * d <= T;
+      if (keep && from == x.a && (x.r0 + (uint64_t)x.a + 1) * d < floor) continue;
+      if (from == upto && !keep) continue;
+      if (from) x.link = (uint32_t)(x.slot0 + from * per - 1);
+      x.slot0 += (uint32_t)(from * per);
+      x.r0 += (uint32_t)from;
+      x.a = (uint32_t)(upto - from);
+      if (partial && !keep) x.cfg_flags &= ~kRpPartial;
+      items = x.a * per + (keep ? rest : 0);
+      if (!keep) group = 1;
+    }
+    out->parts.push_back(x);
+    out->items.push_back(items);
+    out->end_group.push_back(group);
+  }
+}
+
+uint64_t number_pieces(RoundPlan* p, uint32_t piece, uint64_t first_piece) {
+  uint64_t n = first_piece;
+  for (size_t i = 0; i < p->parts.size(); ++i) {
+    p->parts[i].piece0 = (uint32_t)n;
+    n += std::max<uint64_t>(1, (p->items[i] - p->end_group[i] + piece - 1) / piece);
+  }
+  return n - first_piece;
+}
+
+uint32_t auto_piece(uint64_t items) {
+  return (uint32_t)std::min<uint64_t>(kMaxPiece, std::max<uint64_t>(256, items / 1024));
+}
+
 // operation ends of one workgroup at or before time x
 uint64_t ends_le(const CfgRec& r, uint64_t x) {
   if (x >= r.d) return r.b;

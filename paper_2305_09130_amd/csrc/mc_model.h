@@ -151,6 +151,58 @@ struct PartPlan {
 void plan_parts(const ModelHost& h, uint64_t target, std::vector<PartPlan>* out,
                 uint64_t clock_max = ~0ull);
 
+// ---- the round engine (units alike, one-word keys) ------------------------------------
+//
+// On units alike the partitions above hold states whose place is known beforehand: every
+// round is a closure (the sets of started units) and the runs that follow it.  The round
+// engine gives each partition a range of the visited set with one slot per generated
+// state ("item"), so that no other workgroup writes there, and tests its states for
+// duplicates in a hash set of the workgroup's own LDS.  Item order within a partition:
+// its full rounds one after another, each the closure's sets 1 .. 2^m - 1 (where the
+// partition holds the closure), then the run's states ja .. jb - 1, then (kRpEndExtra) the
+// run's last state; then (kRpPartial) the partial round: the closure's sets of up to p
+// units by size and value, then the runs' states, one per choice of p units for each j.
+struct RoundPart {
+  uint32_t model;
+  uint32_t cfg_flags;  // configuration | kRp* flags
+  uint32_t r0;         // first round
+  uint32_t a;          // with the closure: full rounds held; else ja, the first run state
+  uint32_t jb;         // end of the run states held (exclusive)
+  uint32_t slot0;      // slot of item 0
+  uint32_t link;       // with the closure: the slot of the state the first round starts
+                       // from; else the slot of the round's first dispatch leaf
+  uint32_t piece0;     // pieces (of at most RoundQueue::piece items) before this partition's
+};
+static_assert(sizeof(RoundPart) == 32, "RoundPart layout (as large as a Part)");
+constexpr uint32_t kRpCfg = (1u << 24) - 1u;  // configurations are at most 2^20
+constexpr uint32_t kRpClosure = 1u << 24, kRpEndExtra = 1u << 25, kRpPartial = 1u << 26;
+constexpr uint32_t kMaxPiece = 4096;  // most items of a piece but for the last states of a
+                                      // partial round's runs, which stay together
+struct RoundPlan {
+  std::vector<RoundPart> parts;
+  std::vector<uint64_t> items;   // per partition
+  std::vector<uint64_t> end_group;  // last items that have to share a piece
+  uint64_t used = 0;             // slots used: root, SELECT states, items
+};
+// Bits of the time left in a state's code within a piece (the value below all-ones, so that
+// no code is the empty slot's).
+inline uint32_t code_rem_bits(const CfgRec& r) { return 32u - (uint32_t)__builtin_clz(r.d + 1u); }
+// Whether the round engine can explore the model: units alike, one-word keys, and a
+// state's place within a piece (pending count, busy mask, time left) fits in 32 bits.
+bool rounds_model(const ModelHost& h);
+// The round engine's form of a plan (in the order plan_parts gives it): slots are
+// assigned from 1 + n_cfg (the root has slot 0, SELECT(c) slot 1 + c).
+void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>& plan,
+                RoundPlan* out);
+// The partitions of a plan without the rounds and slices that hold no state with clock in
+// [floor, T] (a check drops states past T; a continued exploration has those below floor).
+void trim_rounds(const ModelHost& h, const RoundPlan& plan, uint64_t floor, uint64_t T,
+                 RoundPlan* out);
+// Numbers the pieces of at most `piece` items; returns their total.
+uint64_t number_pieces(RoundPlan* p, uint32_t piece, uint64_t first_piece = 0);
+// Items per piece for a launch generating about `items` states in total.
+uint32_t auto_piece(uint64_t items);
+
 // Whether key word 0 alone tells apart the states of different rounds and of different
 // positions along a round's runs (configuration, pending count and either the clock or,
 // when the clock is implied, the busy mask and time left): the condition for cutting a

@@ -208,7 +208,8 @@ __global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned lon
   const Layout& L = a.L;
   const int m = L.m;
   __shared__ uint32_t sS[kChaseCand + 1];  // a chain's counted flags and their prefix sums
-  uint32_t s = a.ctrl->target_slot;
+  uint32_t s = a.tslot ? a.tslot[a.target] : a.ctrl->target_slot;
+  if (a.tslot && lane == 0) a.ctrl->target_slot = s;
   uint32_t n = 0;
   bool bad = false;
   while (s != kParentRoot) {
