@@ -519,6 +519,8 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
     HIPCHK(hipMemcpyAsync(ctrl, h->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(h->tc_host, h->tc, 4ull * h->mh.n_cfg, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    ctrl->crit_ticks = ctrl->crit_longest >> 32;
+    ctrl->crit_part = (unsigned int)ctrl->crit_longest;
   }
   const int derr = dev_error_code(ctrl->error);
   if (derr == MC_E_ABORTED && h->habort) __atomic_store_n(h->habort, 0u, __ATOMIC_RELEASE);
@@ -896,16 +898,8 @@ void plan_rounds(const ModelHost& mh, const mc_opts& o, const std::vector<PartPl
   RoundPlan p;
   round_plan(mh, 0, plan, &p);
   if (p.used > slots) return;
-  std::vector<uint32_t> order(p.parts.size());
-  for (uint32_t i = 0; i < (uint32_t)order.size(); ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](uint32_t a, uint32_t b) { return p.items[a] > p.items[b]; });
-  out->used = p.used;
-  for (const uint32_t i : order) {
-    out->parts.push_back(p.parts[i]);
-    out->items.push_back(p.items[i]);
-    out->end_group.push_back(p.end_group[i]);
-  }
+  largest_first(&p);
+  *out = std::move(p);
   number_pieces(out, auto_piece(mh.states));
 }
 

@@ -73,12 +73,16 @@ struct BPart {
 
 int width_group(uint32_t W) { return W == 1 ? 0 : W == 2 ? 1 : 2; }
 
-std::vector<BPart> batch_parts(const std::vector<ModelHost>& ms, const mc_batch_opts& o) {
+uint64_t batch_target(const std::vector<ModelHost>& ms, const mc_batch_opts& o) {
   uint64_t total = 0;
   for (const auto& m : ms) total += m.states;
-  const uint64_t target = o.part_states == 0xFFFFFFFFu ? 0u
-                          : o.part_states              ? o.part_states
-                                                       : auto_part_states(total);
+  return o.part_states == 0xFFFFFFFFu ? 0u
+         : o.part_states              ? o.part_states
+                                      : auto_part_states(total);
+}
+
+std::vector<BPart> batch_parts(const std::vector<ModelHost>& ms, const mc_batch_opts& o) {
+  const uint64_t target = batch_target(ms, o);
   std::vector<BPart> ps;
   std::vector<PartPlan> plan;
   for (uint32_t i = 0; i < (uint32_t)ms.size(); ++i) {
@@ -184,6 +188,11 @@ struct mc_batch {
   hipGraphExec_t exec = nullptr;
   bool ran = false;
   uint64_t max_range16 = 0;  // the largest range of the clear, in 16-byte units
+  // models that the round engine explores: their partitions (before the others' in `parts`)
+  uint32_t round_parts = 0, round_pieces = 0, round_piece = 0, round_block = 256;
+  bool round_general = false;
+  std::vector<uint8_t> rounds;  // per model
+  uint32_t n_other = 0;         // models not explored by it
   uint32_t grid[3] = {0, 0, 0};
   uint32_t group_off[3] = {0, 0, 0}, group_n[3] = {0, 0, 0};  // partitions per key width
   Fork fork;
@@ -191,7 +200,36 @@ struct mc_batch {
 
 namespace {
 
+int enqueue_others(mc_batch* b);
+
 int enqueue_query(mc_batch* b) {
+  hipStream_t s = b->stream;
+  const uint32_t n = (uint32_t)b->ms.size();
+  if (b->n_other) {
+    const int rc = enqueue_others(b);
+    if (rc) return rc;
+  }
+  if (b->round_parts) {
+    HIPCHK(launch_rounds_begin_models(s, b->dmd, n, b->head + 3));
+    RoundQueue q;
+    std::memset(&q, 0, sizeof(q));
+    q.models = b->dmd;
+    q.parts = reinterpret_cast<const RoundPart*>(b->parts);
+    q.n_parts = b->round_parts;
+    q.n_pieces = b->round_pieces;
+    q.piece = b->round_piece;
+    q.log2_set = set_log2(q.piece);
+    q.head = b->head + 3;
+    const uint32_t grid = b->opts.grid ? b->opts.grid : 1024u;
+    HIPCHK(launch_rounds(s, std::min(grid, q.n_pieces), b->round_block, q, b->round_general));
+  }
+  HIPCHK(hipMemcpyAsync(b->hctrl, b->ws + b->plan.ctrl, kCtrlStride * n, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(b->htc, b->ws + b->plan.tc, 4ull * b->tc_words, hipMemcpyDeviceToHost, s));
+  return MC_OK;
+}
+
+// The models that the round engine does not explore.
+int enqueue_others(mc_batch* b) {
   hipStream_t s = b->stream;
   const uint32_t n = (uint32_t)b->ms.size();
   {
@@ -222,13 +260,12 @@ int enqueue_query(mc_batch* b) {
     pq[w].abort = nullptr;
   }
   bool general = false, hetero = false;
-  for (const ModelHost& mh : b->ms) {
-    general |= mh.general;
-    hetero |= mh.hetero;
+  for (size_t i = 0; i < b->ms.size(); ++i) {
+    if (b->rounds[i]) continue;
+    general |= b->ms[i].general;
+    hetero |= b->ms[i].hetero;
   }
   HIPCHK(launch_super_fork(s, b->fork, pq, b->grid, b->opts.block, li, general, hetero));
-  HIPCHK(hipMemcpyAsync(b->hctrl, b->ws + b->plan.ctrl, kCtrlStride * n, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(b->htc, b->ws + b->plan.tc, 4ull * b->tc_words, hipMemcpyDeviceToHost, s));
   return MC_OK;
 }
 
@@ -306,6 +343,8 @@ int mc_batch_create(const mc_desc* models, uint32_t n, const mc_batch_opts* o, v
       return rc;
     }
     b->opts = default_bopts(o);
+    // the round engine's workgroups are of 256 threads unless asked otherwise
+    b->round_block = o && (o->block == 512 || o->block == 1024) ? o->block : 256u;
     const std::vector<BPart> ps = batch_parts(b->ms, b->opts);
     rc = plan_batch(b->ms, b->opts, ps.size(), &b->plan);
     if (rc) {
@@ -348,17 +387,60 @@ int mc_batch_create(const mc_desc* models, uint32_t n, const mc_batch_opts* o, v
       d.n_cfg = m.n_cfg;
       d.max_clock = m.max_clock;
     }
+    // Partitions: those of the round engine's models first (units alike, one-word keys, a
+    // slot for every generated state), then the others'.  ps holds each model's in an order
+    // that sorting has mixed, so the round engine's are planned again from the model.
+    RoundPlan rp;
+    b->rounds.assign(n, 0);
+    {
+      std::vector<PartPlan> plan;
+      for (uint32_t i = 0; i < n; ++i) {
+        const ModelHost& m = b->ms[i];
+        RoundPlan own;
+        if (rounds_model(m)) {
+          plan.clear();
+          plan_parts(m, batch_target(b->ms, b->opts), &plan);
+          round_plan(m, i, plan, &own);
+        }
+        if (own.parts.empty() || own.used > b->plan.slots[i]) {
+          ++b->n_other;
+          continue;
+        }
+        b->rounds[i] = 1;
+        b->round_general |= m.general;
+        md[i].tslot = reinterpret_cast<uint32_t*>(b->ws + b->plan.seed_off[i]);
+        rp.parts.insert(rp.parts.end(), own.parts.begin(), own.parts.end());
+        rp.items.insert(rp.items.end(), own.items.begin(), own.items.end());
+        rp.end_group.insert(rp.end_group.end(), own.end_group.begin(), own.end_group.end());
+        rp.used += own.used;
+      }
+    }
+    largest_first(&rp);
+    b->round_parts = (uint32_t)rp.parts.size();
+    b->round_piece = auto_piece(rp.used);
+    const uint64_t n_pieces = number_pieces(&rp, b->round_piece);
+    if (n_pieces > 0xFFFF0000ull) {
+      free_batch(b);
+      return MC_E_INVAL;
+    }
+    b->round_pieces = (uint32_t)n_pieces;
     for (const BPart& q : ps) ++md[q.model].n_parts;
     std::vector<Part> parts(ps.size());
+    static_assert(sizeof(Part) == sizeof(RoundPart), "one array holds both");
+    if (b->round_parts)
+      std::memcpy(static_cast<void*>(parts.data()), rp.parts.data(),
+                  sizeof(RoundPart) * rp.parts.size());
     std::vector<uint32_t> pidx(n, 0u);  // partitions of each model so far
+    size_t at = b->round_parts;
     for (size_t k = 0; k < ps.size(); ++k) {
-      parts[k] = Part{ps[k].model, ps[k].cfg, ps[k].r0, ps[k].r1, pidx[ps[k].model]++, ps[k].j0,
-                      ps[k].j1, 0u};
+      if (b->rounds[ps[k].model]) continue;
+      parts[at++] = Part{ps[k].model, ps[k].cfg, ps[k].r0, ps[k].r1, pidx[ps[k].model]++,
+                         ps[k].j0, ps[k].j1, 0u};
       ++b->group_n[width_group(b->ms[ps[k].model].W)];
     }
-    b->group_off[0] = 0;
-    b->group_off[1] = b->group_n[0];
-    b->group_off[2] = b->group_n[0] + b->group_n[1];
+    b->group_off[0] = b->round_parts;
+    b->group_off[1] = b->group_off[0] + b->group_n[0];
+    b->group_off[2] = b->group_off[1] + b->group_n[1];
     hipStream_t s = b->stream;
     for (uint32_t i = 0; i < n; ++i)
       if (hipMemcpyAsync(b->ws + b->plan.cfg_off[i], b->ms[i].cfgs.data(),
@@ -373,8 +455,8 @@ int mc_batch_create(const mc_desc* models, uint32_t n, const mc_batch_opts* o, v
       const ModelHost& m = b->ms[i];
       const uint64_t bytes = b->plan.slots[i] * (m.hetero ? slot_bytes_for(m.W) : 8ull * m.W);
       ranges[2 * i] = (b->plan.table_off[i] - b->plan.tables) / 16;
-      ranges[2 * i + 1] = bytes / 16;
-      b->max_range16 = std::max<uint64_t>(b->max_range16, bytes / 16);
+      ranges[2 * i + 1] = b->rounds[i] ? 0 : bytes / 16;
+      b->max_range16 = std::max<uint64_t>(b->max_range16, ranges[2 * i + 1]);
     }
     if (hipMemcpyAsync(b->ws + b->plan.ranges, ranges.data(), sizeof(unsigned long long) * 2 * n,
                        hipMemcpyHostToDevice, s) != hipSuccess ||
@@ -463,9 +545,11 @@ int mc_batch_min_time(mc_batch* b, uint32_t* t_min, uint64_t* states, mc_stats* 
     acc.supersteps += c->supersteps;
     acc.batches += c->chunks;
     acc.max_probe = std::max<uint64_t>(acc.max_probe, c->max_probe);
-    if (c->crit_ticks * 10ull > acc.critical_ns) {
-      acc.critical_ns = c->crit_ticks * 10ull;
-      acc.critical_cfg = c->crit_part;
+    const bool longest = c->crit_longest != 0;  // the round engine's: ticks, configuration
+    const uint64_t ticks = longest ? c->crit_longest >> 32 : c->crit_ticks;
+    if (ticks * 10ull > acc.critical_ns) {
+      acc.critical_ns = ticks * 10ull;
+      acc.critical_cfg = longest ? (uint32_t)c->crit_longest : c->crit_part;
     }
   }
   acc.parts = b->plan.n_parts;

@@ -34,7 +34,8 @@ struct Ctrl {
   unsigned int parts_done;       // partitions explored to the end (resumable queues)
   unsigned int bound;            // branch-and-bound min_time: least terminal clock found
                                  // so far (starts at the query's T)
-  unsigned int pad[6];
+  unsigned long long crit_longest;  // round engine: its longest piece's ticks << 32 | configuration
+  unsigned int pad[4];
 };
 static_assert(sizeof(Ctrl) == 160, "Ctrl layout");
 

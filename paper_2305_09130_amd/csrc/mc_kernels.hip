@@ -1608,6 +1608,7 @@ __device__ void seed_model(const ModelDev& md) {
 
 __global__ __launch_bounds__(256) void k_seed_models(const ModelDev* models) {
   const ModelDev md = models[blockIdx.x];
+  if (md.tslot) return;  // a model of the round engine
   switch (md.L.W) {
     case 1: seed_model<1>(md); break;
     case 2: seed_model<2>(md); break;
@@ -1618,6 +1619,9 @@ __global__ __launch_bounds__(256) void k_seed_models(const ModelDev* models) {
 // Per-model counters and clocks of every model of a queue, and the queue heads.
 __global__ void k_reset_models(const ModelDev* models, unsigned int* head, uint32_t n_heads) {
   const ModelDev md = models[blockIdx.x];
+  if (blockIdx.x == 0 && head)
+    for (uint32_t i = threadIdx.x; i < n_heads; i += blockDim.x) head[i] = 0u;
+  if (md.tslot) return;  // a model of the round engine
   unsigned int* cw = reinterpret_cast<unsigned int*>(md.ctrl);
   constexpr uint32_t kBoundWord = offsetof(Ctrl, bound) / 4;
   for (uint32_t i = threadIdx.x; i < sizeof(Ctrl) / 4; i += blockDim.x)
@@ -1625,8 +1629,6 @@ __global__ void k_reset_models(const ModelDev* models, unsigned int* head, uint3
   for (uint32_t i = threadIdx.x; i < md.n_cfg; i += blockDim.x) md.tc[i] = kNoClock;
   if (md.pstate)
     for (uint32_t i = threadIdx.x; i < md.n_parts; i += blockDim.x) md.pstate[i].status = 0u;
-  if (blockIdx.x == 0 && head)
-    for (uint32_t i = threadIdx.x; i < n_heads; i += blockDim.x) head[i] = 0u;
 }
 
 // Prepares models whose exploration continues past an earlier threshold on the same

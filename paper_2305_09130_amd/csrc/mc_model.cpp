@@ -809,7 +809,7 @@ bool rounds_model(const ModelHost& h) {
   // items, or the piece lies within two), the one before and the one after
   for (const CfgRec& r : h.cfgs) {
     const uint64_t span = std::min<uint64_t>(r.n, (kMaxPiece / (((1ull << m) - 1) + r.b) + 4) * m);
-    if (bit_length(span) + m + code_rem_bits(r) > 32u) return false;
+    if (bit_length(span) + m + code_rem_bits(r) > 32u || r.b >= (1u << 24)) return false;
   }
   return true;
 }
@@ -879,6 +879,24 @@ void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>&
     slot += items;
   }
   out->used = slot;
+}
+
+void largest_first(RoundPlan* p) {
+  std::vector<uint32_t> order(p->parts.size());
+  std::iota(order.begin(), order.end(), 0u);
+  std::stable_sort(order.begin(), order.end(),
+                   [&](uint32_t a, uint32_t b) { return p->items[a] > p->items[b]; });
+  RoundPlan q;
+  q.used = p->used;
+  q.parts.reserve(order.size());
+  q.items.reserve(order.size());
+  q.end_group.reserve(order.size());
+  for (const uint32_t i : order) {
+    q.parts.push_back(p->parts[i]);
+    q.items.push_back(p->items[i]);
+    q.end_group.push_back(p->end_group[i]);
+  }
+  *p = std::move(q);
 }
 
 void trim_rounds(const ModelHost& h, const RoundPlan& plan, uint64_t floor, uint64_t T,

@@ -187,13 +187,16 @@ struct RoundPlan {
 // Bits of the time left in a state's code within a piece (the value below all-ones, so that
 // no code is the empty slot's).
 inline uint32_t code_rem_bits(const CfgRec& r) { return 32u - (uint32_t)__builtin_clz(r.d + 1u); }
-// Whether the round engine can explore the model: units alike, one-word keys, and a
-// state's place within a piece (pending count, busy mask, time left) fits in 32 bits.
+// Whether the round engine can explore the model: units alike, one-word keys, a state's
+// place within a piece (pending count, busy mask, time left) fits in 32 bits, and runs of
+// fewer than 2^24 states.
 bool rounds_model(const ModelHost& h);
 // The round engine's form of a plan (in the order plan_parts gives it): slots are
 // assigned from 1 + n_cfg (the root has slot 0, SELECT(c) slot 1 + c).
 void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>& plan,
                 RoundPlan* out);
+// Orders a plan's partitions by items, most first.
+void largest_first(RoundPlan* p);
 // The partitions of a plan without the rounds and slices that hold no state with clock in
 // [floor, T] (a check drops states past T; a continued exploration has those below floor).
 void trim_rounds(const ModelHost& h, const RoundPlan& plan, uint64_t floor, uint64_t T,
