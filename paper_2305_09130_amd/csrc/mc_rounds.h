@@ -14,6 +14,15 @@
 
 namespace mc {
 
+MC_HD uint32_t mul24(uint32_t a, uint32_t b) { return (a & 0xFFFFFFu) * (b & 0xFFFFFFu); }
+// 1 / n to within a unit in the last place
+MC_HD float inverse(uint32_t n) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_rcpf((float)n);
+#else
+  return 1.0f / (float)n;
+#endif
+}
 MC_HD uint32_t bits_set(uint32_t v) { return (uint32_t)__builtin_popcount(v); }
 
 // Items [i0, i1) of a partition (RoundPart gives the item order), and what is common to them.
@@ -27,10 +36,23 @@ struct Piece {
   uint32_t slot0, link;
   uint32_t i0, i1;
   uint32_t q0, q1, loc0;     // first and last round of the piece, from r0; i0's place in it
-  uint32_t magic;            // reciprocal of per, for items of the piece
+  float per_inv;             // 1 / per
+  float choices_inv;         // 1 / choices
+  uint32_t jj0, l0;          // run state and choice of the first item past the full rounds'
+                             // and the closure's that the piece holds
+  uint32_t y0;               // that item's number
+  bool last;                 // the partition's last piece
   uint32_t pmin;             // least pending count of the piece's states
+  uint32_t xloc;             // place in a round of its end, where the runs stop before it
   bool closure, extra, partial;
 };
+
+// x / n given 1 / n, for n up to kSmallRound and x below 2^15: x + 1/2 is at least half off
+// every multiple of n, 2^-16 of it, and the product is off by 2^-22 of it at most.
+constexpr uint32_t kSmallRound = 8192;
+MC_HD uint32_t quotient(uint32_t x, float inv) {
+  return (uint32_t)(((float)x + 0.5f) * inv);
+}
 
 MC_HD Piece piece_of(const RoundPart& pt, const CfgRec& r, uint32_t m, uint32_t piece,
                      uint32_t nth) {
@@ -49,6 +71,7 @@ MC_HD Piece piece_of(const RoundPart& pt, const CfgRec& r, uint32_t m, uint32_t 
   v.cl = v.closure ? v.all : 0u;
   v.per = v.cl + (v.jb - v.ja) + (v.extra ? 1u : 0u);
   v.F = v.nfull * v.per;
+  v.xloc = v.extra ? v.per - 1u : 0xFFFFFFFFu;
   v.slot0 = pt.slot0;
   v.link = pt.link;
   v.sets = 0;
@@ -65,25 +88,34 @@ MC_HD Piece piece_of(const RoundPart& pt, const CfgRec& r, uint32_t m, uint32_t 
       v.F + (v.partial ? (v.closure ? v.sets : 0u) + v.choices * (v.jb - v.ja) : 0u);
   // the last states of a partial round's runs are one state: they share a piece
   const uint32_t group = v.partial && v.jb == r.b ? v.choices : 1u;
-  uint32_t pieces = (items - group + piece - 1u) / piece;
-  pieces = pieces ? pieces : 1u;
   v.i0 = nth * piece;
-  v.i1 = nth + 1u == pieces ? items : v.i0 + piece;
+  v.last = items - v.i0 <= piece + group;  // nth + 1 >= (items - group) / piece
+  v.i1 = v.last ? items : v.i0 + piece;
+  v.per_inv = inverse(v.per);
   v.q0 = v.i0 < v.F ? v.i0 / v.per : v.nfull;
   v.loc0 = v.i0 - v.q0 * v.per;
-  v.q1 = v.i1 > v.F ? v.nfull : (v.i1 - 1u) / v.per;
-  // an item's place past loc0 is below kMaxPiece + 70 + per: exact for per up to 2^13 (0 for
-  // per = 1, a slice of one state), and beyond that a piece reaches into one more round at
-  // most
-  v.magic = v.per <= 8192u ? 0xFFFFFFFFu / v.per + 1u : 0u;
+  // (a piece reaches into one more round at most where rounds are longer than it)
+  const uint32_t x1 = v.i1 - 1u - v.i0 + v.loc0;
+  v.q1 = v.i1 > v.F               ? v.nfull
+         : v.per <= kSmallRound ? v.q0 + quotient(x1, v.per_inv)
+                                : v.q0 + (x1 >= v.per ? 1u : 0u);
+  v.choices_inv = inverse(v.choices);
+  const uint32_t runs = v.F + (v.closure ? v.sets : 0u);
+  v.y0 = v.i0 > runs ? v.i0 : runs;
+  v.jj0 = v.l0 = 0u;
+  if (v.partial && v.i0 > runs) {
+    v.jj0 = (v.i0 - runs) / v.choices;
+    v.l0 = v.i0 - runs - v.jj0 * v.choices;
+  }
   const uint32_t after = (v.r0 + v.q1 + 1u) * m;
   v.pmin = r.n > after ? r.n - after : 0u;
   return v;
 }
 
 struct RoundItem {
-  uint32_t round, mask, j;  // mask: the started units; j: the run state (closure: none)
-  uint32_t slot, root, leaf;
+  uint32_t q;        // its round, from the piece's first
+  uint32_t mask, j;  // the started units; the run state (closure: none)
+  uint32_t slot;
   bool is_cl, is_leaf;
 };
 
@@ -92,16 +124,19 @@ MC_HD RoundItem full_item(const Piece& v, uint32_t i) {
   RoundItem t;
   t.slot = v.slot0 + i;
   const uint32_t x = i - v.i0 + v.loc0;
-  const uint32_t q = v.magic ? (uint32_t)(((uint64_t)x * v.magic) >> 32) : (x >= v.per ? 1u : 0u);
-  const uint32_t loc = x - q * v.per, first = (v.q0 + q) * v.per;
-  t.round = v.r0 + v.q0 + q;
+  uint32_t loc;
+  if (v.per <= kSmallRound) {
+    t.q = quotient(x, v.per_inv);
+    loc = x - mul24(t.q, v.per);
+  } else {
+    t.q = x >= v.per ? 1u : 0u;
+    loc = x - (t.q ? v.per : 0u);
+  }
   t.is_cl = loc < v.cl;
   t.mask = t.is_cl ? loc + 1u : v.all;
-  t.is_leaf = t.is_cl && loc + 1u == v.cl;
+  t.is_leaf = loc + 1u == v.cl;
   t.j = v.ja + loc - v.cl;
-  if (v.extra && loc + 1u == v.per) t.j = v.b - 1u;
-  t.root = first ? v.slot0 + first - 1u : v.link;
-  t.leaf = v.closure ? v.slot0 + first + v.cl - 1u : v.link;
+  t.j = loc == v.xloc ? v.b - 1u : t.j;
   return t;
 }
 
@@ -110,16 +145,45 @@ MC_HD RoundItem part_item(const Piece& v, uint32_t i, const uint8_t* masks) {
   RoundItem t;
   t.slot = v.slot0 + i;
   const uint32_t y = i - v.F, s = v.closure ? v.sets : 0u;
-  t.round = v.r0 + v.nfull;
+  t.q = v.nfull - v.q0;
   t.is_cl = y < s;
-  const uint32_t z = t.is_cl ? 0u : y - s, jj = z / v.choices, l = z - jj * v.choices;
-  t.j = v.ja + jj;
+  // run states and choices from those of the piece's first run item
+  const uint32_t z = t.is_cl ? 0u : i - v.y0 + v.l0, jj = quotient(z, v.choices_inv);
+  const uint32_t l = z - jj * v.choices;
+  t.j = v.ja + v.jj0 + jj;
   t.mask = i < v.i1 ? (uint32_t)masks[t.is_cl ? y : v.sets - v.choices + l] : 0u;
   t.is_leaf = t.is_cl && y + v.choices >= v.sets;
-  t.root = v.F ? v.slot0 + v.F - 1u : v.link;
-  t.leaf = v.closure ? v.slot0 + v.F + v.sets - v.choices + l : v.link + l;
   if (!t.is_cl && t.j + 1u == v.b) t.slot -= l;  // the runs' one last state
   return t;
+}
+
+// The slots that an item's links name: of the all-idle state its round starts from (a
+// leaf's), and of the dispatch leaf its run starts from (a round's end's).
+struct ItemLinks {
+  uint32_t root, leaf;
+};
+
+MC_HD ItemLinks links_of(const Piece& v, uint32_t i, uint32_t q) {
+  ItemLinks k;
+  if (i < v.F) {
+    const uint32_t first = (v.q0 + q) * v.per;
+    k.root = first ? v.slot0 + first - 1u : v.link;
+    k.leaf = v.closure ? v.slot0 + first + v.cl - 1u : v.link;
+  } else {
+    const uint32_t y = i - v.F, s = v.closure ? v.sets : 0u;
+    const uint32_t l = y < s ? 0u : (y - s) % v.choices;
+    k.root = v.F ? v.slot0 + v.F - 1u : v.link;
+    k.leaf = v.closure ? v.slot0 + v.F + v.sets - v.choices + l : v.link + l;
+  }
+  return k;
+}
+
+// Path length from the root to the state of item i.  Along a partition's items it falls only
+// among the closure sets of one round, which are all at one clock, so all new or none, and
+// end on the deepest: over a query, the last new items of its pieces hold the deepest state.
+MC_HD uint32_t depth_of(const Piece& v, uint32_t i, const uint8_t* masks) {
+  const RoundItem t = i < v.F ? full_item(v, i) : part_item(v, i, masks);
+  return 1u + (v.r0 + v.q0 + t.q) * (v.m + v.b) + bits_set(t.mask) + (t.is_cl ? 0u : t.j + 1u);
 }
 
 // The place of set x in a partial round's closure list: sets of fewer units first, then by
@@ -138,7 +202,91 @@ MC_HD uint32_t mask_rank(uint32_t x, uint32_t all) {
 // a state that differs within a piece (rounds_model checks that it fits).
 MC_HD uint32_t state_code(const Piece& v, uint32_t pending, uint32_t busy, uint32_t rem,
                           uint32_t rem_bits) {
-  return (((pending - v.pmin) << v.m | busy) << rem_bits) | rem;
+  return (pending - v.pmin) << (v.m + rem_bits) | rem << v.m | busy;
+}
+
+// Time left after run state j of a workgroup of a configuration: d - end_at(j), with the
+// phases' terms that do not depend on j taken out of the loop over a piece's items.
+// Uniform phases (one operation per period, back to back, one wave): the end of operation j
+// of a phase is off + j lat.  Products are of 24-bit factors (rounds_model checks b, and
+// lat <= 2^20).
+struct UniformEnds {
+  uint32_t i1, i2, i3;     // first operations of the later phases (none: all-ones)
+  uint32_t lat[4], left[4];  // time left = left - j lat
+};
+
+MC_HD UniformEnds uniform_ends(const CfgRec& r) {
+  UniformEnds u;
+  for (int j = 0; j < kMaxPhases; ++j) {
+    u.lat[j] = r.lat[j];
+    u.left[j] = r.d - r.t0[j] + (r.i0[j] - 1u) * r.lat[j];
+  }
+  u.i1 = r.nph > 1u ? r.i0[1] : 0xFFFFFFFFu;
+  u.i2 = r.nph > 2u ? r.i0[2] : 0xFFFFFFFFu;
+  u.i3 = r.nph > 3u ? r.i0[3] : 0xFFFFFFFFu;
+  return u;
+}
+
+MC_HD uint32_t rem_after(const UniformEnds& u, uint32_t j) {
+  uint32_t lat = u.lat[0], left = u.left[0];
+  lat = j >= u.i1 ? u.lat[1] : lat;
+  left = j >= u.i1 ? u.left[1] : left;
+  lat = j >= u.i2 ? u.lat[2] : lat;
+  left = j >= u.i2 ? u.left[2] : left;
+  lat = j >= u.i3 ? u.lat[3] : lat;
+  left = j >= u.i3 ? u.left[3] : left;
+  return left - mul24(j, lat);
+}
+
+// Any phases: waves of dw cycles with bw ends; phases of one or two operations per period.
+struct GeneralEnds {
+  uint32_t bw, recip, dw, d;  // recip = floor(2^32 / bw)
+  uint32_t i1, i2, i3;
+  uint32_t i0[4], t0[4], lat[4], la[4];
+};
+
+MC_HD GeneralEnds general_ends(const CfgRec& r) {
+  GeneralEnds u;
+  u.bw = r.bw;
+  u.recip = r.bw > 1u ? (uint32_t)((1ull << 32) / r.bw) : 0xFFFFFFFFu;
+  u.dw = r.dw;
+  u.d = r.d;
+  for (int j = 0; j < kMaxPhases; ++j) {
+    u.i0[j] = r.i0[j];
+    u.t0[j] = r.t0[j];
+    u.lat[j] = r.lat[j];
+    u.la[j] = r.la[j];
+  }
+  u.i1 = r.nph > 1u ? r.i0[1] : 0xFFFFFFFFu;
+  u.i2 = r.nph > 2u ? r.i0[2] : 0xFFFFFFFFu;
+  u.i3 = r.nph > 3u ? r.i0[3] : 0xFFFFFFFFu;
+  return u;
+}
+
+MC_HD uint32_t rem_after(const GeneralEnds& u, uint32_t j) {
+  uint32_t w = (uint32_t)(((uint64_t)j * u.recip) >> 32);  // j / bw, or one less
+  uint32_t k = j - mul24(w, u.bw);
+  if (k >= u.bw) {
+    k -= u.bw;
+    ++w;
+  }
+  uint32_t i0 = u.i0[0], t0 = u.t0[0], lat = u.lat[0], la = u.la[0];
+  i0 = k >= u.i1 ? u.i0[1] : i0;
+  t0 = k >= u.i1 ? u.t0[1] : t0;
+  lat = k >= u.i1 ? u.lat[1] : lat;
+  la = k >= u.i1 ? u.la[1] : la;
+  i0 = k >= u.i2 ? u.i0[2] : i0;
+  t0 = k >= u.i2 ? u.t0[2] : t0;
+  lat = k >= u.i2 ? u.lat[2] : lat;
+  la = k >= u.i2 ? u.la[2] : la;
+  i0 = k >= u.i3 ? u.i0[3] : i0;
+  t0 = k >= u.i3 ? u.t0[3] : t0;
+  lat = k >= u.i3 ? u.lat[3] : lat;
+  la = k >= u.i3 ? u.la[3] : la;
+  const uint32_t q = k - i0, half = la ? 1u : 0u;
+  // one operation per period: t0 + (q + 1) lat; two: t0 + (q / 2) lat + (la, then lat)
+  const uint32_t step = half && !(q & 1u) ? la : lat;
+  return u.d - w * u.dw - t0 - (q >> half) * lat - step;
 }
 
 }  // namespace mc

@@ -19,10 +19,15 @@
 // What bounds it.  k_superstep, which explored these models before, makes one device-scope
 // compare-and-swap per state on a random line of a table in HBM, at the chip's limit for
 // those (17 G/s); here a state costs a compare-and-swap in LDS, 8 bytes of a coalesced store
-// and about 100 vector instructions, which bound it.  min_time launch, k_superstep and its
-// table's clear -> here: matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.29 ms (200 G
-// states/s, 1.6 TB/s of keys written), matmul64_cu4 (5.15M) 0.44 -> 0.056 ms,
-// abstract_s1024_np4_cu1 0.23 -> 0.026 ms, reduction_g256_cu2 (81k) 45 -> 6 us.
+// and about 90 vector instructions per 64 states, which bound it (the vector units issue in
+// two cycles of three).  min_time launch, k_superstep and its table's clear -> here:
+// matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.228 ms (254 G states/s, 2.0 TB/s of keys
+// written), matmul64_cu4 (5.15M) 0.44 -> 0.035 ms, abstract_s1024_np4_cu1 0.23 -> 0.026 ms,
+// reduction_g256_cu2 (81k) 45 -> 5 us, 512 uneven instances (185M) 20.0 -> 1.17 ms.
+//
+// The loop over a piece's items was 0.29 ms on matmul128_vw_cu8 with the operation ends and the
+// places in a round computed from the configuration record for every item, the statistics
+// reduced over the wavefront for every piece, and branches where selects now are.
 //
 // A workgroup has 256 threads and up to 33 KiB of LDS, so that four share a CU: one's lookups
 // and barriers between pieces overlap another's items.  Pieces of half the size ran slower
@@ -31,6 +36,8 @@
 // Sums go to the host as one 96-byte record per workgroup, stored to pinned memory: added to
 // the model's counters instead, ten atomics of 1,024 workgroups on one line took 60 us.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "mc_launch.h"
 #include "mc_rounds.h"
@@ -81,97 +88,170 @@ __device__ __forceinline__ uint32_t find_part(const RoundPart* parts, uint32_t n
 
 // A workgroup's sums, added to its model's counters: for launches over several models, when
 // a piece of another model comes or the launch ends.
+// One lane per counter: the atomics of a flush go out together, and none returns a value.
 __device__ __forceinline__ void flush_sums(Ctrl* ctrl, RoundRecord& s) {
-  if (threadIdx.x != 0) return;
-  if (s.states) atomicAdd(&ctrl->states, s.states);
-  if (s.terms) atomicAdd(&ctrl->terminals, s.terms);
-  if (s.edges) atomicAdd(&ctrl->edges, s.edges);
-  if (s.dups) atomicAdd(&ctrl->dups, s.dups);
-  if (s.probes) atomicAdd(&ctrl->probes, s.probes);
-  if (s.chunks) atomicAdd(&ctrl->chunks, s.chunks);
-  if (s.rounds) atomicAdd(&ctrl->supersteps, s.rounds);
-  if (s.pieces) atomicAdd(&ctrl->parts_done, s.pieces);
-  if (s.depth) atomicMax(&ctrl->max_depth, (unsigned long long)s.depth);
-  if (s.max_probe) atomicMax(&ctrl->max_probe, s.max_probe);
-  if (s.crit > atomicMax(&ctrl->crit_ticks, (unsigned long long)s.crit))
-    ctrl->crit_part = s.crit_cfg;
-  s = RoundRecord{};
+  const uint32_t tid = threadIdx.x;
+  if (tid >= 64u) return;
+  unsigned long long v = 0, *to = nullptr;
+  switch (tid) {
+    case 0: v = s.states; to = &ctrl->states; break;
+    case 1: v = s.terms; to = &ctrl->terminals; break;
+    case 2: v = s.edges; to = &ctrl->edges; break;
+    case 3: v = s.dups; to = &ctrl->dups; break;
+    case 4: v = s.probes; to = &ctrl->probes; break;
+    case 5: v = s.chunks; to = &ctrl->chunks; break;
+    case 6: v = s.rounds; to = &ctrl->supersteps; break;
+    case 7: v = s.depth; to = &ctrl->max_depth; break;
+    case 8: v = (unsigned long long)s.crit << 32 | s.crit_cfg; to = &ctrl->crit_longest; break;
+    default: break;
+  }
+  if (v && tid < 7u) atomicAdd(to, v);
+  else if (v) atomicMax(to, v);
+  if (tid == 9u && s.max_probe) atomicMax(&ctrl->max_probe, s.max_probe);
+  if (tid == 10u && s.pieces) atomicAdd(&ctrl->parts_done, s.pieces);
+  if (tid == 0u) s = RoundRecord{};  // (the wavefront's reads above are done: one instruction
+                                     // stream)
 }
 
 // What the items of a piece need of its model, configuration and query.
 struct ItemEnv {
-  uint32_t c, T, refloor, rb, sp, sm, sr, log2_set, hkeep;
+  uint32_t c, d, T, refloor, code_shift, sp, sm, set_shift, set_mask, hkeep;
   unsigned long long keys, links;  // addresses of the set's two regions
 };
 
-// Sums of one wavefront over a piece (states .. terms: the same in every lane).
+// Sums of one wavefront, kept in scalar registers (but for `terms`) from piece to piece.
 struct ItemSums {
-  uint32_t states = 0, edges = 0, terms = 0, chunks = 0;
-  uint32_t probes = 0, max_probe = 0, depth = 0;  // per lane
+  uint32_t states = 0, edges = 0, chunks = 0;
+  uint32_t depth = 0;
+  uint32_t last = 0;                            // the piece's last item found new (+ 1)
+  uint32_t probes = 0, max_probe = 0;           // of all lanes; of the lane with most
+  uint32_t terms = 0;                           // per lane
 };
 
+__device__ __forceinline__ uint32_t sum64(uint32_t v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// Adds a wavefront's sums to the workgroup's.
+__device__ __forceinline__ void add_sums(RoundRecord& s, ItemSums& w) {
+  const uint32_t terms = sum64(w.terms);
+  if (lane_id() == 0) {
+    atomicAdd(&s.states, (unsigned long long)w.states);
+    atomicAdd(&s.edges, (unsigned long long)w.edges);
+    if (w.edges != w.states) atomicAdd(&s.dups, (unsigned long long)(w.edges - w.states));
+    if (terms) atomicAdd(&s.terms, (unsigned long long)terms);
+    atomicAdd(&s.probes, (unsigned long long)w.probes);
+    atomicMax(&s.max_probe, w.max_probe);
+    atomicMax(&s.depth, w.depth);
+    if (threadIdx.x == 0) s.chunks += w.chunks;
+  }
+  w = ItemSums{};
+}
+
+// A select takes one scalar operand: values the items select among are kept in vector
+// registers, or each select would copy one there first.
+__device__ __forceinline__ void to_vector(uint32_t& x) { asm("" : "+v"(x)); }
+__device__ __forceinline__ UniformEnds in_vector_registers(UniformEnds u) {
+#pragma unroll
+  for (int j = 0; j < kMaxPhases; ++j) {
+    to_vector(u.lat[j]);
+    to_vector(u.left[j]);
+  }
+  return u;
+}
+__device__ __forceinline__ GeneralEnds in_vector_registers(GeneralEnds u) {
+#pragma unroll
+  for (int j = 0; j < kMaxPhases; ++j) {
+    to_vector(u.i0[j]);
+    to_vector(u.t0[j]);
+    to_vector(u.lat[j]);
+    to_vector(u.la[j]);
+  }
+  return u;
+}
+
 // Items [from, to) of a piece: of its full rounds, or (PART) of its partial round.  Two loops,
-// as the fields of one round kind fill the scalar registers.
-template <int BLOCK, bool GEN, bool PART>
-__device__ __forceinline__ void explore_items(const Piece& v, const CfgRec& r, const ItemEnv& g,
+// as the fields of one round kind fill the scalar registers.  CLOCKS: a query with a
+// threshold or a floor tells states apart by their clocks.
+template <int BLOCK, bool PART, bool CLOCKS, class Ends>
+__device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_in, const ItemEnv& g,
                                               uint32_t from, uint32_t to, uint32_t* set,
                                               const uint8_t* masks, const ModelDev* mdp,
                                               uint32_t* host_tc, ItemSums& sum) {
-  const uint32_t set_mask = (1u << g.log2_set) - 1u;
+  const uint32_t prel0 = v.n - (v.r0 + v.q0) * v.m - v.pmin;  // before the piece's first round
+  const uint32_t clock0 = (v.r0 + v.q0) * g.d;
+  const unsigned long long key0 = (unsigned long long)g.c + ((unsigned long long)v.pmin << g.sp);
+  const uint32_t wave = uniform(threadIdx.x & ~63u);
+  const Ends ends = in_vector_registers(ends_in);
   for (uint32_t base = from; base < to; base += BLOCK) {
     const uint32_t i = base + threadIdx.x;
     ++sum.chunks;
     const RoundItem it = PART ? part_item(v, i, masks) : full_item(v, i);
-    const uint32_t e = it.is_cl ? 0u : (GEN ? end_at(r, it.j) : end_at_uniform(r, it.j));
-    const uint32_t rem = r.d - e, clock = it.round * r.d + e, ns = bits_set(it.mask);
-    const uint32_t pending = r.n - it.round * v.m - ns, busy = rem ? it.mask : 0u;
-    const bool act = i < to && clock <= g.T;
+    const uint32_t run = rem_after(ends, it.j), rem = it.is_cl ? g.d : run;
+    const uint32_t prel = prel0 - mul24(it.q, v.m) - bits_set(it.mask);
+    bool act = i < to;
+    uint32_t clock = 0;
+    if constexpr (CLOCKS) {
+      clock = clock0 + it.q * g.d + (g.d - rem);
+      act = act && clock <= g.T;
+    }
     // the set: exact on (pending, busy, rem).  It has twice the slots of the piece's states,
     // so the probe sequence (linear: codes of a run spread evenly under this multiplier) ends
-    const uint32_t code = state_code(v, pending, busy, rem, g.rb);
+    const uint32_t low = rem << v.m | (rem ? it.mask : 0u);
+    const uint32_t code = prel << g.code_shift | low;
     uint32_t h = code * 0x9E3779B1u;
     if (g.hkeep) h = ((h >> 8) & ((1u << g.hkeep) - 1u)) * 0x9E3779B1u;
-    uint32_t at = h >> (32u - g.log2_set), old = 0u, tries = 0;
-    if (act) {
-      do {
+    uint32_t at = h >> g.set_shift, old = code;
+    if (act) old = atomicCAS(&set[at], kSetEmpty, code);
+    const unsigned long long acts = __builtin_amdgcn_ballot_w64(act);
+    // the lanes that met another state try the next slot
+    unsigned long long met = __builtin_amdgcn_ballot_w64(old != kSetEmpty && old != code);
+    uint32_t trips = 1;
+    sum.probes += (uint32_t)__popcll(acts) + (uint32_t)__popcll(met);
+    while (met) {
+      if (__builtin_amdgcn_inverse_ballot_w64(met)) {
+        at = (at + 1u) & g.set_mask;
         old = atomicCAS(&set[at], kSetEmpty, code);
-        at = (at + 1u) & set_mask;
-        ++tries;
-      } while (old != kSetEmpty && old != code && tries <= set_mask);
+      }
+      met &= __builtin_amdgcn_ballot_w64(old != kSetEmpty && old != code);
+      sum.probes += (uint32_t)__popcll(met);
+      if (++trips > g.set_mask) break;  // (never: there are more slots than states)
     }
+    sum.max_probe = trips > sum.max_probe ? trips : sum.max_probe;
     bool fresh = act && old == kSetEmpty;
-    sum.probes += tries;
-    sum.max_probe = tries > sum.max_probe ? tries : sum.max_probe;
-    const unsigned long long key = (unsigned long long)g.c | (unsigned long long)pending << g.sp |
-                                   (unsigned long long)busy << g.sm |
-                                   (unsigned long long)rem << g.sr;
+    const unsigned long long key =
+        (key0 + (unsigned long long)prel * (1u << g.sp)) + ((unsigned long long)low << g.sm);
     global_u64* kp = (global_u64*)g.keys + it.slot;
     // a continued exploration finds the states below its floor in their slots
-    if (clock < g.refloor && fresh) fresh = *kp != key;
+    if constexpr (CLOCKS)
+      if (clock < g.refloor && fresh) fresh = *kp != key;
     if (fresh) {
       *kp = key;
-      const uint32_t dep = 1u + it.round * (v.m + r.b) + ns + (it.is_cl ? 0u : it.j + 1u);
-      sum.depth = dep > sum.depth ? dep : sum.depth;
       // links, as the counterexample reads them: a dispatch leaf to its round's start, a
       // round's end to the leaf its run starts from (parent and jump)
       if (rem == 0u || it.is_leaf) {
-        const unsigned long long lo = rem ? it.root : it.leaf, hi = rem ? kParentNone : it.leaf;
+        const ItemLinks l = links_of(v, i, it.q);
+        const unsigned long long lo = rem ? l.root : l.leaf, hi = rem ? kParentNone : l.leaf;
         ((global_u64*)g.links)[it.slot] = lo | hi << 32;
+        if (rem == 0u && prel + v.pmin == 0u) {
+          const ModelDev md = load_const(mdp);
+          const uint32_t end = clock0 + it.q * g.d + g.d;
+          ++sum.terms;
+          md.tslot[g.c] = it.slot;
+          // (a configuration has one terminal)
+          if (host_tc) __hip_atomic_store(host_tc + g.c, end, __ATOMIC_RELAXED, kScopeSystem);
+          else atomicMin(&md.tc[g.c], end);
+          if (md.prune) md.ctrl->violated = 1u;
+          if (md.bb) atomicMin(&md.ctrl->bound, end);
+        }
       }
     }
-    const bool term = fresh && rem == 0u && pending == 0u;
-    if (term) {
-      const ModelDev md = load_const(mdp);
-      md.tslot[g.c] = it.slot;
-      // (a configuration has one terminal)
-      if (host_tc) __hip_atomic_store(host_tc + g.c, clock, __ATOMIC_RELAXED, kScopeSystem);
-      else atomicMin(&md.tc[g.c], clock);
-      if (md.prune) md.ctrl->violated = 1u;
-      if (md.bb) atomicMin(&md.ctrl->bound, clock);
-    }
-    sum.edges += (uint32_t)__popcll(__ballot(act));
-    sum.states += (uint32_t)__popcll(__ballot(fresh));
-    sum.terms += (uint32_t)__popcll(__ballot(term));
+    const unsigned long long news = __builtin_amdgcn_ballot_w64(fresh);
+    sum.edges += (uint32_t)__popcll(acts);
+    sum.states += (uint32_t)__popcll(news);
+    if (news) sum.last = base + wave + 64u - (uint32_t)__builtin_clzll(news);
   }
 }
 
@@ -197,6 +277,7 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
   }
   uint32_t model = kParentNone;  // whose sums are held
   Ctrl* ctrl = nullptr;
+  ItemSums sum;
   for (;;) {
     if (tid == 0) s_piece = next;
     __syncthreads();  // the piece before is done: its set, its sums
@@ -208,8 +289,12 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
     const ModelDev md = load_const(a.models + pt.model);
     const uint32_t c = pt.cfg_flags & kRpCfg;
     const CfgRec r = load_const(md.cfgs + c);
-    if (model != pt.model) {  // the sums are added to again only past the next barrier
-      if (model != kParentNone) flush_sums(ctrl, sums);
+    if (model != pt.model) {
+      if (model != kParentNone) {  // (added to again only past the barrier after the clear)
+        add_sums(sums, sum);
+        __syncthreads();
+        flush_sums(ctrl, sums);
+      }
       model = pt.model;
       ctrl = md.ctrl;
     }
@@ -245,42 +330,42 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
     const bool none =  // every state past T, or below the floor of a continued exploration
         (unsigned long long)(v.r0 + v.q0) * r.d > T ||
         (unsigned long long)(v.r0 + v.q1 + 1u) * r.d < md.refloor;
-    ItemSums sum;
+    sum.last = 0;
     if (!uniform(s_skip) && !none) {
       ItemEnv g;
+      const uint32_t rem_bits = 32u - (uint32_t)__clz((int)(r.d + 1u));  // code_rem_bits
       g.c = c;
+      g.d = r.d;
       g.T = T;
       g.refloor = md.refloor;
-      g.rb = 32u - (uint32_t)__clz((int)(r.d + 1u));  // code_rem_bits
+      g.code_shift = v.m + rem_bits;
       g.sp = md.L.shift[kFPending];
       g.sm = md.L.shift[kFRem];
-      g.sr = md.L.shift[kFRem + 1];
-      g.log2_set = a.log2_set;
+      g.set_shift = 32u - a.log2_set;
+      g.set_mask = (1u << a.log2_set) - 1u;
       g.hkeep = md.hkeep;
       g.keys = (unsigned long long)md.table;
       g.links = g.keys + (md.mask + 1ull) * 8ull;
       const ModelDev* mdp = a.models + pt.model;
-      if (v.i0 < v.F)
-        explore_items<BLOCK, GEN, false>(v, r, g, v.i0, v.i1 < v.F ? v.i1 : v.F, set, masks, mdp,
-                                         a.host_tc, sum);
-      if (v.i1 > v.F)
-        explore_items<BLOCK, GEN, true>(v, r, g, v.i0 > v.F ? v.i0 : v.F, v.i1, set, masks, mdp,
-                                        a.host_tc, sum);
+      const auto items = [&](const auto& ends, auto clocks) {
+        if (v.i0 < v.F)
+          explore_items<BLOCK, false, decltype(clocks)::value>(
+              v, ends, g, v.i0, v.i1 < v.F ? v.i1 : v.F, set, masks, mdp, a.host_tc, sum);
+        if (v.i1 > v.F)
+          explore_items<BLOCK, true, decltype(clocks)::value>(
+              v, ends, g, v.i0 > v.F ? v.i0 : v.F, v.i1, set, masks, mdp, a.host_tc, sum);
+      };
+      const auto explore = [&](const auto& ends) {
+        if (T != kNoClock || md.refloor != 0u) items(ends, std::true_type{});
+        else items(ends, std::false_type{});
+      };
+      if constexpr (GEN) explore(general_ends(r));
+      else explore(uniform_ends(r));
     }
-    const unsigned long long w_probes = wave_sum(sum.probes);
-    const uint32_t w_max = (uint32_t)wave_max(sum.max_probe), w_depth = (uint32_t)wave_max(sum.depth);
-    if (lane_id() == 0) {
-      atomicAdd(&sums.states, (unsigned long long)sum.states);
-      atomicAdd(&sums.edges, (unsigned long long)sum.edges);
-      if (sum.edges != sum.states)
-        atomicAdd(&sums.dups, (unsigned long long)(sum.edges - sum.states));
-      if (sum.terms) atomicAdd(&sums.terms, (unsigned long long)sum.terms);
-      atomicAdd(&sums.probes, w_probes);
-      atomicMax(&sums.max_probe, w_max);
-      atomicMax(&sums.depth, w_depth);
-    }
+    // (without a threshold a partition's deepest state is in its last piece)
+    if (sum.last && (v.last || T != kNoClock))
+      sum.depth = max(sum.depth, uniform(depth_of(v, sum.last - 1u, masks)));
     if (tid == 0) {
-      sums.chunks += sum.chunks;
       sums.rounds += v.q1 - v.q0 + 1u;
       sums.pieces += 1u;
       const uint32_t dt = (uint32_t)(__builtin_amdgcn_s_memrealtime() - t0);
@@ -290,6 +375,8 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
       }
     }
   }
+  add_sums(sums, sum);
+  __syncthreads();
   if (a.records) {
     if (tid == 0) sums.t_last = __builtin_amdgcn_s_memrealtime();
     __syncthreads();
