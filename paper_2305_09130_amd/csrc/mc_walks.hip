@@ -15,7 +15,10 @@ namespace mc {
 // One run from the root, choosing uniformly among the successors at every step with
 // the choice of step t drawn from splitmix64(seed ^ splitmix64(t)); successors are
 // ordered by configuration (SELECT) and by unit index (DISPATCH).  A lock-step ADVANCE
-// run has one successor per step; it is taken in one jump that counts its steps.
+// run has one successor per step; it is taken in one jump that counts its steps.  On units
+// of one speed whole rounds are crossed at once as well: with at least m workgroups pending
+// every order of the m dispatches leads through one run to the same all-idle state, and each
+// round takes m + b steps (a draw depends on its step alone, so the later ones are the same).
 
 // Units of unequal speed with no DISPATCH enabled until clock H (the first workgroup end
 // while work is pending, else the last): the ADVANCE steps up to H are one per distinct
@@ -79,6 +82,14 @@ __global__ void k_simulate(QueryArgs a, unsigned long long seed) {
   St x{};
   x.cfg = c;
   x.pending = r.n;
+  bool alike = true;
+  for (int u = 1; u < m; ++u) alike = alike && speed[u] == speed[0];
+  if (alike) {  // 2,048 rounds one dispatch at a time took 2.2 ms
+    const uint32_t rounds = r.n / (uint32_t)m;
+    x.pending -= rounds * (uint32_t)m;
+    x.clock = rounds * speed[0] * r.d;
+    step += (unsigned long long)rounds * ((uint32_t)m + r.b);
+  }
   for (;;) {
     uint32_t freem = 0, busy = 0, brem = 0, bsp = 0;
     bool same = true;
