@@ -1305,6 +1305,9 @@ SwarmPlan swarm_plan(const mc_model* h, uint32_t members, uint32_t bits_log2) {
   return p;
 }
 
+// Most intervals counted before a swarm, one wavefront each (about 20 us for as many).
+constexpr uint64_t kMaxSegments = 1u << 15;
+
 SwarmArgs swarm_args(mc_model* h, const mc_swarm_opts& o, const SwarmPlan& p) {
   SwarmArgs a;
   a.cfgs = h->cfgs;
@@ -1319,6 +1322,23 @@ SwarmArgs swarm_args(mc_model* h, const mc_swarm_opts& o, const SwarmPlan& p) {
   a.bits = reinterpret_cast<uint32_t*>(h->table + p.bits);
   a.out = reinterpret_cast<SwarmMember*>(h->table + p.rec);
   for (int u = 0; u < kMaxCU; ++u) a.speed[u] = h->mh.layout.speed[u];
+  // The counts of units of unequal speed go over the regions past the seeds (frontiers and
+  // trace staging, unused by a swarm), with a count per set of busy units up to four units
+  // where they fit, else for all units busy only.
+  a.seg = nullptr;
+  a.seg_lcm = a.seg_masks = 0u;
+  if (h->mh.hetero) {
+    uint64_t lcm = 1;
+    for (uint32_t u = 0; u < a.m && lcm <= kMaxPeriodLcm; ++u)
+      lcm = std::lcm<uint64_t>(lcm, h->mh.speed[u]);
+    const uint64_t room = h->plan.total - h->plan.seeds;
+    for (const uint64_t masks : {a.m <= 4u ? 1ull << a.m : 1ull, 1ull}) {
+      if (a.seg || lcm * a.n_cfg > kMaxSegments || 4ull * a.n_cfg * lcm * masks > room) continue;
+      a.seg = reinterpret_cast<uint32_t*>(h->ws + h->plan.seeds);
+      a.seg_lcm = (uint32_t)lcm;
+      a.seg_masks = (uint32_t)masks;
+    }
+  }
   return a;
 }
 
@@ -1340,7 +1360,7 @@ int mc_swarm(mc_model* h, const mc_swarm_opts* o, mc_swarm_result* r) {
   h->swarm_members = 0;
   h->swarm_best = false;
   const SwarmArgs a = swarm_args(h, *o, p);
-  HIPCHK(hipMemsetAsync(a.bits, 0, p.total - p.bits, s));
+  if (!swarm_members_in_lds(o->bits_log2)) HIPCHK(hipMemsetAsync(a.bits, 0, p.total - p.bits, s));
   HIPCHK(ev_record(h->ev[4], s));
   HIPCHK(launch_swarm(s, a));
   HIPCHK(ev_record(h->ev[5], s));

@@ -243,7 +243,18 @@ struct SwarmArgs {
   uint32_t* bits;             // members x 2^bits_log2 bits, zero
   SwarmMember* out;           // members records
   uint8_t speed[kMaxCU];      // speed of each unit (1 = full speed)
+  // operation ends counted per interval of a workgroup's duration (k_swarm_segments), or null
+  uint32_t* seg;
+  uint32_t seg_lcm, seg_masks;
+  uint32_t lanes;  // members per wavefront (set by launch_swarm)
 };
+// Members whose bit arrays of 2^bits_log2 bits a wavefront holds in LDS, in a quarter of a
+// CU's 160 KiB (0: one member's array is larger; SwarmArgs::bits is then used, and cleared
+// before the launch).
+inline uint32_t swarm_members_in_lds(uint32_t bits_log2) {
+  const uint32_t n = (40u << 10) >> (bits_log2 - 3u);
+  return n < 64u ? n : 64u;
+}
 hipError_t launch_swarm(hipStream_t st, const SwarmArgs& a);
 // Replays the walk of member seed `mseed` that began at member step `start`, writing the
 // rows (cfg, clock, pending, rem[0..m-1]) of its states root first into `rows` (at most

@@ -6,6 +6,8 @@
 //   k_swarm_replay  one member's walk again, state by state (its counterexample)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "mc_launch.h"
 
 namespace mc {
@@ -163,11 +165,25 @@ __global__ void k_simulate(QueryArgs a, unsigned long long seed) {
 // crossed in one jump that counts their steps, and, with a threshold, stops exactly at
 // the first of them past T.
 
-__device__ __forceinline__ unsigned long long swarm_hash(const St& x, int m) {
-  unsigned long long h = splitmix64((unsigned long long)x.cfg);
+// x mod k for k in 1..8, by way of x mod 840 = lcm(1..8) in 32-bit arithmetic (a 64-bit
+// remainder was most of a dispatch's instructions).
+__device__ __forceinline__ uint32_t small_mod(unsigned long long x, uint32_t k) {
+  constexpr uint32_t kAll = 840u, kFold = (uint32_t)((1ull << 32) % kAll);
+  const uint32_t y = ((uint32_t)(x >> 32) % kAll * kFold + (uint32_t)x % kAll) % kAll;
+  // y + 1/2 is at least half off a multiple of k: far more than the product's error
+  const uint32_t q = (uint32_t)(((float)y + 0.5f) * __builtin_amdgcn_rcpf((float)k));
+  return y - q * k;
+}
+
+// The per-unit loops of a walk run to MU (4 or 8, the least that holds the units), unrolled,
+// so that the times left stay in registers.
+template <int MU>  // h: splitmix64 of the configuration, the same along a walk
+__device__ __forceinline__ unsigned long long swarm_hash(unsigned long long h, const St& x, int m) {
   h = splitmix64(h ^ x.clock);
   h = splitmix64(h ^ x.pending);
-  for (int u = 0; u < m; ++u) h = splitmix64(h ^ x.rem[u]);
+#pragma unroll
+  for (int u = 0; u < MU; ++u)
+    if (u < m) h = splitmix64(h ^ x.rem[u]);
   return h;
 }
 
@@ -177,9 +193,12 @@ struct SwarmView {
   uint32_t k, freem, busy, brem, bsp;
   bool same;
 };
+template <int MU>
 __device__ __forceinline__ SwarmView swarm_view(const St& x, int m, const uint8_t* speed) {
   SwarmView v{0u, 0u, 0u, 0u, 1u, true};
-  for (int u = 0; u < m; ++u) {
+#pragma unroll
+  for (int u = 0; u < MU; ++u) {
+    if (u >= m) continue;
     if (x.rem[u] == 0u) {
       v.freem |= 1u << u;
     } else {
@@ -193,18 +212,76 @@ __device__ __forceinline__ SwarmView swarm_view(const St& x, int m, const uint8_
   return v;
 }
 
+template <int MU>
 __device__ __forceinline__ void swarm_dispatch(St& x, const CfgRec& r, uint32_t freem,
                                                uint32_t pick, int m, const uint8_t* speed) {
-  for (int u = 0; u < m; ++u) {
-    if ((freem >> u) & 1u) {
-      if (pick == 0u) {
-        x.rem[u] = unit_dur<true>(r, speed, u);
-        x.pending -= 1u;
-        return;
+#pragma unroll
+  for (int u = 0; u < MU; ++u)
+    if (((freem >> u) & 1u) && (uint32_t)__popc(freem & ((1u << u) - 1u)) == pick)
+      x.rem[u] = unit_dur<true>(r, speed, u);
+  x.pending -= 1u;
+}
+
+// Operation ends on units of unequal speed, counted once per swarm.  A unit starts its
+// workgroups back to back from clock 0 (dispatch is eager) until none is left, so at clock
+// k d unit u has run (k mod s_u) d of its workgroup, and how many distinct operation ends the
+// units of a mask have in (k d, (k+1) d] depends on k mod lcm(s) alone.  Workgroups end at
+// multiples of d, so a walk crosses an ADVANCE chain by adding these counts, one interval at
+// a time, instead of merging the units' ends step by step: the 4,096-member swarm on
+// matmul32_cu4_s1123 took 177 ms that way, on walks of up to 10^5 steps.
+// a.seg[(c lcm + k) masks + M]: M the busy units (masks = 2^m), or the one count for all
+// units busy (masks = 1).
+__global__ __launch_bounds__(64) void k_swarm_segments(SwarmArgs a) {
+  const uint32_t lane = threadIdx.x, c = blockIdx.x / a.seg_lcm, k = blockIdx.x - c * a.seg_lcm;
+  const CfgRec r = a.cfgs[c];
+  const int m = (int)a.m;
+  uint32_t e0[kMaxCU], lo[kMaxCU], first[kMaxCU + 1];
+  uint32_t total = 0;
+#pragma unroll
+  for (int u = 0; u < kMaxCU; ++u) {
+    first[u] = total;
+    e0[u] = lo[u] = 0u;
+    if (u >= m) continue;
+    const uint32_t sp = a.speed[u];
+    e0[u] = (k % sp) * r.d;
+    lo[u] = ends_upto(r, e0[u] / sp);
+    total += ends_upto(r, (e0[u] + r.d) / sp) - lo[u];
+  }
+  first[kMaxCU] = total;
+  uint32_t count = 0;  // lane M: of mask M (lane 0: of all units where masks = 1)
+  for (uint32_t base = 0; base < total; base += 64u) {
+    const uint32_t i = base + lane;
+    uint32_t tau = 0, unit = 0, lower = 0;  // lower: units of lower index that end at tau
+    if (i < total) {
+      uint32_t eu = e0[0], lu = lo[0], fu = 0, su = a.speed[0];
+#pragma unroll
+      for (int u = 1; u < kMaxCU; ++u)
+        if (u < m && i >= first[u]) {
+          unit = (uint32_t)u;
+          eu = e0[u];
+          lu = lo[u];
+          fu = first[u];
+          su = a.speed[u];
+        }
+      tau = su * end_at(r, lu + (i - fu)) - eu;
+#pragma unroll
+      for (int j = 0; j < kMaxCU; ++j) {
+        if (j >= m || (uint32_t)j >= unit) continue;
+        const uint32_t x = e0[j] + tau, q = x / a.speed[j];
+        if (q * a.speed[j] == x && ends_upto(r, q) != ends_upto(r, q - 1u)) lower |= 1u << j;
       }
-      --pick;
+    }
+    if (a.seg_masks == 1u) {
+      count += (uint32_t)__popcll(__ballot(i < total && lower == 0u));
+    } else {
+      for (uint32_t M = 1; M < a.seg_masks; ++M) {
+        const bool mine = i < total && ((M >> unit) & 1u) && (lower & M) == 0u;
+        const uint32_t n = (uint32_t)__popcll(__ballot(mine));
+        if (lane == M) count += n;
+      }
     }
   }
+  if (lane < a.seg_masks) a.seg[(unsigned long long)blockIdx.x * a.seg_masks + lane] = count;
 }
 
 // A walk's ADVANCE chain on units that are not in lock step: from x on every state has
@@ -214,12 +291,13 @@ __device__ __forceinline__ void swarm_dispatch(St& x, const CfgRec& r, uint32_t 
 // operation-end lookup per unit that ends there.  t counts one model step per state, as
 // one ADVANCE at a time would.  With a threshold it stops on the first state past T and
 // returns true (the walk ends there).  x is left on the chain's last state.
+template <int MU>
 __device__ bool swarm_advance_run(St& x, const CfgRec& r, int m, const uint8_t* speed,
                                   bool prune, uint32_t T, unsigned long long& t) {
-  uint32_t nx[kMaxCU], kk[kMaxCU], wend[kMaxCU], sp[kMaxCU];
+  uint32_t nx[MU], kk[MU], wend[MU], sp[MU];
   uint32_t busy = 0;
 #pragma unroll
-  for (int u = 0; u < kMaxCU; ++u) {
+  for (int u = 0; u < MU; ++u) {
     nx[u] = 0xFFFFFFFFu;
     kk[u] = 0u;
     wend[u] = 0u;
@@ -238,12 +316,12 @@ __device__ bool swarm_advance_run(St& x, const CfgRec& r, int m, const uint8_t* 
   for (;;) {
     uint32_t tmin = 0xFFFFFFFFu;
 #pragma unroll
-    for (int u = 0; u < kMaxCU; ++u) tmin = nx[u] < tmin ? nx[u] : tmin;
+    for (int u = 0; u < MU; ++u) tmin = nx[u] < tmin ? nx[u] : tmin;
     x.clock = tmin;
     ++t;
     bool freed = false;
 #pragma unroll
-    for (int u = 0; u < kMaxCU; ++u) {
+    for (int u = 0; u < MU; ++u) {
       if (nx[u] != tmin) continue;
       if (++kk[u] == r.b) {
         busy &= ~(1u << u);
@@ -260,17 +338,61 @@ __device__ bool swarm_advance_run(St& x, const CfgRec& r, int m, const uint8_t* 
     if (!busy || (freed && x.pending)) break;
   }
 #pragma unroll
-  for (int u = 0; u < kMaxCU; ++u) x.rem[u] = ((busy >> u) & 1u) ? wend[u] - x.clock : 0u;
+  for (int u = 0; u < MU; ++u) x.rem[u] = ((busy >> u) & 1u) ? wend[u] - x.clock : 0u;
   return past;
 }
 
-__global__ __launch_bounds__(256) void k_swarm(SwarmArgs a) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+// The same chain by the counts of k_swarm_segments, while those hold the busy units: x.clock
+// is a multiple of d.  Returns whether the chain is at its end (else the units still busy, or
+// the interval in which the clock passes T, are left to swarm_advance_run).
+template <int MU>
+__device__ __forceinline__ bool swarm_jump(St& x, const CfgRec& r, const SwarmArgs& a,
+                                           unsigned long long& t) {
+  const uint32_t all = (1u << a.m) - 1u;
+  uint32_t k = x.clock / r.d;
+  const uint32_t* seg = a.seg + (unsigned long long)x.cfg * a.seg_lcm * a.seg_masks;
+  uint32_t at = k % a.seg_lcm;
+  for (;;) {
+    uint32_t busy = 0, least = 0xFFFFFFFFu;
+#pragma unroll
+    for (int u = 0; u < MU; ++u)
+      if (u < (int)a.m && x.rem[u]) {
+        busy |= 1u << u;
+        least = x.rem[u] < least ? x.rem[u] : least;
+      }
+    if (!busy) return true;
+    if ((a.seg_masks == 1u && busy != all) || (a.prune && x.clock + least > a.T)) return false;
+    for (uint32_t left = least; left; left -= r.d) {  // least is a multiple of d
+      t += seg[at * a.seg_masks + (a.seg_masks == 1u ? 0u : busy)];
+      at = at + 1u == a.seg_lcm ? 0u : at + 1u;
+    }
+    x.clock += least;
+#pragma unroll
+    for (int u = 0; u < MU; ++u)
+      if (u < (int)a.m && x.rem[u]) x.rem[u] -= least;
+    if (x.pending) return true;  // a unit fell idle
+  }
+}
+
+// LDS: the members' bit arrays are in LDS (swarm_members_in_lds), cleared here, else in a.bits.
+template <int MU, bool LDS>
+__global__ __launch_bounds__(64) void k_swarm(SwarmArgs a) {
+  extern __shared__ uint32_t lds_bits[];
+  if constexpr (LDS) {
+    const uint32_t n4 = a.lanes << (a.bits_log2 - 7u);  // 16-byte units
+    for (uint32_t j = threadIdx.x; j < n4; j += 64u)
+      reinterpret_cast<uint4*>(lds_bits)[j] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+  }
+  if (threadIdx.x >= a.lanes) return;
+  const uint32_t i = blockIdx.x * a.lanes + threadIdx.x;
   if (i >= a.members) return;
   const int m = (int)a.m;
   const unsigned long long seed = splitmix64(a.seed + i);
   const unsigned long long B = 1ull << a.bits_log2;
-  uint32_t* bits = a.bits + (unsigned long long)i * (B >> 5);
+  uint32_t* bits;
+  if constexpr (LDS) bits = lds_bits + threadIdx.x * (uint32_t)(B >> 5);
+  else bits = a.bits + (unsigned long long)i * (B >> 5);
   SwarmMember rec;
   rec.walks = rec.trails = rec.best_walk_start = 0ull;
   rec.first_step = ~0ull;
@@ -289,18 +411,37 @@ __global__ __launch_bounds__(256) void k_swarm(SwarmArgs a) {
     St x{};
     x.cfg = c;
     x.pending = r.n;
-    for (;;) {  // x was just reached by a transition
-      if (a.prune && x.clock > a.T) break;
-      const SwarmView v = swarm_view(x, m, a.speed);
-      if (v.k != 1u) {
-        const unsigned long long h = swarm_hash(x, m);
-        const unsigned long long p0 = h & (B - 1ull), p1 = (h >> 32) & (B - 1ull);
-        const uint32_t w0 = bits[p0 >> 5], w1 = bits[p1 >> 5];
-        const uint32_t m0 = 1u << (p0 & 31ull), m1 = 1u << (p1 & 31ull);
-        if ((w0 & m0) && (w1 & m1)) break;  // visited
-        bits[p0 >> 5] = w0 | m0;
-        bits[p1 >> 5] = bits[p1 >> 5] | m1;
+    // One instant a time, so that the walks of a wavefront stay together: the states at x's
+    // clock, each just reached by a transition (a state with one successor has no place in
+    // the bitstate), through the dispatches there, then the steps to the next instant.
+    const unsigned long long h0 = splitmix64((unsigned long long)c);
+    bool over = false;
+    while (!over) {
+      SwarmView v;
+      for (;;) {
+        v = swarm_view<MU>(x, m, a.speed);
+        if (a.prune && x.clock > a.T) {
+          over = true;
+          break;
+        }
+        if (v.k != 1u) {
+          const unsigned long long h = swarm_hash<MU>(h0, x, m);
+          const unsigned long long p0 = h & (B - 1ull), p1 = (h >> 32) & (B - 1ull);
+          const uint32_t w0 = bits[p0 >> 5], w1 = bits[p1 >> 5];
+          const uint32_t m0 = 1u << (p0 & 31ull), m1 = 1u << (p1 & 31ull);
+          if ((w0 & m0) && (w1 & m1)) {  // visited
+            over = true;
+            break;
+          }
+          bits[p0 >> 5] = w0 | m0;
+          bits[p1 >> 5] = (p1 >> 5) == (p0 >> 5) ? w0 | m0 | m1 : w1 | m1;
+        }
+        if (!(x.pending && v.freem)) break;
+        const uint32_t pick = small_mod(splitmix64(seed ^ splitmix64(t)), v.k);
+        ++t;
+        swarm_dispatch<MU>(x, r, v.freem, pick, m, a.speed);
       }
+      if (over) break;
       if (v.k == 0u) {  // a new terminal: a trail
         ++rec.trails;
         if (rec.first_step == ~0ull) {
@@ -316,12 +457,6 @@ __global__ __launch_bounds__(256) void k_swarm(SwarmArgs a) {
         }
         break;
       }
-      if (x.pending && v.freem) {  // DISPATCH
-        const uint32_t pick = (uint32_t)(splitmix64(seed ^ splitmix64(t)) % v.k);
-        ++t;
-        swarm_dispatch(x, r, v.freem, pick, m, a.speed);
-        continue;
-      }
       if (v.same) {  // a lock-step run to its end, one transition per operation end
         // ends of the busy units' grid bsp*E after the elapsed time e0
         const uint32_t e0 = v.bsp * r.d - v.brem;
@@ -334,10 +469,12 @@ __global__ __launch_bounds__(256) void k_swarm(SwarmArgs a) {
         }
         t += (unsigned long long)(r.b - idx0);
         x.clock += v.brem;
-        for (int u = 0; u < m; ++u) x.rem[u] = 0u;
+#pragma unroll
+        for (int u = 0; u < MU; ++u) x.rem[u] = 0u;
         continue;
       }
-      if (swarm_advance_run(x, r, m, a.speed, a.prune != 0u, a.T, t)) break;
+      if (a.seg && swarm_jump<MU>(x, r, a, t)) continue;
+      if (swarm_advance_run<MU>(x, r, m, a.speed, a.prune != 0u, a.T, t)) break;
     }
   }
   rec.steps = t;
@@ -374,12 +511,12 @@ __global__ void k_swarm_replay(SwarmArgs a, Ctrl* ctrl, unsigned long long seed,
   x.pending = r.n;
   put(x, false);
   for (;;) {
-    const SwarmView v = swarm_view(x, m, a.speed);
+    const SwarmView v = swarm_view<kMaxCU>(x, m, a.speed);
     if (v.k == 0u || bad) break;
     if (x.pending && v.freem) {
       const uint32_t pick = (uint32_t)(splitmix64(seed ^ splitmix64(t)) % v.k);
       ++t;
-      swarm_dispatch(x, r, v.freem, pick, m, a.speed);
+      swarm_dispatch<kMaxCU>(x, r, v.freem, pick, m, a.speed);
     } else {
       advance_once(x, r, m, a.speed);
       ++t;
@@ -393,7 +530,25 @@ __global__ void k_swarm_replay(SwarmArgs a, Ctrl* ctrl, unsigned long long seed,
 // ---- launch helpers (host) ------------------------------------------------------------
 
 hipError_t launch_swarm(hipStream_t st, const SwarmArgs& a) {
-  hipLaunchKernelGGL(k_swarm, dim3((a.members + 255u) / 256u), dim3(256), 0, st, a);
+  if (a.seg)
+    hipLaunchKernelGGL(k_swarm_segments, dim3(a.n_cfg * a.seg_lcm), dim3(64), 0, st, a);
+  // A member's walks are one serial chain, and a wavefront takes every branch that one of its
+  // members takes: up to 1,024 wavefronts (one per SIMD) hold as few members each as that
+  // allows.  Bit arrays of which four wavefronts' fit in a CU's LDS go there (a lookup in HBM
+  // is a 1-2 us link of the chain), with more wavefronts where there are more members.
+  SwarmArgs q = a;
+  const uint32_t spread = std::min<uint32_t>(64u, std::max<uint32_t>(1u, (a.members + 4095u) / 4096u));
+  const uint32_t held = swarm_members_in_lds(a.bits_log2);
+  q.lanes = held ? std::min(spread, held) : spread;
+  const uint32_t lds = held ? q.lanes << (a.bits_log2 - 3u) : 0u;
+  const dim3 grid((a.members + q.lanes - 1u) / q.lanes);
+  if (a.m <= 4u) {
+    if (held) hipLaunchKernelGGL((k_swarm<4, true>), grid, dim3(64), lds, st, q);
+    else hipLaunchKernelGGL((k_swarm<4, false>), grid, dim3(64), 0, st, q);
+  } else {
+    if (held) hipLaunchKernelGGL((k_swarm<8, true>), grid, dim3(64), lds, st, q);
+    else hipLaunchKernelGGL((k_swarm<8, false>), grid, dim3(64), 0, st, q);
+  }
   return hipGetLastError();
 }
 
