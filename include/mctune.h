@@ -494,8 +494,10 @@ typedef struct mc_engine_opts {
     uint32_t max_cfg;        /* largest configuration count a query may have (>= 1) */
     uint32_t block;          /* threads per workgroup: 256, 512, 1024 (0 = 512) */
     uint32_t slice;          /* super-step levels per partition per step while queries
-                                wait for memory (0 = no limit); with none waiting a
-                                step runs its partitions to the end */
+                                wait for memory (0 = no limit; a model explored in pieces
+                                of rounds: about 65,536 states per level, in whole
+                                partitions); with none waiting a step runs its
+                                partitions to the end */
     uint32_t chunk;          /* states per super-step batch (0 = 2 x block x lane_items) */
     uint32_t grid;           /* persistent workgroups per step (0 = up to 1024) */
     float load_factor;       /* visited-set load factor (0 = 0.5) */

@@ -106,6 +106,10 @@ struct Resident {
   std::string key;  // the descriptor, canonically
   ModelHost mh;
   std::vector<PartPlan> parts;  // partitions of an exploration from scratch
+  // explored by the round engine (units alike, one-word keys, a slot per generated state):
+  // its plan, every slot of which stays what it is through the model's residence
+  bool rounds = false;
+  RoundPlan rplan;
   size_t off = 0, bytes = 0;    // arena region
   size_t cfg_off = 0, seed_off = 0, pstate_off = 0, table_off = 0;
   uint64_t slots = 0;
@@ -128,6 +132,8 @@ struct Query {
   uint64_t resident = 0;     // the Resident's id
   int mode = kFresh;
   uint32_t n_parts = 0;      // partitions of its exploration
+  RoundPlan rest;            // round engine: partitions not yet launched
+  size_t next = 0;           // ... the first of them
   uint64_t submit_ns = 0, admit_ns = 0, done_ns = 0;
   uint32_t steps = 0;
   mc_query_result res{};
@@ -203,6 +209,8 @@ struct mc_engine {
   uint32_t* htc = nullptr;                  // pinned
   unsigned int* hny = nullptr;              // pinned
   ModelDev* hmd = nullptr;                  // pinned staging of descriptors
+  ModelDev* hrounds = nullptr;              // pinned: descriptors of the round engine's models
+  RoundPart* hparts = nullptr;              // pinned: partitions of its launch
   unsigned long long* hcount = nullptr;     // pinned
   uint64_t launches = 0;
   Fork fork;
@@ -226,7 +234,13 @@ ModelDev make_dev(mc_engine* e, const Resident* r, const Query* q, uint32_t n_pa
   d.T = q->T;
   d.max_clock = r->mh.max_clock;
   d.n_parts = n_parts;
-  d.pstate = reinterpret_cast<PartState*>(g + r->pstate_off);
+  if (r->rounds) {
+    d.tslot = reinterpret_cast<uint32_t*>(g + r->seed_off);
+    d.index = (uint32_t)r->slot_idx;
+    d.used = (uint32_t)r->rplan.used;
+  } else {
+    d.pstate = reinterpret_cast<PartState*>(g + r->pstate_off);
+  }
   // a continued exploration expands the states it finds again below T_done
   d.refloor = q->mode == kResume ? r->T_done + 1u : 0u;
   return d;
@@ -296,6 +310,60 @@ void finish(mc_engine* e, Query* q) {
                                       : MC_REUSE_ANSWERED;
   q->res.done = 1;
   (void)e;
+}
+
+}  // namespace
+
+namespace {
+
+// Items of a model's pieces that one step explores per level of a time slice (a step over a
+// whole model of 10^6 states takes a few microseconds).
+constexpr uint64_t kSliceItems = 1u << 16;
+
+// One launch of the round engine over the partitions of its active queries; with a slice, up
+// to slice x kSliceItems items of each (at least one partition), the rest in later steps.
+// `behind`: the partitions of the other kernel's launch, which come first in the buffer.
+int launch_round_parts(mc_engine* e, uint32_t slice, size_t behind) {
+  RoundPlan now;
+  uint64_t items = 0;
+  bool general = false;
+  for (Resident* r : e->slots) {
+    if (!r || !r->busy || !r->rounds) continue;
+    Query* q = r->busy;
+    general |= r->mh.general;
+    uint64_t mine = 0;
+    while (q->next < q->rest.parts.size() && (!slice || !mine || mine < slice * kSliceItems)) {
+      now.parts.push_back(q->rest.parts[q->next]);
+      now.items.push_back(q->rest.items[q->next]);
+      now.end_group.push_back(q->rest.end_group[q->next]);
+      mine += q->rest.items[q->next++];
+    }
+    items += mine;
+  }
+  if (now.parts.empty()) return MC_OK;
+  hipStream_t s = e->stream;
+  const uint32_t piece = auto_piece(items);
+  const uint64_t n = number_pieces(&now, piece);
+  if (n > 0xFFFF0000ull) return MC_E_INVAL;
+  std::memcpy(e->hparts, now.parts.data(), sizeof(RoundPart) * now.parts.size());
+  RoundPart* parts = reinterpret_cast<RoundPart*>(e->base + e->parts_off[e->cur]) + behind;
+  unsigned int* head = reinterpret_cast<unsigned int*>(e->base + e->head_off) + 3;
+  HIPCHK(hipMemcpyAsync(parts, e->hparts, sizeof(RoundPart) * now.parts.size(),
+                        hipMemcpyHostToDevice, s));
+  RoundQueue rq;
+  std::memset(&rq, 0, sizeof(rq));
+  rq.models = reinterpret_cast<const ModelDev*>(e->base + e->md_off);
+  rq.parts = parts;
+  rq.n_parts = (uint32_t)now.parts.size();
+  rq.n_pieces = (uint32_t)n;
+  rq.piece = piece;
+  rq.log2_set = set_log2(piece);
+  rq.head = head;
+  const uint32_t grid = std::min<uint32_t>(rq.n_pieces, e->opts.grid ? e->opts.grid : 1024u);
+  if (rq.n_pieces > grid) HIPCHK(hipMemsetAsync(head, 0, 4, s));
+  HIPCHK(launch_rounds(s, grid, 256u, rq, general));
+  ++e->launches;
+  return MC_OK;
 }
 
 }  // namespace
@@ -371,6 +439,10 @@ int mc_engine_create(const mc_engine_opts* o, void* dev_buf, size_t buf_bytes, v
                       hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&e->hcount), 8ull * A, hipHostMallocDefault) !=
             hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&e->hrounds), sizeof(ModelDev) * A,
+                      hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&e->hparts), sizeof(RoundPart) * maxparts,
+                      hipHostMallocDefault) != hipSuccess ||
         e->fork.create() != hipSuccess) {
       (void)hipGetLastError();
       mc_engine_destroy(e);
@@ -394,6 +466,8 @@ int mc_engine_destroy(mc_engine* e) {
   if (e->hny) (void)hipHostFree(e->hny);
   if (e->hmd) (void)hipHostFree(e->hmd);
   if (e->hcount) (void)hipHostFree(e->hcount);
+  if (e->hrounds) (void)hipHostFree(e->hrounds);
+  if (e->hparts) (void)hipHostFree(e->hparts);
   e->fork.destroy();
   delete e;
   return MC_OK;
@@ -455,6 +529,7 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
     std::vector<PartPlan> plan;  // fresh or resumed exploration
   };
   std::vector<Start> starts;
+  std::vector<Query*> round_starts;  // those that the round engine explores
   std::vector<Query*> counts;  // check queries answered by a scan of the set
   std::deque<Query*> still;
   bool blocked = false;  // a query needing new memory did not fit: later ones wait too
@@ -515,6 +590,7 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
           r->parts.clear();
           plan_parts(r->mh, target, &r->parts);
         }
+        if (rounds_model(r->mh)) round_plan(r->mh, 0, r->parts, &r->rplan);
         std::stable_sort(r->parts.begin(), r->parts.end(),
                          [](const PartPlan& a, const PartPlan& b) { return a.states > b.states; });
         const uint64_t need = !e->opts.no_reuse || q->kind == MC_QUERY_MIN_TIME
@@ -523,6 +599,7 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
         r->bytes = footprint(r->mh, need, std::max<size_t>(r->parts.size(), r->mh.n_cfg),
                              e->opts.load_factor, &r->slots, &r->cfg_off, &r->seed_off,
                              &r->pstate_off, &r->table_off);
+        r->rounds = !r->rplan.parts.empty() && r->rplan.used <= r->slots;
         if (!place(e, r)) {
           q->mh = std::move(r->mh);
           delete r;
@@ -558,11 +635,22 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
       r->busy = q;
       if (r->explored && resumable(r->mh)) {
         q->mode = kResume;
+      } else {
+        q->mode = kFresh;
+      }
+      if (r->rounds) {
+        // the rounds that hold a clock past T_done (a fresh exploration: any) and within T
+        q->rest = RoundPlan{};
+        q->next = 0;
+        trim_rounds(r->mh, r->rplan, q->mode == kResume ? r->T_done + 1ull : 0,
+                    q->kind == MC_QUERY_CHECK ? q->T : ~0ull, &q->rest);
+        for (RoundPart& x : q->rest.parts) x.model = (uint32_t)r->slot_idx;
+        round_starts.push_back(q);
+      } else if (q->mode == kResume) {
         Start st{q, r, {}};
         plan_resume(r->mh, r->T_done, r->parts, &st.plan);
         starts.push_back(std::move(st));
       } else {
-        q->mode = kFresh;
         starts.push_back(Start{q, r, r->parts});
       }
     }
@@ -623,20 +711,28 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
       HIPCHK(launch_resume_models(s, stage, (uint32_t)resume_md.size(), nullptr, 0));
     HIPCHK(hipStreamSynchronize(s));
   }
+  if (!round_starts.empty()) {
+    for (size_t i = 0; i < round_starts.size(); ++i)
+      e->hrounds[i] = make_dev(e, e->by_id[round_starts[i]->resident], round_starts[i], 0u);
+    HIPCHK(launch_rounds_begin_staged(s, e->hrounds, (uint32_t)round_starts.size(),
+                                      reinterpret_cast<ModelDev*>(e->base + e->md_off)));
+  }
   // counts of check queries answered from a resident set: states with clock <= T
+  if (!counts.empty())
+    HIPCHK(hipMemsetAsync(e->base + e->count_off, 0, 8ull * e->opts.max_active, s));
   for (Query* q : counts) {
     Resident* r = e->by_id[q->resident];
     unsigned long long* out =
         reinterpret_cast<unsigned long long*>(e->base + e->count_off) + r->slot_idx;
-    HIPCHK(hipMemsetAsync(out, 0, 8, s));
+    const uint64_t slots = r->rounds ? r->rplan.used : r->slots;
     const unsigned char* table = e->base + e->arena_off + r->off + r->table_off;
     const CfgRec* cfgs = reinterpret_cast<const CfgRec*>(e->base + e->arena_off + r->off +
                                                          r->cfg_off);
     hipError_t he;
     switch (r->mh.W) {
-      case 1: he = launch_count_le<1>(s, table, r->slots, r->mh.layout, cfgs, q->T, out); break;
-      case 2: he = launch_count_le<2>(s, table, r->slots, r->mh.layout, cfgs, q->T, out); break;
-      default: he = launch_count_le<4>(s, table, r->slots, r->mh.layout, cfgs, q->T, out); break;
+      case 1: he = launch_count_le<1>(s, table, slots, r->mh.layout, cfgs, q->T, out); break;
+      case 2: he = launch_count_le<2>(s, table, slots, r->mh.layout, cfgs, q->T, out); break;
+      default: he = launch_count_le<4>(s, table, slots, r->mh.layout, cfgs, q->T, out); break;
     }
     HIPCHK(he);
   }
@@ -652,6 +748,8 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
   // per slice (a query waiting for its model's running query gains nothing from slices)
   const uint32_t slice = wait_memory ? e->opts.slice : 0u;
   const bool launch = any_active && !e->pending_parts.empty();
+  const int rrc = launch_round_parts(e, slice, launch ? e->pending_parts.size() : 0u);
+  if (rrc) return rrc;
   if (launch) {
     const int cur = e->cur;
     Part* parts = reinterpret_cast<Part*>(e->base + e->parts_off[cur]);
@@ -677,7 +775,7 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
                           hipMemcpyHostToDevice, s));
     unsigned int* head = reinterpret_cast<unsigned int*>(e->base + e->head_off);
     unsigned int* ny = reinterpret_cast<unsigned int*>(e->base + e->nyield_off);
-    HIPCHK(hipMemsetAsync(head, 0, 16, s));
+    HIPCHK(hipMemsetAsync(head, 0, 12, s));
     HIPCHK(hipMemsetAsync(ny, 0, 4, s));
     const uint32_t li = e->opts.lane_items;  // 0: per key width
     PartQueue pq[3];
@@ -741,7 +839,8 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
     const uint32_t* tc = e->htc + (size_t)e->opts.max_cfg * i;
     mc_query_result& res = q->res;
     const bool failed = c->error != 0u;
-    if (c->parts_done < q->n_parts && !failed) continue;
+    const bool done = r->rounds ? q->next == q->rest.parts.size() : c->parts_done >= q->n_parts;
+    if (!done && !failed) continue;
     res.status = dev_error_code(c->error);
     res.states = c->states;
     res.levels = c->max_depth + 1;
@@ -832,7 +931,12 @@ int engine_trace_w(mc_engine* e, Resident* r, uint32_t cfg, uint32_t clock,
   int rc = MC_OK;
   Ctrl* hc = reinterpret_cast<Ctrl*>(e->hctrl);
   std::vector<uint64_t> keys;
-  if (launch_find<W>(s, q, reinterpret_cast<const unsigned long long*>(words)) != hipSuccess ||
+  if (r->rounds) {  // the terminal's slot is known
+    q.tslot = reinterpret_cast<const uint32_t*>(g + r->seed_off);
+    q.target = cfg;
+  }
+  if ((!r->rounds &&
+       launch_find<W>(s, q, reinterpret_cast<const unsigned long long*>(words)) != hipSuccess) ||
       launch_chase<W>(s, q, buf, (uint32_t)cap) != hipSuccess ||
       hipMemcpyAsync(hc, q.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess) {

@@ -84,6 +84,8 @@ struct ModelDev {
                       // walk reaches the new states past it (0 = a fresh exploration)
   uint32_t* tslot;    // round engine: slot of each configuration's terminal (else null:
                       // the model is not explored by the round engine)
+  uint32_t index;     // round engine, staged descriptors: its place in the models' array
+  uint32_t used;      // ... and the slots of its plan, cleared before a fresh exploration
 };
 
 // One partition of a persistent launch: rounds [r0, r1) of one configuration's subgraph
@@ -153,6 +155,11 @@ hipError_t launch_rounds_begin(hipStream_t st, const ModelDev& md, ModelDev* dst
                                unsigned int* head);
 hipError_t launch_rounds_begin_models(hipStream_t st, const ModelDev* models, uint32_t n,
                                       unsigned int* head);
+// The same for models whose descriptors the host staged (pinned memory) for a round engine
+// that continues or starts them: each is written to models[index]; the slots of those that
+// start (refloor 0) are cleared, so that a scan of the set finds only states.
+hipError_t launch_rounds_begin_staged(hipStream_t st, const ModelDev* staged, uint32_t n,
+                                      ModelDev* models);
 // general: some configuration has waves or two-operation periods.
 hipError_t launch_rounds(hipStream_t st, uint32_t grid, uint32_t block, const RoundQueue& q,
                          bool general);

@@ -437,6 +437,40 @@ __global__ __launch_bounds__(256) void k_rounds_begin_models(const ModelDev* mod
   if (md.tslot) begin_model(md);
 }
 
+// Staged descriptors: block (0, y) begins model y, every block clears a share of its slots
+// but for the root's and the SELECT states', which block (0, y) writes.
+__global__ __launch_bounds__(256) void k_rounds_begin_staged(const ModelDev* staged,
+                                                             ModelDev* models) {
+  __shared__ union {
+    ModelDev md;
+    uint32_t words[sizeof(ModelDev) / 4];
+  } s;
+  const uint32_t* from = reinterpret_cast<const uint32_t*>(staged + blockIdx.y);
+  if (threadIdx.x < sizeof(ModelDev) / 4)
+    s.words[threadIdx.x] =
+        __hip_atomic_load(from + threadIdx.x, __ATOMIC_RELAXED, kScopeSystem);
+  __syncthreads();
+  const ModelDev& md = s.md;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < sizeof(ModelDev) / 4)
+      reinterpret_cast<uint32_t*>(models + md.index)[threadIdx.x] = s.words[threadIdx.x];
+    if (md.refloor) {
+      if (threadIdx.x == 0) {  // counters and clocks run on
+        md.ctrl->parts_done = 0u;
+        md.ctrl->bound = md.T;
+        md.ctrl->violated = 0u;
+      }
+    } else {
+      begin_model(md);
+    }
+  }
+  if (md.refloor) return;
+  unsigned long long* keys = reinterpret_cast<unsigned long long*>(md.table);
+  for (uint32_t i = 1u + md.n_cfg + blockIdx.x * 256u + threadIdx.x; i < md.used;
+       i += gridDim.x * 256u)
+    keys[i] = kEmptyWord;
+}
+
 // ---- launch helpers (host) ------------------------------------------------------------
 
 hipError_t launch_rounds_begin(hipStream_t st, const ModelDev& md, ModelDev* dst,
@@ -448,6 +482,13 @@ hipError_t launch_rounds_begin(hipStream_t st, const ModelDev& md, ModelDev* dst
 hipError_t launch_rounds_begin_models(hipStream_t st, const ModelDev* models, uint32_t n,
                                       unsigned int* head) {
   hipLaunchKernelGGL(k_rounds_begin_models, dim3(n), dim3(256), 0, st, models, head);
+  return hipGetLastError();
+}
+
+hipError_t launch_rounds_begin_staged(hipStream_t st, const ModelDev* staged, uint32_t n,
+                                      ModelDev* models) {
+  static_assert(sizeof(ModelDev) / 4 <= 256, "one thread per word");
+  hipLaunchKernelGGL(k_rounds_begin_staged, dim3(64, n), dim3(256), 0, st, staged, models);
   return hipGetLastError();
 }
 
