@@ -152,6 +152,7 @@ hipError_t ev_ms(float* ms, hipEvent_t a, hipEvent_t b) {
 
 }  // namespace
 
+constexpr uint32_t kTraceWords = 1u << 14;  // key words of a counterexample kept pinned
 constexpr uint32_t kRoundsGrid = 1024;  // four workgroups of 33 KiB LDS on each of 256 CUs
 
 enum { kQueryNone = 0, kQueryMin = 1, kQueryCheck = 2 };
@@ -222,6 +223,7 @@ struct mc_model {
   RoundPlan rplan;
   uint32_t* tslot = nullptr;
   bool on_rounds = false;
+  uint64_t* trace_words = nullptr;  // pinned, kTraceWords (pooled handles)
   RoundRecord* records = nullptr;  // pinned, kRoundsGrid entries (pooled handles)
   unsigned char* stage_parts = nullptr;  // pinned staging of a plan, or null
   // unpooled binding (the static scratch): host staging in ordinary memory, no events
@@ -751,27 +753,51 @@ int trace_w(mc_model* h, uint32_t cfg, uint32_t clock) {
   uint64_t words[4];
   encode_key_host(h->mh.layout, fields, words);
   QueryArgs q = make_args(h, false, 0);
+  TraceOut t{h->trace_buf, (uint32_t)h->plan.trace_cap};
+  if (h->trace_words) {  // pooled handles: paths of up to kTraceWords / W states need no copy
+    t.host_words = kTraceWords;
+    t.host = reinterpret_cast<unsigned long long*>(h->trace_words);
+    t.host_res = h->hpoll + 8;
+  }
   if (h->on_rounds) {
     q.tslot = h->tslot;
     q.target = cfg;
+    HIPCHK(launch_round_path(s, q, t, h->mh.general));
   } else {
     HIPCHK(launch_find<W>(s, q, reinterpret_cast<const unsigned long long*>(words)));
+    HIPCHK(launch_chase<W>(s, q, t));
   }
-  HIPCHK(launch_chase<W>(s, q, h->trace_buf, (uint32_t)h->plan.trace_cap));
-  HIPCHK(hipMemcpyAsync(h->hctrl, h->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  if (h->hctrl->target_slot == kParentNone) return MC_E_STATE;
-  if (h->hctrl->error == kDevErrTrace) return MC_E_DEVICE;
-  const uint32_t n = h->hctrl->trace_len;
-  std::vector<uint64_t> keys((size_t)n * W);
-  if (n)
-    HIPCHK(hipMemcpyAsync(keys.data(), h->trace_buf, 8ull * W * n, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  uint32_t target, n, bad;
+  if (t.host_res) {
+    HIPCHK(hipStreamSynchronize(s));
+    target = t.host_res[0];
+    n = t.host_res[1];
+    bad = t.host_res[2];
+  } else {
+    HIPCHK(hipMemcpyAsync(h->hctrl, h->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    target = h->hctrl->target_slot;
+    n = h->hctrl->trace_len;
+    bad = h->hctrl->error == kDevErrTrace ? 1u : 0u;
+  }
+  if (target == kParentNone) return MC_E_STATE;
+  if (bad) return MC_E_DEVICE;
+  const uint64_t n_words = (uint64_t)n * W;
+  std::vector<uint64_t> rest;  // the words past the pinned ones
+  if (n_words > t.host_words) {
+    rest.resize(n_words - t.host_words);
+    HIPCHK(hipMemcpyAsync(rest.data(), h->trace_buf + t.host_words, 8ull * rest.size(),
+                          hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+  }
   const uint32_t m = h->mh.m, S = 3 + m;
-  h->trace_rows.assign((size_t)n * S, 0);
+  h->trace_rows.resize((size_t)n * S);
   for (uint32_t i = 0; i < n; ++i) {
     uint64_t w[4] = {0, 0, 0, 0};
-    for (int j = 0; j < W; ++j) w[j] = keys[(size_t)(n - 1 - i) * W + j];
+    for (int j = 0; j < W; ++j) {
+      const uint64_t at = (uint64_t)(n - 1 - i) * W + j;
+      w[j] = at < t.host_words ? h->trace_words[at] : rest[at - t.host_words];
+    }
     uint32_t f[kFields];
     decode_key_host(h->mh.layout, w, f, h->mh.cfgs.data());
     uint32_t* row = &h->trace_rows[(size_t)i * S];
@@ -970,7 +996,8 @@ int install(mc_model* h, Loaded& L) {
   // one staging block: counters, poll words, descriptor, clocks and, when small, the
   // staging of the uploads below
   static_assert(sizeof(Ctrl) <= 256 && sizeof(ModelDev) <= 256, "staging block layout");
-  const size_t rec_off = 768, tc_off = rec_off + sizeof(RoundRecord) * kRoundsGrid;
+  const size_t rec_off = 768, trace_off = rec_off + sizeof(RoundRecord) * kRoundsGrid;
+  const size_t tc_off = trace_off + (h->pooled ? 8ull * kTraceWords : 0u);
   const size_t up_off = align_up(tc_off + 4ull * h->mh.n_cfg);
   const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg, part_bytes = sizeof(Part) * h->n_parts;
   const bool stage = cfg_bytes + part_bytes <= (4u << 20);
@@ -994,6 +1021,7 @@ int install(mc_model* h, Loaded& L) {
   // the stop request is a word the kernels read at system scope: pinned memory only
   h->habort = h->pooled ? reinterpret_cast<unsigned int*>(blk + 256 + 128) : nullptr;
   if (h->habort) __atomic_store_n(h->habort, 0u, __ATOMIC_RELEASE);
+  h->trace_words = h->pooled ? reinterpret_cast<uint64_t*>(blk + trace_off) : nullptr;
   h->records = h->pooled ? reinterpret_cast<RoundRecord*>(blk + rec_off) : nullptr;
   h->hmd = reinterpret_cast<ModelDev*>(blk + 512);
   h->tc_host = reinterpret_cast<uint32_t*>(blk + tc_off);

@@ -22,8 +22,20 @@ struct QueryArgs {
   uint32_t max_clock;       // bound of the packed clock field
   uint32_t hkeep;           // bits of the key hash kept (0 = all; testing only)
   // after the round engine: the terminal's slot per configuration, and the one asked for
+  // (launch_round_path)
   const uint32_t* tslot = nullptr;
   uint32_t target = 0;
+};
+
+// Where a counterexample's keys go, terminal first: at most cap of them to `out` (device),
+// the first host_words words of them to `host` instead (pinned memory, or null with 0 words);
+// the target's slot, the path's length and whether it is bad go to host_res[0..2] if given.
+struct TraceOut {
+  unsigned long long* out;
+  uint32_t cap;
+  uint32_t host_words = 0;
+  unsigned long long* host = nullptr;
+  uint32_t* host_res = nullptr;
 };
 
 // Keys each thread of the persistent kernel inserts per round trip: 1 or 2 as asked,
@@ -160,6 +172,8 @@ hipError_t launch_rounds_begin_models(hipStream_t st, const ModelDev* models, ui
 // start (refloor 0) are cleared, so that a scan of the set finds only states.
 hipError_t launch_rounds_begin_staged(hipStream_t st, const ModelDev* staged, uint32_t n,
                                       ModelDev* models);
+// The counterexample of configuration q.target after a query on the round engine (q.tslot).
+hipError_t launch_round_path(hipStream_t st, const QueryArgs& q, const TraceOut& t, bool general);
 // general: some configuration has waves or two-operation periods.
 hipError_t launch_rounds(hipStream_t st, uint32_t grid, uint32_t block, const RoundQueue& q,
                          bool general);
@@ -222,7 +236,7 @@ hipError_t launch_count_le(hipStream_t st, const unsigned char* table, unsigned 
 template <int W>
 hipError_t launch_find(hipStream_t st, const QueryArgs& q, const unsigned long long* key);
 template <int W>
-hipError_t launch_chase(hipStream_t st, const QueryArgs& q, unsigned long long* out, uint32_t cap);
+hipError_t launch_chase(hipStream_t st, const QueryArgs& q, const TraceOut& t);
 hipError_t launch_clear(hipStream_t st, void* p, unsigned long long bytes);
 hipError_t launch_reset(hipStream_t st, Ctrl* ctrl, uint32_t* tc, uint32_t n_cfg);
 hipError_t launch_simulate(hipStream_t st, const QueryArgs& q, unsigned long long seed);

@@ -157,8 +157,9 @@ MC_HD RoundItem part_item(const Piece& v, uint32_t i, const uint8_t* masks) {
   return t;
 }
 
-// The slots that an item's links name: of the all-idle state its round starts from (a
-// leaf's), and of the dispatch leaf its run starts from (a round's end's).
+// The slots that an item's links name: of the all-idle state its round starts from (not known
+// in a slice, whose partition holds the round's leaf instead), and of the dispatch leaf its
+// run starts from.
 struct ItemLinks {
   uint32_t root, leaf;
 };
@@ -167,12 +168,12 @@ MC_HD ItemLinks links_of(const Piece& v, uint32_t i, uint32_t q) {
   ItemLinks k;
   if (i < v.F) {
     const uint32_t first = (v.q0 + q) * v.per;
-    k.root = first ? v.slot0 + first - 1u : v.link;
+    k.root = !v.closure ? kParentNone : first ? v.slot0 + first - 1u : v.link;
     k.leaf = v.closure ? v.slot0 + first + v.cl - 1u : v.link;
   } else {
     const uint32_t y = i - v.F, s = v.closure ? v.sets : 0u;
     const uint32_t l = y < s ? 0u : (y - s) % v.choices;
-    k.root = v.F ? v.slot0 + v.F - 1u : v.link;
+    k.root = !v.closure ? kParentNone : v.F ? v.slot0 + v.F - 1u : v.link;
     k.leaf = v.closure ? v.slot0 + v.F + v.sets - v.choices + l : v.link + l;
   }
   return k;

@@ -229,12 +229,13 @@ __device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_i
       if (clock < g.refloor && fresh) fresh = *kp != key;
     if (fresh) {
       *kp = key;
-      // links, as the counterexample reads them: a dispatch leaf to its round's start, a
-      // round's end to the leaf its run starts from (parent and jump)
+      // links, as the counterexample reads them: a round's end to the state its round starts
+      // from (parent; none in a run slice) and the leaf its run starts from (jump), a dispatch
+      // leaf to its round's start
       if (rem == 0u || it.is_leaf) {
         const ItemLinks l = links_of(v, i, it.q);
-        const unsigned long long lo = rem ? l.root : l.leaf, hi = rem ? kParentNone : l.leaf;
-        ((global_u64*)g.links)[it.slot] = lo | hi << 32;
+        const unsigned long long hi = rem ? kParentNone : l.leaf;
+        ((global_u64*)g.links)[it.slot] = l.root | hi << 32;
         if (rem == 0u && prel + v.pmin == 0u) {
           const ModelDev md = load_const(mdp);
           const uint32_t end = clock0 + it.q * g.d + g.d;
@@ -437,6 +438,124 @@ __global__ __launch_bounds__(256) void k_rounds_begin_models(const ModelDev* mod
   if (md.tslot) begin_model(md);
 }
 
+// ---- counterexample ---------------------------------------------------------------------
+//
+// The path to a configuration's terminal, terminal first.  A round's end links to the state
+// its round starts from, which is the end of the round before: one dependent read of about a
+// microsecond per round, made by the first wavefront for up to kPathRounds rounds at a time.
+// The rounds' leaves are then read side by side (they name the units each round started), and
+// all threads write the states: a round's run from its last state back, then its dispatches,
+// the last of the units in index order first.  Every end and leaf read has to be the state the
+// round structure gives, or the path is bad.  The keys go straight to pinned memory, so that
+// the host waits once.  mc_trace, by way of the general chase -> here: 55 -> 17 us on
+// reduction_g256_cu2, 73 -> 29 us on matmul64_cu4, 75 -> 45 us on matmul128_vw_cu8 (2,834
+// states, of which decoding them on the host takes about 15).
+constexpr uint32_t kPathRounds = 256, kPathBlock = 512;
+
+template <bool GEN>
+__global__ __launch_bounds__(kPathBlock) void k_round_path(QueryArgs a, TraceOut t) {
+  __shared__ uint32_t end[kPathRounds], leaf[kPathRounds];
+  __shared__ uint8_t units[kPathRounds];
+  __shared__ uint32_t s_count, s_at, s_bad;
+  const uint32_t tid = threadIdx.x, c = a.target, m = a.L.m, all = (1u << m) - 1u;
+  const CfgRec r = load_const(a.cfgs + c);
+  const unsigned long long* keys = reinterpret_cast<const unsigned long long*>(a.table);
+  const uint32_t sp = a.L.shift[kFPending], sm = a.L.shift[kFRem], sr = a.L.shift[kFRem + 1];
+  const uint32_t target = a.tslot[c];
+  const uint32_t rounds = (r.n + m - 1u) / m, last = r.n - (rounds - 1u) * m;  // units of the last
+  const uint32_t per = r.b + m;
+  uint32_t n = 0;            // states written
+  uint32_t left = rounds;    // rounds before the ones written
+  if (tid == 0) {
+    s_at = target;
+    s_bad = target == kParentNone || target > a.mask ? 1u : 0u;
+  }
+  __syncthreads();
+  const auto put = [&](uint32_t i, unsigned long long key) {
+    if (i >= t.cap) return;
+    if (i < t.host_words) t.host[i] = key;
+    else t.out[i] = key;
+  };
+  const auto run = [&](const auto& ends) {
+    while (left && !s_bad) {
+      const uint32_t take = left < kPathRounds ? left : kPathRounds;
+      if (tid < 64u) {
+        uint32_t at = s_at, k = 0;
+        while (k < take && at <= a.mask) {
+          const uint2 l = *reinterpret_cast<const uint2*>(slot_parent<1>(a.table, a.mask, at));
+          if (tid == 0) {
+            end[k] = at;
+            leaf[k] = l.y;
+          }
+          at = l.x;
+          // the end of a run slice knows its leaf only, which links to the round's start
+          if (at == kParentNone && l.y <= a.mask) at = *slot_parent<1>(a.table, a.mask, l.y);
+          ++k;
+        }
+        if (tid == 0) {
+          s_at = at;
+          s_count = k;
+        }
+      }
+      __syncthreads();
+      if (s_count < take && tid == 0) s_bad = 1u;
+      for (uint32_t k = tid; k < s_count; k += kPathBlock) {
+        const uint32_t round = left - 1u - k, started = round + 1u == rounds ? last : m;
+        const uint32_t pend = r.n - round * m - started;
+        const unsigned long long want = (unsigned long long)c | (unsigned long long)pend << sp;
+        uint32_t mask = 0;
+        bool ok = keys[end[k]] == want && leaf[k] <= a.mask;
+        if (ok) {
+          const unsigned long long lk = keys[leaf[k]];
+          mask = (uint32_t)(lk >> sm) & all;
+          ok = lk == (want | (unsigned long long)mask << sm | (unsigned long long)r.d << sr) &&
+               bits_set(mask) == started;
+        }
+        units[k] = (uint8_t)mask;
+        if (!ok) s_bad = 1u;
+      }
+      __syncthreads();
+      if (s_bad) break;
+      const uint32_t first = left == rounds ? r.b + last : per;  // states of the chunk's last round
+      const uint32_t rows = first + (take - 1u) * per;
+      for (uint32_t i = tid; i < rows; i += kPathBlock) {
+        const uint32_t k = i < first ? 0u : 1u + (i - first) / per;
+        const uint32_t off = i < first ? i : (i - first) - (k - 1u) * per;
+        const uint32_t round = left - 1u - k, started = round + 1u == rounds ? last : m;
+        uint32_t mask = units[k], rem = r.d;
+        if (off < r.b) {
+          rem = rem_after(ends, r.b - 1u - off);
+        } else {  // the first of the leaf's units, fewer and fewer of them
+          for (uint32_t drop = off - r.b; drop; --drop) mask &= ~(1u << (31 - __clz((int)mask)));
+        }
+        const uint32_t pend = r.n - round * m - (off < r.b ? started : bits_set(mask));
+        put(n + i, (unsigned long long)c | (unsigned long long)pend << sp |
+                       (unsigned long long)(rem ? mask : 0u) << sm | (unsigned long long)rem << sr);
+      }
+      n += rows;
+      left -= take;
+      __syncthreads();
+    }
+  };
+  if constexpr (GEN) run(general_ends(r));
+  else run(uniform_ends(r));
+  if (tid == 0) {
+    // the SELECT state and the root
+    const bool bad = s_bad || s_at != 1u + c || n + 2u > t.cap;
+    put(n, (unsigned long long)c | (unsigned long long)r.n << sp);
+    put(n + 1u, (unsigned long long)a.n_cfg);
+    n += 2u;
+    a.ctrl->trace_len = n;
+    a.ctrl->target_slot = target;
+    if (bad && target != kParentNone) set_error(a.ctrl, kDevErrTrace);
+    if (t.host_res) {
+      t.host_res[0] = target;
+      t.host_res[1] = n;
+      t.host_res[2] = bad ? 1u : 0u;
+    }
+  }
+}
+
 // Staged descriptors: block (0, y) begins model y, every block clears a share of its slots
 // but for the root's and the SELECT states', which block (0, y) writes.
 __global__ __launch_bounds__(256) void k_rounds_begin_staged(const ModelDev* staged,
@@ -489,6 +608,12 @@ hipError_t launch_rounds_begin_staged(hipStream_t st, const ModelDev* staged, ui
                                       ModelDev* models) {
   static_assert(sizeof(ModelDev) / 4 <= 256, "one thread per word");
   hipLaunchKernelGGL(k_rounds_begin_staged, dim3(64, n), dim3(256), 0, st, staged, models);
+  return hipGetLastError();
+}
+
+hipError_t launch_round_path(hipStream_t st, const QueryArgs& q, const TraceOut& t, bool general) {
+  if (general) hipLaunchKernelGGL(k_round_path<true>, dim3(1), dim3(kPathBlock), 0, st, q, t);
+  else hipLaunchKernelGGL(k_round_path<false>, dim3(1), dim3(kPathBlock), 0, st, q, t);
   return hipGetLastError();
 }
 

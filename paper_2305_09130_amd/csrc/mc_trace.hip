@@ -68,8 +68,20 @@ __global__ void k_find(QueryArgs a, Key<W> k) {
 // alike a dispatch leaf links to its closure's root, the inner closure states storing no
 // links: the states between the two are listed by starting the leaf's extra units one at
 // a time in index order.
+template <int W>
+__device__ __forceinline__ void put_key(const TraceOut& t, uint32_t i, const Key<W>& k) {
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const unsigned long long at = (unsigned long long)i * W + w;
+    if (at < t.host_words) t.host[at] = k.w[w];
+    else t.out[at] = k.w[w];
+  }
+}
+
 constexpr int kChaseCand = 1024;  // candidate ends of one chain the trace merges
-constexpr uint32_t kChaseBlock = 256;  // threads of the trace kernel (four wavefronts)
+// threads of the trace kernel (four-word keys at 1,024 spill registers)
+template <int W>
+constexpr uint32_t kChaseBlock = W == 4 ? 512 : 1024;
 
 // The states of a chain of units of unequal speed from f (excluded) to x (included): the
 // distinct operation ends of f's busy units up to x's clock, each a state with the same
@@ -84,7 +96,7 @@ constexpr uint32_t kChaseBlock = 256;  // threads of the trace kernel (four wave
 template <int W>
 __device__ __forceinline__ uint32_t chase_chain(const St& f, const St& x, const Key<W>& xk,
                                                 const CfgRec& r, const Layout& L, int m,
-                                                uint32_t* S, unsigned long long* out, uint32_t n,
+                                                uint32_t* S, const TraceOut& t, uint32_t n,
                                                 uint32_t cap, bool& bad) {
   const uint32_t lane = threadIdx.x;
   uint32_t base[kMaxCU], sp[kMaxCU], k0[kMaxCU], nu[kMaxCU], O[kMaxCU + 1];
@@ -128,7 +140,7 @@ __device__ __forceinline__ uint32_t chase_chain(const St& f, const St& x, const 
     tau = bu_ + su_ * end_at(r, ku_ + ((i) - ou_));               \
   } while (0)
   // counted flags: a time counts on the lowest unit that ends at it
-  for (uint32_t i = lane; i < C; i += kChaseBlock) {
+  for (uint32_t i = lane; i < C; i += kChaseBlock<W>) {
     int u;
     uint32_t tau;
     MC_CHASE_CAND(i, u, tau);
@@ -173,7 +185,7 @@ __device__ __forceinline__ uint32_t chase_chain(const St& f, const St& x, const 
     bad = true;
     return 0u;
   }
-  for (uint32_t i = lane; i < C; i += kChaseBlock) {
+  for (uint32_t i = lane; i < C; i += kChaseBlock<W>) {
     if (S[i + 1u] == S[i]) continue;  // not counted
     int u;
     uint32_t tau;
@@ -197,8 +209,7 @@ __device__ __forceinline__ uint32_t chase_chain(const St& f, const St& x, const 
       y.rem[v] = wend > tau ? wend - tau : 0u;
     }
     const Key<W> yk = encode<W>(y, L);
-#pragma unroll
-    for (int w = 0; w < W; ++w) out[(unsigned long long)(n + cnt - 1u - rank) * W + w] = yk.w[w];
+    put_key<W>(t, n + cnt - 1u - rank, yk);
     if (rank + 1u == cnt) {
       bool same = true;
 #pragma unroll
@@ -213,27 +224,50 @@ __device__ __forceinline__ uint32_t chase_chain(const St& f, const St& x, const 
 #undef MC_CHASE_CAND
 }
 
+// A dependent read of the visited set costs about a microsecond, and following a link is
+// waiting for one: the key and the links of the state a link names are read together, before
+// the states in between are written, and both are carried into its turn (two waits per round
+// of units alike instead of six).
 template <int W>
-__global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned long long* out,
-                                                     uint32_t cap) {
+struct Linked {  // a slot's key and links
+  Key<W> k;
+  uint32_t par, jmp;
+};
+
+template <int W>
+__device__ __forceinline__ Linked<W> read_linked(const QueryArgs& a, uint32_t s) {
+  Linked<W> x;
+  const unsigned long long* p = slot_key<W>(a.table, s);
+#pragma unroll
+  for (int w = 0; w < W; ++w) x.k.w[w] = p[w];
+  const uint2 l = *reinterpret_cast<const uint2*>(slot_parent<W>(a.table, a.mask, s));
+  x.par = l.x;
+  x.jmp = l.y;
+  return x;
+}
+
+template <int W>
+__global__ __launch_bounds__(kChaseBlock<W>) void k_chase(QueryArgs a, TraceOut t) {
   if (blockIdx.x != 0) return;
   const uint32_t lane = threadIdx.x;
   const Layout& L = a.L;
   const int m = L.m;
+  const uint32_t cap = t.cap;
   __shared__ uint32_t sS[kChaseCand + 1];  // a chain's counted flags and their prefix sums
-  uint32_t s = a.tslot ? a.tslot[a.target] : a.ctrl->target_slot;
-  if (a.tslot && lane == 0) a.ctrl->target_slot = s;
+  uint32_t s = a.ctrl->target_slot;
+  const uint32_t target = s;
   uint32_t n = 0;
   bool bad = false;
+  Linked<W> x0;
+  bool have = false;  // x0 is s's
   while (s != kParentRoot) {
     if (s == kParentNone || (unsigned long long)s > a.mask || n >= cap) {
       bad = true;
       break;
     }
-    const unsigned long long* p = slot_key<W>(a.table, s);
-    Key<W> k;
-#pragma unroll
-    for (int w = 0; w < W; ++w) k.w[w] = p[w];
+    if (!have) x0 = read_linked<W>(a, s);
+    have = false;
+    const Key<W> k = x0.k;
     // on units alike a state with busy units short of d is inside a lock-step run: its
     // links, if it stored any, are not read (the link region is not cleared there)
     // (and one whose busy units are all at d may be a dispatch leaf linked to the root of
@@ -248,8 +282,8 @@ __global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned lon
       inside_run = rem != 0u && rem < d;
       leaf_like = rem != 0u && rem == d;
     }
-    const uint32_t par = inside_run ? kParentNone : *slot_parent<W>(a.table, a.mask, s);
-    uint32_t jmp = inside_run ? kParentNone : *slot_jump<W>(a.table, a.mask, s);
+    const uint32_t par = inside_run ? kParentNone : x0.par;
+    uint32_t jmp = inside_run ? kParentNone : x0.jmp;
     if (par == kParentNone && jmp == kParentNone) {
       // an interior state of a lock-step run from a dispatch leaf (it stores no links):
       // the leaf has the same busy units, each at d, and the clock of the run's start
@@ -271,21 +305,16 @@ __global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned lon
       }
     }
     if (jmp == kParentNone || (unsigned long long)jmp > a.mask) {
-      if (lane == 0) {
-#pragma unroll
-        for (int w = 0; w < W; ++w) out[(unsigned long long)n * W + w] = k.w[w];
-      }
+      if (lane == 0) put_key<W>(t, n, k);
       ++n;
       if (leaf_like && par != kParentRoot && par != kParentNone &&
           (unsigned long long)par <= a.mask) {
         // a dispatch leaf linked to its closure's root (the closure's inner states store
         // no links): the states between them start the missing units one at a time, in
         // index order, at the root's clock
-        const unsigned long long* pp = slot_key<W>(a.table, par);
-        Key<W> pk;
-#pragma unroll
-        for (int w = 0; w < W; ++w) pk.w[w] = pp[w];
-        const St root = decode<W>(pk, L, a.cfgs);
+        x0 = read_linked<W>(a, par);
+        have = true;  // par is next
+        const St root = decode<W>(x0.k, L, a.cfgs);
         const St x = decode<W>(k, L, a.cfgs);
         if (root.cfg == x.cfg && root.clock == x.clock && root.pending > x.pending + 1u) {
           const uint32_t gap = root.pending - x.pending - 1u;  // inner states to list
@@ -315,8 +344,7 @@ __global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned lon
               }
             y.pending = root.pending - i;
             const Key<W> yk = encode<W>(y, L);
-#pragma unroll
-            for (int w = 0; w < W; ++w) out[(unsigned long long)(n + lane) * W + w] = yk.w[w];
+            put_key<W>(t, n + lane, yk);
           }
           n += gap;
         }
@@ -326,38 +354,32 @@ __global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned lon
     }
     if (!L.shared_rem) {
       // a chain of units of unequal speed: regenerated from the state it starts from
-      const unsigned long long* fp = slot_key<W>(a.table, jmp);
-      Key<W> fk;
-#pragma unroll
-      for (int w = 0; w < W; ++w) fk.w[w] = fp[w];
-      const St f = decode<W>(fk, L, a.cfgs);
+      const Linked<W> from = read_linked<W>(a, jmp);
+      const St f = decode<W>(from.k, L, a.cfgs);
       const St x = decode<W>(k, L, a.cfgs);
       if (f.cfg != x.cfg || f.cfg >= a.n_cfg || f.pending != x.pending || f.clock >= x.clock) {
         bad = true;
         break;
       }
       const CfgRec r = a.cfgs[f.cfg];
-      const uint32_t cnt = chase_chain<W>(f, x, k, r, L, m, sS, out, n, cap, bad);
+      const uint32_t cnt = chase_chain<W>(f, x, k, r, L, m, sS, t, n, cap, bad);
       if (bad) break;
       if (cnt == 0u) {  // more candidates than flags: the parent link instead
-        if (lane == 0) {
-#pragma unroll
-          for (int w = 0; w < W; ++w) out[(unsigned long long)n * W + w] = k.w[w];
-        }
+        if (lane == 0) put_key<W>(t, n, k);
         ++n;
         s = par;
         continue;
       }
       n += cnt;
       s = jmp;
+      x0 = from;
+      have = true;
       continue;
     }
     // regenerate the run leaf -> s
-    const unsigned long long* lp = slot_key<W>(a.table, jmp);
-    Key<W> lk;
-#pragma unroll
-    for (int w = 0; w < W; ++w) lk.w[w] = lp[w];
-    const St leaf = decode<W>(lk, L, a.cfgs);
+    x0 = read_linked<W>(a, jmp);
+    have = true;  // the leaf is next
+    const St leaf = decode<W>(x0.k, L, a.cfgs);
     const St x = decode<W>(k, L, a.cfgs);
     const CfgRec r = a.cfgs[leaf.cfg];
     uint32_t busy = 0, lrem = 0;
@@ -378,10 +400,10 @@ __global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned lon
       bad = true;
       break;
     }
-    for (uint32_t t0 = 0; t0 < cnt; t0 += kChaseBlock) {
-      const uint32_t t = t0 + lane;
-      if (t < cnt) {
-        const uint32_t pos = cnt - 1u - t;  // terminal-first order
+    for (uint32_t i0 = 0; i0 < cnt; i0 += kChaseBlock<W>) {
+      const uint32_t i = i0 + lane;
+      if (i < cnt) {
+        const uint32_t pos = cnt - 1u - i;  // terminal-first order
         const uint32_t e = end_at(r, idx0 + pos);
         St y = leaf;
         y.clock = leaf.clock + (e - e0);
@@ -389,8 +411,7 @@ __global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned lon
         for (int u = 0; u < kMaxCU; ++u)
           if ((busy >> u) & 1u) y.rem[u] = r.d - e;
         const Key<W> yk = encode<W>(y, L);
-#pragma unroll
-        for (int w = 0; w < W; ++w) out[(unsigned long long)(n + t) * W + w] = yk.w[w];
+        put_key<W>(t, n + i, yk);
       }
     }
     n += cnt;
@@ -399,6 +420,11 @@ __global__ __launch_bounds__(kChaseBlock) void k_chase(QueryArgs a, unsigned lon
   if (lane == 0) {
     if (bad) set_error(a.ctrl, kDevErrTrace);
     a.ctrl->trace_len = n;
+    if (t.host_res) {
+      t.host_res[0] = target;
+      t.host_res[1] = n;
+      t.host_res[2] = bad ? 1u : 0u;
+    }
   }
 }
 
@@ -413,8 +439,8 @@ hipError_t launch_find(hipStream_t st, const QueryArgs& q, const unsigned long l
 }
 
 template <int W>
-hipError_t launch_chase(hipStream_t st, const QueryArgs& q, unsigned long long* out, uint32_t cap) {
-  hipLaunchKernelGGL((k_chase<W>), dim3(1), dim3(kChaseBlock), 0, st, q, out, cap);
+hipError_t launch_chase(hipStream_t st, const QueryArgs& q, const TraceOut& t) {
+  hipLaunchKernelGGL((k_chase<W>), dim3(1), dim3(kChaseBlock<W>), 0, st, q, t);
   return hipGetLastError();
 }
 
@@ -436,8 +462,7 @@ hipError_t launch_count_le(hipStream_t st, const unsigned char* table, unsigned 
                                          uint32_t, unsigned long long*);                    \
   template hipError_t launch_find<W>(hipStream_t, const QueryArgs&,                       \
                                      const unsigned long long*);                           \
-  template hipError_t launch_chase<W>(hipStream_t, const QueryArgs&, unsigned long long*,  \
-                                      uint32_t);
+  template hipError_t launch_chase<W>(hipStream_t, const QueryArgs&, const TraceOut&);
 MC_INSTANTIATE(1)
 MC_INSTANTIATE(2)
 MC_INSTANTIATE(4)

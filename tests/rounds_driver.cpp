@@ -93,7 +93,7 @@ int main() {
           if (code == 0xFFFFFFFFu || pending < v.pmin ||
               ((uint64_t)(pending - v.pmin) << (h.m + rb)) >> 32)
             bad = "code range";
-          if (t.slot < 1 + h.n_cfg || t.slot >= base.used || lk.root >= base.used ||
+          if (t.slot < 1 + h.n_cfg || t.slot >= base.used || (lk.root >= base.used && (v.closure || lk.root != kParentNone)) ||
               lk.leaf >= base.used)
             bad = "slot range";
           if (bad) break;
