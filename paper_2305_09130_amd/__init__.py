@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -62,7 +63,11 @@ class McStats(ctypes.Structure):
                  "cas_fail")]
 
     def as_dict(self) -> dict:
-        return {n: int(getattr(self, n)) for n, _ in self._fields_}
+        return dict(zip(_STATS_NAMES, _STATS_PACK.unpack(self)))
+
+
+_STATS_NAMES = tuple(n for n, _ in McStats._fields_)
+_STATS_PACK = struct.Struct(f"{len(_STATS_NAMES)}Q")  # every field is a uint64
 
 
 class McModelInfo(ctypes.Structure):
@@ -199,6 +204,12 @@ class McError(RuntimeError):
     def __init__(self, where: str, code: int):
         super().__init__(f"{where}: {mc_strerror(code)} ({code})")
         self.code = code
+
+
+def _clocks(tc: np.ndarray) -> list[int | None]:
+    """Terminal clocks as a list, None where no terminal was reached."""
+    out = tc.tolist()
+    return [None if v == NO_CLOCK else v for v in out] if NO_CLOCK in out else out
 
 
 def mc_strerror(code: int) -> str:
@@ -391,7 +402,7 @@ class Model:
                                                arg.ctypes.data_as(_u32p), arg.shape[0],
                                                ctypes.byref(n), ctypes.byref(st)))
         self.last_stats = st.as_dict()
-        return t.value, [int(v) for v in arg[:n.value]]
+        return t.value, arg[:n.value].tolist()
 
     def mc_min_time_bb(self, T_init: int = 0) -> tuple[int, list[int]]:
         """Branch-and-bound min_time (exact T_min and argmin; last_stats counts the states
@@ -404,7 +415,7 @@ class Model:
                                                      arg.ctypes.data_as(_u32p), arg.shape[0],
                                                      ctypes.byref(n), ctypes.byref(st)))
         self.last_stats = st.as_dict()
-        return t.value, [int(v) for v in arg[:n.value]]
+        return t.value, arg[:n.value].tolist()
 
     def mc_check(self, T: int) -> bool:
         v = ctypes.c_int()
@@ -417,7 +428,7 @@ class Model:
         tc = np.zeros(self.n_cfg, dtype=np.uint32)
         _check("mc_terminal_clocks",
                _lib.mc_terminal_clocks(self._h, tc.ctypes.data_as(_u32p), tc.shape[0]))
-        return [None if int(v) == NO_CLOCK else int(v) for v in tc]
+        return _clocks(tc)
 
     def mc_trace(self) -> np.ndarray:
         n = ctypes.c_size_t()
@@ -458,7 +469,9 @@ class Model:
     def mc_swarm_members(self, members: int) -> list[dict]:
         out = (McSwarmMember * members)()
         _check("mc_swarm_members", _lib.mc_swarm_members(self._h, out, members))
-        return [x.as_dict() for x in out]
+        rec = np.frombuffer(out, dtype=McSwarmMember)
+        names = [n for n, _ in McSwarmMember._fields_ if n != "pad"]
+        return [dict(zip(names, row)) for row in zip(*(rec[n].tolist() for n in names))]
 
     def mc_swarm_tune(self, members: int, bits_log2: int, budget: int,
                       seed: int) -> tuple[int, int, dict]:
@@ -577,14 +590,14 @@ class Batch:
                _lib.mc_batch_min_time(self._h, t.ctypes.data_as(_u32p),
                                       st_.ctypes.data_as(_u64p), ctypes.byref(st)))
         self.last_stats = st.as_dict()
-        return [int(v) for v in t], [int(v) for v in st_]
+        return t.tolist(), st_.tolist()
 
     def mc_batch_terminal_clocks(self, i: int) -> list[int | None]:
         nc = len(self.models[i]["params"])
         tc = np.zeros(nc, dtype=np.uint32)
         _check("mc_batch_terminal_clocks",
                _lib.mc_batch_terminal_clocks(self._h, i, tc.ctypes.data_as(_u32p), nc))
-        return [None if int(v) == NO_CLOCK else int(v) for v in tc]
+        return _clocks(tc)
 
 
 MC_QUERY_MIN_TIME, MC_QUERY_CHECK = 0, 1

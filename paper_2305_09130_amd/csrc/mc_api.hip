@@ -61,16 +61,21 @@ uint64_t cas_fails(uint64_t probes, uint64_t states, uint64_t dups) {
   return probes > states + dups ? probes - states - dups : 0u;
 }
 
-int plan_ws(const ModelHost& mh, const mc_opts& o, uint64_t n_parts, WsPlan* p) {
-  if (o.test_hash_bits > 24u) return MC_E_INVAL;
-  uint64_t slots;
+int plan_slots(const ModelHost& mh, const mc_opts& o, uint64_t* slots) {
   if (o.log2_slots) {
     if (o.log2_slots < 4 || o.log2_slots > 31) return MC_E_INVAL;
-    slots = 1ull << o.log2_slots;
+    *slots = 1ull << o.log2_slots;
   } else {
-    slots = std::max<uint64_t>(table_slots(mh.states, o.load_factor), 1024);
-    if (slots > (1ull << 31)) return MC_E_INVAL;
+    *slots = std::max<uint64_t>(table_slots(mh.states, o.load_factor), 1024);
+    if (*slots > (1ull << 31)) return MC_E_INVAL;
   }
+  return MC_OK;
+}
+
+int plan_ws(const ModelHost& mh, const mc_opts& o, uint64_t n_parts, WsPlan* p) {
+  if (o.test_hash_bits > 24u) return MC_E_INVAL;
+  uint64_t slots = 0;
+  if (const int rc = plan_slots(mh, o, &slots)) return rc;
   const uint32_t W = mh.W;
   const size_t entry = 8ull * W + 8ull;
   // the visited set first: it starts at the same place for every model, so a handle that
@@ -225,7 +230,8 @@ struct mc_model {
   bool on_rounds = false;
   uint64_t* trace_words = nullptr;  // pinned, kTraceWords (pooled handles)
   RoundRecord* records = nullptr;  // pinned, kRoundsGrid entries (pooled handles)
-  unsigned char* stage_parts = nullptr;  // pinned staging of a plan, or null
+  unsigned char* stage_parts = nullptr;  // staging of a query's own plan, or null
+  bool in_flight = false;  // the load's upload from pinned staging may not be done yet
   // unpooled binding (the static scratch): host staging in ordinary memory, no events
   bool pooled = true;
   std::vector<unsigned char> host_stage;
@@ -395,13 +401,13 @@ void fill_stats(const mc_model* h, std::chrono::steady_clock::time_point t0, uin
 
 // A query's counters from the workgroups' records, added to what they hold.
 void add_records(Ctrl* c, const RoundRecord* rec, uint32_t n, uint64_t* ticks) {
-  unsigned long long first = ~0ull, last = 0;
+  int32_t first = 0, last = 0;  // relative to the first record's start
   for (uint32_t i = 0; i < n; ++i) {
     const RoundRecord& r = rec[i];
     c->states += r.states;
     c->terminals += r.terms;
     c->edges += r.edges;
-    c->dups += r.dups;
+    c->dups += r.edges - r.states;
     c->probes += r.probes;
     c->chunks += r.chunks;
     c->supersteps += r.rounds;
@@ -413,10 +419,10 @@ void add_records(Ctrl* c, const RoundRecord* rec, uint32_t n, uint64_t* ticks) {
     }
     if (!c->error) c->error = r.error;
     if (r.terms) c->violated = 1u;
-    first = std::min(first, r.t_first);
-    last = std::max(last, r.t_last);
+    first = std::min(first, (int32_t)(r.t_first - rec[0].t_first));
+    last = std::max(last, (int32_t)(r.t_last - rec[0].t_first));
   }
-  *ticks = last > first ? last - first : 0;
+  *ticks = (uint64_t)(last - first);
 }
 
 // A query on the round engine.  resume: the states with clock <= h->resident_T are in the
@@ -454,7 +460,7 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
     if (bytes) HIPCHK(hipMemcpyAsync(h->parts, src, bytes, hipMemcpyHostToDevice, s));
     h->parts_resumed = true;
   } else {
-    n_pieces = number_pieces(&h->rplan, piece);
+    n_pieces = h->rplan.n_pieces;
     if (h->parts_resumed) {
       const size_t bytes = sizeof(RoundPart) * h->rplan.parts.size();
       const void* src = h->rplan.parts.data();
@@ -891,6 +897,7 @@ int mc_model_free(mc_model* h) {
   if (h->pooled) {
     // the side stream may still be clearing bytes of the caller's workspace
     if (h->side) (void)hipStreamSynchronize(h->side);
+    if (h->in_flight) (void)hipStreamSynchronize(h->stream);  // it reads the pinned block
     for (auto& e : h->ev)
       if (e) event_put(e);
     if (h->ev_fork) event_put(h->ev_fork);
@@ -915,17 +922,22 @@ struct Loaded {
   RoundPlan rounds;
 };
 
-// The round engine's form of the load's plan, largest partitions first; empty where that
-// engine cannot explore the model or the visited set has no slot for every generated state
-// (a set given smaller than the model's states has to fill up and say so).
-void plan_rounds(const ModelHost& mh, const mc_opts& o, const std::vector<PartPlan>& plan,
-                 uint64_t slots, RoundPlan* out) {
+uint64_t part_target(const ModelHost& mh, const mc_opts& o) {
+  return o.part_states == 0xFFFFFFFFu ? 0u
+         : o.part_states              ? o.part_states
+                                      : auto_part_states(mh.states, mh.m);
+}
+
+// The round engine's plan; empty where that engine cannot explore the model or the visited
+// set has no slot for every generated state (a set given smaller than the model's states has
+// to fill up and say so).
+void plan_rounds(const ModelHost& mh, const mc_opts& o, uint64_t slots, RoundPlan* out) {
   if (!rounds_model(mh)) return;
-  RoundPlan p;
-  round_plan(mh, 0, plan, &p);
-  if (p.used > slots) return;
-  largest_first(&p);
-  *out = std::move(p);
+  round_plan_largest_first(mh, part_target(mh, o), out);
+  if (out->used > slots) {
+    *out = RoundPlan{};
+    return;
+  }
   number_pieces(out, auto_piece(mh.states));
 }
 
@@ -934,12 +946,16 @@ int prepare_load(const mc_desc* d, const mc_opts& opts_in, size_t ws_bytes, Load
   int rc = build_model(d, &L->mh, &err);
   if (rc) return rc;
   L->opts = opts_in;
-  const std::vector<PartPlan> plan = model_plan(L->mh, L->opts);
-  rc = plan_ws(L->mh, L->opts, plan.size(), &L->plan);
+  // (a visited set too small for the round engine's slots is found after its plan, whose
+  // partitions are as many as the other engine's)
+  uint64_t slots = 0;
+  rc = plan_slots(L->mh, L->opts, &slots);
+  if (rc) return rc;
+  plan_rounds(L->mh, L->opts, slots, &L->rounds);
+  if (L->rounds.parts.empty()) L->parts = sorted_parts(model_plan(L->mh, L->opts));
+  rc = plan_ws(L->mh, L->opts, L->rounds.parts.size() + L->parts.size(), &L->plan);
   if (rc) return rc;
   if (ws_bytes < L->plan.total) return MC_E_NOMEM;
-  plan_rounds(L->mh, L->opts, plan, L->plan.slots, &L->rounds);
-  if (L->rounds.parts.empty()) L->parts = sorted_parts(plan);
   // automatic workgroup size: with fewer partitions than a wide launch has workgroups,
   // each runs nearly alone on its compute unit and its chain of insert round trips is
   // the launch time, which 512 threads shorten; with many, 256 keeps more of them
@@ -999,9 +1015,18 @@ int install(mc_model* h, Loaded& L) {
   const size_t rec_off = 768, trace_off = rec_off + sizeof(RoundRecord) * kRoundsGrid;
   const size_t tc_off = trace_off + (h->pooled ? 8ull * kTraceWords : 0u);
   const size_t up_off = align_up(tc_off + 4ull * h->mh.n_cfg);
+  // the records and partitions are staged as they lie in the workspace, for one copy, and
+  // after them is room for a query's own partitions
   const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg, part_bytes = sizeof(Part) * h->n_parts;
-  const bool stage = cfg_bytes + part_bytes <= (4u << 20);
-  const size_t pin_bytes = stage ? up_off + cfg_bytes + part_bytes : up_off;
+  const size_t part_off = h->plan.order - h->plan.cfgs, up_bytes = part_off + part_bytes;
+  const bool stage = up_bytes <= (4u << 20);
+  const size_t own_off = align_up(up_off + up_bytes);
+  const size_t pin_bytes = stage ? own_off + part_bytes : up_off;
+  if (h->in_flight && hipStreamSynchronize(h->stream) != hipSuccess) {  // the last upload's
+    (void)hipGetLastError();
+    return MC_E_DEVICE;
+  }
+  h->in_flight = false;
   unsigned char* blk = nullptr;
   if (h->pooled) {
     if (!h->pin || pin_bytes > h->pin_bytes) {
@@ -1026,21 +1051,25 @@ int install(mc_model* h, Loaded& L) {
   h->hmd = reinterpret_cast<ModelDev*>(blk + 512);
   h->tc_host = reinterpret_cast<uint32_t*>(blk + tc_off);
   for (uint32_t c = 0; c < h->mh.n_cfg; ++c) h->tc_host[c] = kNoClock;
-  const void* up_cfg = h->mh.cfgs.data();
   const void* up_part = h->rounds ? static_cast<const void*>(h->rplan.parts.data())
                                   : static_cast<const void*>(h->parts_host.data());
   h->stage_parts = nullptr;
-  if (stage) {
-    std::memcpy(blk + up_off, up_cfg, cfg_bytes);
-    std::memcpy(blk + up_off + cfg_bytes, up_part, part_bytes);
-    up_cfg = blk + up_off;
-    up_part = blk + up_off + cfg_bytes;
-    h->stage_parts = blk + up_off + cfg_bytes;
-  }
   hipStream_t s = h->stream;
-  if (hipMemcpyAsync(h->cfgs, up_cfg, cfg_bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
-      hipMemcpyAsync(h->parts, up_part, part_bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess) {
+  hipError_t e;
+  if (stage) {
+    std::memcpy(blk + up_off, h->mh.cfgs.data(), cfg_bytes);
+    std::memcpy(blk + up_off + part_off, up_part, part_bytes);
+    h->stage_parts = blk + own_off;
+    e = hipMemcpyAsync(h->cfgs, blk + up_off, up_bytes, hipMemcpyHostToDevice, s);
+  } else {
+    e = hipMemcpyAsync(h->cfgs, h->mh.cfgs.data(), cfg_bytes, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(h->parts, up_part, part_bytes, hipMemcpyHostToDevice, s);
+  }
+  // pinned staging is left alone until the stream is next waited for
+  if (e == hipSuccess && stage && h->pooled) h->in_flight = true;
+  else if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) {
     (void)hipGetLastError();
     return MC_E_DEVICE;
   }

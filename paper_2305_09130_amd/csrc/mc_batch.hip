@@ -568,8 +568,7 @@ int mc_batch_terminal_clocks(const mc_batch* b, uint32_t model, uint32_t* tc, si
   if (!b || !tc || model >= b->ms.size()) return MC_E_INVAL;
   if (!b->ran) return MC_E_STATE;
   if (cap < b->ms[model].n_cfg) return MC_E_BUFFER;
-  size_t pos = 0;
-  for (uint32_t i = 0; i < model; ++i) pos += b->ms[i].n_cfg;
+  const size_t pos = (b->plan.tc_off[model] - b->plan.tc) / 4;
   std::memcpy(tc, b->htc + pos, 4ull * b->ms[model].n_cfg);
   return MC_OK;
 }

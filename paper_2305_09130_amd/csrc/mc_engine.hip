@@ -19,6 +19,7 @@
 #include <cstring>
 #include <deque>
 #include <map>
+#include <memory>
 #include <new>
 #include <numeric>
 #include <string>
@@ -102,9 +103,11 @@ struct Query;
 
 // A model's explored state on the device.
 struct Resident {
+  explicit Resident(std::shared_ptr<const ModelHost> m) : model(std::move(m)), mh(*model) {}
   uint64_t id = 0;
   std::string key;  // the descriptor, canonically
-  ModelHost mh;
+  std::shared_ptr<const ModelHost> model;
+  const ModelHost& mh;
   std::vector<PartPlan> parts;  // partitions of an exploration from scratch
   // explored by the round engine (units alike, one-word keys, a slot per generated state):
   // its plan, every slot of which stays what it is through the model's residence
@@ -128,7 +131,7 @@ struct Query {
   uint64_t ticket = 0;
   uint32_t kind = 0, T = 0;
   std::string key;
-  ModelHost mh;              // until its Resident is created
+  std::shared_ptr<const ModelHost> model;
   uint64_t resident = 0;     // the Resident's id
   int mode = kFresh;
   uint32_t n_parts = 0;      // partitions of its exploration
@@ -161,6 +164,13 @@ size_t footprint(const ModelHost& mh, uint64_t states, size_t n_parts, float lf,
   off = align_up(off + s * slot_bytes_for(mh.W));
   *slots = s;
   return off;
+}
+
+// Whether the descriptor's arrays can be read as its counts say (build_model's first checks;
+// it is what refuses a descriptor).
+bool describable(const mc_desc* d) {
+  return d->n_cu >= 1 && d->n_cu <= (uint32_t)kMaxCU && d->n_cfg >= 1 && d->n_cfg <= (1u << 20) &&
+         d->params;
 }
 
 std::string model_key(const mc_desc* d) {
@@ -203,6 +213,7 @@ struct mc_engine {
   std::unordered_map<std::string, Resident*> by_key;
   std::unordered_map<uint64_t, Resident*> by_id;
   std::unordered_map<uint64_t, Query*> all;
+  std::unordered_map<std::string, std::weak_ptr<const ModelHost>> hosts;  // models in use
   std::vector<Part> pending_parts;  // partitions of the next launch (host side)
   int cur = 0;
   unsigned char* hctrl = nullptr;           // pinned
@@ -478,16 +489,31 @@ int mc_engine_submit(mc_engine* e, const mc_desc* model, uint32_t kind, uint32_t
   if (!e || !model || !ticket || (kind != MC_QUERY_MIN_TIME && kind != MC_QUERY_CHECK))
     return MC_E_INVAL;
   try {
-    Query* q = new Query();
-    std::string err;
-    const int rc = build_model(model, &q->mh, &err);
-    if (rc) {
-      delete q;
-      return rc;
+    // a descriptor that a waiting or unreleased query or a resident model already has is not
+    // built again
+    std::string key = describable(model) ? model_key(model) : std::string();
+    std::shared_ptr<const ModelHost> host;
+    if (!key.empty()) {
+      auto known = e->hosts.find(key);
+      if (known != e->hosts.end()) host = known->second.lock();
     }
+    if (!host) {
+      auto built = std::make_shared<ModelHost>();
+      std::string err;
+      const int rc = build_model(model, built.get(), &err);
+      if (rc) return rc;
+      host = std::move(built);
+      key = model_key(model);
+      if (e->hosts.size() >= 2 * e->all.size() + 64)  // forget those no longer in use
+        for (auto it = e->hosts.begin(); it != e->hosts.end();)
+          it = it->second.expired() ? e->hosts.erase(it) : std::next(it);
+      e->hosts[key] = host;
+    }
+    Query* q = new Query();
+    q->model = std::move(host);
     q->kind = kind;
     q->T = T;
-    q->key = model_key(model);
+    q->key = std::move(key);
     q->ticket = e->next_ticket++;
     q->submit_ns = now_ns();
     q->res.kind = kind;
@@ -497,13 +523,13 @@ int mc_engine_submit(mc_engine* e, const mc_desc* model, uint32_t kind, uint32_t
     // a model needs room for all its states (any later query can reuse them), or with
     // no_reuse for the states this query inserts
     const uint64_t need = !e->opts.no_reuse || kind == MC_QUERY_MIN_TIME
-                              ? q->mh.states
-                              : count_le_bound(q->mh, T);
+                              ? q->model->states
+                              : count_le_bound(*q->model, T);
     uint64_t slots;
     size_t a, b, c, d;
-    const size_t bytes = footprint(q->mh, need, q->mh.n_cfg + kExtraParts, e->opts.load_factor,
+    const size_t bytes = footprint(*q->model, need, q->model->n_cfg + kExtraParts, e->opts.load_factor,
                                    &slots, &a, &b, &c, &d);
-    if (bytes > e->arena.size() || q->mh.n_cfg > e->opts.max_cfg) {
+    if (bytes > e->arena.size() || q->model->n_cfg > e->opts.max_cfg) {
       q->res.status = MC_E_ADMIT;  // can never fit
       q->res.done = 1;
       q->done_ns = q->submit_ns;
@@ -574,10 +600,9 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
           still.push_back(q);
           continue;
         }
-        r = new Resident();
+        r = new Resident(q->model);
         r->id = e->next_resident++;
         r->key = q->key;
-        r->mh = std::move(q->mh);
         // blocks of about states/256, with larger blocks while the plan has more than
         // kExtraParts partitions beyond one per configuration (whole configurations last)
         const uint32_t ps = e->opts.part_states;
@@ -601,7 +626,6 @@ int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
                              &r->pstate_off, &r->table_off);
         r->rounds = !r->rplan.parts.empty() && r->rplan.used <= r->slots;
         if (!place(e, r)) {
-          q->mh = std::move(r->mh);
           delete r;
           blocked = wait_memory = true;
           still.push_back(q);

@@ -145,16 +145,20 @@ struct RoundQueue {
   struct RoundRecord* records;
   uint32_t* host_tc;
 };
-// One workgroup's sums over a launch (its pieces of one model, where counters are device's).
+// One workgroup's sums over a launch (its pieces of one model, where counters are device's):
+// a line of the host's cache.  A set has at most 2^31 slots, so that the counts of items and
+// states fit in 32 bits.
 struct RoundRecord {
-  unsigned long long states, terms, edges, dups, probes, chunks, rounds;
-  unsigned long long t_first, t_last;  // device clock (100 MHz): its first piece, its end
-  uint32_t pieces;
+  uint32_t states, terms, edges;
+  uint32_t chunks, rounds, pieces;
+  unsigned long long probes;
   uint32_t depth, max_probe;
   uint32_t crit, crit_cfg;  // its longest piece, in ticks
+  uint32_t t_first, t_last; // device clock (100 MHz, its low bits): its first piece, its end
   uint32_t error;
+  uint32_t pad;
 };
-static_assert(sizeof(RoundRecord) == 96, "RoundRecord layout");
+static_assert(sizeof(RoundRecord) == 64, "RoundRecord layout");
 // Least log2 of the slots of a hash set for pieces of `piece` items.
 inline uint32_t set_log2(uint32_t piece) {
   uint32_t l = 9;

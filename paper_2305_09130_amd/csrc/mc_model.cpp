@@ -425,6 +425,13 @@ int build_model(const mc_desc* d, ModelHost* h, std::string* err) {
   uint64_t total = 1, depth = 0, fb = d->n_cfg;
   uint64_t widest_sum = 0;
   uint32_t max_clock = 0, max_n = 0, max_d = 0;
+  // of k units out of m: the choices, the sets of at most k, the widest C(m, j) with j <= k
+  uint64_t choose[kMaxCU + 1], upto[kMaxCU + 1], widest[kMaxCU + 1];
+  for (uint32_t j = 0; j <= m; ++j) {
+    choose[j] = binom(m, j);
+    upto[j] = j ? upto[j - 1] + choose[j] : 0;
+    widest[j] = j ? std::max(widest[j - 1], choose[j]) : 1;
+  }
   // per configuration: latest terminal clock, state count (bound), longest path
   std::vector<uint64_t> c_tc(d->n_cfg), c_depth(d->n_cfg);
   uint64_t walk_work = 0;  // operation ends the walks of units of unequal speed visit
@@ -474,11 +481,7 @@ int build_model(const mc_desc* d, ModelHost* h, std::string* err) {
     } else {
       const uint64_t q = n / m, p = n % m;
       cs = 1 + q * (((1ull << m) - 1) + b);
-      if (p) {
-        uint64_t s = 0;
-        for (uint32_t j = 1; j <= p; ++j) s += binom(m, j);
-        cs += s + binom(m, (uint32_t)p) * (b - 1) + 1;
-      }
+      if (p) cs += upto[p] + choose[p] * (b - 1) + 1;
       cdepth = 1 + n + rounds * b;
     }
     c_tc[c] = tc;
@@ -487,10 +490,7 @@ int build_model(const mc_desc* d, ModelHost* h, std::string* err) {
     max_n = std::max<uint32_t>(max_n, (uint32_t)n);
     max_d = std::max<uint32_t>(max_d, (uint32_t)t);
     // widest level of this subgraph: dispatch levels C(m, j), partial-round runs C(m, p)
-    uint64_t w = 1;
-    const uint32_t jmax = (uint32_t)std::min<uint64_t>(n, m);
-    for (uint32_t j = 0; j <= jmax; ++j) w = std::max<uint64_t>(w, binom(m, j));
-    widest_sum += w;
+    widest_sum += widest[std::min<uint64_t>(n, m)];
   }
   if (h->hetero) {
     h->cut_cands.assign(d->n_cfg, {});
@@ -595,8 +595,12 @@ int build_model(const mc_desc* d, ModelHost* h, std::string* err) {
   return MC_OK;
 }
 
-void plan_parts(const ModelHost& h, uint64_t target, std::vector<PartPlan>* out,
-                uint64_t clock_max) {
+namespace {
+
+// The partitions of configuration c, in order (see plan_parts), given to emit(PartPlan).
+template <class Emit>
+void plan_config(const ModelHost& h, uint32_t c, uint64_t target, uint64_t clock_max,
+                 const Emit& emit) {
   // units of unequal speed pass through no common idle state after whole rounds
   const bool cuttable = target > 0 && word0_orders_rounds(h);
   // ... but their determined part is cut into chain slices, which share no word-0 value
@@ -604,15 +608,15 @@ void plan_parts(const ModelHost& h, uint64_t target, std::vector<PartPlan>* out,
   const Layout& L = h.layout;
   const bool chains = target > 0 && h.hetero && L.word[kFClock] == 0 && L.word[kFPending] == 0;
   const uint64_t chain_target = std::max<uint64_t>(32, target);
-  for (uint32_t c = 0; c < h.n_cfg; ++c) {
+  {
     const CfgRec& r = h.cfgs[c];
     if (chains) {
       std::vector<ChainCut> cuts;
       if (h.cfg_states[c] >= 2 * chain_target)
         chain_cuts(h.cut_cands[h.cut_of[c]], chain_target, &cuts);
       if (cuts.empty()) {
-        out->push_back(PartPlan{c, 0u, kRoundsToEnd, h.cfg_states[c]});
-        continue;
+        emit(PartPlan{c, 0u, kRoundsToEnd, h.cfg_states[c]});
+        return;
       }
       uint64_t prev_t = 0, prev_dep = 0, prev_states = 0;
       for (size_t k = 0; k <= cuts.size(); ++k) {
@@ -622,14 +626,14 @@ void plan_parts(const ModelHost& h, uint64_t target, std::vector<PartPlan>* out,
                     upto > prev_states ? upto - prev_states : 1};
         pp.j0 = (uint32_t)prev_t;
         pp.j1 = (uint32_t)prev_dep;
-        out->push_back(pp);
+        emit(pp);
         if (!last) {
           prev_t = cuts[k].t;
           prev_dep = cuts[k].depth;
           prev_states = cuts[k].states;
         }
       }
-      continue;
+      return;
     }
     const uint64_t q = r.n / h.m;
     const uint64_t per_round = ((1ull << h.m) - 1) + r.b;
@@ -657,7 +661,7 @@ void plan_parts(const ModelHost& h, uint64_t target, std::vector<PartPlan>* out,
         PartPlan sp{c, kRunSlice, (uint32_t)rd, choices * (j1 - j0)};
         sp.j0 = (uint32_t)j0;
         sp.j1 = (uint32_t)j1;
-        out->push_back(sp);
+        emit(sp);
         j0 = j1;
       }
     };
@@ -668,9 +672,9 @@ void plan_parts(const ModelHost& h, uint64_t target, std::vector<PartPlan>* out,
       if (r.b > sl + 1) {
         PartPlan a{c, 0u, kRoundsToEnd, h.cfg_states[c] - choices * (r.b - sl)};
         a.j1 = (uint32_t)sl;
-        out->push_back(a);
+        emit(a);
         add_slices(0, choices, sl, true);
-        continue;
+        return;
       }
     }
     const uint64_t sl1 = slice_of(1);
@@ -682,37 +686,45 @@ void plan_parts(const ModelHost& h, uint64_t target, std::vector<PartPlan>* out,
         if (k * r.d > clock_max) break;  // the round starts past every state asked for
         PartPlan b{c, (uint32_t)k, (uint32_t)(k + 1), per_round - (r.b - 1 - sl1)};
         b.j1 = (uint32_t)sl1;
-        out->push_back(b);
+        emit(b);
         add_slices(k, 1, sl1, false);
       }
-      if ((p ? q : q - 1) * r.d > clock_max) continue;
+      if ((p ? q : q - 1) * r.d > clock_max) return;
       if (p) {  // the partial round, to the terminals
         const uint64_t choices = binom(h.m, (uint32_t)p), slp = slice_of(choices);
         const bool cut = r.b > slp + 1;
         PartPlan b{c, (uint32_t)q, kRoundsToEnd,
                    h.cfg_states[c] - q * per_round - (cut ? choices * (r.b - slp) : 0)};
         b.j1 = cut ? (uint32_t)slp : 0u;
-        out->push_back(b);
+        emit(b);
         if (cut) add_slices(q, choices, slp, true);
       } else {  // the last full round, to the terminal
         PartPlan b{c, (uint32_t)(q - 1), kRoundsToEnd, (uint64_t)h.cfg_states[c] -
                                                       (q - 1) * per_round - (r.b - sl1)};
         b.j1 = (uint32_t)sl1;
-        out->push_back(b);
+        emit(b);
         add_slices(q - 1, 1, sl1, true);
       }
-      continue;
+      return;
     }
     if (!cuttable || K < 2) {
-      out->push_back(PartPlan{c, 0u, kRoundsToEnd, h.cfg_states[c]});
-      continue;
+      emit(PartPlan{c, 0u, kRoundsToEnd, h.cfg_states[c]});
+      return;
     }
     for (uint64_t k = 0; k + 1 < K && k * R * r.d <= clock_max; ++k)
-      out->push_back(PartPlan{c, (uint32_t)(k * R), (uint32_t)((k + 1) * R), R * per_round});
+      emit(PartPlan{c, (uint32_t)(k * R), (uint32_t)((k + 1) * R), R * per_round});
     const uint64_t r0 = (K - 1) * R;
     if (r0 * r.d <= clock_max)
-      out->push_back(PartPlan{c, (uint32_t)r0, kRoundsToEnd, h.cfg_states[c] - r0 * per_round});
+      emit(PartPlan{c, (uint32_t)r0, kRoundsToEnd, h.cfg_states[c] - r0 * per_round});
   }
+}
+
+}  // namespace
+
+void plan_parts(const ModelHost& h, uint64_t target, std::vector<PartPlan>* out,
+                uint64_t clock_max) {
+  for (uint32_t c = 0; c < h.n_cfg; ++c)
+    plan_config(h, c, target, clock_max, [&](const PartPlan& p) { out->push_back(p); });
 }
 
 bool word0_orders_rounds(const ModelHost& h) {
@@ -814,71 +826,112 @@ bool rounds_model(const ModelHost& h) {
   return true;
 }
 
-void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>& plan,
-                RoundPlan* out) {
-  const uint64_t m = h.m, cl = (1ull << m) - 1;
-  uint64_t slot = 1ull + h.n_cfg;
-  uint32_t cfg = kNoClock;
-  uint64_t root = 0, leaf = 0;  // of the configuration's next round / of the head's round
-  out->parts.reserve(out->parts.size() + plan.size());
-  for (const PartPlan& q : plan) {
-    const CfgRec& r = h.cfgs[q.cfg];
-    if (q.cfg != cfg) {
-      cfg = q.cfg;
-      root = 1ull + cfg;  // its SELECT state
+namespace {
+
+// Turns a configuration's partitions, in plan order, into the round engine's.
+class RoundBuilder {
+ public:
+  RoundBuilder(const ModelHost& h, uint32_t model, RoundPlan* out)
+      : h_(h), model_(model), out_(out), slot_(1ull + h.n_cfg), sets_((1ull << h.m) - 1) {
+    for (uint32_t j = 0; j <= h.m; ++j) {
+      choose_[j] = binom(h.m, j);
+      upto_[j] = j ? upto_[j - 1] + choose_[j] : 0;
     }
-    const uint64_t full = r.n / m, p = r.n % m;
+  }
+
+  void add(const PartPlan& q) {
+    const CfgRec& r = h_.cfgs[q.cfg];
+    if (q.cfg != cfg_) {
+      cfg_ = q.cfg;
+      root_ = 1ull + cfg_;  // its SELECT state
+      full_ = r.n / h_.m;
+      p_ = r.n % h_.m;
+    }
     RoundPart x{};
-    x.model = model;
-    x.cfg_flags = cfg;
-    x.slot0 = (uint32_t)slot;
+    x.model = model_;
+    x.cfg_flags = cfg_;
+    x.slot0 = (uint32_t)slot_;
     uint64_t nfull, ja = 0, jb = r.b, extra = 0;
     bool partial, closure = true;
     if (q.r0 == kRunSlice) {
       closure = false;
       ja = q.j0;
       jb = q.j1;
-      partial = q.r1 >= full;
+      partial = q.r1 >= full_;
       nfull = partial ? 0 : 1;
       x.r0 = q.r1;
       x.a = (uint32_t)ja;
-      x.link = (uint32_t)leaf;
+      x.link = (uint32_t)leaf_;
     } else {
-      partial = q.r1 == kRoundsToEnd && p != 0;
-      nfull = (q.r1 == kRoundsToEnd ? full : q.r1) - q.r0;
+      partial = q.r1 == kRoundsToEnd && p_ != 0;
+      nfull = (q.r1 == kRoundsToEnd ? full_ : q.r1) - q.r0;
       if (q.j1) {
         jb = q.j1;
         extra = q.r1 == kRoundsToEnd ? 0 : 1;  // its round's end starts the next round
       }
       x.r0 = q.r0;
       x.a = (uint32_t)nfull;
-      x.link = (uint32_t)root;
+      x.link = (uint32_t)root_;
     }
     x.jb = (uint32_t)jb;
-    const uint64_t per = (closure ? cl : 0) + (jb - ja) + extra;
+    const uint64_t per = (closure ? sets_ : 0) + (jb - ja) + extra;
     uint64_t items = nfull * per, group = 1;
     if (partial) {
-      const uint64_t choices = binom((uint32_t)m, (uint32_t)p);
-      uint64_t sets = 0;
-      for (uint32_t j = 1; j <= p; ++j) sets += binom((uint32_t)m, j);
       if (closure) {
-        leaf = slot + items + sets - choices;
-        items += sets;
+        leaf_ = slot_ + items + upto_[p_] - choose_[p_];
+        items += upto_[p_];
       }
-      items += choices * (jb - ja);
-      if (jb == r.b) group = choices;  // the runs end in one state
+      items += choose_[p_] * (jb - ja);
+      if (jb == r.b) group = choose_[p_];  // the runs end in one state
     } else if (closure) {
-      leaf = slot + (nfull - 1) * per + cl - 1;
-      root = slot + items - 1;  // the last round's end, where it is held
+      leaf_ = slot_ + (nfull - 1) * per + sets_ - 1;
+      root_ = slot_ + items - 1;  // the last round's end, where it is held
     }
     x.cfg_flags |= (closure ? kRpClosure : 0u) | (extra ? kRpEndExtra : 0u) |
                    (partial ? kRpPartial : 0u);
-    out->parts.push_back(x);
-    out->items.push_back(items);
-    out->end_group.push_back(group);
-    slot += items;
+    out_->parts.push_back(x);
+    out_->items.push_back(items);
+    out_->end_group.push_back((uint32_t)group);
+    slot_ += items;
   }
-  out->used = slot;
+
+  void done() { out_->used = slot_; }
+
+ private:
+  const ModelHost& h_;
+  const uint32_t model_;
+  RoundPlan* out_;
+  uint64_t slot_, sets_;
+  uint64_t choose_[kMaxCU + 1], upto_[kMaxCU + 1];
+  uint32_t cfg_ = kNoClock;
+  uint64_t full_ = 0, p_ = 0;
+  uint64_t root_ = 0, leaf_ = 0;  // of the configuration's next round / of the head's round
+};
+
+}  // namespace
+
+void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>& plan,
+                RoundPlan* out) {
+  RoundBuilder b(h, model, out);
+  out->parts.reserve(out->parts.size() + plan.size());
+  for (const PartPlan& q : plan) b.add(q);
+  b.done();
+}
+
+void round_plan_largest_first(const ModelHost& h, uint64_t target, RoundPlan* out) {
+  std::vector<uint32_t> order(h.n_cfg);
+  std::iota(order.begin(), order.end(), 0u);
+  std::sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
+    return h.cfg_states[a] != h.cfg_states[b] ? h.cfg_states[a] > h.cfg_states[b] : a < b;
+  });
+  RoundBuilder b(h, 0u, out);
+  const size_t guess = h.n_cfg + (target ? h.states / target + 1 : 0);
+  out->parts.reserve(guess);
+  out->items.reserve(guess);
+  out->end_group.reserve(guess);
+  for (const uint32_t c : order)
+    plan_config(h, c, target, ~0ull, [&](const PartPlan& q) { b.add(q); });
+  b.done();
 }
 
 void largest_first(RoundPlan* p) {
@@ -903,10 +956,18 @@ void trim_rounds(const ModelHost& h, const RoundPlan& plan, uint64_t floor, uint
                  RoundPlan* out) {
   const uint64_t m = h.m, cl = (1ull << m) - 1;
   out->used = plan.used;
+  uint32_t cfg = kNoClock;
+  uint64_t t_round = 0, over = 0;  // the round that holds T; rounds that end below the floor
   for (size_t i = 0; i < plan.parts.size(); ++i) {
     RoundPart x = plan.parts[i];
-    const CfgRec& r = h.cfgs[x.cfg_flags & kRpCfg];
+    const uint32_t c = x.cfg_flags & kRpCfg;
+    const CfgRec& r = h.cfgs[c];
     const uint64_t d = r.d, start = (uint64_t)x.r0 * d;
+    if (c != cfg) {
+      cfg = c;
+      t_round = T / d;
+      over = floor ? (floor - 1) / d : 0;
+    }
     if (start > T) continue;
     uint64_t items = plan.items[i], group = plan.end_group[i];
     if (!(x.cfg_flags & kRpClosure)) {  // a slice: clocks of its states ja .. jb - 1
@@ -915,9 +976,7 @@ void trim_rounds(const ModelHost& h, const RoundPlan& plan, uint64_t floor, uint
       const uint64_t per = cl + x.jb + (x.cfg_flags & kRpEndExtra ? 1 : 0);
       const bool partial = (x.cfg_flags & kRpPartial) != 0;
       const uint64_t rest = items - x.a * per;  // the partial round's
-      const uint64_t upto = std::min<uint64_t>(x.a, T / d - x.r0 + 1);
-      // rounds that end below the floor
-      const uint64_t over = floor ? (floor - 1) / d : 0;
+      const uint64_t upto = std::min<uint64_t>(x.a, t_round - x.r0 + 1);
       const uint64_t from = std::min<uint64_t>(upto, over > x.r0 ? over - x.r0 : 0);
       const bool keep = partial && upto == x.a && (x.r0 + (uint64_t)x.a) * d <= T;
       if (keep && from == x.a && (x.r0 + (uint64_t)x.a + 1) * d < floor) continue;
@@ -940,9 +999,13 @@ uint64_t number_pieces(RoundPlan* p, uint32_t piece, uint64_t first_piece) {
   uint64_t n = first_piece;
   for (size_t i = 0; i < p->parts.size(); ++i) {
     p->parts[i].piece0 = (uint32_t)n;
-    n += std::max<uint64_t>(1, (p->items[i] - p->end_group[i] + piece - 1) / piece);
+    const uint64_t over = p->items[i] - p->end_group[i];
+    if (over <= piece) n += 1;  // most partitions
+    else n += over < 0x80000000ull ? ((uint32_t)over + piece - 1u) / piece
+                                   : (over + piece - 1) / piece;
   }
-  return n - first_piece;
+  p->n_pieces = n - first_piece;
+  return p->n_pieces;
 }
 
 uint32_t auto_piece(uint64_t items) {

@@ -181,8 +181,9 @@ constexpr uint32_t kMaxPiece = 4096;  // most items of a piece but for the last 
 struct RoundPlan {
   std::vector<RoundPart> parts;
   std::vector<uint64_t> items;   // per partition
-  std::vector<uint64_t> end_group;  // last items that have to share a piece
+  std::vector<uint32_t> end_group;  // last items that have to share a piece
   uint64_t used = 0;             // slots used: root, SELECT states, items
+  uint64_t n_pieces = 0;         // as numbered last (number_pieces)
 };
 // Bits of the time left in a state's code within a piece (the value below all-ones, so that
 // no code is the empty slot's).
@@ -195,6 +196,8 @@ bool rounds_model(const ModelHost& h);
 // assigned from 1 + n_cfg (the root has slot 0, SELECT(c) slot 1 + c).
 void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>& plan,
                 RoundPlan* out);
+// The same for plan_parts(h, target), the configurations with most states first.
+void round_plan_largest_first(const ModelHost& h, uint64_t target, RoundPlan* out);
 // Orders a plan's partitions by items, most first.
 void largest_first(RoundPlan* p);
 // The partitions of a plan without the rounds and slices that hold no state with clock in

@@ -33,7 +33,7 @@
 // and barriers between pieces overlap another's items.  Pieces of half the size ran slower
 // (matmul128_vw_cu8 0.40 -> 0.47 ms when measured): a piece costs about 3 us beyond its items.
 //
-// Sums go to the host as one 96-byte record per workgroup, stored to pinned memory: added to
+// Sums go to the host as one 64-byte record per workgroup, stored to pinned memory: added to
 // the model's counters instead, ten atomics of 1,024 workgroups on one line took 60 us.
 #include <hip/hip_runtime.h>
 
@@ -97,7 +97,7 @@ __device__ __forceinline__ void flush_sums(Ctrl* ctrl, RoundRecord& s) {
     case 0: v = s.states; to = &ctrl->states; break;
     case 1: v = s.terms; to = &ctrl->terminals; break;
     case 2: v = s.edges; to = &ctrl->edges; break;
-    case 3: v = s.dups; to = &ctrl->dups; break;
+    case 3: v = s.edges - s.states; to = &ctrl->dups; break;
     case 4: v = s.probes; to = &ctrl->probes; break;
     case 5: v = s.chunks; to = &ctrl->chunks; break;
     case 6: v = s.rounds; to = &ctrl->supersteps; break;
@@ -138,10 +138,9 @@ __device__ __forceinline__ uint32_t sum64(uint32_t v) {
 __device__ __forceinline__ void add_sums(RoundRecord& s, ItemSums& w) {
   const uint32_t terms = sum64(w.terms);
   if (lane_id() == 0) {
-    atomicAdd(&s.states, (unsigned long long)w.states);
-    atomicAdd(&s.edges, (unsigned long long)w.edges);
-    if (w.edges != w.states) atomicAdd(&s.dups, (unsigned long long)(w.edges - w.states));
-    if (terms) atomicAdd(&s.terms, (unsigned long long)terms);
+    atomicAdd(&s.states, w.states);
+    atomicAdd(&s.edges, w.edges);
+    if (terms) atomicAdd(&s.terms, terms);
     atomicAdd(&s.probes, (unsigned long long)w.probes);
     atomicMax(&s.max_probe, w.max_probe);
     atomicMax(&s.depth, w.depth);
@@ -274,7 +273,7 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
   uint32_t next = blockIdx.x;
   if (tid == 0) {
     sums = RoundRecord{};
-    sums.t_first = __builtin_amdgcn_s_memrealtime();
+    sums.t_first = (uint32_t)__builtin_amdgcn_s_memrealtime();
   }
   uint32_t model = kParentNone;  // whose sums are held
   Ctrl* ctrl = nullptr;
@@ -379,7 +378,7 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
   add_sums(sums, sum);
   __syncthreads();
   if (a.records) {
-    if (tid == 0) sums.t_last = __builtin_amdgcn_s_memrealtime();
+    if (tid == 0) sums.t_last = (uint32_t)__builtin_amdgcn_s_memrealtime();
     __syncthreads();
     if (tid < sizeof(RoundRecord) / 4u)
       __hip_atomic_store(reinterpret_cast<uint32_t*>(a.records + blockIdx.x) + tid,
