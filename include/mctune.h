@@ -59,7 +59,9 @@
  * counted even where tails meet, so the count is an upper bound, exact on the
  * determined part).  Round blocks are not cut for such models, and the graph is no
  * longer graded (tails meet at different depths): `levels` of the super-step engine is
- * then the depth of each state's first claim, not its BFS depth.
+ * then no BFS depth.  A single model's query counts the steps of every configuration's
+ * determined part and the most that any tail adds in each of its pieces (at most the model's
+ * longest path); a batch or an engine takes the depth of each state's first claim.
  *
  * Conventions.  Every call returns an int: MC_OK (0) or a negative MC_E_* code; no
  * call aborts and no C++ exception crosses the ABI.  Device pointers are plain
@@ -185,7 +187,8 @@ typedef struct mc_stats {
                                 one (device clock) */
     uint64_t critical_cfg;   /* the configuration of that partition */
     uint64_t parts;          /* partitions of the persistent launch (configurations, or
-                                blocks of whole rounds of them) */
+                                blocks of whole rounds of them; on units of unequal speed
+                                windows of their clocks) */
     uint64_t cas_fail;       /* probes whose compare-and-swap met a slot holding another
                                 state: every insert ends on one deciding probe (its claim,
                                 or its own key found), so this is probes - new states -

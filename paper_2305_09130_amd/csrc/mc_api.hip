@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/mctune.h"
+#include "mc_chains.h"
 #include "mc_host_pool.h"
 #include "mc_launch.h"
 #include "mc_model.h"
@@ -159,6 +160,7 @@ hipError_t ev_ms(float* ms, hipEvent_t a, hipEvent_t b) {
 
 constexpr uint32_t kTraceWords = 1u << 14;  // key words of a counterexample kept pinned
 constexpr uint32_t kRoundsGrid = 1024;  // four workgroups of 33 KiB LDS on each of 256 CUs
+static_assert(kMaxChainPieces <= 2 * kTraceWords, "a word per piece where a counterexample goes");
 
 enum { kQueryNone = 0, kQueryMin = 1, kQueryCheck = 2 };
 
@@ -228,6 +230,13 @@ struct mc_model {
   RoundPlan rplan;
   uint32_t* tslot = nullptr;
   bool on_rounds = false;
+  // the chain engine explores this model (units of unequal speed, room for a slot per
+  // generated state, a handle with pinned memory): its plan, whose tables are in the place of
+  // `parts_host`, and whether the last query ran on it
+  bool chains = false;
+  ChainPlan cplan;
+  bool on_chains = false;
+  std::vector<uint32_t> piece_words;  // ChainArgs::words of that query
   uint64_t* trace_words = nullptr;  // pinned, kTraceWords (pooled handles)
   RoundRecord* records = nullptr;  // pinned, kRoundsGrid entries (pooled handles)
   unsigned char* stage_parts = nullptr;  // staging of a query's own plan, or null
@@ -514,6 +523,7 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
   uint64_t ticks = 0;
   if (h->records) {
     HIPCHK(hipStreamSynchronize(s));
+    h->in_flight = false;
     if (!resume) {
       std::memset(ctrl, 0, sizeof(Ctrl));
       ctrl->states = ctrl->probes = 1ull + h->mh.n_cfg;
@@ -537,6 +547,80 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
   return MC_OK;
 }
 
+// What a launch of the chain engine needs of a handle.
+ChainArgs chain_args(mc_model* h, bool prune, uint32_t T) {
+  ChainArgs a{};
+  a.q = make_args(h, prune, T);
+  a.blob = reinterpret_cast<const uint32_t*>(h->parts);
+  a.lcm = h->cplan.lcm;
+  a.uniform = h->cplan.uniform ? 1u : 0u;
+  a.tails_at = h->cplan.tails_at;
+  a.sets_at = h->cplan.sets_at;
+  a.n_pieces = (uint32_t)h->cplan.n_pieces;
+  a.head = h->head;
+  a.abort = h->habort;
+  a.records = h->records;
+  a.words = reinterpret_cast<uint32_t*>(h->trace_words);
+  return a;
+}
+
+// A query on the chain engine.  Every one explores from the start.
+int run_chains(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb) {
+  const auto t0 = std::chrono::steady_clock::now();
+  hipStream_t s = h->stream;
+  h->trace_ready = false;
+  h->last = kQueryNone;
+  h->on_rounds = false;
+  h->swarm_members = 0;  // the visited set overwrites a swarm's records
+  h->q_slots = h->plan.slots;
+  h->resident = false;
+  HIPCHK(join_side(h));
+  // nothing is cleared before or after it: a slot is read only where this exploration wrote
+  h->behind_lo = h->behind_hi = 0;
+  h->dirty_in = std::max<uint64_t>(
+      h->dirty_in, std::min<uint64_t>(8ull * h->mh.W * h->cplan.used, h->max_need));
+  ChainArgs a = chain_args(h, prune, T);
+  a.bb = bb ? 1u : 0u;
+  h->q_parts = a.n_pieces;
+  const uint32_t grid = std::min<uint32_t>(
+      {h->opts.grid ? h->opts.grid : kRoundsGrid, kRoundsGrid, a.n_pieces});
+  HIPCHK(launch_chains(s, h->mh.W, grid, a));
+  h->on_chains = true;
+  HIPCHK(hipStreamSynchronize(s));
+  h->in_flight = false;
+  Ctrl* ctrl = h->hctrl;
+  std::memset(ctrl, 0, sizeof(Ctrl));
+  ctrl->states = ctrl->probes = 1ull + h->mh.n_cfg;
+  ctrl->edges = h->mh.n_cfg;
+  ctrl->max_depth = 1;
+  ctrl->max_probe = 1;
+  uint64_t ticks = 0;
+  add_records(ctrl, h->records, grid, &ticks);
+  h->piece_words.assign(a.words, a.words + a.n_pieces);
+  // Per configuration: the earliest terminal, and the longest path of its pieces (the chain's
+  // steps are counted as found; of the tails' the most of any set in each piece)
+  for (uint32_t c = 0; c < h->mh.n_cfg; ++c) {
+    const ChainCfg& x = h->cplan.cfgs()[c];
+    const uint32_t n = x.windows + x.tail_n * x.tsub;
+    uint64_t depth = 1;
+    h->tc_host[c] = kNoClock;
+    for (uint32_t i = 0; i < n; ++i) {
+      const uint32_t w = h->piece_words[x.piece0 + i];
+      depth += w & 0x7FFFFFFFu;
+      // a terminal ends every workgroup, at K d or at an interval's start
+      if ((w >> 31) && h->tc_host[c] == kNoClock)
+        h->tc_host[c] = (x.K + (i < x.windows ? 0u : (i - x.windows) / x.tsub)) * h->mh.cfgs[c].d;
+    }
+    ctrl->max_depth = std::max<unsigned long long>(ctrl->max_depth, depth);
+  }
+  ctrl->max_depth = std::min<unsigned long long>(ctrl->max_depth, h->mh.max_depth);
+  const int derr = dev_error_code(ctrl->error);
+  if (derr == MC_E_ABORTED && h->habort) __atomic_store_n(h->habort, 0u, __ATOMIC_RELEASE);
+  if (derr != MC_OK) return derr;
+  fill_stats(h, t0, 2, ticks * 10ull, ticks * 10ull, 0, st);
+  return MC_OK;
+}
+
 // prune: drop states with clock > T.  bb (super-step engine): branch and bound, the
 // threshold falls to the least terminal clock found so far and partitions are taken
 // smallest first.
@@ -544,11 +628,12 @@ int run_query(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb = false
               uint32_t T_size = 0) {
   if (h->rounds && h->opts.engine == MC_ENGINE_SUPERSTEP)
     return run_rounds(h, prune, T, st, bb, false);
+  if (h->chains && h->opts.engine == MC_ENGINE_SUPERSTEP) return run_chains(h, prune, T, st, bb);
   const auto t0 = std::chrono::steady_clock::now();
   hipStream_t s = h->stream;
   h->trace_ready = false;
   h->last = kQueryNone;
-  h->on_rounds = false;
+  h->on_rounds = h->on_chains = false;
   h->swarm_members = 0;  // the visited set overwrites a swarm's records
   // a check(T) inserts only the states with clock <= T: its visited set is the prefix of
   // the table sized for their number at the same load factor
@@ -667,6 +752,7 @@ int finish_query(mc_model* h, std::chrono::steady_clock::time_point t0, bool cle
   HIPCHK(hipMemcpyAsync(h->tc_host, h->tc, 4ull * h->mh.n_cfg, hipMemcpyDeviceToHost, s));
   if (const int crc = clear_behind(h)) return crc;
   HIPCHK(hipStreamSynchronize(s));
+  h->in_flight = false;
   const int derr = dev_error_code(h->hctrl->error);
   if (derr == MC_E_ABORTED && h->habort) __atomic_store_n(h->habort, 0u, __ATOMIC_RELEASE);
   if (derr != MC_OK) return derr;
@@ -689,6 +775,12 @@ int run_resume(mc_model* h, uint32_t T, mc_stats* st) {
     const int rc = run_rounds(h, true, T, st, false, true);
     if (rc == MC_OK) h->resident_T = T;
     else h->resident = false;
+    return rc;
+  }
+  if (h->chains) {  // explores from the start
+    const int rc = run_chains(h, true, T, st, false);
+    h->resident = rc == MC_OK;
+    h->resident_T = T;
     return rc;
   }
   const auto t0 = std::chrono::steady_clock::now();
@@ -769,6 +861,22 @@ int trace_w(mc_model* h, uint32_t cfg, uint32_t clock) {
     q.tslot = h->tslot;
     q.target = cfg;
     HIPCHK(launch_round_path(s, q, t, h->mh.general));
+  } else if (h->on_chains) {
+    ChainArgs a = chain_args(h, false, clock);
+    a.q.target = cfg;
+    // a workgroup per chain piece, or per so many that the places fit where the records were
+    const ChainCfg& x = h->cplan.cfgs()[cfg];
+    const uint32_t per = (x.windows + kRoundsGrid - 1) / kRoundsGrid;
+    const uint32_t groups = (x.windows + per - 1) / per;
+    uint32_t* base = reinterpret_cast<uint32_t*>(h->records);
+    uint32_t at = 2;  // past the root and the SELECT state
+    for (uint32_t i = 0; i < x.windows; ++i) {
+      if (i % per == 0) base[i / per] = at;
+      at += h->piece_words[x.piece0 + i] & 0x7FFFFFFFu;
+    }
+    base[groups] = at;
+    t.host_res[0] = t.host_res[1] = t.host_res[2] = 0u;
+    HIPCHK(launch_chain_path(s, W, a, t, groups + 1, base, per));
   } else {
     HIPCHK(launch_find<W>(s, q, reinterpret_cast<const unsigned long long*>(words)));
     HIPCHK(launch_chase<W>(s, q, t));
@@ -801,7 +909,7 @@ int trace_w(mc_model* h, uint32_t cfg, uint32_t clock) {
   for (uint32_t i = 0; i < n; ++i) {
     uint64_t w[4] = {0, 0, 0, 0};
     for (int j = 0; j < W; ++j) {
-      const uint64_t at = (uint64_t)(n - 1 - i) * W + j;
+      const uint64_t at = (uint64_t)(h->on_chains ? i : n - 1 - i) * W + j;  // its order
       w[j] = at < t.host_words ? h->trace_words[at] : rest[at - t.host_words];
     }
     uint32_t f[kFields];
@@ -874,24 +982,6 @@ int mc_config_ends(const mc_desc* d, uint32_t cfg, uint32_t* n, uint32_t* b, uin
   }
 }
 
-int mc_workspace_bytes(const mc_desc* d, const mc_opts* o, size_t* bytes) {
-  if (!bytes) return MC_E_INVAL;
-  try {
-    ModelHost mh;
-    std::string err;
-    int rc = build_model(d, &mh, &err);
-    if (rc) return rc;
-    WsPlan p;
-    const mc_opts oo = default_opts(o);
-    rc = plan_ws(mh, oo, model_plan(mh, oo).size(), &p);
-    if (rc) return rc;
-    *bytes = p.total;
-    return MC_OK;
-  } catch (...) {
-    return MC_E_INVAL;
-  }
-}
-
 int mc_model_free(mc_model* h) {
   if (!h) return MC_E_INVAL;
   if (h->pooled) {
@@ -920,6 +1010,7 @@ struct Loaded {
   WsPlan plan;
   std::vector<Part> parts;
   RoundPlan rounds;
+  ChainPlan chains;
 };
 
 uint64_t part_target(const ModelHost& mh, const mc_opts& o) {
@@ -941,7 +1032,15 @@ void plan_rounds(const ModelHost& mh, const mc_opts& o, uint64_t slots, RoundPla
   number_pieces(out, auto_piece(mh.states));
 }
 
-int prepare_load(const mc_desc* d, const mc_opts& opts_in, size_t ws_bytes, Loaded* L) {
+// The chain engine's plan; empty where that engine cannot explore the model.
+void plan_chains(const ModelHost& mh, const mc_opts& o, uint64_t slots, ChainPlan* out) {
+  const uint64_t target = o.part_states == 0xFFFFFFFFu ? kChainCap : o.part_states;
+  chain_plan(mh, slots, target, out);
+}
+size_t chain_parts(const ChainPlan& p) { return (4 * p.blob.size() + sizeof(Part) - 1) / sizeof(Part); }
+
+int prepare_load(const mc_desc* d, const mc_opts& opts_in, size_t ws_bytes, bool pooled,
+                 Loaded* L) {
   std::string err;
   int rc = build_model(d, &L->mh, &err);
   if (rc) return rc;
@@ -952,8 +1051,10 @@ int prepare_load(const mc_desc* d, const mc_opts& opts_in, size_t ws_bytes, Load
   rc = plan_slots(L->mh, L->opts, &slots);
   if (rc) return rc;
   plan_rounds(L->mh, L->opts, slots, &L->rounds);
-  if (L->rounds.parts.empty()) L->parts = sorted_parts(model_plan(L->mh, L->opts));
-  rc = plan_ws(L->mh, L->opts, L->rounds.parts.size() + L->parts.size(), &L->plan);
+  if (L->rounds.parts.empty() && pooled) plan_chains(L->mh, L->opts, slots, &L->chains);
+  if (L->rounds.parts.empty() && !L->chains.ok()) L->parts = sorted_parts(model_plan(L->mh, L->opts));
+  rc = plan_ws(L->mh, L->opts,
+               L->rounds.parts.size() + chain_parts(L->chains) + L->parts.size(), &L->plan);
   if (rc) return rc;
   if (ws_bytes < L->plan.total) return MC_E_NOMEM;
   // automatic workgroup size: with fewer partitions than a wide launch has workgroups,
@@ -963,7 +1064,7 @@ int prepare_load(const mc_desc* d, const mc_opts& opts_in, size_t ws_bytes, Load
   // units of unequal speed: 512 (their chain listing is block-wide; on the 1.4M-state
   // workload the launch took 0.70 ms against 0.95 with 256 and 0.83 with 1024)
   if (!L->opts.block) {
-    if (!L->rounds.parts.empty()) L->opts.block = 256u;
+    if (!L->rounds.parts.empty() || L->chains.ok()) L->opts.block = 256u;
     else L->opts.block = (L->mh.hetero || L->parts.size() < kWideParts) ? 512u : 256u;
   }
   return MC_OK;
@@ -983,7 +1084,9 @@ int install(mc_model* h, Loaded& L) {
   h->parts_host = std::move(L.parts);
   h->rplan = std::move(L.rounds);
   h->rounds = !h->rplan.parts.empty();
-  h->on_rounds = false;
+  h->cplan = std::move(L.chains);
+  h->chains = h->cplan.ok();
+  h->on_rounds = h->on_chains = false;
   h->ctrl = reinterpret_cast<Ctrl*>(h->ws + h->plan.ctrl);
   h->tc = reinterpret_cast<uint32_t*>(h->ws + h->plan.tc);
   h->cfgs = reinterpret_cast<CfgRec*>(h->ws + h->plan.cfgs);
@@ -998,7 +1101,9 @@ int install(mc_model* h, Loaded& L) {
   h->q_slots = h->plan.slots;
   h->q_parts = 0;
   h->tslot = reinterpret_cast<uint32_t*>(h->ws + h->plan.seeds);
-  h->n_parts = (uint32_t)(h->rounds ? h->rplan.parts.size() : h->parts_host.size());
+  h->n_parts = (uint32_t)(h->rounds   ? h->rplan.parts.size()
+                          : h->chains ? chain_parts(h->cplan)
+                                      : h->parts_host.size());
   h->trace_ready = false;
   h->trace_rows.clear();
   h->last = kQueryNone;
@@ -1017,7 +1122,7 @@ int install(mc_model* h, Loaded& L) {
   const size_t up_off = align_up(tc_off + 4ull * h->mh.n_cfg);
   // the records and partitions are staged as they lie in the workspace, for one copy, and
   // after them is room for a query's own partitions
-  const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg, part_bytes = sizeof(Part) * h->n_parts;
+  const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg, part_bytes = h->chains ? 4 * h->cplan.blob.size() : sizeof(Part) * h->n_parts;
   const size_t part_off = h->plan.order - h->plan.cfgs, up_bytes = part_off + part_bytes;
   const bool stage = up_bytes <= (4u << 20);
   const size_t own_off = align_up(up_off + up_bytes);
@@ -1051,8 +1156,9 @@ int install(mc_model* h, Loaded& L) {
   h->hmd = reinterpret_cast<ModelDev*>(blk + 512);
   h->tc_host = reinterpret_cast<uint32_t*>(blk + tc_off);
   for (uint32_t c = 0; c < h->mh.n_cfg; ++c) h->tc_host[c] = kNoClock;
-  const void* up_part = h->rounds ? static_cast<const void*>(h->rplan.parts.data())
-                                  : static_cast<const void*>(h->parts_host.data());
+  const void* up_part = h->rounds   ? static_cast<const void*>(h->rplan.parts.data())
+                        : h->chains ? static_cast<const void*>(h->cplan.blob.data())
+                                    : static_cast<const void*>(h->parts_host.data());
   h->stage_parts = nullptr;
   hipStream_t s = h->stream;
   hipError_t e;
@@ -1089,7 +1195,7 @@ int bind_model(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes
   try {
     Loaded L;
     const mc_opts opts_in = default_opts(o);
-    int rc = prepare_load(d, opts_in, ws_bytes, &L);
+    int rc = prepare_load(d, opts_in, ws_bytes, pooled, &L);
     if (rc) return rc;
     h = new mc_model();
     h->pooled = pooled;
@@ -1150,6 +1256,31 @@ int min_time_in_place(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t w
 
 extern "C" {
 
+int mc_workspace_bytes(const mc_desc* d, const mc_opts* o, size_t* bytes) {
+  if (!bytes) return MC_E_INVAL;
+  try {
+    ModelHost mh;
+    std::string err;
+    int rc = build_model(d, &mh, &err);
+    if (rc) return rc;
+    WsPlan p;
+    const mc_opts oo = default_opts(o);
+    size_t n_parts = model_plan(mh, oo).size();
+    uint64_t slots = 0;
+    if (mh.hetero && plan_slots(mh, oo, &slots) == MC_OK) {
+      ChainPlan chains;
+      plan_chains(mh, oo, slots, &chains);
+      n_parts = std::max(n_parts, chain_parts(chains));
+    }
+    rc = plan_ws(mh, oo, n_parts, &p);
+    if (rc) return rc;
+    *bytes = p.total;
+    return MC_OK;
+  } catch (...) {
+    return MC_E_INVAL;
+  }
+}
+
 int mc_model_load(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes, void* stream,
                   mc_model** out) {
   return bind_model(d, o, dev_ws, ws_bytes, stream, true, out);
@@ -1159,7 +1290,7 @@ int mc_model_reload(mc_model* h, const mc_desc* d) {
   if (!h || !d) return MC_E_INVAL;
   try {
     Loaded L;
-    const int rc = prepare_load(d, h->opts_in, h->ws_bytes, &L);
+    const int rc = prepare_load(d, h->opts_in, h->ws_bytes, h->pooled, &L);
     if (rc) return rc;  // the handle keeps its model
     // the new model's tables go past its visited set: where the side stream is still
     // clearing bytes there, the uploads wait for it (its own queries wait anyway)

@@ -1,0 +1,638 @@
+// mc_chains.hip -- the chain engine: exhaustive exploration on units of unequal speed with
+// every workgroup's part of the visited set in its own LDS.
+//
+// On units of unequal speed a configuration's states up to its last dispatches are one per
+// operation end of any unit and the closures of the dispatches at multiples of d; after them
+// each choice of the last p units runs on by itself (mc_chains.h).  States at different clocks
+// differ, so the visited set can be cut by clocks: a workgroup takes a piece (a window of a
+// configuration's clocks), generates the window's states from their numbers, tests each in a
+// hash set in LDS, exact on (clock, busy units), and writes the new ones to slots of their own
+// in the visited set in HBM, a unit's ends one after another.  The duplicates are ends of
+// several units at one clock; their slots are written empty.
+//
+// What bounds it.  k_superstep, which explored these models before, lists a chain state by
+// state between two dispatches, in turns of the whole workgroup, and claims each state with a
+// device-scope compare-and-swap in a table that has to be cleared first.  Here nothing in a
+// piece waits for a state before it: a piece costs its fixed part, about 10 us (its tables,
+// its window's counts and barriers, a chain of dependent reads), and some hundred vector
+// instructions per 64 states.  min_time launch, k_superstep -> here: reduction_g256_cu4_s1123
+// (86k states) 229 -> 13 us, matmul32_cu4_s1123 (1.44M) 642 -> 44 us; check one below the
+// optimum 157 -> 9 us and 194 -> 31 us.
+//
+// A workgroup has 256 threads and 18 KiB of LDS.  Its registers (118 vector registers with
+// two-word keys) let four share a CU, as many as a launch has.  With the loops for any number
+// of units and any kind of operation list matmul32 took 63 us instead of 49 (pieces of 1,024):
+// four units and lists of uniform phases have builds of their own.
+//
+// Each piece stores a word to pinned memory: the steps it adds to a path, which give a
+// counterexample's places and the longest path, and whether a terminal was found, whose clock
+// follows from the piece.  So no counter on the device is added to, and nothing is copied.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "mc_chains.h"
+#include "mc_launch.h"
+
+namespace mc {
+
+namespace {
+
+constexpr uint32_t kSetEmpty = 0xFFFFFFFFu;
+constexpr uint32_t kChainBlock = 256;
+
+// A window from LDS, in scalar registers.
+__device__ __forceinline__ ChainWindow load_window(const ChainWindow& s) {
+  static_assert(sizeof(ChainWindow) % 4 == 0, "whole words");
+  union {
+    ChainWindow v;
+    uint32_t w[sizeof(ChainWindow) / 4];
+  } u;
+  const uint32_t* p = reinterpret_cast<const uint32_t*>(&s);
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(ChainWindow) / 4; ++i) u.w[i] = uniform(p[i]);
+  return u.v;
+}
+
+// Operation ends.  UNIFORM: every configuration of the model has uniform phases and one wave.
+template <bool UNIFORM>
+struct DeviceEnds;
+template <>
+struct DeviceEnds<false> {
+  GeneralEnds g;
+  const CfgRec& r;
+  __device__ __forceinline__ explicit DeviceEnds(const CfgRec& c) : g(general_ends(c)), r(c) {}
+  __device__ __forceinline__ uint32_t at(uint32_t j) const { return r.d - rem_after(g, j); }
+  __device__ __forceinline__ uint32_t upto(uint32_t x) const { return ends_upto(r, x); }
+};
+template <>
+struct DeviceEnds<true> {
+  UniformEnds g;
+  const CfgRec& r;
+  __device__ __forceinline__ explicit DeviceEnds(const CfgRec& c) : g(uniform_ends(c)), r(c) {}
+  __device__ __forceinline__ uint32_t at(uint32_t j) const { return r.d - rem_after(g, j); }
+  __device__ __forceinline__ uint32_t upto(uint32_t x) const { return ends_upto_uniform(r, x); }
+};
+
+// The configuration that holds piece p: the last whose first piece is at most p.
+__device__ __forceinline__ uint32_t find_cfg(const ChainCfg* cfgs, uint32_t n, uint32_t p) {
+  uint32_t lo = 0, len = n;
+  while (len > 1u) {
+    const uint32_t step = (len + 63u) / 64u, at = lane_id() * step;
+    const bool le = at < len && cfgs[lo + at].piece0 <= p;
+    const uint32_t c = (uint32_t)__popcll(__ballot(le));  // at least one: cfgs[lo]
+    const uint32_t skip = (c - 1u) * step;
+    lo += skip;
+    len = step < len - skip ? step : len - skip;
+  }
+  return uniform(lo);
+}
+
+template <int W, int M>
+__device__ __forceinline__ Key<W> key_of(const ChainItem& it, uint32_t c, uint32_t clock,
+                                         const Layout& L) {
+  St y;
+  y.cfg = c;
+  y.pending = it.pending;
+  y.clock = clock;
+#pragma unroll
+  for (int u = 0; u < kMaxCU; ++u) y.rem[u] = u < M ? it.rem[u] : 0u;
+  return encode<W>(y, L);
+}
+
+// The sets of busy units of F_K in a tail window, ascending, listed by the first wavefront;
+// returns their number.
+__device__ __forceinline__ uint32_t list_sets(uint32_t p, uint32_t alive, uint32_t dead_n,
+                                              uint8_t* list) {
+  uint32_t n = 0;
+  for (uint32_t b = 0; b < 1u << bits_set(alive); b += 64u) {
+    const uint32_t x = b + lane_id(), set = spread_bits(x, alive);
+    const bool ok = x < 1u << bits_set(alive) && tail_set(p, dead_n, set);
+    const unsigned long long in = __ballot(ok);
+    if (ok) list[n + (uint32_t)__popcll(in & ((1ull << lane_id()) - 1ull))] = (uint8_t)set;
+    n += (uint32_t)__popcll(in);
+  }
+  return n;
+}
+
+struct ChainShared {
+  ChainWindow w;
+  uint32_t whole[kMaxCU];
+  uint32_t sets_n;
+  uint8_t list[256];
+  uint32_t per_set[256];  // new ends of each set
+};
+
+// Fills s.w for [s.w.t0, s.w.t1); every thread calls it.
+template <class E>
+__device__ __forceinline__ void fill_window(ChainShared& s, const ChainCfg& x, const ChainEnv& g,
+                                            const E& ends, const ChainTail& tl,
+                                            bool tail, uint32_t interval) {
+  const uint32_t tid = threadIdx.x;
+  if (tid < (uint32_t)kMaxCU) {
+    uint32_t whole = 0;
+    if (tail) whole = tail_window_unit(s.w, x, g, ends, interval, tid);
+    else chain_window_unit(s.w, x, g, ends, tid);
+    s.whole[tid] = whole;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    if (tail) tail_window_rest(s.w, x, g, tl, interval, s.whole);
+    else chain_window_rest(s.w, x, g);
+  }
+  __syncthreads();
+  if (tail && tid < 64u) {
+    const uint32_t n = list_sets(x.p, s.w.alive, s.w.dead_n, s.list);
+    if (tid == 0) {
+      s.w.sets_n = n;
+      s.w.items = n * s.w.before[kMaxCU];
+    }
+  }
+  if (tail) __syncthreads();
+}
+
+}  // namespace
+
+// Counters, the root (slot 0) and the SELECT states (slot 1 + c).
+template <int W>
+__global__ __launch_bounds__(256) void k_chains_begin(ChainArgs a) {
+  const uint32_t tid = threadIdx.x;
+  unsigned int* cw = reinterpret_cast<unsigned int*>(a.q.ctrl);
+  for (uint32_t i = tid; i < sizeof(Ctrl) / 4; i += 256u) cw[i] = 0u;
+  __syncthreads();
+  if (tid == 0) {
+    a.q.ctrl->bound = a.q.T;
+    a.q.ctrl->target_slot = kParentNone;
+    *a.head = 0u;
+  }
+  for (uint32_t i = tid; i <= a.q.n_cfg; i += 256u) {
+    St y = {};
+    y.cfg = i ? i - 1u : a.q.n_cfg;
+    y.pending = i ? a.q.cfgs[i - 1u].n : 0u;
+    const Key<W> k = encode<W>(y, a.q.L);
+    unsigned long long* to = reinterpret_cast<unsigned long long*>(a.q.table) + (unsigned long long)i * W;
+#pragma unroll
+    for (int w = 0; w < W; ++w) to[w] = k.w[w];
+  }
+}
+
+template <int W, int M, bool UNIFORM>
+__global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
+  __shared__ uint32_t set[1u << kChainSetLog2];
+  __shared__ ChainShared s;
+  __shared__ union {
+    RoundRecord rec;
+    uint32_t words[sizeof(RoundRecord) / 4];
+  } s_sums;
+  RoundRecord& sums = s_sums.rec;
+  __shared__ uint32_t s_piece, s_T, s_skip, s_steps, s_term;
+  const uint32_t tid = threadIdx.x;
+  const ChainCfg* cfgs = reinterpret_cast<const ChainCfg*>(a.blob);
+  const ChainTail* tails = reinterpret_cast<const ChainTail*>(a.blob + a.tails_at);
+  uint32_t next = blockIdx.x;
+  if (tid == 0) {
+    sums = RoundRecord{};
+    sums.t_first = (uint32_t)__builtin_amdgcn_s_memrealtime();
+  }
+  // sums of a wavefront (uniform in it)
+  uint32_t states = 0, edges = 0, probes = 0, max_probe = 0, terms = 0;
+  for (;;) {
+    if (tid == 0) s_piece = next;
+    __syncthreads();  // the piece before is done
+    const uint32_t piece = uniform(s_piece);
+    if (piece >= a.n_pieces) break;
+    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+    const uint32_t c = find_cfg(cfgs, a.q.n_cfg, piece);
+    const ChainCfg x = load_const(cfgs + c);
+    const CfgRec r = load_const(a.q.cfgs + c);
+    const ChainEnv g = chain_env(r, a.q.L.speed, a.q.L.m, a.lcm, a.blob + a.sets_at);
+    const DeviceEnds<UNIFORM> ends(r);
+    if (tid == 0) {
+      uint32_t T = a.q.prune ? a.q.T : kNoClock;
+      if (a.bb) {
+        const uint32_t b = __hip_atomic_load(&a.q.ctrl->bound, __ATOMIC_RELAXED, kScopeAgent);
+        T = b < T ? b : T;
+      }
+      const uint32_t stop = abort_asked(a.abort, piece);
+      if (stop) {
+        set_error(a.q.ctrl, kDevErrAbort);
+        sums.error = kDevErrAbort;
+      }
+      s_T = T;
+      s_skip = stop | __hip_atomic_load(&a.q.ctrl->error, __ATOMIC_RELAXED, kScopeAgent);
+      s_steps = s_term = 0u;
+      next = a.n_pieces > gridDim.x ? gridDim.x + atomicAdd(a.head, 1u) : a.n_pieces;
+    }
+    __syncthreads();
+    const ChainSpan span = chain_span(x, g, piece - x.piece0, uniform(s_T));
+    const bool tail = span.tail;
+    const ChainTail tl = load_const(tails + (tail ? x.tail0 + span.interval : 0u));
+    uint32_t steps = 0;  // of the longest path through the piece (thread 0)
+    uint32_t from = uniform(s_skip) ? span.t1 : span.t0;
+    while (from < span.t1) {
+      uint32_t to = span.t1;
+      for (;;) {
+        if (tid == 0) {
+          s.w.t0 = from;
+          s.w.t1 = to;
+        }
+        __syncthreads();
+        fill_window(s, x, g, ends, tl, tail, span.interval);
+        const uint32_t items = uniform(s.w.items);
+        __syncthreads();
+        if (items <= kChainCap || to - from == 1u) break;
+        to = from + (to - from) / 2u;
+      }
+      {
+        uint4* s4 = reinterpret_cast<uint4*>(set);
+        for (uint32_t i = tid; i < 1u << (kChainSetLog2 - 2u); i += kChainBlock)
+          s4[i] = make_uint4(kSetEmpty, kSetEmpty, kSetEmpty, kSetEmpty);
+        s.per_set[tid] = 0u;
+      }
+      __syncthreads();
+      // (two loops: the fields of either kind of window fill the scalar registers)
+      const auto explore = [&](auto is_tail) {
+        constexpr bool kTail = decltype(is_tail)::value;
+        const ChainWindow w = load_window(s.w);
+        const uint32_t items = w.items < kChainCap ? w.items : kChainCap;
+        const float per_inv = inverse(w.before[kMaxCU]);
+        uint32_t ends_new = 0;
+        for (uint32_t base = 0; base < items; base += kChainBlock) {
+          const uint32_t i = base + tid < items ? base + tid : items - 1u;
+          ChainItem it;
+          uint32_t rank = 0;
+          if constexpr (kTail) {
+            rank = quotient(i, per_inv);
+            tail_item<M>(w, x, g, ends, i - rank * w.before[kMaxCU], rank, s.list[rank], &it);
+          } else {
+            chain_item<M>(w, x, g, ends, r.n, i, &it);
+          }
+          const bool in = base + tid < items, act = in && it.active;
+          const uint32_t code = it.t << g.m | it.busy;
+          uint32_t h = code * 0x9E3779B1u;
+          if (a.q.hkeep) h = ((h >> 8) & ((1u << a.q.hkeep) - 1u)) * 0x9E3779B1u;
+          uint32_t at = h >> (32u - kChainSetLog2), old = code;
+          if (act) old = atomicCAS(&set[at], kSetEmpty, code);
+          const unsigned long long acts = __builtin_amdgcn_ballot_w64(act);
+          unsigned long long met =
+              __builtin_amdgcn_ballot_w64(act && old != kSetEmpty && old != code);
+          uint32_t trips = 1;
+          probes += (uint32_t)__popcll(acts) + (uint32_t)__popcll(met);
+          while (met) {
+            if (__builtin_amdgcn_inverse_ballot_w64(met)) {
+              at = (at + 1u) & ((1u << kChainSetLog2) - 1u);
+              old = atomicCAS(&set[at], kSetEmpty, code);
+            }
+            met &= __builtin_amdgcn_ballot_w64(old != kSetEmpty && old != code);
+            probes += (uint32_t)__popcll(met);
+            if (++trips >> kChainSetLog2) break;  // (never: there are more slots than states)
+          }
+          max_probe = trips > max_probe ? trips : max_probe;
+          const bool fresh = act && old == kSetEmpty;
+          if (in) {
+            const Key<W> key = key_of<W, M>(it, c, w.t0 + it.t, a.q.L);
+            global_u64* kp = (global_u64*)a.q.table + (unsigned long long)it.slot * W;
+#pragma unroll
+            for (int j = 0; j < W; ++j) kp[j] = fresh ? key.w[j] : kEmptyWord;
+          }
+          if (kTail && fresh) atomicAdd(&s.per_set[rank], 1u);
+          const unsigned long long news = __builtin_amdgcn_ballot_w64(fresh);
+          edges += (uint32_t)__popcll(acts);
+          states += (uint32_t)__popcll(news);
+          if constexpr (!kTail)
+            ends_new += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(fresh && it.is_end));
+          const unsigned long long over =
+              __builtin_amdgcn_ballot_w64(fresh && (it.pending | it.busy) == 0u);
+          if (over) {
+            terms += (uint32_t)__popcll(over);
+            if (__builtin_amdgcn_inverse_ballot_w64(over)) {
+              s_term = 1u;
+              if (a.bb) atomicMin(&a.q.ctrl->bound, w.t0 + it.t);
+            }
+          }
+        }
+        // the steps this window adds to a path: every end and dispatch of the chain, and of a
+        // tail the ends of the set with most
+        if (!kTail && ends_new && lane_id() == 0) atomicAdd(&s_steps, ends_new);
+        __syncthreads();
+        if (kTail) {
+          if (tid < 64u) {
+            uint32_t most = 0;
+            for (uint32_t q = tid; q < 256u; q += 64u) most = max(most, s.per_set[q]);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, o));
+            steps += most;
+          }
+        } else {
+          steps += starts_between(g, w.k0, w.k1) + (w.part_n ? x.p : 0u);
+        }
+        if (tid == 0) sums.chunks += (items + kChainBlock - 1u) / kChainBlock;
+      };
+      if (tail) explore(std::true_type{});
+      else explore(std::false_type{});
+      from = to;
+      __syncthreads();
+    }
+    if (tid == 0) {
+      __hip_atomic_store(a.words + piece, (s_steps + steps) | (s_term << 31), __ATOMIC_RELAXED,
+                         kScopeSystem);
+      sums.rounds += 1u;
+      sums.pieces += 1u;
+      const uint32_t dt = (uint32_t)(__builtin_amdgcn_s_memrealtime() - t0);
+      if (dt > sums.crit) {
+        sums.crit = dt;
+        sums.crit_cfg = c;
+      }
+    }
+  }
+  if (lane_id() == 0) {
+    atomicAdd(&sums.states, states);
+    atomicAdd(&sums.edges, edges);
+    if (terms) atomicAdd(&sums.terms, terms);
+    atomicAdd(&sums.probes, (unsigned long long)probes);
+    atomicMax(&sums.max_probe, max_probe);
+  }
+  __syncthreads();
+  if (tid == 0) sums.t_last = (uint32_t)__builtin_amdgcn_s_memrealtime();
+  __syncthreads();
+  if (tid < sizeof(RoundRecord) / 4u)
+    __hip_atomic_store(reinterpret_cast<uint32_t*>(a.records + blockIdx.x) + tid,
+                       s_sums.words[tid], __ATOMIC_RELAXED, kScopeSystem);
+}
+
+// ---- counterexample ---------------------------------------------------------------------
+//
+// The path to a terminal of configuration q.target at clock q.T, root first.  Up to the last
+// dispatches every end of the chain is on it, and of each dispatch the units in index order;
+// then the least set of p units whose tail ends at q.T.  The exploration counted each chain
+// piece's states on the path, so a workgroup knows where its pieces' states go (base[b] for
+// workgroup b); the last one lists the tail.  Within a window of clocks an end belongs to the
+// lowest unit that ends there, its place is the ends before it (of each unit, by a prefix sum
+// over those that belong to it) and the dispatches before it.  Every state has to be in a slot
+// of its own or, an end of several units, in one of theirs, or the path is bad.
+//
+// It waits for its reads and barriers, window by window.  One workgroup for the whole path took
+// 64 and 71 us on the two models above, a workgroup for each piece 34 and 36, most of it the
+// tail's intervals, one after another.
+constexpr uint32_t kPathEnds = kChainCap, kChainPathBlock = 512;
+
+template <int W, int M, bool UNIFORM>
+__global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, TraceOut t,
+                                                               const uint32_t* base,
+                                                               uint32_t per) {
+  __shared__ ChainShared s;
+  __shared__ uint32_t own[kPathEnds + 1], covered[kPathEnds / 32], wave_sums[kChainPathBlock / 64];
+  __shared__ uint32_t s_bad, s_set, s_rank;
+  const uint32_t tid = threadIdx.x, c = a.q.target, T = a.q.T;
+  const ChainCfg x = load_const(reinterpret_cast<const ChainCfg*>(a.blob) + c);
+  const ChainTail* tails = reinterpret_cast<const ChainTail*>(a.blob + a.tails_at);
+  const CfgRec r = load_const(a.q.cfgs + c);
+  const ChainEnv g = chain_env(r, a.q.L.speed, a.q.L.m, a.lcm, a.blob + a.sets_at);
+  const DeviceEnds<UNIFORM> ends(r);
+  const unsigned long long* keys = reinterpret_cast<const unsigned long long*>(a.q.table);
+  const auto there = [&](uint32_t slot, const Key<W>& k) {
+    bool same = slot <= a.q.mask;
+#pragma unroll
+    for (int w = 0; w < W; ++w) same = same && keys[(unsigned long long)slot * W + w] == k.w[w];
+    return same;
+  };
+  const auto put = [&](uint32_t i, const Key<W>& k) {
+    if (i >= t.cap) return;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const unsigned long long at = (unsigned long long)i * W + w;
+      if (at < t.host_words) t.host[at] = k.w[w];
+      else t.out[at] = k.w[w];
+    }
+  };
+  if (tid == 0) {
+    s_bad = 0u;
+    s_set = 0x100u;
+  }
+  __syncthreads();
+  const bool last = blockIdx.x + 1u == gridDim.x;
+  uint32_t n = base[blockIdx.x];
+  if (blockIdx.x == 0u && tid < 2u) {  // the root and the SELECT state
+    St y = {};
+    y.cfg = tid ? c : a.q.n_cfg;
+    y.pending = tid ? r.n : 0u;
+    const Key<W> k = encode<W>(y, a.q.L);
+    if (!there(tid ? 1u + c : 0u, k)) s_bad = 1u;
+    put(tid, k);
+  }
+  // the least set of p units of F_K whose tail ends at T (none where the chain ends there)
+  if (tid < 256u && (tid & ~x.idle) == 0u && bits_set(tid) == x.p) {
+    uint32_t end = x.K * g.d;
+    for (uint32_t u = 0; u < g.m; ++u)
+      if (((tid | ~x.idle) >> u) & 1u)
+        end = max(end, tail_start(x, g, u) + g.speed[u] * g.d);
+    if (end == T) atomicMin(&s_set, tid);
+  }
+  __syncthreads();
+  const uint32_t chosen = uniform(s_set);
+  bool bad = chosen > 0xFFu;
+  const uint32_t on = (g.all & ~x.idle) | chosen;  // units busy in the tail
+  // the workgroup's chain pieces, one at a time, or the tail's intervals
+  const bool tail = last;
+  uint32_t phase = last ? 0u : blockIdx.x * per;
+  const uint32_t phases = last ? x.tail_n : min(phase + per, x.windows);
+  for (; !bad && phase < phases; ++phase) {
+    const uint32_t interval = tail ? phase : 0u;
+    const ChainSpan span = chain_span(x, g, phase, kNoClock);
+    uint32_t from = tail ? tail_from(x, g, interval) : span.t0;
+    uint32_t end = tail ? (x.K + interval + 1u) * g.d : span.t1;
+    if (tail && end > T + 1u) end = T + 1u;
+    const ChainTail tl = load_const(tails + (tail ? x.tail0 + interval : 0u));
+    while (from < end) {
+      uint32_t to = end;
+      for (;;) {
+        if (tid == 0) {
+          s.w.t0 = from;
+          s.w.t1 = to;
+        }
+        __syncthreads();
+        fill_window(s, x, g, ends, tl, tail, interval);
+        const uint32_t k = uniform(s.w.before[kMaxCU]);
+        __syncthreads();
+        if (k <= kPathEnds || to - from == 1u) break;
+        to = from + (to - from) / 2u;
+      }
+      const ChainWindow w = load_window(s.w);
+      const uint32_t N = w.before[kMaxCU], set = chosen & w.alive;
+      if (tid == 0) s_rank = 0u;
+      for (uint32_t i = tid; i < (N + 31u) / 32u; i += kChainPathBlock) covered[i] = 0u;
+      __syncthreads();
+      if (tail && tid < w.sets_n && s.list[tid] == set) s_rank = tid;
+      __syncthreads();
+      const uint32_t rank = uniform(s_rank);
+      // unit v's ends before clock `at`, from the window's first on
+      const auto ends_to = [&](uint32_t v, uint32_t at) {
+        uint32_t k;
+        if (!tail) return ends_before(ends, g, g.speed[v], at) - s.w.first[v];
+        return ends_of_one(ends, g.speed[v], tail_start(x, g, v), w.t0, at, &k);
+      };
+      const auto counts = [&](uint32_t v) {
+        return tail ? tail_lists(x, g, v) && ((on >> v) & 1u) : ((g.reps >> v) & 1u) != 0u;
+      };
+      const auto item = [&](uint32_t i, ChainItem* it) {
+        if (tail) tail_item<M>(w, x, g, ends, i, rank, set, it);
+        else chain_item<M>(w, x, g, ends, r.n, i, it);
+      };
+      for (uint32_t i = tid; i < N; i += kChainPathBlock) {
+        ChainItem it;
+        item(i, &it);
+        const uint32_t at = w.t0 + it.t;
+        uint32_t owner = kParentNone;
+        for (uint32_t v = 0; v < g.m && owner == kParentNone; ++v) {
+          if (!counts(v) || !s.w.count[v]) continue;
+          const uint32_t k = ends_to(v, at);
+          if (ends_to(v, at + 1u) > k) owner = s.w.before[v] + k;
+        }
+        own[i] = owner == i ? 1u : 0u;
+        if (owner < N && it.active && there(it.slot, key_of<W, M>(it, c, at, a.q.L)))
+          atomicOr(&covered[owner >> 5], 1u << (owner & 31u));
+      }
+      __syncthreads();
+      {  // exclusive prefix sum of `own`, own[N] = their number
+        constexpr uint32_t kPer = kPathEnds / kChainPathBlock;
+        uint32_t v[kPer], sum = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < kPer; ++q) {
+          const uint32_t i = tid * kPer + q;
+          v[q] = i < N ? own[i] : 0u;
+          sum += v[q];
+        }
+        uint32_t incl = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t y = __shfl_up(incl, o);
+          if ((int)lane_id() >= o) incl += y;
+        }
+        if (lane_id() == 63u) wave_sums[tid >> 6] = incl;
+        __syncthreads();
+        uint32_t run = incl - sum;
+        for (uint32_t q = 0; q < tid >> 6; ++q) run += wave_sums[q];
+#pragma unroll
+        for (uint32_t q = 0; q < kPer; ++q) {
+          const uint32_t i = tid * kPer + q;
+          if (i <= N) own[i] = run;
+          run += v[q];
+        }
+        if (tid == kChainPathBlock - 1u && N == kPathEnds) own[N] = run;
+      }
+      __syncthreads();
+      const uint32_t total_ends = own[N];
+      const auto before = [&](uint32_t at) {  // ends of the path before clock `at`
+        uint32_t k = 0;
+        for (uint32_t v = 0; v < g.m; ++v)
+          if (counts(v) && s.w.count[v])
+            k += own[s.w.before[v] + ends_to(v, at)] - own[s.w.before[v]];
+        return k;
+      };
+      for (uint32_t i = tid; i < N; i += kChainPathBlock) {
+        if (own[i + 1u] == own[i]) continue;
+        ChainItem it;
+        item(i, &it);
+        const uint32_t at = w.t0 + it.t;
+        if (!((covered[i >> 5] >> (i & 31u)) & 1u)) s_bad = 1u;
+        uint32_t k = div_up(at, g.d);
+        k = k < w.k1 ? k : w.k1;
+        put(n + before(at) + (tail ? 0u : starts_between(g, w.k0, k)),
+            key_of<W, M>(it, c, at, a.q.L));
+      }
+      n += total_ends;
+      if (!tail) {
+        const uint32_t starts = starts_between(g, w.k0, w.k1);
+        for (uint32_t y = tid; y < starts + (w.part_n ? x.p : 0u); y += kChainPathBlock) {
+          uint32_t k, j, place;
+          const bool part = y >= starts;
+          if (part) {  // the units of the chosen set, in index order
+            k = x.K;
+            j = y - starts + 1u;
+            place = n + y;
+          } else {
+            uint32_t u = 0, loc = y;
+            for (; u + 1u < g.m; ++u) {
+              const uint32_t cnt = div_up(w.k1, g.speed[u]) - div_up(w.k0, g.speed[u]);
+              if (loc < cnt) break;
+              loc -= cnt;
+            }
+            k = (div_up(w.k0, g.speed[u]) + loc) * g.speed[u];
+            j = bits_set(idle_at(g, k) & ((2u << u) - 1u));
+            place = n - total_ends + before(k * g.d + 1u) + starts_between(g, w.k0, k) + j - 1u;
+          }
+          uint32_t sub = (1u << j) - 1u, slot;
+          if (part) {
+            uint32_t left = j, at = 0;
+            sub = 0;
+            for (uint32_t u = 0; u < g.m; ++u)
+              if ((x.idle >> u) & 1u) {
+                if (left && ((chosen >> u) & 1u)) {
+                  sub |= 1u << at;
+                  --left;
+                }
+                ++at;
+              }
+            slot = x.slot0 + x.part_off + sub - 1u;
+          } else {
+            slot = x.slot0 + x.close_off + closures_before(g, k) + sub - 1u;
+          }
+          ChainItem it;
+          chain_state<M>(w, g, r.n, k - w.kw, 0u, sub, true, &it);
+          const Key<W> key = key_of<W, M>(it, c, k * g.d, a.q.L);
+          if (!there(slot, key)) s_bad = 1u;
+          put(place, key);
+        }
+        n += starts + (w.part_n ? x.p : 0u);
+      }
+      from = to;
+      __syncthreads();
+      bad = s_bad != 0u;
+      if (bad) break;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    // (the host cleared the flag)
+    if (bad || s_bad || n > t.cap || (!last && n != base[blockIdx.x + 1u]))
+      __hip_atomic_store(t.host_res + 2, 1u, __ATOMIC_RELAXED, kScopeSystem);
+    if (last) __hip_atomic_store(t.host_res + 1, n, __ATOMIC_RELAXED, kScopeSystem);
+  }
+}
+
+// ---- launch helpers (host) ------------------------------------------------------------
+
+// f(W, M, UNIFORM) as compile-time constants
+template <class F>
+hipError_t for_model(const ChainArgs& a, uint32_t W, const F& f) {
+  const auto units = [&](auto w, auto uniform) {
+    if (a.q.L.m <= 4u) f(w, std::integral_constant<int, 4>{}, uniform);
+    else f(w, std::integral_constant<int, kMaxCU>{}, uniform);
+  };
+  const auto words = [&](auto uniform) {
+    if (W == 1) units(std::integral_constant<int, 1>{}, uniform);
+    else if (W == 2) units(std::integral_constant<int, 2>{}, uniform);
+    else units(std::integral_constant<int, 4>{}, uniform);
+  };
+  if (a.uniform) words(std::true_type{});
+  else words(std::false_type{});
+  return hipGetLastError();
+}
+
+hipError_t launch_chains(hipStream_t st, uint32_t W, uint32_t grid, const ChainArgs& a) {
+  return for_model(a, W, [&](auto w, auto m, auto uniform) {
+    hipLaunchKernelGGL((k_chains_begin<decltype(w)::value>), dim3(1), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_chains<decltype(w)::value, decltype(m)::value, decltype(uniform)::value>),
+                       dim3(grid), dim3(kChainBlock), 0, st, a);
+  });
+}
+
+hipError_t launch_chain_path(hipStream_t st, uint32_t W, const ChainArgs& a, const TraceOut& t,
+                             uint32_t grid, const uint32_t* base, uint32_t per) {
+  return for_model(a, W, [&](auto w, auto m, auto uniform) {
+    hipLaunchKernelGGL(
+        (k_chain_path<decltype(w)::value, decltype(m)::value, decltype(uniform)::value>),
+        dim3(grid), dim3(kChainPathBlock), 0, st, a, t, base, per);
+  });
+}
+
+}  // namespace mc

@@ -182,6 +182,27 @@ hipError_t launch_round_path(hipStream_t st, const QueryArgs& q, const TraceOut&
 hipError_t launch_rounds(hipStream_t st, uint32_t grid, uint32_t block, const RoundQueue& q,
                          bool general);
 
+// A launch of the chain engine (one model, a handle with pinned memory).
+struct ChainArgs {
+  QueryArgs q;
+  const uint32_t* blob;       // ChainPlan::blob
+  uint32_t lcm, tails_at, sets_at;
+  uint32_t n_pieces;
+  uint32_t bb;                // as ModelDev::bb
+  uint32_t uniform;           // ChainPlan::uniform
+  unsigned int* head;
+  const unsigned int* abort;  // as PartQueue::abort
+  RoundRecord* records;       // a record per workgroup, in pinned memory
+  uint32_t* words;            // per piece, in pinned memory: the steps it adds to the longest
+                              // path, in bit 31 whether it holds a terminal
+};
+hipError_t launch_chains(hipStream_t st, uint32_t W, uint32_t grid, const ChainArgs& a);
+// The counterexample of configuration q.target that ends at clock q.T, root first, by `grid`
+// workgroups: `per` chain pieces each, the tail the last.  base: the place of the first state of
+// each (device-readable); the caller clears t.host_res[2].
+hipError_t launch_chain_path(hipStream_t st, uint32_t W, const ChainArgs& a, const TraceOut& t,
+                             uint32_t grid, const uint32_t* base, uint32_t per);
+
 template <int W>
 hipError_t launch_seed(hipStream_t st, const QueryArgs& q, Seed* seeds, void* front0);
 template <int W>

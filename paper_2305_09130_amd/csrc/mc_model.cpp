@@ -12,6 +12,8 @@
 // trace buffer; the exploration itself does not use them.
 #include "mc_model.h"
 
+#include "mc_chains.h"
+
 #include <algorithm>
 #include <map>
 #include <array>
@@ -1006,6 +1008,147 @@ uint64_t number_pieces(RoundPlan* p, uint32_t piece, uint64_t first_piece) {
   }
   p->n_pieces = n - first_piece;
   return p->n_pieces;
+}
+
+namespace {
+
+struct HostEnds {
+  const CfgRec& r;
+  uint32_t at(uint32_t j) const { return (uint32_t)end_at_host(r, j); }
+  uint32_t upto(uint32_t x) const { return (uint32_t)ends_le(r, x); }
+};
+
+}  // namespace
+
+void chain_plan(const ModelHost& h, uint64_t slots, uint64_t target, ChainPlan* out) {
+  *out = ChainPlan{};
+  if (!h.hetero || slots > (1ull << 31)) return;
+  const uint32_t m = h.m;
+  uint8_t speed[kMaxCU];
+  uint64_t lcm = 1, slowest = 1;
+  for (uint32_t u = 0; u < m; ++u) {
+    speed[u] = (uint8_t)h.speed[u];
+    slowest = std::max<uint64_t>(slowest, speed[u]);
+    lcm = std::lcm<uint64_t>(lcm, speed[u]);
+    if (lcm > kMaxPeriodLcm) return;
+  }
+  uint64_t per_period = 0;  // workgroups started
+  for (uint32_t u = 0; u < m; ++u) per_period += lcm / speed[u];
+  std::vector<uint32_t> sets(lcm + 1, 0u);
+  std::vector<ChainCfg> cfgs(h.n_cfg);
+  std::vector<ChainTail> tails;
+  std::vector<uint64_t> chain_items(h.n_cfg), tail_items(h.n_cfg), cfg_slots(h.n_cfg);
+  std::vector<uint32_t> done(h.n_cfg, 0u);
+  uint64_t slot = 1ull + h.n_cfg, items = 0;
+  for (uint32_t c = 0; c < h.n_cfg; ++c) {
+    const CfgRec& r = h.cfgs[c];
+    const uint32_t w = h.cut_of[c];  // the first configuration like it
+    ChainCfg& x = cfgs[c];
+    if (done[w]) {
+      x = cfgs[w];
+      chain_items[c] = chain_items[w];
+      tail_items[c] = tail_items[w];
+      cfg_slots[c] = cfg_slots[w];
+    } else {
+      const ChainEnv g = chain_env(r, speed, m, (uint32_t)lcm, sets.data());
+      const HostEnds ends{r};
+      if (!sets[lcm])
+        for (uint32_t k = 0; k < lcm; ++k)
+          sets[k + 1] = sets[k] + (1u << bits_set(idle_at(g, k))) - 1u;
+      const uint64_t periods = r.n / per_period;
+      uint64_t k = periods * lcm, left = r.n - periods * per_period;
+      uint32_t f = g.all;
+      while (left >= bits_set(f)) {
+        left -= bits_set(f);
+        f = idle_at(g, (uint32_t)(++k % lcm));
+      }
+      if ((k + slowest + 1) * r.d >= (1ull << 31) || r.b >= (1u << 24)) return;
+      std::memset(&x, 0, sizeof(x));
+      x.K = (uint32_t)k;
+      x.p = (uint32_t)left;
+      x.idle = f;
+      uint64_t at = 0;
+      for (uint32_t u = 0; u < m; ++u) {
+        if (!((g.reps >> u) & 1u)) continue;
+        x.unit_off[u] = (uint32_t)at;
+        at += (k / speed[u]) * r.b + ends.upto((uint32_t)((k % speed[u]) * r.d / speed[u]));
+        if (at >= (1ull << 31)) return;
+      }
+      x.close_off = (uint32_t)at;
+      at += (k / lcm) * sets[lcm] + sets[k % lcm];
+      if (at >= (1ull << 31)) return;
+      x.part_off = (uint32_t)at;
+      if (left) at += (1ull << bits_set(f)) - 1;
+      chain_items[c] = at;
+      const uint32_t on = tail_units(x, g);
+      uint32_t reach = 0;
+      for (uint32_t u = 0; u < m; ++u)
+        if ((on >> u) & 1u) reach = std::max(reach, speed[u] - x.K % speed[u]);
+      x.tail_n = on ? reach + 1u : 0u;
+      x.tail0 = (uint32_t)tails.size();
+      for (uint32_t i = 0; i < x.tail_n; ++i) {
+        ChainWindow v;
+        v.t0 = tail_from(x, g, i);
+        v.t1 = (x.K + i + 1u) * r.d;
+        ChainTail tl{(uint32_t)at, 0u};
+        if (v.t0 < v.t1)
+          for (uint32_t u = 0; u < m; ++u) tl.count += tail_window_unit(v, x, g, ends, i, u);
+        uint64_t n_sets = 0;
+        const uint32_t run = x.p ? f : 0u;
+        uint32_t alive = 0;
+        for (uint32_t u = 0; u < m; ++u)
+          if (((run >> u) & 1u) && speed[u] > i) alive |= 1u << u;
+        const uint32_t dead = bits_set(run) - bits_set(alive);
+        for (uint32_t s = 0; s <= alive; ++s)
+          if ((s & ~alive) == 0u && tail_set(x.p, dead, s)) ++n_sets;
+        tails.push_back(tl);
+        tail_items[c] = std::max(tail_items[c], n_sets * tl.count);
+        at += n_sets * tl.count;
+        if (at >= (1ull << 31)) return;
+      }
+      cfg_slots[c] = at;
+      done[c] = 1u;
+    }
+    x.slot0 = (uint32_t)slot;
+    slot += cfg_slots[c];
+    items += cfg_slots[c];
+    if (slot > slots) return;
+  }
+  // As many pieces as the chip holds workgroups, but a piece costs about 10 us beyond its items
+  // (min_time launch, reduction_g256_cu4_s1123: pieces of 256 items 14 us, of 768 12.7, of 2048
+  // 21; its check 20, 9 and 9), and windows fuller than 1,536 of kChainCap are split here and
+  // there (matmul32_cu4_s1123: 1,024 items 49 us, 1,536 44, 2048 49).
+  if (!target) target = std::min<uint64_t>(1536, std::max<uint64_t>(768, items / 1024));
+  target = std::min<uint64_t>(kChainCap, std::max<uint64_t>(32, target));
+  uint64_t pieces = 0;
+  for (uint32_t c = 0; c < h.n_cfg; ++c) {
+    ChainCfg& x = cfgs[c];
+    const uint64_t d = h.cfgs[c].d, span = x.K * d + 1;
+    uint64_t n = std::min<uint64_t>(span, chain_items[c] / target + 1);
+    const uint64_t delta = std::min<uint64_t>((span + n - 1) / n, (kMaxChainIntervals - 2) * d);
+    n = (span + delta - 1) / delta;
+    x.delta = (uint32_t)delta;
+    x.windows = (uint32_t)n;
+    x.tsub = (uint32_t)std::min<uint64_t>({64, d, tail_items[c] / target + 1});
+    x.piece0 = (uint32_t)pieces;
+    pieces += n + (uint64_t)x.tail_n * x.tsub;
+    if (pieces > kMaxChainPieces || bit_length(std::max(delta, d) + 1) + m > 31) return;
+  }
+  out->uniform = true;
+  for (const CfgRec& r : h.cfgs)
+    for (uint32_t j = 0, t = 0; j < r.nph; t += r.cnt[j] * r.lat[j], ++j)
+      if (r.waves != 1u || r.la[j] || r.t0[j] != t) out->uniform = false;
+  out->lcm = (uint32_t)lcm;
+  out->tails_at = (uint32_t)(sizeof(ChainCfg) / 4 * cfgs.size());
+  out->sets_at = out->tails_at + (uint32_t)(2 * tails.size());
+  out->blob.resize(out->sets_at + sets.size());
+  std::memcpy(out->blob.data(), cfgs.data(), sizeof(ChainCfg) * cfgs.size());
+  if (!tails.empty())
+    std::memcpy(out->blob.data() + out->tails_at, tails.data(), sizeof(ChainTail) * tails.size());
+  std::memcpy(out->blob.data() + out->sets_at, sets.data(), 4 * sets.size());
+  out->used = slot;
+  out->items = items;
+  out->n_pieces = pieces;
 }
 
 uint32_t auto_piece(uint64_t items) {

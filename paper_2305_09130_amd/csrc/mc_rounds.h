@@ -7,7 +7,8 @@
 #include "mc_model.h"
 
 #ifdef __HIP__
-#define MC_HD __host__ __device__ __forceinline__
+#define MC_HD \
+  __attribute__((host)) __attribute__((device)) inline __attribute__((always_inline))
 #else
 #define MC_HD inline
 #endif

@@ -48,29 +48,6 @@ namespace {
 
 constexpr uint32_t kSetEmpty = 0xFFFFFFFFu;
 
-// Pointers read from a descriptor carry no address space, and a store through such a pointer
-// counts as an LDS access too: the next wait for the set would wait for HBM.
-typedef __attribute__((address_space(1))) unsigned long long global_u64;
-
-// Uniform loads of a launch's constant tables, as scalar loads.
-template <class T>
-__device__ __forceinline__ T load_const(const T* p) {
-  static_assert(sizeof(T) % 4 == 0, "whole words");
-  typedef const __attribute__((address_space(4))) uint32_t* cptr;
-  cptr c = (cptr)(uintptr_t)p;
-  union {
-    T v;
-    uint32_t w[sizeof(T) / 4];
-  } u;
-#pragma unroll
-  for (uint32_t i = 0; i < sizeof(T) / 4; ++i) u.w[i] = c[i];
-  return u.v;
-}
-
-__device__ __forceinline__ uint32_t uniform(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
-
 // The partition that holds piece p: the last whose first piece is at most p.  The wavefront
 // looks at 64 partitions at a time (3,828 partitions: two steps).
 __device__ __forceinline__ uint32_t find_part(const RoundPart* parts, uint32_t n, uint32_t p) {
