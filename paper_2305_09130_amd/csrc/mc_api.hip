@@ -23,6 +23,8 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
+constexpr size_t kHeadBytes = 4 * (kStopWord + 1);
+
 uint64_t next_pow2(uint64_t x) {
   uint64_t p = 1;
   while (p < x) p <<= 1;
@@ -92,7 +94,7 @@ int plan_ws(const ModelHost& mh, const mc_opts& o, uint64_t n_parts, WsPlan* p) 
   p->n_parts = n_parts;
   p->order = off;  off = align_up(off + sizeof(Part) * n_parts);
   p->md = off;     off = align_up(off + sizeof(ModelDev));
-  p->head = off;   off = align_up(off + 4);
+  p->head = off;   off = align_up(off + kHeadBytes);
   p->seeds = off;  off = align_up(off + sizeof(Seed) * mh.n_cfg);
   p->fcap = mh.frontier_bound + 64;
   p->front0 = off; off = align_up(off + entry * p->fcap);
@@ -178,6 +180,9 @@ struct mc_model {
   uint32_t q_parts = 0;  // partitions of the last query's launch
   ModelDev* dmd = nullptr;
   unsigned int* head = nullptr;
+  // launches that begin their model themselves (RoundQueue::launch; handles with pinned
+  // memory): the count head stands at, zero after a load, and the last launch's number
+  uint32_t head0 = 0, launch = 0;
   unsigned char* pin = nullptr;  // pooled pinned block: hctrl, hpoll, hmd, tc_host, uploads
   size_t pin_bytes = 0;
   ModelDev* hmd = nullptr;  // pinned host staging of the device descriptor
@@ -247,6 +252,8 @@ struct mc_model {
 };
 
 namespace {
+
+uint32_t next_launch(mc_model* h) { return ++h->launch ? h->launch : ++h->launch; }
 
 QueryArgs make_args(mc_model* h, bool prune, uint32_t T) {
   QueryArgs q;
@@ -479,7 +486,8 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
     }
   }
   h->q_parts = (uint32_t)plan->parts.size();
-  ModelDev& md = *h->hmd;
+  const bool self = h->pooled && !bb;
+  ModelDev md;
   std::memset(&md, 0, sizeof(md));
   md.ctrl = h->ctrl;
   md.tc = h->tc;
@@ -500,10 +508,17 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
       {h->opts.grid ? h->opts.grid : kRoundsGrid, kRoundsGrid, (uint32_t)std::max<uint64_t>(n_pieces, 1)});
   if (!resume)  // the host's copies run on in a continued exploration
     for (uint32_t c = 0; c < h->mh.n_cfg; ++c) h->tc_host[c] = kNoClock;
-  HIPCHK(launch_rounds_begin(s, md, h->dmd, h->head));
-  uint64_t launches = 1;
-  if (n_pieces) {
+  uint64_t launches = 0;
+  if (!self) {
+    HIPCHK(launch_rounds_begin(s, md, h->dmd, h->head));
+    ++launches;
+    h->head0 = 0u;
+  }
+  if (n_pieces || self) {
     RoundQueue q;
+    q.launch = self ? next_launch(h) : 0u;
+    q.head0 = h->head0;
+    q.one = md;
     q.models = h->dmd;
     q.parts = reinterpret_cast<const RoundPart*>(h->parts);
     q.n_parts = h->q_parts;
@@ -517,6 +532,8 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
     q.host_tc = h->records ? h->tc_host : nullptr;
     HIPCHK(launch_rounds(s, grid, h->opts.block, q, h->mh.general));
     ++launches;
+    // every piece but the first of each workgroup, and every workgroup's last look, counts one
+    if (n_pieces > grid) h->head0 += (uint32_t)n_pieces;
   }
   h->on_rounds = true;
   Ctrl* ctrl = h->hctrl;
@@ -584,7 +601,10 @@ int run_chains(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb) {
   h->q_parts = a.n_pieces;
   const uint32_t grid = std::min<uint32_t>(
       {h->opts.grid ? h->opts.grid : kRoundsGrid, kRoundsGrid, a.n_pieces});
+  a.launch = next_launch(h);
+  a.head0 = h->head0;
   HIPCHK(launch_chains(s, h->mh.W, grid, a));
+  if (a.n_pieces > grid) h->head0 += a.n_pieces;  // as run_rounds counts
   h->on_chains = true;
   HIPCHK(hipStreamSynchronize(s));
   h->in_flight = false;
@@ -617,7 +637,7 @@ int run_chains(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb) {
   const int derr = dev_error_code(ctrl->error);
   if (derr == MC_E_ABORTED && h->habort) __atomic_store_n(h->habort, 0u, __ATOMIC_RELEASE);
   if (derr != MC_OK) return derr;
-  fill_stats(h, t0, 2, ticks * 10ull, ticks * 10ull, 0, st);
+  fill_stats(h, t0, bb ? 2 : 1, ticks * 10ull, ticks * 10ull, 0, st);
   return MC_OK;
 }
 
@@ -1123,7 +1143,9 @@ int install(mc_model* h, Loaded& L) {
   // the records and partitions are staged as they lie in the workspace, for one copy, and
   // after them is room for a query's own partitions
   const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg, part_bytes = h->chains ? 4 * h->cplan.blob.size() : sizeof(Part) * h->n_parts;
-  const size_t part_off = h->plan.order - h->plan.cfgs, up_bytes = part_off + part_bytes;
+  // (the descriptor's room and the head's words, which start as zeros, follow)
+  const size_t part_off = h->plan.order - h->plan.cfgs, head_off = h->plan.head - h->plan.cfgs;
+  const size_t up_bytes = head_off + kHeadBytes;
   const bool stage = up_bytes <= (4u << 20);
   const size_t own_off = align_up(up_off + up_bytes);
   const size_t pin_bytes = stage ? own_off + part_bytes : up_off;
@@ -1165,13 +1187,17 @@ int install(mc_model* h, Loaded& L) {
   if (stage) {
     std::memcpy(blk + up_off, h->mh.cfgs.data(), cfg_bytes);
     std::memcpy(blk + up_off + part_off, up_part, part_bytes);
+    std::memset(blk + up_off + head_off, 0, kHeadBytes);
     h->stage_parts = blk + own_off;
     e = hipMemcpyAsync(h->cfgs, blk + up_off, up_bytes, hipMemcpyHostToDevice, s);
   } else {
     e = hipMemcpyAsync(h->cfgs, h->mh.cfgs.data(), cfg_bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
       e = hipMemcpyAsync(h->parts, up_part, part_bytes, hipMemcpyHostToDevice, s);
+    static const unsigned int zeros[kStopWord + 1] = {};
+    if (e == hipSuccess) e = hipMemcpyAsync(h->head, zeros, kHeadBytes, hipMemcpyHostToDevice, s);
   }
+  h->head0 = 0u;
   // pinned staging is left alone until the stream is next waited for
   if (e == hipSuccess && stage && h->pooled) h->in_flight = true;
   else if (e == hipSuccess) e = hipStreamSynchronize(s);

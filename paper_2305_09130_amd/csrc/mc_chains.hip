@@ -153,28 +153,23 @@ __device__ __forceinline__ void fill_window(ChainShared& s, const ChainCfg& x, c
 
 }  // namespace
 
-// Counters, the root (slot 0) and the SELECT states (slot 1 + c).
+// The root (slot 0) and the SELECT states (slot 1 + c), by threads i, i + step, ..
 template <int W>
-__global__ __launch_bounds__(256) void k_chains_begin(ChainArgs a) {
-  const uint32_t tid = threadIdx.x;
-  unsigned int* cw = reinterpret_cast<unsigned int*>(a.q.ctrl);
-  for (uint32_t i = tid; i < sizeof(Ctrl) / 4; i += 256u) cw[i] = 0u;
-  __syncthreads();
-  if (tid == 0) {
-    a.q.ctrl->bound = a.q.T;
-    a.q.ctrl->target_slot = kParentNone;
-    *a.head = 0u;
-  }
-  for (uint32_t i = tid; i <= a.q.n_cfg; i += 256u) {
+__device__ __forceinline__ void write_roots(const QueryArgs& q, uint32_t i, uint32_t step) {
+  for (; i <= q.n_cfg; i += step) {
     St y = {};
-    y.cfg = i ? i - 1u : a.q.n_cfg;
-    y.pending = i ? a.q.cfgs[i - 1u].n : 0u;
-    const Key<W> k = encode<W>(y, a.q.L);
-    unsigned long long* to = reinterpret_cast<unsigned long long*>(a.q.table) + (unsigned long long)i * W;
+    y.cfg = i ? i - 1u : q.n_cfg;
+    y.pending = i ? q.cfgs[i - 1u].n : 0u;
+    const Key<W> k = encode<W>(y, q.L);
+    unsigned long long* to =
+        reinterpret_cast<unsigned long long*>(q.table) + (unsigned long long)i * W;
 #pragma unroll
     for (int w = 0; w < W; ++w) to[w] = k.w[w];
   }
 }
+
+// The incumbent of branch and bound.
+__global__ void k_chains_bound(Ctrl* ctrl, uint32_t T) { ctrl->bound = T; }
 
 template <int W, int M, bool UNIFORM>
 __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
@@ -194,6 +189,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
     sums = RoundRecord{};
     sums.t_first = (uint32_t)__builtin_amdgcn_s_memrealtime();
   }
+  write_roots<W>(a.q, blockIdx.x * kChainBlock + tid, gridDim.x * kChainBlock);
   // sums of a wavefront (uniform in it)
   uint32_t states = 0, edges = 0, probes = 0, max_probe = 0, terms = 0;
   for (;;) {
@@ -215,13 +211,14 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
       }
       const uint32_t stop = abort_asked(a.abort, piece);
       if (stop) {
-        set_error(a.q.ctrl, kDevErrAbort);
+        __hip_atomic_store(a.head + kStopWord, a.launch, __ATOMIC_RELAXED, kScopeAgent);
         sums.error = kDevErrAbort;
       }
       s_T = T;
-      s_skip = stop | __hip_atomic_load(&a.q.ctrl->error, __ATOMIC_RELAXED, kScopeAgent);
+      s_skip = stop || __hip_atomic_load(a.head + kStopWord, __ATOMIC_RELAXED, kScopeAgent) == a.launch;
       s_steps = s_term = 0u;
-      next = a.n_pieces > gridDim.x ? gridDim.x + atomicAdd(a.head, 1u) : a.n_pieces;
+      next = a.n_pieces;
+      if (a.n_pieces > gridDim.x) next = gridDim.x + (atomicAdd(a.head, 1u) - a.head0);
     }
     __syncthreads();
     const ChainSpan span = chain_span(x, g, piece - x.piece0, uniform(s_T));
@@ -619,8 +616,8 @@ hipError_t for_model(const ChainArgs& a, uint32_t W, const F& f) {
 }
 
 hipError_t launch_chains(hipStream_t st, uint32_t W, uint32_t grid, const ChainArgs& a) {
+  if (a.bb) hipLaunchKernelGGL(k_chains_bound, dim3(1), dim3(1), 0, st, a.q.ctrl, a.q.T);
   return for_model(a, W, [&](auto w, auto m, auto uniform) {
-    hipLaunchKernelGGL((k_chains_begin<decltype(w)::value>), dim3(1), dim3(256), 0, st, a);
     hipLaunchKernelGGL((k_chains<decltype(w)::value, decltype(m)::value, decltype(uniform)::value>),
                        dim3(grid), dim3(kChainBlock), 0, st, a);
   });

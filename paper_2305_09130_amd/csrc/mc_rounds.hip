@@ -33,6 +33,11 @@
 // and barriers between pieces overlap another's items.  Pieces of half the size ran slower
 // (matmul128_vw_cu8 0.40 -> 0.47 ms when measured): a piece costs about 3 us beyond its items.
 //
+// A query of one model is one launch: it writes the root and SELECT states itself and takes its
+// descriptor as an argument, no counter has to be cleared for it, and its pieces' descriptors
+// are two dependent reads nearer.  With a launch before it that began the model:
+// reduction_g256_cu2, load to check 85 -> 81 us, abstract_s1024_np4_cu1 121 -> 116 us.
+//
 // Sums go to the host as one 64-byte record per workgroup, stored to pinned memory: added to
 // the model's counters instead, ten atomics of 1,024 workgroups on one line took 60 us.
 #include <hip/hip_runtime.h>
@@ -151,10 +156,10 @@ __device__ __forceinline__ GeneralEnds in_vector_registers(GeneralEnds u) {
 // Items [from, to) of a piece: of its full rounds, or (PART) of its partial round.  Two loops,
 // as the fields of one round kind fill the scalar registers.  CLOCKS: a query with a
 // threshold or a floor tells states apart by their clocks.
-template <int BLOCK, bool PART, bool CLOCKS, class Ends>
+template <int BLOCK, bool PART, bool CLOCKS, class Ends, class Model>
 __device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_in, const ItemEnv& g,
                                               uint32_t from, uint32_t to, uint32_t* set,
-                                              const uint8_t* masks, const ModelDev* mdp,
+                                              const uint8_t* masks, const Model& model,
                                               uint32_t* host_tc, ItemSums& sum) {
   const uint32_t prel0 = v.n - (v.r0 + v.q0) * v.m - v.pmin;  // before the piece's first round
   const uint32_t clock0 = (v.r0 + v.q0) * g.d;
@@ -213,7 +218,7 @@ __device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_i
         const unsigned long long hi = rem ? kParentNone : l.leaf;
         ((global_u64*)g.links)[it.slot] = l.root | hi << 32;
         if (rem == 0u && prel + v.pmin == 0u) {
-          const ModelDev md = load_const(mdp);
+          const ModelDev md = model();
           const uint32_t end = clock0 + it.q * g.d + g.d;
           ++sum.terms;
           md.tslot[g.c] = it.slot;
@@ -232,9 +237,26 @@ __device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_i
   }
 }
 
+// A model's root (slot 0) and SELECT states (slot 1 + c), by threads i, i + step, ..
+__device__ __forceinline__ void write_roots(const ModelDev& md, uint32_t i, uint32_t step) {
+  unsigned long long* keys = reinterpret_cast<unsigned long long*>(md.table);
+  for (; i <= md.n_cfg; i += step) {
+    if (i == 0u) {
+      keys[0] = (unsigned long long)md.n_cfg;  // configuration n_cfg, all else 0
+      set_links<1>(md.table, md.mask, 0, kParentRoot, kParentNone);
+    } else {
+      const uint32_t c = i - 1u;
+      keys[i] = (unsigned long long)c |
+                (unsigned long long)md.cfgs[c].n << md.L.shift[kFPending];
+      set_links<1>(md.table, md.mask, i, 0u, kParentNone);
+    }
+  }
+}
+
 }  // namespace
 
-template <int BLOCK, bool GEN>
+// ONE: RoundQueue::one (a.launch != 0), else the models of the queue.
+template <int BLOCK, bool GEN, bool ONE>
 __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
   extern __shared__ uint32_t set[];  // 1 << log2_set slots
   __shared__ uint8_t masks[256];     // a partial round's closure sets, by size and value
@@ -255,6 +277,7 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
   uint32_t model = kParentNone;  // whose sums are held
   Ctrl* ctrl = nullptr;
   ItemSums sum;
+  if (ONE && !a.one.refloor) write_roots(a.one, blockIdx.x * BLOCK + tid, gridDim.x * BLOCK);
   for (;;) {
     if (tid == 0) s_piece = next;
     __syncthreads();  // the piece before is done: its set, its sums
@@ -263,10 +286,14 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
     const uint32_t piece = a.reverse ? a.n_pieces - 1u - taken : taken;
     const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
     const RoundPart pt = load_const(a.parts + find_part(a.parts, a.n_parts, piece));
-    const ModelDev md = load_const(a.models + pt.model);
+    const auto get_model = [&] {
+      if constexpr (ONE) return a.one;
+      else return load_const(a.models + pt.model);
+    };
+    const ModelDev md = get_model();
     const uint32_t c = pt.cfg_flags & kRpCfg;
     const CfgRec r = load_const(md.cfgs + c);
-    if (model != pt.model) {
+    if (!ONE && model != pt.model) {
       if (model != kParentNone) {  // (added to again only past the barrier after the clear)
         add_sums(sums, sum);
         __syncthreads();
@@ -278,18 +305,21 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
     const Piece v = piece_of(pt, r, md.L.m, a.piece, piece - pt.piece0);
     if (tid == 0) {
       uint32_t T = md.prune ? md.T : kNoClock;
-      if (md.bb) {
+      if (!ONE && md.bb) {
         const uint32_t b = __hip_atomic_load(&md.ctrl->bound, __ATOMIC_RELAXED, kScopeAgent);
         T = b < T ? b : T;
       }
       const uint32_t stop = abort_asked(a.abort, taken);
-      if (stop) {
-        set_error(md.ctrl, kDevErrAbort);
-        sums.error = kDevErrAbort;
-      }
+      if (stop) sums.error = kDevErrAbort;
       s_T = T;
-      // one read of the error flag for the whole workgroup: others set it concurrently
-      s_skip = stop | __hip_atomic_load(&md.ctrl->error, __ATOMIC_RELAXED, kScopeAgent);
+      // one read of the flag for the whole workgroup: others set it concurrently
+      if constexpr (ONE) {
+        if (stop) __hip_atomic_store(a.head + kStopWord, a.launch, __ATOMIC_RELAXED, kScopeAgent);
+        s_skip = stop || __hip_atomic_load(a.head + kStopWord, __ATOMIC_RELAXED, kScopeAgent) == a.launch;
+      } else {
+        if (stop) set_error(md.ctrl, kDevErrAbort);
+        s_skip = stop | __hip_atomic_load(&md.ctrl->error, __ATOMIC_RELAXED, kScopeAgent);
+      }
     }
     {
       uint4* s4 = reinterpret_cast<uint4*>(set);
@@ -301,7 +331,9 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
         masks[mask_rank(x, v.all)] = (uint8_t)x;
     __syncthreads();
     if (tid == 0) {  // taken while this piece is explored
-      next = a.n_pieces > gridDim.x ? gridDim.x + atomicAdd(a.head, 1u) : a.n_pieces;
+      next = a.n_pieces;
+      if (a.n_pieces > gridDim.x)
+        next = gridDim.x + (atomicAdd(a.head, 1u) - (ONE ? a.head0 : 0u));
     }
     const uint32_t T = uniform(s_T);
     const bool none =  // every state past T, or below the floor of a continued exploration
@@ -323,14 +355,13 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
       g.hkeep = md.hkeep;
       g.keys = (unsigned long long)md.table;
       g.links = g.keys + (md.mask + 1ull) * 8ull;
-      const ModelDev* mdp = a.models + pt.model;
       const auto items = [&](const auto& ends, auto clocks) {
         if (v.i0 < v.F)
           explore_items<BLOCK, false, decltype(clocks)::value>(
-              v, ends, g, v.i0, v.i1 < v.F ? v.i1 : v.F, set, masks, mdp, a.host_tc, sum);
+              v, ends, g, v.i0, v.i1 < v.F ? v.i1 : v.F, set, masks, get_model, a.host_tc, sum);
         if (v.i1 > v.F)
           explore_items<BLOCK, true, decltype(clocks)::value>(
-              v, ends, g, v.i0 > v.F ? v.i0 : v.F, v.i1, set, masks, mdp, a.host_tc, sum);
+              v, ends, g, v.i0 > v.F ? v.i0 : v.F, v.i1, set, masks, get_model, a.host_tc, sum);
       };
       const auto explore = [&](const auto& ends) {
         if (T != kNoClock || md.refloor != 0u) items(ends, std::true_type{});
@@ -365,15 +396,13 @@ __global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
   }
 }
 
-// Counters, clocks and terminal slots of a model, its root (slot 0) and SELECT states (slot
-// 1 + c).
+// Counters, clocks and terminal slots of a model, its root and SELECT states.
 __device__ void begin_model(const ModelDev& md) {
   const uint32_t tid = threadIdx.x;
   Ctrl* ctrl = md.ctrl;
   unsigned int* cw = reinterpret_cast<unsigned int*>(ctrl);
   for (uint32_t i = tid; i < sizeof(Ctrl) / 4; i += blockDim.x) cw[i] = 0u;
   __syncthreads();
-  unsigned long long* keys = reinterpret_cast<unsigned long long*>(md.table);
   if (tid == 0) {
     ctrl->states = ctrl->probes = 1ull + md.n_cfg;
     ctrl->edges = md.n_cfg;
@@ -382,15 +411,12 @@ __device__ void begin_model(const ModelDev& md) {
     ctrl->max_probe = 1u;
     ctrl->bound = md.T;
     ctrl->target_slot = kParentNone;
-    keys[0] = (unsigned long long)md.n_cfg;  // the root: configuration n_cfg, all else 0
-    set_links<1>(md.table, md.mask, 0, kParentRoot, kParentNone);
   }
   for (uint32_t c = tid; c < md.n_cfg; c += blockDim.x) {
     md.tc[c] = kNoClock;
     md.tslot[c] = kParentNone;
-    keys[1u + c] = (unsigned long long)c | (unsigned long long)md.cfgs[c].n << md.L.shift[kFPending];
-    set_links<1>(md.table, md.mask, 1u + c, 0u, kParentNone);
   }
+  write_roots(md, tid, blockDim.x);
 }
 
 __global__ __launch_bounds__(256) void k_rounds_begin(ModelDev md, ModelDev* dst,
@@ -596,15 +622,21 @@ hipError_t launch_round_path(hipStream_t st, const QueryArgs& q, const TraceOut&
 hipError_t launch_rounds(hipStream_t st, uint32_t grid, uint32_t block, const RoundQueue& q,
                          bool general) {
   const uint32_t lds = 4u << q.log2_set;
-#define MC_LAUNCH_ROUNDS(B)                                                                  \
-  do {                                                                                       \
-    if (general) hipLaunchKernelGGL((k_rounds<B, true>), dim3(grid), dim3(B), lds, st, q);   \
-    else hipLaunchKernelGGL((k_rounds<B, false>), dim3(grid), dim3(B), lds, st, q);          \
+#define MC_LAUNCH_ROUNDS_(B, G)                                                                \
+  do {                                                                                         \
+    if (q.launch) hipLaunchKernelGGL((k_rounds<B, G, true>), dim3(grid), dim3(B), lds, st, q); \
+    else hipLaunchKernelGGL((k_rounds<B, G, false>), dim3(grid), dim3(B), lds, st, q);         \
+  } while (0)
+#define MC_LAUNCH_ROUNDS(B)                 \
+  do {                                      \
+    if (general) MC_LAUNCH_ROUNDS_(B, true); \
+    else MC_LAUNCH_ROUNDS_(B, false);       \
   } while (0)
   if (block == 1024) MC_LAUNCH_ROUNDS(1024);
   else if (block == 512) MC_LAUNCH_ROUNDS(512);
   else MC_LAUNCH_ROUNDS(256);
 #undef MC_LAUNCH_ROUNDS
+#undef MC_LAUNCH_ROUNDS_
   return hipGetLastError();
 }
 
