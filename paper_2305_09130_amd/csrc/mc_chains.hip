@@ -266,9 +266,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
           }
           const bool in = base + tid < items, act = in && it.active;
           const uint32_t code = it.t << g.m | it.busy;
-          uint32_t h = code * 0x9E3779B1u;
-          if (a.q.hkeep) h = ((h >> 8) & ((1u << a.q.hkeep) - 1u)) * 0x9E3779B1u;
-          uint32_t at = h >> (32u - kChainSetLog2), old = code;
+          uint32_t at = probe_start(code, 32u - kChainSetLog2, a.q.hkeep), old = code;
           if (act) old = atomicCAS(&set[at], kSetEmpty, code);
           const unsigned long long acts = __builtin_amdgcn_ballot_w64(act);
           unsigned long long met =
@@ -277,7 +275,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
           probes += (uint32_t)__popcll(acts) + (uint32_t)__popcll(met);
           while (met) {
             if (__builtin_amdgcn_inverse_ballot_w64(met)) {
-              at = (at + 1u) & ((1u << kChainSetLog2) - 1u);
+              at = (at + trips) & ((1u << kChainSetLog2) - 1u);
               old = atomicCAS(&set[at], kSetEmpty, code);
             }
             met &= __builtin_amdgcn_ballot_w64(old != kSetEmpty && old != code);

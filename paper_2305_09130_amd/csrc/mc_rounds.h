@@ -207,6 +207,24 @@ MC_HD uint32_t state_code(const Piece& v, uint32_t pending, uint32_t busy, uint3
   return (pending - v.pmin) << (v.m + rem_bits) | rem << v.m | busy;
 }
 
+// Where a code's probe sequence starts in a set of 2^(32 - shift) slots; it goes on 1, 2, 3, ..
+// slots further at every probe, which reaches all of them.  keep: bits kept (0: all; testing
+// only).  The codes of a piece are a lattice (time left by round), which a multiplication alone
+// maps to another: for some operation times many lie together, and steps of one slot walk
+// through all of them.  With such steps and the multiplier 0x9E3779B1, the probes of a
+// wavefront's slowest lane, averaged over a piece, came to 311 at worst over 720 models of all
+// kinds with operation times 1 to 42 (counted on the host), and to 2.1 - 3.4 by kind of model;
+// so, to 8, and to 1.4 - 2.5.  A second multiplication takes the lattice away, and with it what
+// keeps the codes of one run apart: 3 - 5.4.  min_time launch, mean (most) over 21 settings of
+// the operation times, then -> now: abstract_s1024_np4_cu1 35 (184) -> 25 (27) us,
+// minimum_s1024_np4_cu4 21 (40) -> 19.5 (20), matmul64_cu4 37.5 (42) -> 37.8 (40),
+// matmul128_vw_cu8 246 (320) -> 227 (241).
+MC_HD uint32_t probe_start(uint32_t code, uint32_t shift, uint32_t keep) {
+  uint32_t h = code * 0xEB91CE37u;
+  if (keep) h = ((h >> 8) & ((1u << keep) - 1u)) * 0xEB91CE37u;
+  return h >> shift;
+}
+
 // Time left after run state j of a workgroup of a configuration: d - end_at(j), with the
 // phases' terms that do not depend on j taken out of the loop over a piece's items.
 // Uniform phases (one operation per period, back to back, one wave): the end of operation j

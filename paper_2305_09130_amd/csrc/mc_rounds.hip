@@ -179,12 +179,10 @@ __device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_i
       act = act && clock <= g.T;
     }
     // the set: exact on (pending, busy, rem).  It has twice the slots of the piece's states,
-    // so the probe sequence (linear: codes of a run spread evenly under this multiplier) ends
+    // so the probe sequence ends (probe_start: why this one)
     const uint32_t low = rem << v.m | (rem ? it.mask : 0u);
     const uint32_t code = prel << g.code_shift | low;
-    uint32_t h = code * 0x9E3779B1u;
-    if (g.hkeep) h = ((h >> 8) & ((1u << g.hkeep) - 1u)) * 0x9E3779B1u;
-    uint32_t at = h >> g.set_shift, old = code;
+    uint32_t at = probe_start(code, g.set_shift, g.hkeep), old = code;
     if (act) old = atomicCAS(&set[at], kSetEmpty, code);
     const unsigned long long acts = __builtin_amdgcn_ballot_w64(act);
     // the lanes that met another state try the next slot
@@ -193,7 +191,7 @@ __device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_i
     sum.probes += (uint32_t)__popcll(acts) + (uint32_t)__popcll(met);
     while (met) {
       if (__builtin_amdgcn_inverse_ballot_w64(met)) {
-        at = (at + 1u) & g.set_mask;
+        at = (at + trips) & g.set_mask;
         old = atomicCAS(&set[at], kSetEmpty, code);
       }
       met &= __builtin_amdgcn_ballot_w64(old != kSetEmpty && old != code);
