@@ -136,6 +136,7 @@ struct ChainWindow {
   uint32_t count[kMaxCU], first[kMaxCU];
   uint32_t slot[kMaxCU];         // chain: slot of the unit's end 0; tail: of its end 0 were it
                                  // in the interval, for the first set
+  uint32_t speed[kMaxCU];
   uint32_t j0[kMaxCU], idx0[kMaxCU];    // chain: workgroup and end of the first
   uint32_t km[kMaxCU], kq[kMaxCU];      // chain: kw mod s, kw / s
   uint32_t close0, close_n;      // closure states before the window, in it
@@ -146,11 +147,13 @@ struct ChainWindow {
   uint32_t interval, alive, dead_n, sets_n, per;  // alive: units of F_K busy past its start
 };
 
-// Unit u's part of a chain window (u < kMaxCU), then the rest of it.
+// Unit u's part of a chain window (u < kMaxCU); s its speed, off its ChainCfg::unit_off (given,
+// as an index known at run time only would put those arrays into memory).
 template <class E>
 MC_HD void chain_window_unit(ChainWindow& w, const ChainCfg& x, const ChainEnv& g, const E& ends,
-                             uint32_t u) {
-  const uint32_t s = g.speed[u], kw = w.t0 / g.d;
+                             uint32_t u, uint32_t s, uint32_t off) {
+  const uint32_t kw = w.t0 / g.d;
+  w.speed[u] = s;
   w.km[u] = kw % s;
   w.kq[u] = kw / s;
   w.count[u] = w.first[u] = w.j0[u] = w.idx0[u] = w.slot[u] = 0u;
@@ -160,7 +163,7 @@ MC_HD void chain_window_unit(ChainWindow& w, const ChainCfg& x, const ChainEnv& 
   w.count[u] = ends_before(ends, g, s, w.t1) - a;
   w.j0[u] = a / g.b;
   w.idx0[u] = a % g.b;
-  w.slot[u] = x.slot0 + x.unit_off[u];
+  w.slot[u] = x.slot0 + off;
 }
 MC_HD void window_prefix(ChainWindow& w) {
   uint32_t n = 0;
@@ -248,20 +251,13 @@ MC_HD void chain_item(const ChainWindow& w, const ChainCfg& x, const ChainEnv& g
   it->active = true;
   it->is_end = i < w.before[kMaxCU];
   if (it->is_end) {
-    uint32_t s = g.speed[0], slot = w.slot[0], first = w.first[0], j0 = w.j0[0], i0 = w.idx0[0], o = 0;
+    uint32_t u = 0;
 #pragma unroll
-    for (int u = 1; u < M; ++u) {
-      const bool in = i >= w.before[u];
-      s = in ? g.speed[u] : s;
-      slot = in ? w.slot[u] : slot;
-      first = in ? w.first[u] : first;
-      j0 = in ? w.j0[u] : j0;
-      i0 = in ? w.idx0[u] : i0;
-      o = in ? w.before[u] : o;
-    }
-    it->slot = slot + first + (i - o);
+    for (int v = 1; v < M; ++v) u = i >= w.before[v] ? (uint32_t)v : u;
+    const uint32_t s = w.speed[u], at = i - w.before[u];
+    it->slot = w.slot[u] + w.first[u] + at;
     // (a workgroup of more than kSmallRound ends holds the window's but for one wrap)
-    const uint32_t y = i0 + (i - o);
+    const uint32_t y = w.idx0[u] + at;
     const uint32_t q = g.b <= kSmallRound ? quotient(y, g.inv_b) : (y >= g.b ? 1u : 0u);
     const uint32_t e = s * ends.at(y - q * g.b);
     uint32_t k = (uint32_t)((float)e * g.inv_d);
@@ -273,7 +269,7 @@ MC_HD void chain_item(const ChainWindow& w, const ChainCfg& x, const ChainEnv& g
       ++k;
       past -= g.d;
     }
-    k += (j0 + q) * s;
+    k += (w.j0[u] + q) * s;
     dk = k - w.kw;
   } else if (i - w.before[kMaxCU] < w.close_n) {
     closure = true;
@@ -310,29 +306,37 @@ MC_HD void chain_item(const ChainWindow& w, const ChainCfg& x, const ChainEnv& g
 MC_HD uint32_t tail_units(const ChainCfg& x, const ChainEnv& g) {
   return x.p ? g.all : g.all & ~x.idle;
 }
-// Start of the workgroup that unit u runs in the tails.
-MC_HD uint32_t tail_start(const ChainCfg& x, const ChainEnv& g, uint32_t u) {
-  return (x.K - x.K % g.speed[u]) * g.d;
+// Start of the workgroup that a unit of speed s runs in the tails.
+MC_HD uint32_t tail_start(const ChainCfg& x, const ChainEnv& g, uint32_t s) {
+  return (x.K - x.K % s) * g.d;
 }
-// Whether the tails' ends of unit u are listed: the busy units of one speed end alike.
-MC_HD bool tail_lists(const ChainCfg& x, const ChainEnv& g, uint32_t u) {
-  if (!((tail_units(x, g) >> u) & 1u)) return false;
-  if ((x.idle >> u) & 1u) return true;
-  for (uint32_t v = 0; v < u; ++v)
-    if (g.speed[v] == g.speed[u]) return false;  // (then v is busy at K d as u is)
-  return true;
+// The units whose ends are listed in the tails: those of F_K, and of the ones busy at K d the
+// lowest of every speed (which end alike).
+MC_HD uint32_t tail_listed(const ChainCfg& x, const ChainEnv& g) {
+  uint32_t out = 0;
+#pragma unroll
+  for (uint32_t u = 0; u < (uint32_t)kMaxCU; ++u) {
+    bool first = true;  // (a lower unit of the same speed is busy at K d as u is)
+#pragma unroll
+    for (uint32_t v = 0; v < u; ++v) first = first && g.speed[v] != g.speed[u];
+    out |= first || ((x.idle >> u) & 1u) ? 1u << u : 0u;
+  }
+  return out & tail_units(x, g);
 }
 MC_HD uint32_t tail_from(const ChainCfg& x, const ChainEnv& g, uint32_t interval) {
   return (x.K + interval) * g.d + (interval ? 0u : 1u);
 }
 
-// Unit u's part of a tail window of `interval`; *in_interval: its ends in the whole interval.
+// Unit u's part of a tail window of `interval` (s its speed; listed: it is one of
+// tail_listed); returns its ends in the whole interval.
 template <class E>
 MC_HD uint32_t tail_window_unit(ChainWindow& w, const ChainCfg& x, const ChainEnv& g,
-                                const E& ends, uint32_t interval, uint32_t u) {
+                                const E& ends, uint32_t interval, uint32_t u, uint32_t s,
+                                bool listed) {
   w.count[u] = w.first[u] = w.slot[u] = w.j0[u] = w.idx0[u] = w.km[u] = w.kq[u] = 0u;
-  if (!tail_lists(x, g, u)) return 0u;
-  const uint32_t s = g.speed[u], ws = tail_start(x, g, u);
+  w.speed[u] = s;
+  if (!listed) return 0u;
+  const uint32_t ws = tail_start(x, g, s);
   uint32_t n0, a;
   const uint32_t whole =
       ends_of_one(ends, s, ws, tail_from(x, g, interval), (x.K + interval + 1u) * g.d, &n0);
@@ -372,18 +376,11 @@ MC_HD bool tail_set(uint32_t p, uint32_t dead_n, uint32_t set) {
 template <int M, class E>
 MC_HD void tail_item(const ChainWindow& w, const ChainCfg& x, const ChainEnv& g, const E& ends,
                      uint32_t i, uint32_t rank, uint32_t set, ChainItem* it) {
-  uint32_t u = 0, s = g.speed[0], slot = w.slot[0], first = w.first[0], o = 0;
+  uint32_t u = 0;
 #pragma unroll
-  for (int v = 1; v < M; ++v) {
-    const bool in = i >= w.before[v];
-    u = in ? (uint32_t)v : u;
-    s = in ? g.speed[v] : s;
-    slot = in ? w.slot[v] : slot;
-    first = in ? w.first[v] : first;
-    o = in ? w.before[v] : o;
-  }
-  const uint32_t n = first + (i - o);
-  it->slot = slot + n + rank * w.per;
+  for (int v = 1; v < M; ++v) u = i >= w.before[v] ? (uint32_t)v : u;
+  const uint32_t s = w.speed[u], n = w.first[u] + (i - w.before[u]);
+  it->slot = w.slot[u] + n + rank * w.per;
   it->is_end = true;
   const uint32_t t = (x.K - x.K % s) * g.d + s * ends.at(n);
   it->t = t - w.t0;

@@ -13,16 +13,20 @@
 // What bounds it.  k_superstep, which explored these models before, lists a chain state by
 // state between two dispatches, in turns of the whole workgroup, and claims each state with a
 // device-scope compare-and-swap in a table that has to be cleared first.  Here nothing in a
-// piece waits for a state before it: a piece costs its fixed part, about 10 us (its tables,
-// its window's counts and barriers, a chain of dependent reads), and some hundred vector
-// instructions per 64 states.  min_time launch, k_superstep -> here: reduction_g256_cu4_s1123
-// (86k states) 229 -> 13 us, matmul32_cu4_s1123 (1.44M) 642 -> 44 us; check one below the
-// optimum 157 -> 9 us and 194 -> 31 us.
+// piece waits for a state before it: a piece costs its fixed part (its tables, its window's
+// counts and barriers, a chain of dependent reads: 4 us when it is alone, twice that among
+// 1,024) and some hundred vector instructions per 64 states.  min_time launch, k_superstep ->
+// here: reduction_g256_cu4_s1123 (86k states) 229 -> 12 us, matmul32_cu4_s1123 (1.44M) 642 ->
+// 38 us; check one below the optimum 157 -> 9 us and 194 -> 26 us.
 //
-// A workgroup has 256 threads and 18 KiB of LDS.  Its registers (118 vector registers with
-// two-word keys) let four share a CU, as many as a launch has.  With the loops for any number
-// of units and any kind of operation list matmul32 took 63 us instead of 49 (pieces of 1,024):
-// four units and lists of uniform phases have builds of their own.
+// A workgroup has 256 threads and 18 KiB of LDS.  Its registers (124 vector registers with
+// two-word keys and up to four units) let four share a CU, as many as a launch has.  Steps to
+// that on matmul32_cu4_s1123, pieces of 1,024 items unless said: loops for any number of units
+// and any kind of operation list 63 us, builds of their own for four units and for uniform
+// phases 49; pieces of 1,536 47; no array indexed by lane in private memory (it was written to
+// HBM, 51 KB for every piece) 45; a window's fields read from LDS where they are used rather
+// than held in scalar registers, which spilled, the next piece's number taken while a piece is
+// explored, and the closures' counts in LDS 38.
 //
 // Each piece stores a word to pinned memory: the steps it adds to a path, which give a
 // counterexample's places and the longest path, and whether a terminal was found, whose clock
@@ -41,18 +45,9 @@ namespace {
 constexpr uint32_t kSetEmpty = 0xFFFFFFFFu;
 constexpr uint32_t kChainBlock = 256;
 
-// A window from LDS, in scalar registers.
-__device__ __forceinline__ ChainWindow load_window(const ChainWindow& s) {
-  static_assert(sizeof(ChainWindow) % 4 == 0, "whole words");
-  union {
-    ChainWindow v;
-    uint32_t w[sizeof(ChainWindow) / 4];
-  } u;
-  const uint32_t* p = reinterpret_cast<const uint32_t*>(&s);
-#pragma unroll
-  for (uint32_t i = 0; i < sizeof(ChainWindow) / 4; ++i) u.w[i] = uniform(p[i]);
-  return u.v;
-}
+typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) u64x2 global_u64x2;  // (a slot of W >= 2 words is
+                                                               // 16-byte aligned)
 
 // Operation ends.  UNIFORM: every configuration of the model has uniform phases and one wave.
 template <bool UNIFORM>
@@ -115,24 +110,43 @@ __device__ __forceinline__ uint32_t list_sets(uint32_t p, uint32_t alive, uint32
   return n;
 }
 
+__device__ __forceinline__ uint32_t unit_speed(const Layout& L, uint32_t u) {
+  return u < L.m ? L.speed[u] : 1u;
+}
+
+constexpr uint32_t kChainSets = 64;  // closure counts held in LDS
+
 struct ChainShared {
   ChainWindow w;
+  uint32_t sets[kChainSets];
+  uint32_t speed[kMaxCU];
   uint32_t whole[kMaxCU];
   uint32_t sets_n;
   uint8_t list[256];
   uint32_t per_set[256];  // new ends of each set
 };
 
-// Fills s.w for [s.w.t0, s.w.t1); every thread calls it.
+// The closures' counts: in LDS where they fit (read by lanes one after another), else the
+// table.
+__device__ __forceinline__ const uint32_t* load_sets(ChainShared& s, const ChainArgs& a) {
+  const uint32_t* table = a.blob + a.sets_at;
+  if (a.lcm >= kChainSets) return table;
+  if (threadIdx.x <= a.lcm) s.sets[threadIdx.x] = table[threadIdx.x];
+  return s.sets;
+}
+
+// Fills s.w for [s.w.t0, s.w.t1); every thread calls it.  x: *xp in scalar registers.
 template <class E>
-__device__ __forceinline__ void fill_window(ChainShared& s, const ChainCfg& x, const ChainEnv& g,
-                                            const E& ends, const ChainTail& tl,
+__device__ __forceinline__ void fill_window(ChainShared& s, const ChainCfg& x,
+                                            const ChainCfg* xp, const ChainEnv& g, const E& ends, const ChainTail& tl,
                                             bool tail, uint32_t interval) {
   const uint32_t tid = threadIdx.x;
+  const uint32_t listed = tail_listed(x, g);
   if (tid < (uint32_t)kMaxCU) {
     uint32_t whole = 0;
-    if (tail) whole = tail_window_unit(s.w, x, g, ends, interval, tid);
-    else chain_window_unit(s.w, x, g, ends, tid);
+    const uint32_t sp = s.speed[tid];
+    if (tail) whole = tail_window_unit(s.w, x, g, ends, interval, tid, sp, (listed >> tid) & 1u);
+    else chain_window_unit(s.w, x, g, ends, tid, sp, xp->unit_off[tid]);
     s.whole[tid] = whole;
   }
   __syncthreads();
@@ -185,10 +199,12 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
   const ChainCfg* cfgs = reinterpret_cast<const ChainCfg*>(a.blob);
   const ChainTail* tails = reinterpret_cast<const ChainTail*>(a.blob + a.tails_at);
   uint32_t next = blockIdx.x;
+  if (tid < (uint32_t)kMaxCU) s.speed[tid] = unit_speed(a.q.L, tid);
   if (tid == 0) {
     sums = RoundRecord{};
     sums.t_first = (uint32_t)__builtin_amdgcn_s_memrealtime();
   }
+  const uint32_t* sets = load_sets(s, a);
   write_roots<W>(a.q, blockIdx.x * kChainBlock + tid, gridDim.x * kChainBlock);
   // sums of a wavefront (uniform in it)
   uint32_t states = 0, edges = 0, probes = 0, max_probe = 0, terms = 0;
@@ -201,7 +217,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
     const uint32_t c = find_cfg(cfgs, a.q.n_cfg, piece);
     const ChainCfg x = load_const(cfgs + c);
     const CfgRec r = load_const(a.q.cfgs + c);
-    const ChainEnv g = chain_env(r, a.q.L.speed, a.q.L.m, a.lcm, a.blob + a.sets_at);
+    const ChainEnv g = chain_env(r, a.q.L.speed, a.q.L.m, a.lcm, sets);
     const DeviceEnds<UNIFORM> ends(r);
     if (tid == 0) {
       uint32_t T = a.q.prune ? a.q.T : kNoClock;
@@ -218,13 +234,17 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
       s_skip = stop || __hip_atomic_load(a.head + kStopWord, __ATOMIC_RELAXED, kScopeAgent) == a.launch;
       s_steps = s_term = 0u;
       next = a.n_pieces;
-      if (a.n_pieces > gridDim.x) next = gridDim.x + (atomicAdd(a.head, 1u) - a.head0);
     }
     __syncthreads();
     const ChainSpan span = chain_span(x, g, piece - x.piece0, uniform(s_T));
     const bool tail = span.tail;
     const ChainTail tl = load_const(tails + (tail ? x.tail0 + span.interval : 0u));
     uint32_t steps = 0;  // of the longest path through the piece (thread 0)
+    bool took = a.n_pieces <= gridDim.x;
+    const auto take = [&] {  // the next piece, while this one is explored
+      if (!took && tid == 0) next = gridDim.x + (atomicAdd(a.head, 1u) - a.head0);
+      took = true;
+    };
     uint32_t from = uniform(s_skip) ? span.t1 : span.t0;
     while (from < span.t1) {
       uint32_t to = span.t1;
@@ -234,7 +254,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
           s.w.t1 = to;
         }
         __syncthreads();
-        fill_window(s, x, g, ends, tl, tail, span.interval);
+        fill_window(s, x, cfgs + c, g, ends, tl, tail, span.interval);
         const uint32_t items = uniform(s.w.items);
         __syncthreads();
         if (items <= kChainCap || to - from == 1u) break;
@@ -247,11 +267,15 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
         s.per_set[tid] = 0u;
       }
       __syncthreads();
+      take();
       // (two loops: the fields of either kind of window fill the scalar registers)
       const auto explore = [&](auto is_tail) {
         constexpr bool kTail = decltype(is_tail)::value;
-        const ChainWindow w = load_window(s.w);
-        const uint32_t items = w.items < kChainCap ? w.items : kChainCap;
+        const ChainWindow& w = s.w;  // (its lanes' fields are read as they are needed: in
+                                     // scalar registers they spilled)
+        const uint32_t w_t0 = uniform(w.t0);
+        const uint32_t w_items = uniform(w.items);
+        const uint32_t items = w_items < kChainCap ? w_items : kChainCap;
         const float per_inv = inverse(w.before[kMaxCU]);
         uint32_t ends_new = 0;
         for (uint32_t base = 0; base < items; base += kChainBlock) {
@@ -266,7 +290,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
           }
           const bool in = base + tid < items, act = in && it.active;
           const uint32_t code = it.t << g.m | it.busy;
-          uint32_t at = probe_start(code, 32u - kChainSetLog2, a.q.hkeep), old = code;
+          uint32_t at = probe_start<0x9E3779B1u>(code, 32u - kChainSetLog2, a.q.hkeep), old = code;
           if (act) old = atomicCAS(&set[at], kSetEmpty, code);
           const unsigned long long acts = __builtin_amdgcn_ballot_w64(act);
           unsigned long long met =
@@ -285,10 +309,19 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
           max_probe = trips > max_probe ? trips : max_probe;
           const bool fresh = act && old == kSetEmpty;
           if (in) {
-            const Key<W> key = key_of<W, M>(it, c, w.t0 + it.t, a.q.L);
+            const Key<W> key = key_of<W, M>(it, c, w_t0 + it.t, a.q.L);
             global_u64* kp = (global_u64*)a.q.table + (unsigned long long)it.slot * W;
+            if constexpr (W == 1) {
+              *kp = fresh ? key.w[0] : kEmptyWord;
+            } else {
 #pragma unroll
-            for (int j = 0; j < W; ++j) kp[j] = fresh ? key.w[j] : kEmptyWord;
+              for (int j = 0; j < W; j += 2) {
+                u64x2 v;
+                v.x = fresh ? key.w[j] : kEmptyWord;
+                v.y = fresh ? key.w[j + 1] : kEmptyWord;
+                *(global_u64x2*)(kp + j) = v;
+              }
+            }
           }
           if (kTail && fresh) atomicAdd(&s.per_set[rank], 1u);
           const unsigned long long news = __builtin_amdgcn_ballot_w64(fresh);
@@ -302,7 +335,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
             terms += (uint32_t)__popcll(over);
             if (__builtin_amdgcn_inverse_ballot_w64(over)) {
               s_term = 1u;
-              if (a.bb) atomicMin(&a.q.ctrl->bound, w.t0 + it.t);
+              if (a.bb) atomicMin(&a.q.ctrl->bound, w_t0 + it.t);
             }
           }
         }
@@ -328,6 +361,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
       from = to;
       __syncthreads();
     }
+    take();
     if (tid == 0) {
       __hip_atomic_store(a.words + piece, (s_steps + steps) | (s_term << 31), __ATOMIC_RELAXED,
                          kScopeSystem);
@@ -367,7 +401,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
 // of its own or, an end of several units, in one of theirs, or the path is bad.
 //
 // It waits for its reads and barriers, window by window.  One workgroup for the whole path took
-// 64 and 71 us on the two models above, a workgroup for each piece 34 and 36, most of it the
+// 64 and 71 us on the two models above, a workgroup for each piece 29 and 30, most of it the
 // tail's intervals, one after another.
 constexpr uint32_t kPathEnds = kChainCap, kChainPathBlock = 512;
 
@@ -379,10 +413,11 @@ __global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, Tra
   __shared__ uint32_t own[kPathEnds + 1], covered[kPathEnds / 32], wave_sums[kChainPathBlock / 64];
   __shared__ uint32_t s_bad, s_set, s_rank;
   const uint32_t tid = threadIdx.x, c = a.q.target, T = a.q.T;
-  const ChainCfg x = load_const(reinterpret_cast<const ChainCfg*>(a.blob) + c);
+  const ChainCfg* xp = reinterpret_cast<const ChainCfg*>(a.blob) + c;
+  const ChainCfg x = load_const(xp);
   const ChainTail* tails = reinterpret_cast<const ChainTail*>(a.blob + a.tails_at);
   const CfgRec r = load_const(a.q.cfgs + c);
-  const ChainEnv g = chain_env(r, a.q.L.speed, a.q.L.m, a.lcm, a.blob + a.sets_at);
+  const ChainEnv g = chain_env(r, a.q.L.speed, a.q.L.m, a.lcm, load_sets(s, a));
   const DeviceEnds<UNIFORM> ends(r);
   const unsigned long long* keys = reinterpret_cast<const unsigned long long*>(a.q.table);
   const auto there = [&](uint32_t slot, const Key<W>& k) {
@@ -400,6 +435,7 @@ __global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, Tra
       else t.out[at] = k.w[w];
     }
   };
+  if (tid < (uint32_t)kMaxCU) s.speed[tid] = unit_speed(a.q.L, tid);
   if (tid == 0) {
     s_bad = 0u;
     s_set = 0x100u;
@@ -420,7 +456,7 @@ __global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, Tra
     uint32_t end = x.K * g.d;
     for (uint32_t u = 0; u < g.m; ++u)
       if (((tid | ~x.idle) >> u) & 1u)
-        end = max(end, tail_start(x, g, u) + g.speed[u] * g.d);
+        end = max(end, tail_start(x, g, s.speed[u]) + s.speed[u] * g.d);
     if (end == T) atomicMin(&s_set, tid);
   }
   __syncthreads();
@@ -446,13 +482,13 @@ __global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, Tra
           s.w.t1 = to;
         }
         __syncthreads();
-        fill_window(s, x, g, ends, tl, tail, interval);
+        fill_window(s, x, xp, g, ends, tl, tail, interval);
         const uint32_t k = uniform(s.w.before[kMaxCU]);
         __syncthreads();
         if (k <= kPathEnds || to - from == 1u) break;
         to = from + (to - from) / 2u;
       }
-      const ChainWindow w = load_window(s.w);
+      const ChainWindow& w = s.w;
       const uint32_t N = w.before[kMaxCU], set = chosen & w.alive;
       if (tid == 0) s_rank = 0u;
       for (uint32_t i = tid; i < (N + 31u) / 32u; i += kChainPathBlock) covered[i] = 0u;
@@ -463,12 +499,12 @@ __global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, Tra
       // unit v's ends before clock `at`, from the window's first on
       const auto ends_to = [&](uint32_t v, uint32_t at) {
         uint32_t k;
-        if (!tail) return ends_before(ends, g, g.speed[v], at) - s.w.first[v];
-        return ends_of_one(ends, g.speed[v], tail_start(x, g, v), w.t0, at, &k);
+        const uint32_t sp = s.speed[v];
+        if (!tail) return ends_before(ends, g, sp, at) - s.w.first[v];
+        return ends_of_one(ends, sp, tail_start(x, g, sp), w.t0, at, &k);
       };
-      const auto counts = [&](uint32_t v) {
-        return tail ? tail_lists(x, g, v) && ((on >> v) & 1u) : ((g.reps >> v) & 1u) != 0u;
-      };
+      const uint32_t counted = tail ? tail_listed(x, g) & on : g.reps;
+      const auto counts = [&](uint32_t v) { return ((counted >> v) & 1u) != 0u; };
       const auto item = [&](uint32_t i, ChainItem* it) {
         if (tail) tail_item<M>(w, x, g, ends, i, rank, set, it);
         else chain_item<M>(w, x, g, ends, r.n, i, it);
@@ -547,11 +583,11 @@ __global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, Tra
           } else {
             uint32_t u = 0, loc = y;
             for (; u + 1u < g.m; ++u) {
-              const uint32_t cnt = div_up(w.k1, g.speed[u]) - div_up(w.k0, g.speed[u]);
+              const uint32_t cnt = div_up(w.k1, s.speed[u]) - div_up(w.k0, s.speed[u]);
               if (loc < cnt) break;
               loc -= cnt;
             }
-            k = (div_up(w.k0, g.speed[u]) + loc) * g.speed[u];
+            k = (div_up(w.k0, s.speed[u]) + loc) * s.speed[u];
             j = bits_set(idle_at(g, k) & ((2u << u) - 1u));
             place = n - total_ends + before(k * g.d + 1u) + starts_between(g, w.k0, k) + j - 1u;
           }

@@ -1092,7 +1092,9 @@ void chain_plan(const ModelHost& h, uint64_t slots, uint64_t target, ChainPlan* 
         v.t1 = (x.K + i + 1u) * r.d;
         ChainTail tl{(uint32_t)at, 0u};
         if (v.t0 < v.t1)
-          for (uint32_t u = 0; u < m; ++u) tl.count += tail_window_unit(v, x, g, ends, i, u);
+          for (uint32_t u = 0; u < m; ++u)
+            tl.count += tail_window_unit(v, x, g, ends, i, u, speed[u],
+                                         (tail_listed(x, g) >> u) & 1u);
         uint64_t n_sets = 0;
         const uint32_t run = x.p ? f : 0u;
         uint32_t alive = 0;
@@ -1114,10 +1116,11 @@ void chain_plan(const ModelHost& h, uint64_t slots, uint64_t target, ChainPlan* 
     items += cfg_slots[c];
     if (slot > slots) return;
   }
-  // As many pieces as the chip holds workgroups, but a piece costs about 10 us beyond its items
-  // (min_time launch, reduction_g256_cu4_s1123: pieces of 256 items 14 us, of 768 12.7, of 2048
-  // 21; its check 20, 9 and 9), and windows fuller than 1,536 of kChainCap are split here and
-  // there (matmul32_cu4_s1123: 1,024 items 49 us, 1,536 44, 2048 49).
+  // As many pieces as the chip holds workgroups, but a piece costs some microseconds beyond its
+  // items, explored or not (reduction_g256_cu4_s1123, min_time and check launches: pieces of
+  // 256 items 12.0 and 15.1 us, of 768 12.2 and 8.7, of 2,048 19.0 and 8.8), and windows fuller
+  // than 1,536 of kChainCap are split here and there (matmul32_cu4_s1123: 1,024 items 41.6 and
+  // 33.5 us, 1,536 37.8 and 25.9, 2,048 38.2 and 23.0).
   if (!target) target = std::min<uint64_t>(1536, std::max<uint64_t>(768, items / 1024));
   target = std::min<uint64_t>(kChainCap, std::max<uint64_t>(32, target));
   uint64_t pieces = 0;

@@ -219,9 +219,12 @@ MC_HD uint32_t state_code(const Piece& v, uint32_t pending, uint32_t busy, uint3
 // the operation times, then -> now: abstract_s1024_np4_cu1 35 (184) -> 25 (27) us,
 // minimum_s1024_np4_cu4 21 (40) -> 19.5 (20), matmul64_cu4 37.5 (42) -> 37.8 (40),
 // matmul128_vw_cu8 246 (320) -> 227 (241).
+// Windows of clocks are lattices that the first multiplier suits better (it is the chain
+// engine's): 1.1 - 2.6 probes against 1.2 - 3.0.
+template <uint32_t MUL = 0xEB91CE37u>
 MC_HD uint32_t probe_start(uint32_t code, uint32_t shift, uint32_t keep) {
-  uint32_t h = code * 0xEB91CE37u;
-  if (keep) h = ((h >> 8) & ((1u << keep) - 1u)) * 0xEB91CE37u;
+  uint32_t h = code * MUL;
+  if (keep) h = ((h >> 8) & ((1u << keep) - 1u)) * MUL;
   return h >> shift;
 }
 

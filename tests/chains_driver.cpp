@@ -125,7 +125,8 @@ int main() {
             w.t1 = to;
             if (s.tail) {
               for (uint32_t u = 0; u < (uint32_t)kMaxCU; ++u)
-                whole[u] = u < h.m ? tail_window_unit(w, x, g, ends, s.interval, u)
+                whole[u] = u < h.m ? tail_window_unit(w, x, g, ends, s.interval, u, g.speed[u],
+                                                      (tail_listed(x, g) >> u) & 1u)
                                    : (w.count[u] = w.first[u] = w.slot[u] = 0u);
               tail_window_rest(w, x, g, tails[x.tail0 + s.interval], s.interval, whole);
               masks.clear();
@@ -136,7 +137,7 @@ int main() {
               w.items = (uint32_t)masks.size() * w.before[kMaxCU];
             } else {
               for (uint32_t u = 0; u < (uint32_t)kMaxCU; ++u)
-                chain_window_unit(w, x, g, ends, u);
+                chain_window_unit(w, x, g, ends, u, g.speed[u], x.unit_off[u]);
               chain_window_rest(w, x, g);
             }
             if (w.items <= kChainCap) break;
