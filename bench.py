@@ -56,15 +56,28 @@ def bytes_per_state(key_bytes: int, r_dup: float) -> float:
     return 2 * LINE_BYTES + 2 * key_bytes + r_dup * LINE_BYTES
 
 
-def algo_bytes_per_state(mc, model, step) -> float:
+def table_bytes_per_state(mc, model, step) -> float:
     """bytes_per_state for the model's key width, with r_dup = duplicate edges of the
     state graph per reachable state (graph_edges), or, on units of unequal speed, the
-    duplicate inserts the run counted."""
+    duplicate inserts the run counted: what the search would move with its visited set in a
+    table in HBM."""
     key_bytes = 8 * mc.mc_describe(model)["key_words"]
     n = step["min_states"]
     edges = graph_edges(mc, model)
     dup = edges - (n - 1) if edges is not None else step["min_dups"]
     return bytes_per_state(key_bytes, dup / n)
+
+
+def algo_bytes_per_state(mc, model) -> float:
+    """Algorithmic HBM bytes per new state of the engines that run: its key, written once to a
+    slot of its own (the visited set's test is in LDS)."""
+    return 8.0 * mc.mc_describe(model)["key_words"]
+
+
+def explorer(model) -> str:
+    """The kernel that explores the model by default."""
+    unequal = model.get("speed") is not None and len(set(model["speed"])) > 1
+    return "k_chains" if unequal else "k_rounds"
 
 
 def _progress(msg: str) -> None:
@@ -73,7 +86,8 @@ def _progress(msg: str) -> None:
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("mc_kernels.hip", "mc_device.h", "mc_launch.h"):
+    for f in ("mc_rounds.hip", "mc_rounds.h", "mc_chains.hip", "mc_chains.h", "mc_device.h",
+              "mc_launch.h"):
         with open(os.path.join(ROOT, "paper_2305_09130_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -302,15 +316,15 @@ def swarm_leg(mc, workloads, names, members: int = 16384, bits_log2: int = 16,
 def units_leg(mc, torch, workloads, reps: int = 5, cpu: bool = True):
     """The paper's own unit models (abstract kernel, Minimum problem; NP elements per
     unit, WG/NP waves) at S = 1024: the same step as the timed one (load + min_time +
-    trace + check(T_min - 1)) on the super-step engine built for general phases, with
+    trace + check(T_min - 1)) on the round engine's build for general phases, with
     its roofline figure and, on the CPU, the oracle on the same step."""
     return model_leg(mc, torch, {k: f() for k, f in workloads.UNIT_WORKLOADS.items()},
                      reps, cpu)
 
 
 def hetero_leg(mc, torch, workloads, reps: int = 5, cpu: bool = True):
-    """Models on units of unequal speed (1, 1, 2, 3): the same step, the general-phase
-    engine with determined ADVANCE chains, and the oracle on the same step."""
+    """Models on units of unequal speed (1, 1, 2, 3): the same step on the chain engine, and
+    the oracle on the same step."""
     return model_leg(mc, torch, workloads.hetero_workloads(), reps, cpu)
 
 
@@ -331,7 +345,7 @@ def model_leg(mc, torch, models: dict, reps: int, cpu: bool):
         del ws
         states = sum(s["states"] for s in steps)
         eng_s = sum(s["engine_ns_min"] for s in steps) * 1e-9 / reps
-        bps = algo_bytes_per_state(mc, model, steps[0])
+        bps = algo_bytes_per_state(mc, model)
         achieved = steps[0]["min_states"] * bps / eng_s / 1e9
         rec = {"kind": model["kind"], "cu": model["m"], "configurations": len(model["params"]),
                "Lg": model["Lg"], "Ll": model["Ll"],
@@ -626,14 +640,14 @@ def main():
     def pct(p):
         return lat[min(len(lat) - 1, int(p * len(lat)))]
 
-    # roofline of the dominant kernel (the persistent super-step engine), per launch:
-    # the min_time launch, timed with HIP events on the query's stream
+    # roofline of the dominant kernel (the exploration), per launch: the min_time launch, from
+    # its first workgroup's start to its last one's end on the device clock
     eng_s = sum(s["engine_ns_min"] for s in steps) * 1e-9 / len(steps)
-    bps = algo_bytes_per_state(mc, model, steps[-1])
+    bps = algo_bytes_per_state(mc, model)
     algo_bytes = steps[-1]["min_states"] * bps
     achieved = algo_bytes / eng_s / 1e9
     src_hash = kernel_source_hash()
-    traffic = read_traffic(args.workload, "k_superstep", src_hash, steps[-1]["slots"])
+    traffic = read_traffic(args.workload, explorer(model), src_hash, steps[-1]["slots"])
 
     legs = set(x for x in args.legs.split(",") if x)
     _progress(f"timed step done: {1e3 * elapsed / args.steps:.3f} ms/step")
@@ -693,14 +707,16 @@ def main():
 
     roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                "kernel": "k_superstep", "launch": "min_time exploration",
+                "kernel": explorer(model), "launch": "min_time exploration",
+                "limited_by": "vector instruction issue",
+                "table_bytes_per_state": table_bytes_per_state(mc, model, steps[-1]),
                 "algo_bytes_per_state": bps, "algo_bytes_per_launch": algo_bytes,
                 "states_per_launch": steps[-1]["min_states"],
                 "avg_launch_ms": eng_s * 1e3, "kernel_source_hash": src_hash,
                 "table_slots": steps[-1]["slots"]}
     if peak:
-        # the measured random-access ceiling: random 64-byte line reads (the granule of
-        # every visited-set touch) and random 64-bit CAS (one per claim)
+        # the measured random-access ceiling, which bounds a visited set in a table in HBM:
+        # random 64-byte line reads and random 64-bit CAS (one per claim)
         roofline["peak_measured"] = peak["random_read_GBps"]
         roofline["frac_measured"] = achieved / peak["random_read_GBps"]
         roofline["states_per_s_launch"] = steps[-1]["min_states"] / eng_s

@@ -130,13 +130,15 @@ typedef struct mc_desc {
                                   workgroup, zero-time closures and lock-step runs
                                   expanded in one super-step; on units alike with one-word
                                   keys, pieces of a configuration's rounds per workgroup,
-                                  each piece's visited states in the workgroup's LDS */
+                                  and for a single model on units of unequal speed windows
+                                  of its clocks, each piece's visited states in the
+                                  workgroup's LDS */
 #define MC_ENGINE_LEVEL 1u     /* plain level-synchronous BFS, one launch per level */
 
 typedef struct mc_opts {
     uint32_t engine;         /* MC_ENGINE_* */
     uint32_t block;          /* threads per workgroup: 256, 512 or 1024 (0 = automatic:
-                                256 where pieces of rounds are explored; else 512 when the
+                                256 where pieces are explored; else 512 when the
                                 query has fewer than 256 partitions, whose critical chains
                                 of inserts then decide the launch time, or when the units
                                 have unequal speeds; else 256) */
@@ -145,19 +147,20 @@ typedef struct mc_opts {
                                 0.375 after rounding the slots up to a power of two, or
                                 0.5 where that passes 2^31 slots) */
     uint32_t grid;           /* persistent workgroups (0 = automatic; at most 1024 where
-                                pieces of rounds are explored) */
+                                pieces are explored) */
     uint32_t batch_items;    /* super-step engine: states generated from one frontier state
                                 before waiting for the visited set (0 = 2 x lanes); unused
-                                where pieces of rounds are explored */
+                                where pieces are explored */
     uint32_t lane_items;     /* keys each thread inserts per round trip: 1 or 2
                                 (else automatic: 2 for keys of up to 128 bits,
-                                1 for wider keys); unused where pieces of rounds are
-                                explored */
+                                1 for wider keys); unused where pieces are explored */
     uint32_t part_states;    /* super-step engine: target states per partition when a
                                 configuration's subgraph is cut into blocks of whole
                                 rounds and its long lock-step runs into run slices (a
                                 round's states j0..j1-1 of every run; 1024..8192 states per
-                                slice) (0 = automatic, UINT32_MAX = never cut) */
+                                slice); where windows of clocks are explored, the states
+                                of a window, 32..2048 (0 = automatic, UINT32_MAX = never
+                                cut, or the widest windows) */
     uint32_t test_hash_bits; /* testing only: 0 = the full key hash; k in 1..24 keeps k
                                 bits of it, so that keys crowd into 2^k probe sequences
                                 (long probe chains, and keys of several words that share
@@ -310,8 +313,10 @@ int mc_simulate(mc_model *h, uint64_t seed, uint32_t *t_end, uint32_t *cfg);
  * (sized for T_ini): a check at or below the largest threshold explored so far is
  * answered from the per-configuration least clocks, a check above it continues that
  * exploration instead of starting over (the repeated verifier runs that Sec. 8 names);
- * st->states is then the number of states explored in all, once each.  Otherwise every
- * check is a fresh mc_check and st->states sums their counts. */
+ * st->states is then the number of states explored in all, once each.  So on units of
+ * unequal speed, where a single model's check above the largest threshold explores its
+ * windows of clocks from the start.  Otherwise every check is a fresh mc_check and
+ * st->states sums their counts. */
 int mc_tune_bisect(mc_model *h, uint64_t seed, uint32_t *t_min, uint32_t *n_checks,
                    mc_stats *st);
 

@@ -52,7 +52,7 @@ constexpr uint32_t kMaxChainIntervals = 1u << 12;  // most intervals of a window
 struct ChainPlan {
   std::vector<uint32_t> blob;
   uint32_t lcm = 0, tails_at = 0, sets_at = 0;  // places in the blob, in words
-  uint64_t used = 0, items = 0, n_pieces = 0;
+  uint64_t used = 0, n_pieces = 0;
   bool uniform = false;  // every configuration has uniform phases back to back in one wave
   bool ok() const { return n_pieces != 0; }
   const ChainCfg* cfgs() const { return reinterpret_cast<const ChainCfg*>(blob.data()); }

@@ -8,6 +8,10 @@
 //                each super-step expands a frontier state's zero-time DISPATCH
 //                closure and the lock-step ADVANCE runs that follow it in one
 //                parallel batch of visited-set inserts
+// Single models explored in pieces (mc_rounds.hip, mc_chains.hip) do not come here; k_superstep
+// takes what those leave: keys of several words on units alike, sets with fewer slots than
+// items, units of unequal speed in a batch, an engine or without pinned memory, and long common
+// periods.
 // The seeded walks (simulation and swarm search) are in mc_walks.hip; the counterexample
 // and the count of a visited set up to a clock in mc_trace.hip.
 #include <hip/hip_runtime.h>

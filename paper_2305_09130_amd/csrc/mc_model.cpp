@@ -1150,7 +1150,6 @@ void chain_plan(const ModelHost& h, uint64_t slots, uint64_t target, ChainPlan* 
     std::memcpy(out->blob.data() + out->tails_at, tails.data(), sizeof(ChainTail) * tails.size());
   std::memcpy(out->blob.data() + out->sets_at, sets.data(), 4 * sets.size());
   out->used = slot;
-  out->items = items;
   out->n_pieces = pieces;
 }
 

@@ -21,8 +21,8 @@
 // those (17 G/s); here a state costs a compare-and-swap in LDS, 8 bytes of a coalesced store
 // and about 90 vector instructions per 64 states, which bound it (the vector units issue in
 // two cycles of three).  min_time launch, k_superstep and its table's clear -> here:
-// matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.228 ms (254 G states/s, 2.0 TB/s of keys
-// written), matmul64_cu4 (5.15M) 0.44 -> 0.035 ms, abstract_s1024_np4_cu1 0.23 -> 0.026 ms,
+// matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.226 ms (257 G states/s, 2.1 TB/s of keys
+// written), matmul64_cu4 (5.15M) 0.44 -> 0.038 ms, abstract_s1024_np4_cu1 0.23 -> 0.025 ms,
 // reduction_g256_cu2 (81k) 45 -> 5 us, 512 uneven instances (185M) 20.0 -> 1.17 ms.
 //
 // The loop over a piece's items was 0.29 ms on matmul128_vw_cu8 with the operation ends and the
