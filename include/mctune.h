@@ -138,7 +138,8 @@ typedef struct mc_desc {
 typedef struct mc_opts {
     uint32_t engine;         /* MC_ENGINE_* */
     uint32_t block;          /* threads per workgroup: 256, 512 or 1024 (0 = automatic:
-                                256 where pieces are explored; else 512 when the
+                                where pieces are explored 256, or 512 for pieces of
+                                rounds of 1,024 items or more; else 512 when the
                                 query has fewer than 256 partitions, whose critical chains
                                 of inserts then decide the launch time, or when the units
                                 have unequal speeds; else 256) */

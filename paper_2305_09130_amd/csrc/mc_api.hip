@@ -530,7 +530,8 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
     q.abort = h->habort;
     q.records = h->records;
     q.host_tc = h->records ? h->tc_host : nullptr;
-    HIPCHK(launch_rounds(s, grid, h->opts.block, q, h->mh.general));
+    HIPCHK(launch_rounds(s, grid, h->opts_in.block ? h->opts.block : rounds_block(piece), q,
+                         h->mh.general));
     ++launches;
     // every piece but the first of each workgroup, and every workgroup's last look, counts one
     if (n_pieces > grid) h->head0 += (uint32_t)n_pieces;

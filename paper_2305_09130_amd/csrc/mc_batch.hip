@@ -189,7 +189,7 @@ struct mc_batch {
   bool ran = false;
   uint64_t max_range16 = 0;  // the largest range of the clear, in 16-byte units
   // models that the round engine explores: their partitions (before the others' in `parts`)
-  uint32_t round_parts = 0, round_pieces = 0, round_piece = 0, round_block = 256;
+  uint32_t round_parts = 0, round_pieces = 0, round_piece = 0, round_block = 0;
   bool round_general = false;
   std::vector<uint8_t> rounds;  // per model
   uint32_t n_other = 0;         // models not explored by it
@@ -221,7 +221,9 @@ int enqueue_query(mc_batch* b) {
     q.log2_set = set_log2(q.piece);
     q.head = b->head + 3;
     const uint32_t grid = b->opts.grid ? b->opts.grid : 1024u;
-    HIPCHK(launch_rounds(s, std::min(grid, q.n_pieces), b->round_block, q, b->round_general));
+    HIPCHK(launch_rounds(s, std::min(grid, q.n_pieces),
+                         b->round_block ? b->round_block : rounds_block(q.piece), q,
+                         b->round_general));
   }
   HIPCHK(hipMemcpyAsync(b->hctrl, b->ws + b->plan.ctrl, kCtrlStride * n, hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync(b->htc, b->ws + b->plan.tc, 4ull * b->tc_words, hipMemcpyDeviceToHost, s));
@@ -343,8 +345,8 @@ int mc_batch_create(const mc_desc* models, uint32_t n, const mc_batch_opts* o, v
       return rc;
     }
     b->opts = default_bopts(o);
-    // the round engine's workgroups are of 256 threads unless asked otherwise
-    b->round_block = o && (o->block == 512 || o->block == 1024) ? o->block : 256u;
+    // the round engine's workgroups are as its pieces want them unless asked otherwise
+    b->round_block = o && (o->block == 256 || o->block == 512 || o->block == 1024) ? o->block : 0u;
     const std::vector<BPart> ps = batch_parts(b->ms, b->opts);
     rc = plan_batch(b->ms, b->opts, ps.size(), &b->plan);
     if (rc) {

@@ -372,7 +372,7 @@ int launch_round_parts(mc_engine* e, uint32_t slice, size_t behind) {
   rq.head = head;
   const uint32_t grid = std::min<uint32_t>(rq.n_pieces, e->opts.grid ? e->opts.grid : 1024u);
   if (rq.n_pieces > grid) HIPCHK(hipMemsetAsync(head, 0, 4, s));
-  HIPCHK(launch_rounds(s, grid, 256u, rq, general));
+  HIPCHK(launch_rounds(s, grid, rounds_block(piece), rq, general));
   ++e->launches;
   return MC_OK;
 }

@@ -176,6 +176,12 @@ inline uint32_t set_log2(uint32_t piece) {
   while ((1u << l) < 2u * piece) ++l;
   return l;
 }
+// Threads per workgroup for pieces of `piece` items, where the caller leaves them open: 512 take
+// a large piece in half the turns, with the same set for twice the wavefronts (min_time launch,
+// 256 -> 512: matmul64_cu4 38 -> 29 us, abstract_s1024_np4_cu4 25.3 -> 21.8,
+// matmul128_vw_cu8 219 -> 210); a small one is over in a few turns, and its barriers cost more
+// (checks of 256 items: 6.3 -> 8.2 us on matmul64_cu4; reduction_g256_cu2 5.3 -> 6.4).
+inline uint32_t rounds_block(uint32_t piece) { return piece >= 1024u ? 512u : 256u; }
 // Counters, clocks, root and SELECT states of one model (its descriptor is written to
 // dst), or of every model of a queue that the round engine explores.
 hipError_t launch_rounds_begin(hipStream_t st, const ModelDev& md, ModelDev* dst,

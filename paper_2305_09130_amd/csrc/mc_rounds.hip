@@ -21,16 +21,16 @@
 // those (17 G/s); here a state costs a compare-and-swap in LDS, 8 bytes of a coalesced store
 // and about 90 vector instructions per 64 states, which bound it (the vector units issue in
 // two cycles of three).  min_time launch, k_superstep and its table's clear -> here:
-// matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.226 ms (257 G states/s, 2.1 TB/s of keys
-// written), matmul64_cu4 (5.15M) 0.44 -> 0.038 ms, abstract_s1024_np4_cu1 0.23 -> 0.025 ms,
+// matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.210 ms (276 G states/s, 2.2 TB/s of keys
+// written), matmul64_cu4 (5.15M) 0.44 -> 0.029 ms, abstract_s1024_np4_cu1 0.23 -> 0.025 ms,
 // reduction_g256_cu2 (81k) 45 -> 5 us, 512 uneven instances (185M) 20.0 -> 1.17 ms.
 //
 // The loop over a piece's items was 0.29 ms on matmul128_vw_cu8 with the operation ends and the
 // places in a round computed from the configuration record for every item, the statistics
 // reduced over the wavefront for every piece, and branches where selects now are.
 //
-// A workgroup has 256 threads and up to 33 KiB of LDS, so that four share a CU: one's lookups
-// and barriers between pieces overlap another's items.  Pieces of half the size ran slower
+// A workgroup has 256 or 512 threads (rounds_block) and up to 33 KiB of LDS, so that four share a
+// CU: one's lookups and barriers between pieces overlap another's items.  Pieces of half the size ran slower
 // (matmul128_vw_cu8 0.40 -> 0.47 ms when measured): a piece costs about 3 us beyond its items.
 //
 // A query of one model is one launch: it writes the root and SELECT states itself and takes its
@@ -254,8 +254,11 @@ __device__ __forceinline__ void write_roots(const ModelDev& md, uint32_t i, uint
 }  // namespace
 
 // ONE: RoundQueue::one (a.launch != 0), else the models of the queue.
+// 512 threads ask for eight waves per SIMD, so that four workgroups share a CU as with 256 (left
+// alone the compiler takes the scalar registers of seven: three workgroups, 219 instead of 210 us
+// on matmul128_vw_cu8).
 template <int BLOCK, bool GEN, bool ONE>
-__global__ __launch_bounds__(BLOCK) void k_rounds(RoundQueue a) {
+__global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 8 : 1) void k_rounds(RoundQueue a) {
   extern __shared__ uint32_t set[];  // 1 << log2_set slots
   __shared__ uint8_t masks[256];     // a partial round's closure sets, by size and value
   __shared__ union {
