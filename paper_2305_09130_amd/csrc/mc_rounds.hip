@@ -19,19 +19,20 @@
 // What bounds it.  k_superstep, which explored these models before, makes one device-scope
 // compare-and-swap per state on a random line of a table in HBM, at the chip's limit for
 // those (17 G/s); here a state costs a compare-and-swap in LDS, 8 bytes of a coalesced store
-// and about 90 vector instructions per 64 states, which bound it (the vector units issue in
-// two cycles of three).  min_time launch, k_superstep and its table's clear -> here:
-// matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.210 ms (276 G states/s, 2.2 TB/s of keys
-// written), matmul64_cu4 (5.15M) 0.44 -> 0.029 ms, abstract_s1024_np4_cu1 0.23 -> 0.025 ms,
-// reduction_g256_cu2 (81k) 45 -> 5 us, 512 uneven instances (185M) 20.0 -> 1.17 ms.
+// and some 125 vector instructions per 64 states, which bound it (the vector units issue in
+// about 85 of 100 cycles that they could).  min_time launch, k_superstep and its table's clear
+// -> here: matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.218 ms (266 G states/s, 2.1 TB/s of
+// keys written), matmul64_cu4 (5.15M) 0.44 -> 0.029 ms, abstract_s1024_np4_cu1 0.23 -> 0.023 ms,
+// reduction_g256_cu2 (81k) 45 -> 5 us, 512 uneven instances (228M) 15.4 -> 1.06 ms.
 //
 // The loop over a piece's items was 0.29 ms on matmul128_vw_cu8 with the operation ends and the
 // places in a round computed from the configuration record for every item, the statistics
 // reduced over the wavefront for every piece, and branches where selects now are.
 //
-// A workgroup has 256 or 512 threads (rounds_block) and up to 33 KiB of LDS, so that four share a
-// CU: one's lookups and barriers between pieces overlap another's items.  Pieces of half the size ran slower
-// (matmul128_vw_cu8 0.40 -> 0.47 ms when measured): a piece costs about 3 us beyond its items.
+// A workgroup has 256 or 512 threads (rounds_block) and up to 33 KiB of LDS, so that four share
+// a CU: one's lookups and barriers between pieces overlap another's items.  Pieces of half the
+// size ran slower (matmul128_vw_cu8 0.40 -> 0.47 ms when measured): a piece costs about 3 us
+// beyond its items.
 //
 // A query of one model is one launch: it writes the root and SELECT states itself and takes its
 // descriptor as an argument, no counter has to be cleared for it, and its pieces' descriptors
