@@ -310,18 +310,18 @@ MC_HD uint32_t tail_units(const ChainCfg& x, const ChainEnv& g) {
 MC_HD uint32_t tail_start(const ChainCfg& x, const ChainEnv& g, uint32_t s) {
   return (x.K - x.K % s) * g.d;
 }
-// The units whose ends are listed in the tails: those of F_K, and of the ones busy at K d the
-// lowest of every speed (which end alike).
+// The units whose ends are listed in the tails: the lowest of every speed.  Those of one speed
+// are all idle at K d or all busy, and end alike.
 MC_HD uint32_t tail_listed(const ChainCfg& x, const ChainEnv& g) {
+  return g.reps & tail_units(x, g);
+}
+// The units of speed s.
+template <int M>
+MC_HD uint32_t units_of_speed(const ChainEnv& g, uint32_t s) {
   uint32_t out = 0;
 #pragma unroll
-  for (uint32_t u = 0; u < (uint32_t)kMaxCU; ++u) {
-    bool first = true;  // (a lower unit of the same speed is busy at K d as u is)
-#pragma unroll
-    for (uint32_t v = 0; v < u; ++v) first = first && g.speed[v] != g.speed[u];
-    out |= first || ((x.idle >> u) & 1u) ? 1u << u : 0u;
-  }
-  return out & tail_units(x, g);
+  for (uint32_t u = 0; u < (uint32_t)M; ++u) out |= u < g.m && g.speed[u] == s ? 1u << u : 0u;
+  return out;
 }
 MC_HD uint32_t tail_from(const ChainCfg& x, const ChainEnv& g, uint32_t interval) {
   return (x.K + interval) * g.d + (interval ? 0u : 1u);
@@ -384,9 +384,10 @@ MC_HD void tail_item(const ChainWindow& w, const ChainCfg& x, const ChainEnv& g,
   it->is_end = true;
   const uint32_t t = (x.K - x.K % s) * g.d + s * ends.at(n);
   it->t = t - w.t0;
-  // an end of a unit of F_K: of one of the set, or the last of one that was started beside it
+  // an end of units of F_K: of one of the set, or the last of one that was started beside it
   const bool chosen = (x.idle >> u) & 1u;
-  it->active = !chosen || ((set >> u) & 1u) || (!((w.alive >> u) & 1u) && bits_set(set) < x.p);
+  it->active = !chosen || (set & units_of_speed<M>(g, s)) != 0u ||
+               (!((w.alive >> u) & 1u) && bits_set(set) < x.p);
   it->pending = 0u;
   it->busy = 0u;
   const uint32_t on = (g.all & ~x.idle) | set;

@@ -503,7 +503,14 @@ __global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, Tra
         if (!tail) return ends_before(ends, g, sp, at) - s.w.first[v];
         return ends_of_one(ends, sp, tail_start(x, g, sp), w.t0, at, &k);
       };
-      const uint32_t counted = tail ? tail_listed(x, g) & on : g.reps;
+      uint32_t counted = g.reps;
+      if (tail) {  // the listed units of whose speed one runs
+        counted = 0u;
+        const uint32_t listed = tail_listed(x, g);
+#pragma unroll
+        for (uint32_t v = 0; v < (uint32_t)M; ++v)
+          if (((listed >> v) & 1u) && (units_of_speed<M>(g, g.speed[v]) & on)) counted |= 1u << v;
+      }
       const auto counts = [&](uint32_t v) { return ((counted >> v) & 1u) != 0u; };
       const auto item = [&](uint32_t i, ChainItem* it) {
         if (tail) tail_item<M>(w, x, g, ends, i, rank, set, it);
