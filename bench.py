@@ -84,10 +84,11 @@ def _progress(msg: str) -> None:
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def kernel_source_hash() -> str:
+def kernel_source_hash(kernel: str) -> str:
+    """Of the files that hold `kernel` (k_rounds, k_chains) and what it is built from."""
     h = hashlib.sha256()
-    for f in ("mc_rounds.hip", "mc_rounds.h", "mc_chains.hip", "mc_chains.h", "mc_device.h",
-              "mc_launch.h"):
+    own = ("mc_chains.hip", "mc_chains.h") if kernel == "k_chains" else ("mc_rounds.hip",)
+    for f in own + ("mc_rounds.h", "mc_device.h", "mc_launch.h"):
         with open(os.path.join(ROOT, "paper_2305_09130_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -646,7 +647,7 @@ def main():
     bps = algo_bytes_per_state(mc, model)
     algo_bytes = steps[-1]["min_states"] * bps
     achieved = algo_bytes / eng_s / 1e9
-    src_hash = kernel_source_hash()
+    src_hash = kernel_source_hash(explorer(model))
     traffic = read_traffic(args.workload, explorer(model), src_hash, steps[-1]["slots"])
 
     legs = set(x for x in args.legs.split(",") if x)
