@@ -464,7 +464,9 @@ int build_model(const mc_desc* d, ModelHost* h, std::string* err) {
     r.dw = (uint32_t)ws.t;
     r.bw = (uint32_t)bw;
     for (uint32_t j = 0; j < ws.nph; ++j)
-      if (r.la[j] || r.t0[j] != (j ? r.t0[j - 1] + r.cnt[j - 1] * r.lat[j - 1] : 0u)) h->general = true;
+      if (r.la[j] || r.t0[j] != (j ? r.t0[j - 1] + r.cnt[j - 1] * r.lat[j - 1] : 0u) ||
+          r.lat[j] >= kLongOperation)
+        h->general = true;
     if (r.waves > 1) h->general = true;
     if (b == 0) return fail(err, "workgroup without timed operations");
     const uint64_t rounds = (n + m - 1) / m;
@@ -1140,7 +1142,8 @@ void chain_plan(const ModelHost& h, uint64_t slots, uint64_t target, ChainPlan* 
   out->uniform = true;
   for (const CfgRec& r : h.cfgs)
     for (uint32_t j = 0, t = 0; j < r.nph; t += r.cnt[j] * r.lat[j], ++j)
-      if (r.waves != 1u || r.la[j] || r.t0[j] != t) out->uniform = false;
+      if (r.waves != 1u || r.la[j] || r.t0[j] != t || r.lat[j] >= kLongOperation)
+        out->uniform = false;
   out->lcm = (uint32_t)lcm;
   out->tails_at = (uint32_t)(sizeof(ChainCfg) / 4 * cfgs.size());
   out->sets_at = out->tails_at + (uint32_t)(2 * tails.size());

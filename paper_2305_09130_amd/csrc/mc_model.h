@@ -24,6 +24,9 @@ constexpr uint32_t kParentNone = 0xFFFFFFFFu;  // no parent recorded (empty slot
 constexpr uint32_t kParentRoot = 0xFFFFFFFEu;  // the root has no parent
 constexpr uint64_t kEmptyWord = ~0ull;         // empty slot (word 0)
 constexpr uint32_t kNoClock = 0xFFFFFFFFu;
+// Operations this long do not fit the 24-bit products that give the ends of uniform phases (a
+// latency is at most 2^20, but the abstract kernel with Lg <= Ll loads a tile in one operation).
+constexpr uint32_t kLongOperation = 1u << 24;
 
 // Packed key layout.  Fields never straddle a 64-bit word; the configuration index
 // sits in the low bits of word 0 and all-ones never encodes a valid configuration,
@@ -92,8 +95,9 @@ struct ModelHost {
   std::vector<CfgRec> cfgs;
   Layout layout{};
   uint32_t m = 0, n_cfg = 0, W = 1;
-  bool general = false;          // some configuration has waves or two-operation periods,
-                                 // or the units have unequal speeds
+  bool general = false;          // some configuration has waves, two-operation periods or
+                                 // operations of kLongOperation cycles, or the units have
+                                 // unequal speeds
   bool hetero = false;           // units of unequal speed (no closed-form counts)
   uint32_t speed[kMaxCU] = {1, 1, 1, 1, 1, 1, 1, 1};
   uint64_t states = 0;           // exact reachable count, root included

@@ -231,8 +231,8 @@ MC_HD uint32_t probe_start(uint32_t code, uint32_t shift, uint32_t keep) {
 // Time left after run state j of a workgroup of a configuration: d - end_at(j), with the
 // phases' terms that do not depend on j taken out of the loop over a piece's items.
 // Uniform phases (one operation per period, back to back, one wave): the end of operation j
-// of a phase is off + j lat.  Products are of 24-bit factors (rounds_model checks b, and
-// lat <= 2^20).
+// of a phase is off + j lat.  Products are of 24-bit factors (rounds_model and chain_plan check
+// b; models with operations of kLongOperation cycles take GeneralEnds).
 struct UniformEnds {
   uint32_t i1, i2, i3;     // first operations of the later phases (none: all-ones)
   uint32_t lat[4], left[4];  // time left = left - j lat

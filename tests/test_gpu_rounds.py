@@ -126,3 +126,27 @@ def test_simulated_rounds(mc, m, speed):
         for seed in range(1, 6):
             assert g.mc_simulate(seed) == oracle.simulate(model, seed), (G, wg, seed)
         g.close()
+
+
+@pytest.mark.parametrize("speeds", [None, [1], [1, 1], [1, 2], [2, 2, 1]])
+def test_operations_of_2_24_cycles_and_more(mc, speeds):
+    """Operation times past 24 bits: clocks, counts up to a clock and every row of a path (the
+    abstract kernel with Lg <= Ll loads a tile of TS items in Lg TS + 1 cycles)."""
+    model = w.unit_model("abstract", 64, 4, len(speeds) if speeds else 2, [1, 2, 4],
+                         [8, 16, 32] if not speeds else [8, 16], 1 << 20, 1 << 20)
+    if speeds and set(speeds) != {1}:
+        model = w.with_speeds(model, speeds)
+    print(f"[gpu] {w.describe(model)} {speeds}", flush=True)
+    r = oracle.explore(model)
+    g = mc.Model(model)
+    assert g.mc_min_time() == (r["t_min"], r["argmin"])
+    assert g.last_stats["states"] == r["reachable"]
+    oracle.check_trace(model, g.mc_trace(), target_clock=r["t_min"], cfgs=r["argmin"])
+    for T in (1 << 24, r["t_min"] // 3, r["t_min"] - 1, r["t_min"], max(r["tc"]) - 1):
+        q = oracle.explore(model, T=T, trace=False)
+        assert g.mc_check(T) == q["violated"], T
+        assert g.last_stats["states"] == q["reachable"], T
+        if q["violated"]:
+            oracle.check_trace(model, g.mc_trace(), max_clock=T)
+    assert g.mc_tune_bisect(1)[0] == r["t_min"]
+    g.close()

@@ -91,3 +91,15 @@ def test_trimmed_plans(driver, target):
         words = line.split()
         assert words[0] == "ok", (line, workloads.describe(case[0]), case[1:])
         assert int(words[1]) == n, (line, n, workloads.describe(case[0]), case[1:])
+
+
+@pytest.mark.parametrize("m", [1, 2])
+def test_operations_of_2_24_cycles_and_more(driver, m):
+    """One operation per phase may last longer than a 24-bit product holds: the abstract kernel
+    with Lg <= Ll loads a tile of TS items in Lg TS + 1 cycles."""
+    models = [workloads.unit_model("abstract", 64, 4, m, [1, 2, 4], [ts], 1 << 20, 1 << 20)
+              for ts in (16, 32)]
+    for model, line in zip(models, driver([(x, 0, 256) for x in models])):
+        words = line.split()
+        assert words[0] == "ok", (line, workloads.describe(model))
+        assert int(words[1]) == cf.summary(model, with_E=False)["reachable"]
