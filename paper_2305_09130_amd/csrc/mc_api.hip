@@ -289,15 +289,6 @@ hipError_t join_side(mc_model* h) {
   return hipStreamWaitEvent(h->stream, h->ev_side, 0);
 }
 
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return true;  // unknown: keep to the one stream
-  }
-  return st != hipStreamCaptureStatusNone;
-}
-
 // Before a query whose visited set has q slots: clears the dirty part of what it needs on
 // the handle's stream (between events ev[0] and ev[1]; *cleared says whether it did), and
 // notes the dirty bytes past what it touches, which finish_query hands to the side stream.
@@ -307,7 +298,7 @@ int prepare_table(mc_model* h, uint64_t q, bool* cleared) {
   const uint64_t need = need_bytes(h, q), touched = touched_bytes(h, q);
   const uint64_t now = std::min<uint64_t>(need, h->dirty_in);
   h->behind_lo = h->behind_hi = 0;
-  if (h->dirty_in > touched && h->side && !capturing(s)) {
+  if (h->dirty_in > touched && h->side) {
     h->behind_lo = touched;
     h->behind_hi = h->dirty_in;
   }
@@ -647,6 +638,9 @@ int run_chains(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb) {
 // smallest first.
 int run_query(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb = false,
               uint32_t T_size = 0) {
+  // every query waits for its stream; refused here, it leaves the handle as it is (a recorded
+  // launch would not run, and the counts that run on from launch to launch would)
+  if (capturing(h->stream)) return MC_E_DEVICE;
   if (h->rounds && h->opts.engine == MC_ENGINE_SUPERSTEP)
     return run_rounds(h, prune, T, st, bb, false);
   if (h->chains && h->opts.engine == MC_ENGINE_SUPERSTEP) return run_chains(h, prune, T, st, bb);
@@ -1008,7 +1002,12 @@ int mc_model_free(mc_model* h) {
   if (h->pooled) {
     // the side stream may still be clearing bytes of the caller's workspace
     if (h->side) (void)hipStreamSynchronize(h->side);
-    if (h->in_flight) (void)hipStreamSynchronize(h->stream);  // it reads the pinned block
+    // the load's upload reads the pinned block: where that cannot be waited for (a capture of
+    // the stream has begun since), the block is not given to another handle
+    if (h->in_flight && (capturing(h->stream) || hipStreamSynchronize(h->stream) != hipSuccess)) {
+      (void)hipGetLastError();
+      h->pin = nullptr;
+    }
     for (auto& e : h->ev)
       if (e) event_put(e);
     if (h->ev_fork) event_put(h->ev_fork);
@@ -1224,6 +1223,7 @@ int bind_model(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes
     const mc_opts opts_in = default_opts(o);
     int rc = prepare_load(d, opts_in, ws_bytes, pooled, &L);
     if (rc) return rc;
+    if (capturing(reinterpret_cast<hipStream_t>(stream))) return MC_E_DEVICE;  // as a query is
     h = new mc_model();
     h->pooled = pooled;
     h->opts_in = opts_in;
@@ -1319,6 +1319,7 @@ int mc_model_reload(mc_model* h, const mc_desc* d) {
     Loaded L;
     const int rc = prepare_load(d, h->opts_in, h->ws_bytes, h->pooled, &L);
     if (rc) return rc;  // the handle keeps its model
+    if (capturing(h->stream)) return MC_E_DEVICE;  // and here
     // the new model's tables go past its visited set: where the side stream is still
     // clearing bytes there, the uploads wait for it (its own queries wait anyway)
     if (h->side_pending && h->side_hi > L.plan.table + L.plan.table_bytes &&

@@ -548,6 +548,8 @@ int mc_engine_submit(mc_engine* e, const mc_desc* model, uint32_t kind, uint32_t
 int mc_engine_step(mc_engine* e, uint32_t* n_active, uint32_t* n_waiting) {
   if (!e) return MC_E_INVAL;
   hipStream_t s = e->stream;
+  // a step waits for the stream: refused before it admits anything, it can be made again
+  if (capturing(s)) return MC_E_DEVICE;
   // ---- admission (arrival order) ----
   struct Start {
     Query* q;

@@ -27,6 +27,17 @@ struct QueryArgs {
   uint32_t target = 0;
 };
 
+// Whether work on the stream would be recorded into a graph instead of run (or, of a stream in
+// an unknown state, might be).  Calls that prepare or wait for work are refused on such a stream.
+inline bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 // Where a counterexample's keys go, terminal first: at most cap of them to `out` (device),
 // the first host_words words of them to `host` instead (pinned memory, or null with 0 words);
 // the target's slot, the path's length and whether it is bad go to host_res[0..2] if given.
