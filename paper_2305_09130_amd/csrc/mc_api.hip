@@ -1071,7 +1071,14 @@ int prepare_load(const mc_desc* d, const mc_opts& opts_in, size_t ws_bytes, bool
   rc = plan_slots(L->mh, L->opts, &slots);
   if (rc) return rc;
   plan_rounds(L->mh, L->opts, slots, &L->rounds);
-  if (L->rounds.parts.empty() && pooled) plan_chains(L->mh, L->opts, slots, &L->chains);
+  if (L->rounds.parts.empty() && pooled) {
+    // a workspace without room for the chain engine's tables may still hold the other's
+    // partitions
+    plan_chains(L->mh, L->opts, slots, &L->chains);
+    rc = plan_ws(L->mh, L->opts, chain_parts(L->chains), &L->plan);
+    if (rc) return rc;
+    if (ws_bytes < L->plan.total) L->chains = ChainPlan{};
+  }
   if (L->rounds.parts.empty() && !L->chains.ok()) L->parts = sorted_parts(model_plan(L->mh, L->opts));
   rc = plan_ws(L->mh, L->opts,
                L->rounds.parts.size() + chain_parts(L->chains) + L->parts.size(), &L->plan);

@@ -104,3 +104,24 @@ def test_stop_request(mc):
     assert e.value.code == mc.MC_E_ABORTED
     assert g.mc_min_time() == (r["t_min"], r["argmin"])
     g.close()
+
+
+def test_workspace_without_room_for_the_tables(mc):
+    """The chain engine's tables can need more room than the partitions of the table engine, for
+    which a workspace was always enough: the least one that is taken holds the latter's."""
+    import torch
+    model = _red(64, 4, [1, 2, 4, 8], [1, 2], [1, 2, 3, 4])
+    model["params"] = model["params"] * 32
+    r = oracle.explore(model, trace=False)
+    n_cfg = len(model["params"])
+    # 80 bytes of table for a configuration, and its tails', against 32 for one partition: taken
+    # uncut (part_states all-ones), so that there is one each
+    cut = dict(part_states=0xFFFFFFFF)
+    full = mc.mc_workspace_bytes(model, mc.make_opts(**cut))
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda:0")
+    for less in (0, 48 * n_cfg // 256 * 256):
+        g = mc.Model(model, workspace=ws[:full - less], **cut)
+        assert g.mc_min_time() == (r["t_min"], r["argmin"]), less
+        assert g.last_stats["states"] == r["reachable"], less
+        oracle.check_trace(model, g.mc_trace(), target_clock=r["t_min"], cfgs=r["argmin"])
+        g.close()
