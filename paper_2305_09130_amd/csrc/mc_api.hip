@@ -1044,7 +1044,7 @@ uint64_t part_target(const ModelHost& mh, const mc_opts& o) {
 // to fill up and say so).
 void plan_rounds(const ModelHost& mh, const mc_opts& o, uint64_t slots, RoundPlan* out) {
   if (!rounds_model(mh)) return;
-  round_plan_largest_first(mh, part_target(mh, o), out);
+  round_plan_largest_first(mh, part_target(mh, o), slots, out);
   if (out->used > slots) {
     *out = RoundPlan{};
     return;

@@ -922,20 +922,26 @@ void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>&
   b.done();
 }
 
-void round_plan_largest_first(const ModelHost& h, uint64_t target, RoundPlan* out) {
+void round_plan_largest_first(const ModelHost& h, uint64_t target, uint64_t slots,
+                              RoundPlan* out) {
   std::vector<uint32_t> order(h.n_cfg);
   std::iota(order.begin(), order.end(), 0u);
   std::sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
     return h.cfg_states[a] != h.cfg_states[b] ? h.cfg_states[a] > h.cfg_states[b] : a < b;
   });
   RoundBuilder b(h, 0u, out);
-  const size_t guess = h.n_cfg + (target ? h.states / target + 1 : 0);
+  // (long rounds and slices make fewer partitions than the target asks for, and a plan that is
+  // found to need more slots than there are may be of any size)
+  const size_t guess =
+      h.n_cfg + (target ? std::min<uint64_t>(h.states / target + 1, 1u << 16) : 0);
   out->parts.reserve(guess);
   out->items.reserve(guess);
   out->end_group.reserve(guess);
-  for (const uint32_t c : order)
+  for (const uint32_t c : order) {
     plan_config(h, c, target, ~0ull, [&](const PartPlan& q) { b.add(q); });
-  b.done();
+    b.done();
+    if (out->used > slots) break;
+  }
 }
 
 void largest_first(RoundPlan* p) {

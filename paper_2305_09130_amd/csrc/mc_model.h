@@ -200,8 +200,10 @@ bool rounds_model(const ModelHost& h);
 // assigned from 1 + n_cfg (the root has slot 0, SELECT(c) slot 1 + c).
 void round_plan(const ModelHost& h, uint32_t model, const std::vector<PartPlan>& plan,
                 RoundPlan* out);
-// The same for plan_parts(h, target), the configurations with most states first.
-void round_plan_largest_first(const ModelHost& h, uint64_t target, RoundPlan* out);
+// The same for plan_parts(h, target), the configurations with most states first; given up after
+// the configuration with which it needs more than `slots` slots.
+void round_plan_largest_first(const ModelHost& h, uint64_t target, uint64_t slots,
+                              RoundPlan* out);
 // Orders a plan's partitions by items, most first.
 void largest_first(RoundPlan* p);
 // The partitions of a plan without the rounds and slices that hold no state with clock in

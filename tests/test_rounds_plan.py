@@ -103,3 +103,24 @@ def test_operations_of_2_24_cycles_and_more(driver, m):
         words = line.split()
         assert words[0] == "ok", (line, workloads.describe(model))
         assert int(words[1]) == cf.summary(model, with_E=False)["reachable"]
+
+
+def test_a_plan_far_larger_than_the_set():
+    """A model of 9 billion states, a set of 2^16 slots and a partition wanted for every state: a
+    check of small T is a use of it, so the load must not fail for want of host memory.  Without
+    a GPU it gets as far as the stream."""
+    import ctypes
+
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("loads into memory that is not there")
+    import paper_2305_09130_amd as mc
+    model = workloads.reduction_model(1 << 24, 8, [4], [1 << 11], 1, 1)
+    model["params"] = model["params"] * 4
+    opts = mc.make_opts(log2_slots=16, part_states=1)
+    need = mc.mc_workspace_bytes(model, opts)
+    desc, keep = mc.make_desc(model)
+    h = ctypes.c_void_p()
+    rc = mc._lib.mc_model_load(ctypes.byref(desc), ctypes.byref(opts), ctypes.c_void_p(256),
+                               ctypes.c_size_t(need), None, ctypes.byref(h))
+    assert rc == mc.MC_E_DEVICE
