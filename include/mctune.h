@@ -93,7 +93,7 @@ extern "C" {
 #define MC_E_NOTFOUND (-9)   /* no such ticket / state */
 #define MC_E_INTERNAL (-10)  /* an internal consistency check failed (a round block of a
                                 configuration did not end on its predicted state) */
-#define MC_E_ABORTED (-11)   /* the query was stopped by mc_abort / mc_batch_abort before
+#define MC_E_ABORTED (-11)   /* the query was stopped by mc_abort before
                                 it finished; it has no result */
 
 /* ---- model descriptor ---------------------------------------------------------- */
@@ -328,11 +328,12 @@ int mc_set_engine(mc_model *h, uint32_t engine);
 /* Asks the query running on h (or, when none runs, the next one started) to stop.  It
  * is the one call that may come from another host thread while a query runs on h: it
  * stores to a pinned host word that the exploration kernels read when a workgroup takes
- * its next partition (super-step engine) or a launch starts (level engine).  Partitions
- * already being explored finish, the rest are skipped, and every kernel exits
+ * the launch's first partition (or piece of one) or a later one 50 microseconds or more
+ * after the word was last read (super-step engine), or a launch starts (level engine).
+ * Partitions already being explored finish, the rest are skipped, and every kernel exits
  * normally; the query then returns MC_E_ABORTED with no result, which consumes the
- * request.  A request made after the exploration kernel has finished stays pending
- * for the next query.  Not a paper operation: it serves callers (servers, test
+ * request.  A request made when no partition is left to take stops nothing and stays
+ * pending for the next query.  Not a paper operation: it serves callers (servers, test
  * harnesses) that must bound a query's time. */
 int mc_abort(mc_model *h);
 

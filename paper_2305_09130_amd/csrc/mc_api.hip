@@ -23,7 +23,7 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
-constexpr size_t kHeadBytes = 4 * (kStopWord + 1);
+constexpr size_t kHeadBytes = 4 * (kWatchWord + 2);
 
 uint64_t next_pow2(uint64_t x) {
   uint64_t p = 1;
@@ -180,8 +180,8 @@ struct mc_model {
   uint32_t q_parts = 0;  // partitions of the last query's launch
   ModelDev* dmd = nullptr;
   unsigned int* head = nullptr;
-  // launches that begin their model themselves (RoundQueue::launch; handles with pinned
-  // memory): the count head stands at, zero after a load, and the last launch's number
+  // the count that head stands at before a launch that begins its model itself
+  // (RoundQueue::self), zero after a load, and the last launch's number
   uint32_t head0 = 0, launch = 0;
   unsigned char* pin = nullptr;  // pooled pinned block: hctrl, hpoll, hmd, tc_host, uploads
   size_t pin_bytes = 0;
@@ -507,7 +507,9 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
   }
   if (n_pieces || self) {
     RoundQueue q;
-    q.launch = self ? next_launch(h) : 0u;
+    q.self = self ? 1u : 0u;
+    q.watch = watch_of(h->head);
+    q.launch = next_launch(h);
     q.head0 = h->head0;
     q.one = md;
     q.models = h->dmd;
@@ -593,6 +595,7 @@ int run_chains(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb) {
   h->q_parts = a.n_pieces;
   const uint32_t grid = std::min<uint32_t>(
       {h->opts.grid ? h->opts.grid : kRoundsGrid, kRoundsGrid, a.n_pieces});
+  a.watch = watch_of(h->head);
   a.launch = next_launch(h);
   a.head0 = h->head0;
   HIPCHK(launch_chains(s, h->mh.W, grid, a));
@@ -737,6 +740,8 @@ int run_query(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb = false
     pq.yielded = nullptr;
     pq.n_yielded = nullptr;
     pq.abort = h->habort;
+    pq.watch = watch_of(h->head);
+    pq.launch = next_launch(h);
     const uint32_t grid =
         h->opts.grid ? h->opts.grid : std::max<uint32_t>(1u, std::min<uint32_t>(n_parts, 4096u));
     HIPCHK(launch_super(s, h->mh.W, grid, h->opts.block, li, pq, h->mh.general, h->mh.hetero));
@@ -846,6 +851,8 @@ int run_resume(mc_model* h, uint32_t T, mc_stats* st) {
     pq.yielded = nullptr;
     pq.n_yielded = nullptr;
     pq.abort = h->habort;
+    pq.watch = watch_of(h->head);
+    pq.launch = next_launch(h);
     const uint32_t grid = h->opts.grid ? h->opts.grid : std::min<uint32_t>(pq.n_parts, 4096u);
     HIPCHK(launch_super(s, h->mh.W, grid, h->opts.block, li, pq, h->mh.general, h->mh.hetero));
     ++launches;
@@ -1201,7 +1208,7 @@ int install(mc_model* h, Loaded& L) {
     e = hipMemcpyAsync(h->cfgs, h->mh.cfgs.data(), cfg_bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
       e = hipMemcpyAsync(h->parts, up_part, part_bytes, hipMemcpyHostToDevice, s);
-    static const unsigned int zeros[kStopWord + 1] = {};
+    static const unsigned int zeros[kHeadBytes / 4] = {};
     if (e == hipSuccess) e = hipMemcpyAsync(h->head, zeros, kHeadBytes, hipMemcpyHostToDevice, s);
   }
   h->head0 = 0u;

@@ -260,6 +260,8 @@ int enqueue_others(mc_batch* b) {
     pq[w].yielded = nullptr;
     pq[w].n_yielded = nullptr;
     pq[w].abort = nullptr;
+    pq[w].watch = nullptr;
+    pq[w].launch = 0u;
   }
   bool general = false, hetero = false;
   for (size_t i = 0; i < b->ms.size(); ++i) {

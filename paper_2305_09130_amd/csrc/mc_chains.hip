@@ -225,13 +225,10 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
         const uint32_t b = __hip_atomic_load(&a.q.ctrl->bound, __ATOMIC_RELAXED, kScopeAgent);
         T = b < T ? b : T;
       }
-      const uint32_t stop = abort_asked(a.abort, piece);
-      if (stop) {
-        __hip_atomic_store(a.head + kStopWord, a.launch, __ATOMIC_RELAXED, kScopeAgent);
-        sums.error = kDevErrAbort;
-      }
+      const uint32_t stop = stop_asked(a.abort, a.watch, a.launch, piece, t0);
+      if (stop) sums.error = kDevErrAbort;
       s_T = T;
-      s_skip = stop || __hip_atomic_load(a.head + kStopWord, __ATOMIC_RELAXED, kScopeAgent) == a.launch;
+      s_skip = stop;
       s_steps = s_term = 0u;
       next = a.n_pieces;
     }

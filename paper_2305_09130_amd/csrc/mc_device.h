@@ -633,14 +633,38 @@ __device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
 // Records the first error of a query (later ones keep it).
 __device__ __forceinline__ void set_error(Ctrl* ctrl, unsigned int e) { atomicCAS(&ctrl->error, 0u, e); }
 
-// The host's stop request, as read by the workgroup that takes item `taken` of a queue.  The
-// word is in host memory and reads of it serialise on the link: one read per partition cost
-// the 644-partition search of matmul32_cu4_s1123 52 us of 684 (the 530-partition one of
-// reduction_g256_cu4_s1123 38 of 263).  One item in 64 reads it, and the rest see the error
-// flag that it sets.
-__device__ __forceinline__ uint32_t abort_asked(const unsigned int* abort, uint32_t taken) {
-  if (!abort || (taken & 63u)) return 0u;
-  return __hip_atomic_load(abort, __ATOMIC_RELAXED, kScopeSystem);
+// The host's stop request, as the workgroup that takes item `taken` of a launch's queue finds
+// it at the device clock given: whether the item is to be skipped.  The word is in host memory,
+// and reads of it serialise on the link: one read per partition cost the 644-partition search of
+// matmul32_cu4_s1123 52 us of 684 (the 530-partition one of reduction_g256_cu4_s1123 38 of 263).
+// So the launch reads it as item 0 is taken and then, whoever takes the next item, once
+// kLookTicks have passed since it was read last: a request is seen by the first workgroup to
+// take an item that long after it.
+// (It was read with one item in 64, which in a launch of few or long items was never.)
+// *watch: the launch's number, the clock of its last look (bit 0 cleared) and, in bit 0, whether
+// it is to stop; another launch's number is one that has not looked yet.
+constexpr int32_t kLookTicks = 5000;  // 50 us of the 100 MHz device clock
+
+__device__ __forceinline__ uint32_t stop_asked(const unsigned int* abort,
+                                               unsigned long long* watch, uint32_t launch,
+                                               uint32_t taken, unsigned long long clock) {
+  if (!abort) return 0u;
+  const uint32_t now = (uint32_t)clock & ~1u;
+  const unsigned long long mark = (unsigned long long)launch << 32 | now;
+  const unsigned long long last = __hip_atomic_load(watch, __ATOMIC_RELAXED, kScopeAgent);
+  const bool ours = (uint32_t)(last >> 32) == launch;
+  const uint32_t stop = ours ? (uint32_t)last & 1u : 0u;
+  const bool due = taken == 0u || (ours && !stop && (int32_t)(now - (uint32_t)last) >= kLookTicks);
+  if (__builtin_expect(!due, 1)) return stop;  // (laid out off the path: 212 -> 208 us of a
+                                               // launch of 14,300 pieces)
+  if (taken == 0u) {
+    __hip_atomic_store(watch, mark, __ATOMIC_RELAXED, kScopeAgent);
+  } else if (atomicCAS(watch, last, mark) != last) {
+    return 0u;  // another workgroup looks
+  }
+  if (!__hip_atomic_load(abort, __ATOMIC_RELAXED, kScopeSystem)) return 0u;
+  __hip_atomic_store(watch, mark | 1u, __ATOMIC_RELAXED, kScopeAgent);
+  return 1u;
 }
 
 // Pointers read from a descriptor carry no address space, and a store through such a pointer

@@ -1502,7 +1502,8 @@ __global__ __launch_bounds__(BLOCK, (HET && BLOCK == 512) ? 4 : 1) void k_supers
       // it concurrently, and every wave must take the same branch around the barriers
       // of the exploration
       bool stop = __hip_atomic_load(&sh.md.ctrl->error, __ATOMIC_RELAXED, kScopeAgent) != 0u;
-      if (!stop && abort_asked(a.abort, part)) {
+      if (!stop && stop_asked(a.abort, a.watch, a.launch, part,
+                              __builtin_amdgcn_s_memrealtime())) {
         set_error(sh.md.ctrl, kDevErrAbort);
         stop = true;
       }

@@ -136,14 +136,20 @@ struct PartQueue {
   unsigned int* n_yielded;
   // host-set stop request (a pinned host word read at system scope), or null: a
   // partition taken after it is set is not explored, so the launch drains quickly and
-  // every workgroup still exits normally
+  // every workgroup still exits normally (with it: where the launch notes its looks at the
+  // word, and the number, not 0, that tells its notes from those of other launches there)
   const unsigned int* abort;
+  unsigned long long* watch;
+  uint32_t launch;
 };
 
-// Place of the stop word behind a queue's head: every workgroup reads it for every piece, on
-// a line of its own, past the head's atomics (next to the head the reads waited for them:
-// matmul128_vw_cu8, 14,300 pieces, 0.22 -> 0.95 ms).
-constexpr uint32_t kStopWord = 64;
+// Place of the watch word (stop_asked; 64 bits) behind a queue's head: every workgroup reads it
+// for every piece, on a line of its own, past the head's atomics (next to the head the reads
+// waited for them: matmul128_vw_cu8, 14,300 pieces, 0.22 -> 0.95 ms).
+constexpr uint32_t kWatchWord = 64;
+inline unsigned long long* watch_of(unsigned int* head) {
+  return reinterpret_cast<unsigned long long*>(head + kWatchWord);
+}
 
 // A launch of the round engine.
 struct RoundQueue {
@@ -154,18 +160,20 @@ struct RoundQueue {
   uint32_t log2_set;    // slots of a piece's hash set, at least twice its items
   uint32_t reverse;     // take the pieces last first
   unsigned int* head;
-  const unsigned int* abort;  // as PartQueue::abort
+  const unsigned int* abort;  // as PartQueue
   // One model, a handle with pinned memory: every workgroup stores its sums here (grid
   // records in host memory) and every terminal its clock in host_tc; else null, and the
   // sums are added to the models' counters and the clocks to ModelDev::tc.
   struct RoundRecord* records;
   uint32_t* host_tc;
-  // With records, and no incumbent to share: the launch begins the model itself.  Its
-  // descriptor, the count that head stands at, and the launch's number, which a workgroup that
-  // sees a stop request writes to head[kStopWord] (0: the model was begun before).
-  uint32_t launch;
+  // With records, and no incumbent to share: the launch begins the model itself (self), by its
+  // descriptor; head0 is the count that head stands at.
+  uint32_t self;
   uint32_t head0;
   ModelDev one;
+  // with abort: as PartQueue
+  unsigned long long* watch;
+  uint32_t launch;
 };
 // One workgroup's sums over a launch (its pieces of one model, where counters are device's):
 // a line of the host's cache.  A set has at most 2^31 slots, so that the counts of items and
@@ -219,8 +227,10 @@ struct ChainArgs {
   uint32_t bb;                // as ModelDev::bb
   uint32_t uniform;           // ChainPlan::uniform
   unsigned int* head;
-  uint32_t launch, head0;     // as RoundQueue
-  const unsigned int* abort;  // as PartQueue::abort
+  uint32_t head0;             // as RoundQueue
+  const unsigned int* abort;  // as PartQueue
+  unsigned long long* watch;
+  uint32_t launch;
   RoundRecord* records;       // a record per workgroup, in pinned memory
   uint32_t* words;            // per piece, in pinned memory: the steps it adds to the longest
                               // path, in bit 31 whether it holds a terminal

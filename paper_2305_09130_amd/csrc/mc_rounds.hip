@@ -254,7 +254,7 @@ __device__ __forceinline__ void write_roots(const ModelDev& md, uint32_t i, uint
 
 }  // namespace
 
-// ONE: RoundQueue::one (a.launch != 0), else the models of the queue.
+// ONE: RoundQueue::one (a.self), else the models of the queue.
 // 512 threads ask for eight waves per SIMD, so that four workgroups share a CU as with 256 (left
 // alone the compiler takes the scalar registers of seven: three workgroups, 219 instead of 210 us
 // on matmul128_vw_cu8).
@@ -311,17 +311,11 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 8 : 1) void k_rounds(RoundQue
         const uint32_t b = __hip_atomic_load(&md.ctrl->bound, __ATOMIC_RELAXED, kScopeAgent);
         T = b < T ? b : T;
       }
-      const uint32_t stop = abort_asked(a.abort, taken);
+      // one read of the flag for the whole workgroup: others set it concurrently
+      const uint32_t stop = stop_asked(a.abort, a.watch, a.launch, taken, t0);
       if (stop) sums.error = kDevErrAbort;
       s_T = T;
-      // one read of the flag for the whole workgroup: others set it concurrently
-      if constexpr (ONE) {
-        if (stop) __hip_atomic_store(a.head + kStopWord, a.launch, __ATOMIC_RELAXED, kScopeAgent);
-        s_skip = stop || __hip_atomic_load(a.head + kStopWord, __ATOMIC_RELAXED, kScopeAgent) == a.launch;
-      } else {
-        if (stop) set_error(md.ctrl, kDevErrAbort);
-        s_skip = stop | __hip_atomic_load(&md.ctrl->error, __ATOMIC_RELAXED, kScopeAgent);
-      }
+      s_skip = stop;
     }
     {
       uint4* s4 = reinterpret_cast<uint4*>(set);
@@ -626,7 +620,7 @@ hipError_t launch_rounds(hipStream_t st, uint32_t grid, uint32_t block, const Ro
   const uint32_t lds = 4u << q.log2_set;
 #define MC_LAUNCH_ROUNDS_(B, G)                                                                \
   do {                                                                                         \
-    if (q.launch) hipLaunchKernelGGL((k_rounds<B, G, true>), dim3(grid), dim3(B), lds, st, q); \
+    if (q.self) hipLaunchKernelGGL((k_rounds<B, G, true>), dim3(grid), dim3(B), lds, st, q); \
     else hipLaunchKernelGGL((k_rounds<B, G, false>), dim3(grid), dim3(B), lds, st, q);         \
   } while (0)
 #define MC_LAUNCH_ROUNDS(B)                 \
