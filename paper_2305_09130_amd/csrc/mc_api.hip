@@ -872,7 +872,7 @@ int trace_w(mc_model* h, uint32_t cfg, uint32_t clock) {
   fields[kFClock] = clock;
   uint64_t words[4];
   encode_key_host(h->mh.layout, fields, words);
-  QueryArgs q = make_args(h, false, 0);
+  const QueryArgs q = make_args(h, false, 0);
   TraceOut t{h->trace_buf, (uint32_t)h->plan.trace_cap};
   if (h->trace_words) {  // pooled handles: paths of up to kTraceWords / W states need no copy
     t.host_words = kTraceWords;
@@ -880,12 +880,10 @@ int trace_w(mc_model* h, uint32_t cfg, uint32_t clock) {
     t.host_res = h->hpoll + 8;
   }
   if (h->on_rounds) {
-    q.tslot = h->tslot;
-    q.target = cfg;
-    HIPCHK(launch_round_path(s, q, t, h->mh.general));
+    HIPCHK(launch_round_path(s, q, h->tslot, cfg, t, h->mh.general));
   } else if (h->on_chains) {
     ChainArgs a = chain_args(h, false, clock);
-    a.q.target = cfg;
+    a.target = cfg;
     // a workgroup per chain piece, or per so many that the places fit where the records were
     const ChainCfg& x = h->cplan.cfgs()[cfg];
     const uint32_t per = (x.windows + kRoundsGrid - 1) / kRoundsGrid;

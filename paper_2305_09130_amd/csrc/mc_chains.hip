@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
 
 // ---- counterexample ---------------------------------------------------------------------
 //
-// The path to a terminal of configuration q.target at clock q.T, root first.  Up to the last
+// The path to a terminal of configuration a.target at clock q.T, root first.  Up to the last
 // dispatches every end of the chain is on it, and of each dispatch the units in index order;
 // then the least set of p units whose tail ends at q.T.  The exploration counted each chain
 // piece's states on the path, so a workgroup knows where its pieces' states go (base[b] for
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(kChainPathBlock) void k_chain_path(ChainArgs a, Tra
   __shared__ ChainShared s;
   __shared__ uint32_t own[kPathEnds + 1], covered[kPathEnds / 32], wave_sums[kChainPathBlock / 64];
   __shared__ uint32_t s_bad, s_set, s_rank;
-  const uint32_t tid = threadIdx.x, c = a.q.target, T = a.q.T;
+  const uint32_t tid = threadIdx.x, c = a.target, T = a.q.T;
   const ChainCfg* xp = reinterpret_cast<const ChainCfg*>(a.blob) + c;
   const ChainCfg x = load_const(xp);
   const ChainTail* tails = reinterpret_cast<const ChainTail*>(a.blob + a.tails_at);

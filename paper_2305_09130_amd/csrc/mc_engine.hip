@@ -959,12 +959,11 @@ int engine_trace_w(mc_engine* e, Resident* r, uint32_t cfg, uint32_t clock,
   int rc = MC_OK;
   Ctrl* hc = reinterpret_cast<Ctrl*>(e->hctrl);
   std::vector<uint64_t> keys;
-  q.tslot = r->rounds ? reinterpret_cast<const uint32_t*>(g + r->seed_off) : nullptr;
-  q.target = cfg;
   const TraceOut to{buf, (uint32_t)cap};
   hipError_t he;
   if (r->rounds) {
-    he = launch_round_path(s, q, to, r->mh.general);
+    he = launch_round_path(s, q, reinterpret_cast<const uint32_t*>(g + r->seed_off), cfg, to,
+                           r->mh.general);
   } else {
     he = launch_find<W>(s, q, reinterpret_cast<const unsigned long long*>(words));
     if (he == hipSuccess) he = launch_chase<W>(s, q, to);

@@ -21,10 +21,6 @@ struct QueryArgs {
   uint32_t T;
   uint32_t max_clock;       // bound of the packed clock field
   uint32_t hkeep;           // bits of the key hash kept (0 = all; testing only)
-  // after the round engine: the terminal's slot per configuration, and the one asked for
-  // (launch_round_path)
-  const uint32_t* tslot = nullptr;
-  uint32_t target = 0;
 };
 
 // Whether work on the stream would be recorded into a graph instead of run (or, of a stream in
@@ -212,8 +208,10 @@ hipError_t launch_rounds_begin_models(hipStream_t st, const ModelDev* models, ui
 // start (refloor 0) are cleared, so that a scan of the set finds only states.
 hipError_t launch_rounds_begin_staged(hipStream_t st, const ModelDev* staged, uint32_t n,
                                       ModelDev* models);
-// The counterexample of configuration q.target after a query on the round engine (q.tslot).
-hipError_t launch_round_path(hipStream_t st, const QueryArgs& q, const TraceOut& t, bool general);
+// The counterexample of configuration `target` after a query on the round engine; tslot: the
+// slot of each configuration's terminal.
+hipError_t launch_round_path(hipStream_t st, const QueryArgs& q, const uint32_t* tslot,
+                             uint32_t target, const TraceOut& t, bool general);
 // general: some configuration has waves or two-operation periods.
 hipError_t launch_rounds(hipStream_t st, uint32_t grid, uint32_t block, const RoundQueue& q,
                          bool general);
@@ -232,11 +230,12 @@ struct ChainArgs {
   unsigned long long* watch;
   uint32_t launch;
   RoundRecord* records;       // a record per workgroup, in pinned memory
+  uint32_t target;            // launch_chain_path: the configuration
   uint32_t* words;            // per piece, in pinned memory: the steps it adds to the longest
                               // path, in bit 31 whether it holds a terminal
 };
 hipError_t launch_chains(hipStream_t st, uint32_t W, uint32_t grid, const ChainArgs& a);
-// The counterexample of configuration q.target that ends at clock q.T, root first, by `grid`
+// The counterexample of configuration a.target that ends at clock q.T, root first, by `grid`
 // workgroups: `per` chain pieces each, the tail the last.  base: the place of the first state of
 // each (device-readable); the caller clears t.host_res[2].
 hipError_t launch_chain_path(hipStream_t st, uint32_t W, const ChainArgs& a, const TraceOut& t,

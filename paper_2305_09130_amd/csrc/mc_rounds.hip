@@ -451,15 +451,16 @@ __global__ __launch_bounds__(256) void k_rounds_begin_models(const ModelDev* mod
 constexpr uint32_t kPathRounds = 256, kPathBlock = 512;
 
 template <bool GEN>
-__global__ __launch_bounds__(kPathBlock) void k_round_path(QueryArgs a, TraceOut t) {
+__global__ __launch_bounds__(kPathBlock) void k_round_path(QueryArgs a, const uint32_t* tslot,
+                                                           uint32_t c, TraceOut t) {
   __shared__ uint32_t end[kPathRounds], leaf[kPathRounds];
   __shared__ uint8_t units[kPathRounds];
   __shared__ uint32_t s_count, s_at, s_bad;
-  const uint32_t tid = threadIdx.x, c = a.target, m = a.L.m, all = (1u << m) - 1u;
+  const uint32_t tid = threadIdx.x, m = a.L.m, all = (1u << m) - 1u;
   const CfgRec r = load_const(a.cfgs + c);
   const unsigned long long* keys = reinterpret_cast<const unsigned long long*>(a.table);
   const uint32_t sp = a.L.shift[kFPending], sm = a.L.shift[kFRem], sr = a.L.shift[kFRem + 1];
-  const uint32_t target = a.tslot[c];
+  const uint32_t target = tslot[c];
   const uint32_t rounds = (r.n + m - 1u) / m, last = r.n - (rounds - 1u) * m;  // units of the last
   const uint32_t per = r.b + m;
   uint32_t n = 0;            // states written
@@ -609,9 +610,11 @@ hipError_t launch_rounds_begin_staged(hipStream_t st, const ModelDev* staged, ui
   return hipGetLastError();
 }
 
-hipError_t launch_round_path(hipStream_t st, const QueryArgs& q, const TraceOut& t, bool general) {
-  if (general) hipLaunchKernelGGL(k_round_path<true>, dim3(1), dim3(kPathBlock), 0, st, q, t);
-  else hipLaunchKernelGGL(k_round_path<false>, dim3(1), dim3(kPathBlock), 0, st, q, t);
+hipError_t launch_round_path(hipStream_t st, const QueryArgs& q, const uint32_t* tslot,
+                             uint32_t target, const TraceOut& t, bool general) {
+  const dim3 one(1), block(kPathBlock);
+  if (general) hipLaunchKernelGGL(k_round_path<true>, one, block, 0, st, q, tslot, target, t);
+  else hipLaunchKernelGGL(k_round_path<false>, one, block, 0, st, q, tslot, target, t);
   return hipGetLastError();
 }
 
