@@ -1588,7 +1588,8 @@ int mc_swarm(mc_model* h, const mc_swarm_opts* o, mc_swarm_result* r) {
   h->swarm_members = 0;
   h->swarm_best = false;
   const SwarmArgs a = swarm_args(h, *o, p);
-  if (!swarm_members_in_lds(o->bits_log2)) HIPCHK(hipMemsetAsync(a.bits, 0, p.total - p.bits, s));
+  if (!swarm_in_lds(o->members, o->bits_log2))
+    HIPCHK(hipMemsetAsync(a.bits, 0, p.total - p.bits, s));
   HIPCHK(ev_record(h->ev[4], s));
   HIPCHK(launch_swarm(s, a));
   HIPCHK(ev_record(h->ev[5], s));

@@ -6,8 +6,6 @@
 //   k_swarm_replay  one member's walk again, state by state (its counterexample)
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-
 #include "mc_launch.h"
 
 namespace mc {
@@ -374,9 +372,12 @@ __device__ __forceinline__ bool swarm_jump(St& x, const CfgRec& r, const SwarmAr
   }
 }
 
-// LDS: the members' bit arrays are in LDS (swarm_members_in_lds), cleared here, else in a.bits.
+// LDS: the members' bit arrays are in LDS (swarm_in_lds), cleared here, else in a.bits.  Four
+// waves per SIMD are asked for: left alone, the build for eight units takes 137 registers, which
+// three share (262,144 members on eight units of eight speeds, walks not counted by interval:
+// 82 -> 60 ms).
 template <int MU, bool LDS>
-__global__ __launch_bounds__(64) void k_swarm(SwarmArgs a) {
+__global__ __launch_bounds__(64, 4) void k_swarm(SwarmArgs a) {
   extern __shared__ uint32_t lds_bits[];
   if constexpr (LDS) {
     const uint32_t n4 = a.lanes << (a.bits_log2 - 7u);  // 16-byte units
@@ -532,14 +533,9 @@ __global__ void k_swarm_replay(SwarmArgs a, Ctrl* ctrl, unsigned long long seed,
 hipError_t launch_swarm(hipStream_t st, const SwarmArgs& a) {
   if (a.seg)
     hipLaunchKernelGGL(k_swarm_segments, dim3(a.n_cfg * a.seg_lcm), dim3(64), 0, st, a);
-  // A member's walks are one serial chain, and a wavefront takes every branch that one of its
-  // members takes: up to 1,024 wavefronts (one per SIMD) hold as few members each as that
-  // allows.  Bit arrays of which four wavefronts' fit in a CU's LDS go there (a lookup in HBM
-  // is a 1-2 us link of the chain), with more wavefronts where there are more members.
   SwarmArgs q = a;
-  const uint32_t spread = std::min<uint32_t>(64u, std::max<uint32_t>(1u, (a.members + 4095u) / 4096u));
-  const uint32_t held = swarm_members_in_lds(a.bits_log2);
-  q.lanes = held ? std::min(spread, held) : spread;
+  q.lanes = swarm_lanes(a.members);
+  const bool held = swarm_in_lds(a.members, a.bits_log2);
   const uint32_t lds = held ? q.lanes << (a.bits_log2 - 3u) : 0u;
   const dim3 grid((a.members + q.lanes - 1u) / q.lanes);
   if (a.m <= 4u) {

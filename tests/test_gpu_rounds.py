@@ -150,3 +150,18 @@ def test_operations_of_2_24_cycles_and_more(mc, speeds):
             oracle.check_trace(model, g.mc_trace(), max_clock=T)
     assert g.mc_tune_bisect(1)[0] == r["t_min"]
     g.close()
+
+
+@pytest.mark.parametrize("speeds", [[1, 2, 3], [8, 7, 6, 5, 4, 3, 2, 1], [64, 63, 61]])
+@pytest.mark.parametrize("members,bits_log2", [(1280, 18), (1281, 18), (4096, 10), (4097, 10), (8193, 13)])
+def test_swarm_sizes(mc, speeds, members, bits_log2):
+    """The largest swarm whose bit arrays are in LDS and the smallest in memory; the largest of
+    one member to a wavefront and the smallest of more."""
+    model = w.with_speeds(w.reduction_model(64, len(speeds), [1, 4], [1, 2], 9, 2), speeds)
+    need = members * (80 + (1 << bits_log2) // 8) + (1 << 20)
+    g = mc.Model(model, log2_slots=(need // 8).bit_length())
+    g.mc_swarm(members, bits_log2, 150, 7, None)
+    want = oracle.swarm(model, 7, members, 150, bits_log2, None)
+    for a, b in zip(g.mc_swarm_members(members), want):
+        assert {k: a[k] for k in KEYS} == {k: b[k] for k in KEYS}
+    g.close()
