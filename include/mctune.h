@@ -346,7 +346,9 @@ int mc_abort(mc_model *h);
  * loads d into the scratch, runs the query on `stream` (a hipStream_t, NULL = null
  * stream), waits for it and returns the results as mc_min_time does (argmin, cap,
  * n_argmin and st likewise; st's timings are host wall-clock only).  MC_E_NOMEM if
- * mc_workspace_bytes(d, o) exceeds MC_STATIC_SCRATCH_BYTES, with nothing run.  Calls
+ * the model's workspace (mc_workspace_bytes(d, o), without the tables of the windows of
+ * clocks, which this call does not explore) exceeds MC_STATIC_SCRATCH_BYTES, with nothing
+ * run.  Calls
  * on one device share its array: calls that overlap on one device (from several host
  * threads or streams) race and must not be made; successive calls are independent
  * (each clears what it reads). */

@@ -23,8 +23,6 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
-constexpr size_t kHeadBytes = 4 * (kWatchWord + 2);
-
 uint64_t next_pow2(uint64_t x) {
   uint64_t p = 1;
   while (p < x) p <<= 1;
@@ -93,8 +91,8 @@ int plan_ws(const ModelHost& mh, const mc_opts& o, uint64_t n_parts, WsPlan* p) 
   p->cfgs = off;   off = align_up(off + sizeof(CfgRec) * mh.n_cfg);
   p->n_parts = n_parts;
   p->order = off;  off = align_up(off + sizeof(Part) * n_parts);
-  p->md = off;     off = align_up(off + sizeof(ModelDev));
-  p->head = off;   off = align_up(off + kHeadBytes);
+  p->md = off;     off = align_up(off + kWatchOff + 8);
+  p->head = off;   off = align_up(off + 4);
   p->seeds = off;  off = align_up(off + sizeof(Seed) * mh.n_cfg);
   p->fcap = mh.frontier_bound + 64;
   p->front0 = off; off = align_up(off + entry * p->fcap);
@@ -180,6 +178,7 @@ struct mc_model {
   uint32_t q_parts = 0;  // partitions of the last query's launch
   ModelDev* dmd = nullptr;
   unsigned int* head = nullptr;
+  unsigned long long* watch = nullptr;  // stop_asked
   // the count that head stands at before a launch that begins its model itself
   // (RoundQueue::self), zero after a load, and the last launch's number
   uint32_t head0 = 0, launch = 0;
@@ -508,7 +507,7 @@ int run_rounds(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb, bool 
   if (n_pieces || self) {
     RoundQueue q;
     q.self = self ? 1u : 0u;
-    q.watch = watch_of(h->head);
+    q.watch = h->watch;
     q.launch = next_launch(h);
     q.head0 = h->head0;
     q.one = md;
@@ -595,7 +594,7 @@ int run_chains(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb) {
   h->q_parts = a.n_pieces;
   const uint32_t grid = std::min<uint32_t>(
       {h->opts.grid ? h->opts.grid : kRoundsGrid, kRoundsGrid, a.n_pieces});
-  a.watch = watch_of(h->head);
+  a.watch = h->watch;
   a.launch = next_launch(h);
   a.head0 = h->head0;
   HIPCHK(launch_chains(s, h->mh.W, grid, a));
@@ -740,7 +739,7 @@ int run_query(mc_model* h, bool prune, uint32_t T, mc_stats* st, bool bb = false
     pq.yielded = nullptr;
     pq.n_yielded = nullptr;
     pq.abort = h->habort;
-    pq.watch = watch_of(h->head);
+    pq.watch = h->watch;
     pq.launch = next_launch(h);
     const uint32_t grid =
         h->opts.grid ? h->opts.grid : std::max<uint32_t>(1u, std::min<uint32_t>(n_parts, 4096u));
@@ -851,7 +850,7 @@ int run_resume(mc_model* h, uint32_t T, mc_stats* st) {
     pq.yielded = nullptr;
     pq.n_yielded = nullptr;
     pq.abort = h->habort;
-    pq.watch = watch_of(h->head);
+    pq.watch = h->watch;
     pq.launch = next_launch(h);
     const uint32_t grid = h->opts.grid ? h->opts.grid : std::min<uint32_t>(pq.n_parts, 4096u);
     HIPCHK(launch_super(s, h->mh.W, grid, h->opts.block, li, pq, h->mh.general, h->mh.hetero));
@@ -1125,6 +1124,7 @@ int install(mc_model* h, Loaded& L) {
   h->parts = reinterpret_cast<Part*>(h->ws + h->plan.order);
   h->dmd = reinterpret_cast<ModelDev*>(h->ws + h->plan.md);
   h->head = reinterpret_cast<unsigned int*>(h->ws + h->plan.head);
+  h->watch = reinterpret_cast<unsigned long long*>(h->ws + h->plan.md + kWatchOff);
   h->seeds = reinterpret_cast<Seed*>(h->ws + h->plan.seeds);
   h->front[0] = h->ws + h->plan.front0;
   h->front[1] = h->ws + h->plan.front1;
@@ -1149,18 +1149,23 @@ int install(mc_model* h, Loaded& L) {
   // one staging block: counters, poll words, descriptor, clocks and, when small, the
   // staging of the uploads below
   static_assert(sizeof(Ctrl) <= 256 && sizeof(ModelDev) <= 256, "staging block layout");
-  const size_t rec_off = 768, trace_off = rec_off + sizeof(RoundRecord) * kRoundsGrid;
+  const size_t rec_off = 768;
+  const size_t trace_off = rec_off + (h->pooled ? sizeof(RoundRecord) * kRoundsGrid : 0u);
   const size_t tc_off = trace_off + (h->pooled ? 8ull * kTraceWords : 0u);
   const size_t up_off = align_up(tc_off + 4ull * h->mh.n_cfg);
   // the records and partitions are staged as they lie in the workspace, for one copy, and
   // after them is room for a query's own partitions
-  const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg, part_bytes = h->chains ? 4 * h->cplan.blob.size() : sizeof(Part) * h->n_parts;
-  // (the descriptor's room and the head's words, which start as zeros, follow)
-  const size_t part_off = h->plan.order - h->plan.cfgs, head_off = h->plan.head - h->plan.cfgs;
-  const size_t up_bytes = head_off + kHeadBytes;
+  const size_t cfg_bytes = sizeof(CfgRec) * h->mh.n_cfg;
+  const size_t part_bytes = h->chains ? 4 * h->cplan.blob.size() : sizeof(Part) * h->n_parts;
+  // (the watch word and the head, which start as zeros, follow one on the other)
+  const size_t part_off = h->plan.order - h->plan.cfgs;
+  constexpr size_t watch_bytes = 8 + 4;
+  const size_t watch_off = h->plan.md + kWatchOff - h->plan.cfgs;
+  const size_t up_bytes = watch_off + watch_bytes;
   const bool stage = up_bytes <= (4u << 20);
   const size_t own_off = align_up(up_off + up_bytes);
-  const size_t pin_bytes = stage ? own_off + part_bytes : up_off;
+  const size_t pin_bytes =
+      !stage ? up_off : h->pooled ? own_off + part_bytes : up_off + up_bytes;
   if (h->in_flight && hipStreamSynchronize(h->stream) != hipSuccess) {  // the last upload's
     (void)hipGetLastError();
     return MC_E_DEVICE;
@@ -1199,15 +1204,15 @@ int install(mc_model* h, Loaded& L) {
   if (stage) {
     std::memcpy(blk + up_off, h->mh.cfgs.data(), cfg_bytes);
     std::memcpy(blk + up_off + part_off, up_part, part_bytes);
-    std::memset(blk + up_off + head_off, 0, kHeadBytes);
-    h->stage_parts = blk + own_off;
+    std::memset(blk + up_off + watch_off, 0, watch_bytes);
+    if (h->pooled) h->stage_parts = blk + own_off;
     e = hipMemcpyAsync(h->cfgs, blk + up_off, up_bytes, hipMemcpyHostToDevice, s);
   } else {
     e = hipMemcpyAsync(h->cfgs, h->mh.cfgs.data(), cfg_bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
       e = hipMemcpyAsync(h->parts, up_part, part_bytes, hipMemcpyHostToDevice, s);
-    static const unsigned int zeros[kHeadBytes / 4] = {};
-    if (e == hipSuccess) e = hipMemcpyAsync(h->head, zeros, kHeadBytes, hipMemcpyHostToDevice, s);
+    static const unsigned char zeros[watch_bytes] = {};
+    if (e == hipSuccess) e = hipMemcpyAsync(h->watch, zeros, watch_bytes, hipMemcpyHostToDevice, s);
   }
   h->head0 = 0u;
   // pinned staging is left alone until the stream is next waited for
@@ -1224,10 +1229,10 @@ int install(mc_model* h, Loaded& L) {
 // are staged in a pooled pinned block, the query is timed with pooled events and dead
 // bytes of the visited set are cleared on a pooled side stream (the ordinary handle);
 // otherwise they are staged in ordinary host memory and no runtime object is created
-// (the handle over the static scratch).
-int bind_model(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes, void* stream,
-               bool pooled, mc_model** out) {
-  if (!out || !dev_ws) return MC_E_INVAL;
+// (the handle over the static scratch, which `room` gives).
+int bind_model(const mc_desc* d, const mc_opts* o, int (*room)(void**), void* dev_ws,
+               size_t ws_bytes, void* stream, bool pooled, mc_model** out) {
+  if (!out || (!dev_ws && !room)) return MC_E_INVAL;
   *out = nullptr;
   mc_model* h = nullptr;
   try {
@@ -1235,6 +1240,7 @@ int bind_model(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes
     const mc_opts opts_in = default_opts(o);
     int rc = prepare_load(d, opts_in, ws_bytes, pooled, &L);
     if (rc) return rc;
+    if (room && (rc = room(&dev_ws)) != MC_OK) return rc;
     if (capturing(reinterpret_cast<hipStream_t>(stream))) return MC_E_DEVICE;  // as a query is
     h = new mc_model();
     h->pooled = pooled;
@@ -1279,12 +1285,12 @@ int bind_model(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes
 
 namespace mc {
 
-int min_time_in_place(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes,
+int min_time_in_place(const mc_desc* d, const mc_opts* o, int (*room)(void**), size_t ws_bytes,
                       void* stream, uint32_t* t_min, uint32_t* argmin, size_t cap,
                       size_t* n_argmin, mc_stats* st) {
   if (!t_min || !n_argmin) return MC_E_INVAL;
   mc_model* h = nullptr;
-  int rc = bind_model(d, o, dev_ws, ws_bytes, stream, false, &h);
+  int rc = bind_model(d, o, room, nullptr, ws_bytes, stream, false, &h);
   if (rc) return rc;
   rc = mc_min_time(h, t_min, argmin, cap, n_argmin, st);
   mc_model_free(h);
@@ -1322,7 +1328,7 @@ int mc_workspace_bytes(const mc_desc* d, const mc_opts* o, size_t* bytes) {
 
 int mc_model_load(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes, void* stream,
                   mc_model** out) {
-  return bind_model(d, o, dev_ws, ws_bytes, stream, true, out);
+  return bind_model(d, o, nullptr, dev_ws, ws_bytes, stream, true, out);
 }
 
 int mc_model_reload(mc_model* h, const mc_desc* d) {

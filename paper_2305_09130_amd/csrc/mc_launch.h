@@ -139,13 +139,12 @@ struct PartQueue {
   uint32_t launch;
 };
 
-// Place of the watch word (stop_asked; 64 bits) behind a queue's head: every workgroup reads it
-// for every piece, on a line of its own, past the head's atomics (next to the head the reads
-// waited for them: matmul128_vw_cu8, 14,300 pieces, 0.22 -> 0.95 ms).
-constexpr uint32_t kWatchWord = 64;
-inline unsigned long long* watch_of(unsigned int* head) {
-  return reinterpret_cast<unsigned long long*>(head + kWatchWord);
-}
+// Place of the watch word (stop_asked): the last of the 256 bytes that a handle's device
+// descriptor has in its workspace.  Every workgroup reads it for every piece, so not on the line
+// of the queue's head, for whose atomics the reads waited (matmul128_vw_cu8, 14,300 pieces, 0.22
+// -> 0.95 ms).
+constexpr size_t kWatchOff = 256 - 8;
+static_assert(sizeof(ModelDev) <= kWatchOff, "the descriptor and the watch word");
 
 // A launch of the round engine.
 struct RoundQueue {

@@ -282,9 +282,10 @@ void encode_key_host(const Layout& L, const uint32_t* fields, uint64_t* words);
 void decode_key_host(const Layout& L, const uint64_t* words, uint32_t* fields,
                      const CfgRec* cfgs);
 
-// min_time of a descriptor over a caller's device workspace, with no pinned staging and
-// no runtime objects created (mc_api.hip): the query path of mc_min_time_static.
-int min_time_in_place(const mc_desc* d, const mc_opts* o, void* dev_ws, size_t ws_bytes,
+// min_time of a descriptor over a device workspace of ws_bytes, which `room` gives once the
+// model is known to fit, with no pinned staging and no runtime objects created (mc_api.hip): the
+// query path of mc_min_time_static.
+int min_time_in_place(const mc_desc* d, const mc_opts* o, int (*room)(void**), size_t ws_bytes,
                       void* stream, uint32_t* t_min, uint32_t* argmin, size_t cap,
                       size_t* n_argmin, mc_stats* st);
 

@@ -51,15 +51,8 @@ extern "C" {
 int mc_min_time_static(const mc_desc* d, const mc_opts* o, void* stream, uint32_t* t_min,
                        uint32_t* argmin, size_t cap, size_t* n_argmin, mc_stats* st) {
   if (!d || !t_min || !n_argmin) return MC_E_INVAL;
-  size_t need = 0;
-  int rc = mc_workspace_bytes(d, o, &need);
-  if (rc) return rc;
-  if (need > kScratchBytes) return MC_E_NOMEM;
-  void* ws = nullptr;
-  rc = scratch_ptr(&ws);
-  if (rc) return rc;
-  return mc::min_time_in_place(d, o, ws, kScratchBytes, stream, t_min, argmin, cap, n_argmin,
-                               st);
+  return mc::min_time_in_place(d, o, scratch_ptr, kScratchBytes, stream, t_min, argmin, cap,
+                               n_argmin, st);
 }
 
 }  // extern "C"

@@ -6,6 +6,7 @@ import os
 import random
 import shutil
 import subprocess
+from types import SimpleNamespace
 
 import pytest
 
@@ -78,3 +79,23 @@ def test_models_left_to_the_other_engine(driver):
     alike = w.with_speeds(w.reduction_model(64, 2, [1], [1], 9, 2), [1, 1])
     long = w.with_speeds(w.reduction_model(64, 3, [1], [1], 9, 2), [64, 63, 61])
     assert driver([(m, 0, 0x7FFFFFFF) for m in (alike, long)]) == ["not a chain-engine model"] * 2
+
+
+@pytest.mark.parametrize("rows,log2_slots", [(9392, 22), (23482, 21)])
+def test_static_scratch_holds_what_it_held(rows, log2_slots):
+    """mc_min_time_static does not explore windows of clocks, so their tables take no room of its
+    scratch: 134,215,936 and 134,217,728 of its 134,217,728 bytes are enough for these models'
+    other tables (the second's to the byte).  Without a GPU a call gets as far as the device."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("a test of the sizes, without a GPU")
+    import paper_2305_09130_amd as mc
+    G = 8 if log2_slots == 22 else 32
+    model = workloads.with_speeds(workloads.reduction_model(G, 8, [1], [1], 9, 2),
+                                  [1, 1, 2, 2] * 2)
+    for n, code in ((rows, mc.MC_E_DEVICE), (rows + 8, mc.MC_E_NOMEM)):
+        with pytest.raises(mc.McError) as e:
+            mc.mc_min_time_static(dict(model, params=model["params"] * n),
+                                  mc.make_opts(log2_slots=log2_slots, part_states=0xFFFFFFFF),
+                                  stream=SimpleNamespace(cuda_stream=0))
+        assert e.value.code == code, n
