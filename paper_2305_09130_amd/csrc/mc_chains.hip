@@ -359,6 +359,9 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
       __syncthreads();
     }
     take();
+    // (crowded sets make more probes over a launch than 32 bits count, a window 2^23 at most)
+    if (lane_id() == 0) atomicAdd(&sums.probes, (unsigned long long)probes);
+    probes = 0;
     if (tid == 0) {
       __hip_atomic_store(a.words + piece, (s_steps + steps) | (s_term << 31), __ATOMIC_RELAXED,
                          kScopeSystem);
@@ -375,7 +378,6 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
     atomicAdd(&sums.states, states);
     atomicAdd(&sums.edges, edges);
     if (terms) atomicAdd(&sums.terms, terms);
-    atomicAdd(&sums.probes, (unsigned long long)probes);
     atomicMax(&sums.max_probe, max_probe);
   }
   __syncthreads();

@@ -107,7 +107,8 @@ struct ItemSums {
   uint32_t states = 0, edges = 0, chunks = 0;
   uint32_t depth = 0;
   uint32_t last = 0;                            // the piece's last item found new (+ 1)
-  uint32_t probes = 0, max_probe = 0;           // of all lanes; of the lane with most
+  uint32_t probes = 0, max_probe = 0;           // of all lanes, in this piece; of the lane with
+                                                // most
   uint32_t terms = 0;                           // per lane
 };
 
@@ -124,7 +125,6 @@ __device__ __forceinline__ void add_sums(RoundRecord& s, ItemSums& w) {
     atomicAdd(&s.states, w.states);
     atomicAdd(&s.edges, w.edges);
     if (terms) atomicAdd(&s.terms, terms);
-    atomicAdd(&s.probes, (unsigned long long)w.probes);
     atomicMax(&s.max_probe, w.max_probe);
     atomicMax(&s.depth, w.depth);
     if (threadIdx.x == 0) s.chunks += w.chunks;
@@ -369,6 +369,9 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 8 : 1) void k_rounds(RoundQue
     // (without a threshold a partition's deepest state is in its last piece)
     if (sum.last && (v.last || T != kNoClock))
       sum.depth = max(sum.depth, uniform(depth_of(v, sum.last - 1u, masks)));
+    // (crowded sets make more probes over a launch than 32 bits count, a piece 2^26 at most)
+    if (lane_id() == 0) atomicAdd(&sums.probes, (unsigned long long)sum.probes);
+    sum.probes = 0;
     if (tid == 0) {
       sums.rounds += v.q1 - v.q0 + 1u;
       sums.pieces += 1u;
