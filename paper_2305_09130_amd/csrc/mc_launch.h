@@ -152,7 +152,7 @@ struct RoundQueue {
   const RoundPart* parts;
   uint32_t n_parts, n_pieces;
   uint32_t piece;       // items per piece
-  uint32_t log2_set;    // slots of a piece's hash set, at least twice its items
+  uint32_t log2_set;    // slots of a piece's hash set: set_log2(piece)
   uint32_t reverse;     // take the pieces last first
   unsigned int* head;
   const unsigned int* abort;  // as PartQueue
@@ -184,7 +184,11 @@ struct RoundRecord {
   uint32_t pad;
 };
 static_assert(sizeof(RoundRecord) == 64, "RoundRecord layout");
-// Least log2 of the slots of a hash set for pieces of `piece` items.
+// Least log2 of the slots of a hash set for pieces of `piece` items: twice as many slots, 512 at
+// least.  A partition's last piece can hold kMaxEndGroup more, the last states of a partial
+// round's runs; it leaves slots free even so, and on a free one every probe sequence ends.
+constexpr uint32_t kMaxEndGroup = 70;  // choices of 4 units of 8
+static_assert(256 + kMaxEndGroup < 512 && kMaxPiece >= 256, "auto_piece gives 256 at least");
 inline uint32_t set_log2(uint32_t piece) {
   uint32_t l = 9;
   while ((1u << l) < 2u * piece) ++l;

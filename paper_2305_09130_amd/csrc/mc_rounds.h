@@ -201,10 +201,53 @@ MC_HD uint32_t mask_rank(uint32_t x, uint32_t all) {
 }
 
 // A state's code in a piece's set: exact on (pending, busy mask, time left), which is all of
-// a state that differs within a piece (rounds_model checks that it fits).
+// a state that differs within a piece (rounds_model checks that it fits).  item_state forms it
+// for an item; this is for checks on the host.
 MC_HD uint32_t state_code(const Piece& v, uint32_t pending, uint32_t busy, uint32_t rem,
                           uint32_t rem_bits) {
   return (pending - v.pmin) << (v.m + rem_bits) | rem << v.m | busy;
+}
+
+// What the states of a piece's items have in common: of configuration c, d cycles long, with keys
+// that hold the pending count at bit sp and the units at bit sm.
+struct ItemBase {
+  uint32_t d, code_shift, sp, sm;
+  uint32_t prel0;   // pending past Piece::pmin before the piece's first round
+  uint32_t clock0;  // that round's clock
+  uint64_t key0;
+};
+
+MC_HD ItemBase item_base(const Piece& v, uint32_t c, uint32_t d, uint32_t rem_bits, uint32_t sp,
+                         uint32_t sm) {
+  ItemBase b;
+  b.d = d;
+  b.code_shift = v.m + rem_bits;
+  b.sp = sp;
+  b.sm = sm;
+  b.prel0 = v.n - (v.r0 + v.q0) * v.m - v.pmin;
+  b.clock0 = (v.r0 + v.q0) * d;
+  b.key0 = (uint64_t)c + ((uint64_t)v.pmin << sp);
+  return b;
+}
+
+struct ItemState {
+  uint32_t rem;    // time left
+  uint32_t prel;   // pending past Piece::pmin
+  uint32_t clock;  // (32 bits, as terminal clocks fit)
+  uint32_t code;
+  uint64_t key;
+};
+
+// An item's state; run: the time left after its run state.
+MC_HD ItemState item_state(const Piece& v, const ItemBase& b, const RoundItem& it, uint32_t run) {
+  ItemState s;
+  s.rem = it.is_cl ? b.d : run;
+  s.prel = b.prel0 - mul24(it.q, v.m) - bits_set(it.mask);
+  s.clock = b.clock0 + it.q * b.d + (b.d - s.rem);
+  const uint32_t low = s.rem << v.m | (s.rem ? it.mask : 0u);
+  s.code = s.prel << b.code_shift | low;
+  s.key = (b.key0 + (uint64_t)s.prel * (1u << b.sp)) + ((uint64_t)low << b.sm);
+  return s;
 }
 
 // Where a code's probe sequence starts in a set of 2^(32 - shift) slots; it goes on 1, 2, 3, ..

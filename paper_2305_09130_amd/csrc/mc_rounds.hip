@@ -11,7 +11,7 @@
 //
 // So a duplicate can only meet its first copy within a partition, and the set that tells new
 // states from found ones need not be shared: a workgroup takes a piece of a partition (at
-// most kMaxPiece generated states), tests each in an open-addressing hash set in LDS and
+// most kMaxPiece generated states, and the last of a partial round's runs), tests each in an open-addressing hash set in LDS and
 // writes the new ones to the partition's own slots of the visited set in HBM, consecutive
 // states to consecutive slots.  The set is exact: it holds the state's (pending, mask, time
 // left), which is all of a state that varies within a piece, in 32 bits.
@@ -98,7 +98,7 @@ __device__ __forceinline__ void flush_sums(Ctrl* ctrl, RoundRecord& s) {
 
 // What the items of a piece need of its model, configuration and query.
 struct ItemEnv {
-  uint32_t c, d, T, refloor, code_shift, sp, sm, set_shift, set_mask, hkeep;
+  uint32_t c, d, T, refloor, rem_bits, sp, sm, set_shift, set_mask, hkeep;
   unsigned long long keys, links;  // addresses of the set's two regions
 };
 
@@ -162,27 +162,19 @@ __device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_i
                                               uint32_t from, uint32_t to, uint32_t* set,
                                               const uint8_t* masks, const Model& model,
                                               uint32_t* host_tc, ItemSums& sum) {
-  const uint32_t prel0 = v.n - (v.r0 + v.q0) * v.m - v.pmin;  // before the piece's first round
-  const uint32_t clock0 = (v.r0 + v.q0) * g.d;
-  const unsigned long long key0 = (unsigned long long)g.c + ((unsigned long long)v.pmin << g.sp);
+  const ItemBase b = item_base(v, g.c, g.d, g.rem_bits, g.sp, g.sm);
   const uint32_t wave = uniform(threadIdx.x & ~63u);
   const Ends ends = in_vector_registers(ends_in);
   for (uint32_t base = from; base < to; base += BLOCK) {
     const uint32_t i = base + threadIdx.x;
     ++sum.chunks;
     const RoundItem it = PART ? part_item(v, i, masks) : full_item(v, i);
-    const uint32_t run = rem_after(ends, it.j), rem = it.is_cl ? g.d : run;
-    const uint32_t prel = prel0 - mul24(it.q, v.m) - bits_set(it.mask);
+    const ItemState x = item_state(v, b, it, rem_after(ends, it.j));
+    const uint32_t code = x.code;
     bool act = i < to;
-    uint32_t clock = 0;
-    if constexpr (CLOCKS) {
-      clock = clock0 + it.q * g.d + (g.d - rem);
-      act = act && clock <= g.T;
-    }
-    // the set: exact on (pending, busy, rem).  It has twice the slots of the piece's states,
-    // so the probe sequence ends (probe_start: why this one)
-    const uint32_t low = rem << v.m | (rem ? it.mask : 0u);
-    const uint32_t code = prel << g.code_shift | low;
+    if constexpr (CLOCKS) act = act && x.clock <= g.T;
+    // the set: exact on (pending, busy, time left).  It has more slots than the piece has
+    // items, so the probe sequence ends (probe_start: why this one)
     uint32_t at = probe_start(code, g.set_shift, g.hkeep), old = code;
     if (act) old = atomicCAS(&set[at], kSetEmpty, code);
     const unsigned long long acts = __builtin_amdgcn_ballot_w64(act);
@@ -197,28 +189,27 @@ __device__ __forceinline__ void explore_items(const Piece& v, const Ends& ends_i
       }
       met &= __builtin_amdgcn_ballot_w64(old != kSetEmpty && old != code);
       sum.probes += (uint32_t)__popcll(met);
-      if (++trips > g.set_mask) break;  // (never: there are more slots than states)
+      if (++trips > g.set_mask) break;  // (never: set_log2)
     }
     sum.max_probe = trips > sum.max_probe ? trips : sum.max_probe;
     bool fresh = act && old == kSetEmpty;
-    const unsigned long long key =
-        (key0 + (unsigned long long)prel * (1u << g.sp)) + ((unsigned long long)low << g.sm);
+    const unsigned long long key = x.key;
     global_u64* kp = (global_u64*)g.keys + it.slot;
     // a continued exploration finds the states below its floor in their slots
     if constexpr (CLOCKS)
-      if (clock < g.refloor && fresh) fresh = *kp != key;
+      if (x.clock < g.refloor && fresh) fresh = *kp != key;
     if (fresh) {
       *kp = key;
       // links, as the counterexample reads them: a round's end to the state its round starts
       // from (parent; none in a run slice) and the leaf its run starts from (jump), a dispatch
       // leaf to its round's start
-      if (rem == 0u || it.is_leaf) {
+      if (x.rem == 0u || it.is_leaf) {
         const ItemLinks l = links_of(v, i, it.q);
-        const unsigned long long hi = rem ? kParentNone : l.leaf;
+        const unsigned long long hi = x.rem ? kParentNone : l.leaf;
         ((global_u64*)g.links)[it.slot] = l.root | hi << 32;
-        if (rem == 0u && prel + v.pmin == 0u) {
+        if (x.rem == 0u && x.prel + v.pmin == 0u) {
           const ModelDev md = model();
-          const uint32_t end = clock0 + it.q * g.d + g.d;
+          const uint32_t end = b.clock0 + it.q * b.d + b.d;  // x.clock, needed here only
           ++sum.terms;
           md.tslot[g.c] = it.slot;
           // (a configuration has one terminal)
@@ -338,12 +329,11 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 8 : 1) void k_rounds(RoundQue
     sum.last = 0;
     if (!uniform(s_skip) && !none) {
       ItemEnv g;
-      const uint32_t rem_bits = 32u - (uint32_t)__clz((int)(r.d + 1u));  // code_rem_bits
       g.c = c;
       g.d = r.d;
       g.T = T;
       g.refloor = md.refloor;
-      g.code_shift = v.m + rem_bits;
+      g.rem_bits = 32u - (uint32_t)__clz((int)(r.d + 1u));  // code_rem_bits
       g.sp = md.L.shift[kFPending];
       g.sm = md.L.shift[kFRem];
       g.set_shift = 32u - a.log2_set;

@@ -124,3 +124,39 @@ def test_a_plan_far_larger_than_the_set():
     rc = mc._lib.mc_model_load(ctypes.byref(desc), ctypes.byref(opts), ctypes.c_void_p(256),
                                ctypes.c_size_t(need), None, ctypes.byref(h))
     assert rc == mc.MC_E_DEVICE
+
+
+@pytest.fixture(scope="module")
+def items_driver(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if not cxx:
+        pytest.skip("no g++")
+    exe = str(tmp_path_factory.mktemp("round_items") / "driver")
+    subprocess.check_call([cxx, "-O2", "-g", "-std=c++17", "-fsanitize=address,undefined",
+                           "-fno-sanitize-recover=all", "-I", CSRC,
+                           os.path.join(ROOT, "tests", "round_items_driver.cpp"),
+                           os.path.join(CSRC, "mc_model.cpp"), "-pthread", "-o", exe])
+
+    def run(cases):
+        text = "\n".join(_line(*c) for c in cases)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True)
+        assert out.returncode == 0, out.stderr[-2000:]
+        return out.stdout.splitlines()
+    return run
+
+
+@pytest.mark.parametrize("target", [0, 32, 2048])
+def test_states_keys_and_links_as_the_kernel_forms_them(items_driver, target):
+    """On whole plans and on trimmed ones, whose partitions start at a later round and link to
+    the end of the one before, which an earlier exploration found."""
+    cases = []
+    for model in _models(70 + target):
+        top = max(c["tc"] for c in cf.per_config(model, with_E=False))
+        cases += [(model, target, 256)] + [
+            (model, target, 256, lo, hi) for lo, hi in (
+                (0, top // 2), (top // 3 + 1, top // 2), (top // 2 + 1, top - 1), (1, top - 1))
+            if lo <= hi]
+    lines = items_driver(cases)
+    assert len(lines) == len(cases)
+    for case, line in zip(cases, lines):
+        assert line.startswith("ok "), (line, workloads.describe(case[0]), case[1:])
