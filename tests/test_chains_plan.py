@@ -99,3 +99,16 @@ def test_static_scratch_holds_what_it_held(rows, log2_slots):
                                   mc.make_opts(log2_slots=log2_slots, part_states=0xFFFFFFFF),
                                   stream=SimpleNamespace(cuda_stream=0))
         assert e.value.code == code, n
+
+
+@pytest.mark.parametrize("target", [0, 32, 2048])
+def test_units_of_one_speed_above_one(driver, target):
+    """All fall idle together, and one unit is listed for all."""
+    cases = []
+    for m, speed in ((1, 5), (2, 2), (3, 3), (4, 2), (8, 3), (8, 64)):
+        for G, wg in ((256, [1, 2, 8]), (16, [2, 4, 16])):  # the second: a last round of a few
+            model = workloads.with_speeds(workloads.reduction_model(G, m, wg, [1, 4], 9, 2),
+                                          [speed] * m)
+            cases += [(model, target, T) for T in (0x7FFFFFFF, 40 * speed, 3000)]
+    for case, line in zip(cases, driver(cases)):
+        assert line.startswith("ok "), (workloads.describe(case[0]), case[1:], line)

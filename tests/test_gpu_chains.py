@@ -125,3 +125,33 @@ def test_workspace_without_room_for_the_tables(mc):
         assert g.last_stats["states"] == r["reachable"], less
         oracle.check_trace(model, g.mc_trace(), target_clock=r["t_min"], cfgs=r["argmin"])
         g.close()
+
+
+@pytest.mark.parametrize("m,speed", [(1, 5), (2, 2), (8, 3)])
+def test_units_of_one_speed_above_one(mc, m, speed):
+    """All fall idle together, with and without a last round of a few."""
+    for G, wg in ((256, [1, 2, 8]), (16, [2, 4, 16])):
+        model = _red(G, m, wg, [1, 4], [speed] * m)
+        r = oracle.explore(model)
+        g = mc.Model(model)
+        assert g.mc_min_time() == (r["t_min"], r["argmin"])
+        assert g.last_stats["states"] == r["reachable"]
+        assert g.mc_terminal_clocks() == r["tc"]
+        oracle.check_trace(model, g.mc_trace(), target_clock=r["t_min"], cfgs=r["argmin"])
+        for T in (r["t_min"] // 2, r["t_min"] - 1, r["t_min"]):
+            q = oracle.explore(model, T=T, trace=False)
+            assert g.mc_check(T) == q["violated"], T
+            assert g.last_stats["states"] == q["reachable"], T
+        assert g.mc_min_time_bb(0) == (r["t_min"], r["argmin"])
+        g.close()
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_trace_after_bisection(mc, name):
+    model, opts = CASES[name]
+    r = oracle.explore(model, trace=False)
+    g = mc.Model(model, **opts)
+    for seed in (1, 2, 3):
+        assert g.mc_tune_bisect(seed)[0] == r["t_min"]
+        oracle.check_trace(model, g.mc_trace(), target_clock=r["t_min"], cfgs=r["argmin"])
+    g.close()

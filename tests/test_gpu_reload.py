@@ -149,3 +149,35 @@ def test_bench_pattern(mc):
         assert g.mc_check(r["t_min"] - 1) is False
         assert g.last_stats["states"] == q["reachable"]
     g.close()
+
+
+def test_reload_across_engines(mc):
+    """One handle taken from models explored in pieces, whose slots are not cleared, to models
+    left to the table (a long common period, a key of two words), whose slots have to be, and
+    back; the last query's states lie where the next model's table is."""
+    w = workloads
+    red = w.reduction_model
+    models = [red(256, 3, [1, 2], [1, 2], 9, 2),                                     # rounds
+              w.with_speeds(red(32, 3, [1, 2], [1], 9, 2), [64, 63, 61]),            # table
+              w.with_speeds(red(128, 4, [1, 2, 4], [1, 2], 9, 2), [1, 1, 2, 3]),     # chains
+              w.with_speeds(red(16, 3, [1, 2], [1], 3, 2), [63, 64, 59]),            # table
+              red(64, 8, [1, 4], [1], 9, 2),                                         # rounds
+              w.with_speeds(red(64, 2, [1, 2], [1], 37, 3), [61, 64])]               # chains
+    refs = [oracle.explore(m, trace=False) for m in models]
+    g = mc.Model(models[0], workspace=_workspace(mc, models))
+    n = len(models)
+    for prev, i in ((a, b) for a in range(n) for b in range(n) if a != b):
+        g.mc_model_reload(models[prev])
+        assert g.mc_min_time() == (refs[prev]["t_min"], refs[prev]["argmin"])
+        assert g.last_stats["states"] == refs[prev]["reachable"]
+        model, ref = models[i], refs[i]
+        g.mc_model_reload(model)
+        for again in range(2):
+            assert g.mc_min_time() == (ref["t_min"], ref["argmin"]), (prev, i)
+            assert g.last_stats["states"] == ref["reachable"], (prev, i)
+        oracle.check_trace(model, g.mc_trace(), target_clock=ref["t_min"],
+                           cfgs=ref["argmin"])
+        q = oracle.explore(model, T=ref["t_min"] - 1, trace=False)
+        assert g.mc_check(ref["t_min"] - 1) is False
+        assert g.last_stats["states"] == q["reachable"], (prev, i)
+    g.close()

@@ -165,3 +165,15 @@ def test_swarm_sizes(mc, speeds, members, bits_log2):
     for a, b in zip(g.mc_swarm_members(members), want):
         assert {k: a[k] for k in KEYS} == {k: b[k] for k in KEYS}
     g.close()
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_trace_after_bisection(mc, name):
+    """Its path crosses states of several continued explorations, each on a trimmed plan."""
+    model, opts = CASES[name]
+    r = oracle.explore(model, trace=False)
+    g = mc.Model(model, **opts)
+    for seed in (1, 2, 3):
+        assert g.mc_tune_bisect(seed)[0] == r["t_min"]
+        oracle.check_trace(model, g.mc_trace(), target_clock=r["t_min"], cfgs=r["argmin"])
+    g.close()
