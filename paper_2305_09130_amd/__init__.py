@@ -125,9 +125,6 @@ class McSwarmMember(ctypes.Structure):
                 ("best_cfg", ctypes.c_uint32), ("first_clock", ctypes.c_uint32),
                 ("first_cfg", ctypes.c_uint32), ("pad", ctypes.c_uint32 * 2)]
 
-    def as_dict(self) -> dict:
-        return {n: int(getattr(self, n)) for n, _ in self._fields_ if n != "pad"}
-
 
 class McQueryResult(ctypes.Structure):
     _fields_ = [("kind", ctypes.c_uint32), ("T", ctypes.c_uint32), ("status", ctypes.c_int),

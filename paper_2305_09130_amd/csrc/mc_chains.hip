@@ -69,20 +69,6 @@ struct DeviceEnds<true> {
   __device__ __forceinline__ uint32_t upto(uint32_t x) const { return ends_upto_uniform(r, x); }
 };
 
-// The configuration that holds piece p: the last whose first piece is at most p.
-__device__ __forceinline__ uint32_t find_cfg(const ChainCfg* cfgs, uint32_t n, uint32_t p) {
-  uint32_t lo = 0, len = n;
-  while (len > 1u) {
-    const uint32_t step = (len + 63u) / 64u, at = lane_id() * step;
-    const bool le = at < len && cfgs[lo + at].piece0 <= p;
-    const uint32_t c = (uint32_t)__popcll(__ballot(le));  // at least one: cfgs[lo]
-    const uint32_t skip = (c - 1u) * step;
-    lo += skip;
-    len = step < len - skip ? step : len - skip;
-  }
-  return uniform(lo);
-}
-
 template <int W, int M>
 __device__ __forceinline__ Key<W> key_of(const ChainItem& it, uint32_t c, uint32_t clock,
                                          const Layout& L) {
@@ -214,7 +200,7 @@ __global__ __launch_bounds__(kChainBlock) void k_chains(ChainArgs a) {
     const uint32_t piece = uniform(s_piece);
     if (piece >= a.n_pieces) break;
     const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-    const uint32_t c = find_cfg(cfgs, a.q.n_cfg, piece);
+    const uint32_t c = find_piece(cfgs, a.q.n_cfg, piece);
     const ChainCfg x = load_const(cfgs + c);
     const CfgRec r = load_const(a.q.cfgs + c);
     const ChainEnv g = chain_env(r, a.q.L.speed, a.q.L.m, a.lcm, sets);

@@ -690,6 +690,22 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
+// The entry of a table that holds piece p: the last of its n whose first piece (piece0) is at
+// most p.  The wavefront looks at 64 entries at a time (3,828 partitions: two steps).
+template <class T>
+__device__ __forceinline__ uint32_t find_piece(const T* table, uint32_t n, uint32_t p) {
+  uint32_t lo = 0, len = n;
+  while (len > 1u) {
+    const uint32_t step = (len + 63u) / 64u, at = lane_id() * step;
+    const bool le = at < len && table[lo + at].piece0 <= p;
+    const uint32_t c = (uint32_t)__popcll(__ballot(le));  // at least one: table[lo]
+    const uint32_t skip = (c - 1u) * step;
+    lo += skip;
+    len = step < len - skip ? step : len - skip;
+  }
+  return uniform(lo);
+}
+
 // splitmix64 (Steele, Lea, Flood 2014)
 __device__ __forceinline__ unsigned long long splitmix64(unsigned long long z) {
   z += 0x9E3779B97F4A7C15ull;

@@ -11,10 +11,11 @@
 //
 // So a duplicate can only meet its first copy within a partition, and the set that tells new
 // states from found ones need not be shared: a workgroup takes a piece of a partition (at
-// most kMaxPiece generated states, and the last of a partial round's runs), tests each in an open-addressing hash set in LDS and
-// writes the new ones to the partition's own slots of the visited set in HBM, consecutive
-// states to consecutive slots.  The set is exact: it holds the state's (pending, mask, time
-// left), which is all of a state that varies within a piece, in 32 bits.
+// most kMaxPiece generated states, and the last of a partial round's runs), tests each in an
+// open-addressing hash set in LDS and writes the new ones to the partition's own slots of the
+// visited set in HBM, consecutive states to consecutive slots.  The set is exact: it holds the
+// state's (pending, mask, time left), which is all of a state that varies within a piece, in 32
+// bits.
 //
 // What bounds it.  k_superstep, which explored these models before, makes one device-scope
 // compare-and-swap per state on a random line of a table in HBM, at the chip's limit for
@@ -53,21 +54,6 @@ namespace mc {
 namespace {
 
 constexpr uint32_t kSetEmpty = 0xFFFFFFFFu;
-
-// The partition that holds piece p: the last whose first piece is at most p.  The wavefront
-// looks at 64 partitions at a time (3,828 partitions: two steps).
-__device__ __forceinline__ uint32_t find_part(const RoundPart* parts, uint32_t n, uint32_t p) {
-  uint32_t lo = 0, len = n;
-  while (len > 1u) {
-    const uint32_t step = (len + 63u) / 64u, at = lane_id() * step;
-    const bool le = at < len && parts[lo + at].piece0 <= p;
-    const uint32_t c = (uint32_t)__popcll(__ballot(le));  // at least one: parts[lo]
-    const uint32_t skip = (c - 1u) * step;
-    lo += skip;
-    len = step < len - skip ? step : len - skip;
-  }
-  return uniform(lo);
-}
 
 // A workgroup's sums, added to its model's counters: for launches over several models, when
 // a piece of another model comes or the launch ends.
@@ -278,7 +264,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 8 : 1) void k_rounds(RoundQue
     if (taken >= a.n_pieces) break;
     const uint32_t piece = a.reverse ? a.n_pieces - 1u - taken : taken;
     const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-    const RoundPart pt = load_const(a.parts + find_part(a.parts, a.n_parts, piece));
+    const RoundPart pt = load_const(a.parts + find_piece(a.parts, a.n_parts, piece));
     const auto get_model = [&] {
       if constexpr (ONE) return a.one;
       else return load_const(a.models + pt.model);

@@ -153,8 +153,7 @@ def test_bench_pattern(mc):
 
 def test_reload_across_engines(mc):
     """One handle taken from models explored in pieces, whose slots are not cleared, to models
-    left to the table (a long common period, a key of two words), whose slots have to be, and
-    back; the last query's states lie where the next model's table is."""
+    left to the table (long common periods), whose slots have to be, and back; the last query's states lie where the next model's table is."""
     w = workloads
     red = w.reduction_model
     models = [red(256, 3, [1, 2], [1, 2], 9, 2),                                     # rounds
