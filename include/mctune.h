@@ -68,7 +68,9 @@
  * hipMalloc'd (or torch-allocated) device addresses; host pointers are ordinary host
  * memory.  A model handle is not thread-safe; separate handles on separate streams
  * may run concurrently.  Query calls are synchronous with respect to the host: they
- * enqueue on the handle's stream and wait for it.
+ * enqueue on the handle's stream and wait for it.  So they cannot be recorded: loads,
+ * queries and engine steps on a stream that is being captured return MC_E_DEVICE, change
+ * nothing and leave the capture going.
  */
 #ifndef MCTUNE_H
 #define MCTUNE_H
@@ -178,7 +180,7 @@ typedef struct mc_stats {
     uint64_t probes;         /* hash-slot probes (engine-specific) */
     uint64_t launches;       /* kernel launches of the exploration */
     uint64_t explore_ns;     /* GPU time of the exploration kernels (HIP events; where pieces
-                                of rounds are explored, from the first workgroup's start to
+                                are explored, from the first workgroup's start to
                                 the last one's end on the device clock) */
     uint64_t total_ns;       /* host wall time of the query call */
     uint64_t clear_ns;       /* GPU time clearing the visited set */
@@ -234,13 +236,16 @@ int mc_config_ends(const mc_desc *d, uint32_t cfg, uint32_t *n, uint32_t *b, uin
  * the caller's workspace and binds the stream.  dev_ws: device memory of ws_bytes
  * bytes owned by the caller, kept alive and left alone until mc_model_free.  stream:
  * hipStream_t (NULL = default stream).  The library owns *out.
- * Every call on the handle is ordered on that stream.  Besides it the handle holds a side
+ * Every call on the handle is ordered on that stream; a load does not wait for it, but d and
+ * its arrays are not read after it returns.  Besides it the handle holds a side
  * stream of its own: a query that needs less of the visited set than earlier queries
  * wrote clears the bytes past its own there, once its results are queued (while the host
  * reads them and loads the next query), so that a later larger query finds them cleared;
  * the handle's stream waits for that clear before it next touches the bytes, and
  * mc_model_free waits for it too.
- * MC_E_NOMEM if ws_bytes < mc_workspace_bytes(); MC_E_DEVICE wraps a HIP error. */
+ * MC_E_NOMEM if the workspace is too small (mc_workspace_bytes() is enough; on units of
+ * unequal speed less may do, where the tables of the windows of clocks are what does not
+ * fit: the model is then explored without them); MC_E_DEVICE wraps a HIP error. */
 int mc_model_load(const mc_desc *d, const mc_opts *o, void *dev_ws, size_t ws_bytes,
                   void *stream, mc_model **out);
 
@@ -251,7 +256,7 @@ int mc_model_load(const mc_desc *d, const mc_opts *o, void *dev_ws, size_t ws_by
  * what earlier queries wrote of what it needs.
  * MC_E_INVAL (bad descriptor) and MC_E_NOMEM (the workspace is too small for d): the
  * handle keeps its model.  MC_E_DEVICE wraps a HIP error; the handle can then only be
- * freed. */
+ * freed (but for a stream under capture, when it keeps its model). */
 int mc_model_reload(mc_model *h, const mc_desc *d);
 
 /* Frees the handle after waiting for its side stream; the workspace is the caller's
@@ -434,16 +439,19 @@ int mc_swarm_trace(mc_model *h, uint32_t *rows, size_t cap, size_t *len);
 typedef struct mc_batch mc_batch;
 
 typedef struct mc_batch_opts {
-    uint32_t block;          /* threads per workgroup: 256, 512, 1024 (0 = 512) */
+    uint32_t block;          /* threads per workgroup: 256, 512, 1024 (0 = 512; for models
+                                explored in pieces of rounds 256, or 512 for pieces of
+                                1,024 items or more) */
     uint32_t grid;           /* persistent workgroups (0 = automatic) */
     float load_factor;       /* visited-set load factor (0 = 0.5) */
     uint32_t chunk;          /* states generated per super-step before waiting for the
-                                visited set (0 = 2 x block x lane_items) */
+                                visited set (0 = 2 x block x lane_items); unused where
+                                pieces are explored */
     uint32_t use_graph;      /* 1: capture the query's launch sequence once in a hipGraph
                                 and replay it (needs a non-null stream: MC_E_INVAL) */
     uint32_t lane_items;     /* keys each thread inserts per round trip: 1 or 2
                                 (else automatic: 2 for keys of up to 128 bits,
-                                1 for wider keys) */
+                                1 for wider keys); unused where pieces are explored */
     uint32_t part_states;    /* target states per partition when a configuration's
                                 subgraph is cut into blocks of whole rounds
                                 (0 = automatic, UINT32_MAX = never cut) */
@@ -504,18 +512,21 @@ typedef struct mc_engine mc_engine;
 typedef struct mc_engine_opts {
     uint32_t max_active;     /* model slots: queries on the device at once (>= 1) */
     uint32_t max_cfg;        /* largest configuration count a query may have (>= 1) */
-    uint32_t block;          /* threads per workgroup: 256, 512, 1024 (0 = 512) */
+    uint32_t block;          /* threads per workgroup: 256, 512, 1024 (0 = 512); a model
+                                explored in pieces of rounds takes 256, or 512 for pieces
+                                of 1,024 items or more, whatever is given */
     uint32_t slice;          /* super-step levels per partition per step while queries
                                 wait for memory (0 = no limit; a model explored in pieces
                                 of rounds: about 65,536 states per level, in whole
                                 partitions); with none waiting a step runs its
                                 partitions to the end */
-    uint32_t chunk;          /* states per super-step batch (0 = 2 x block x lane_items) */
+    uint32_t chunk;          /* states per super-step batch (0 = 2 x block x lane_items);
+                                unused where pieces are explored */
     uint32_t grid;           /* persistent workgroups per step (0 = up to 1024) */
     float load_factor;       /* visited-set load factor (0 = 0.5) */
     uint32_t lane_items;     /* keys each thread inserts per round trip: 1 or 2
                                 (else automatic: 2 for keys of up to 128 bits,
-                                1 for wider keys) */
+                                1 for wider keys); unused where pieces are explored */
     uint32_t part_states;    /* target states per partition when a query's configurations
                                 are cut into blocks of whole rounds (0 = automatic: about
                                 states/256, at most 256 more partitions than

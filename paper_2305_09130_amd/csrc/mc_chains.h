@@ -44,7 +44,8 @@ struct ChainTail {
 
 constexpr uint32_t kChainCap = 2048;       // most items of a window explored at once
 constexpr uint32_t kChainSetLog2 = 12;     // slots of its hash set: twice its items
-constexpr uint32_t kMaxChainPieces = 1u << 15;
+constexpr uint32_t kMaxChainPieces = 1u << 15;  // a word for each goes where a counterexample's
+                                                // keys are staged
 constexpr uint32_t kMaxChainIntervals = 1u << 12;  // most intervals of a window (see quotient)
 
 // Host plan of the chain engine: the device tables as they are uploaded (configurations,
@@ -59,8 +60,12 @@ struct ChainPlan {
 };
 
 // The plan; n_pieces 0 where the chain engine cannot explore the model: units alike, a period
-// of more than kMaxPeriodLcm intervals, clocks of 2^31 or more, fewer than `slots` slots, or a
-// state's place within a window (time, busy units) that does not fit in 32 bits.
+// of more than kMaxPeriodLcm intervals, clocks of 2^31 or more, workgroups of 2^24 operation ends
+// or more, more slots needed than `slots`, a state's place within a window (time, busy units)
+// that does not fit in 32 bits, or more than kMaxChainPieces pieces.  The last leaves the largest
+// models to k_superstep: of 1,536 items each, 32,768 pieces hold some 50 million items
+// (matmul128 on units of speeds 1, 1, 2, 3, 68M states, has 67,492 and takes 19 ms there), and
+// models of many thousand configurations, which need two pieces or more each.
 // target: items per piece (0: chosen).
 void chain_plan(const ModelHost& h, uint64_t slots, uint64_t target, ChainPlan* out);
 

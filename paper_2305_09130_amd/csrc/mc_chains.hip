@@ -15,9 +15,11 @@
 // device-scope compare-and-swap in a table that has to be cleared first.  Here nothing in a
 // piece waits for a state before it: a piece costs its fixed part (its tables, its window's
 // counts and barriers, a chain of dependent reads: 4 us when it is alone, twice that among
-// 1,024) and some hundred vector instructions per 64 states.  min_time launch, k_superstep ->
-// here: reduction_g256_cu4_s1123 (86k states) 229 -> 12 us, matmul32_cu4_s1123 (1.44M) 642 ->
-// 38 us; check one below the optimum 157 -> 9 us and 194 -> 26 us.
+// 1,024) and some 430 vector instructions per 64 states.  min_time launch by kernel trace,
+// k_superstep -> here: reduction_g256_cu4_s1123 (86k states) 267 -> 15 us, matmul32_cu4_s1123
+// (1.44M) 710 -> 45; check one below the optimum 180 -> 13 and 219 -> 27.  The times below, and
+// mc_stats, are from the first workgroup's start to the last one's end on the device clock: 11
+// and 36 us, checks 8 and 25.
 //
 // A workgroup has 256 threads and 18 KiB of LDS.  Its registers (124 vector registers with
 // two-word keys and up to four units) let four share a CU, as many as a launch has.  Steps to

@@ -21,10 +21,14 @@
 // compare-and-swap per state on a random line of a table in HBM, at the chip's limit for
 // those (17 G/s); here a state costs a compare-and-swap in LDS, 8 bytes of a coalesced store
 // and some 125 vector instructions per 64 states, which bound it (the vector units issue in
-// about 85 of 100 cycles that they could).  min_time launch, k_superstep and its table's clear
-// -> here: matmul128_vw_cu8 (58.0M states) 3.89 + 0.38 -> 0.218 ms (266 G states/s, 2.1 TB/s of
-// keys written), matmul64_cu4 (5.15M) 0.44 -> 0.029 ms, abstract_s1024_np4_cu1 0.23 -> 0.023 ms,
-// reduction_g256_cu2 (81k) 45 -> 5 us, 512 uneven instances (228M) 15.4 -> 1.06 ms.
+// about 85 of 100 cycles that they could).  min_time launch by kernel trace, k_superstep (which
+// needs its table cleared besides: 330 us of the first) -> here: matmul128_vw_cu8 (58.0M states)
+// 3,876 -> 226 us, matmul64_cu4 (5.15M) 457 -> 37, abstract_s1024_np4_cu4 280 -> 28,
+// minimum_s1024_np4_cu4 133 -> 23; 512 uneven instances (228M) by HIP events 15.4 -> 1.11 ms.
+// The other times here, and mc_stats, are from the first workgroup's start to the last one's end
+// on the device clock, 7 to 9 us less than the trace has for the same launch: 218 us on
+// matmul128_vw_cu8 within a tuning step (266 G states/s, 2.1 TB/s of keys written) and 209 in a
+// row of queries, 29 on matmul64_cu4.
 //
 // The loop over a piece's items was 0.29 ms on matmul128_vw_cu8 with the operation ends and the
 // places in a round computed from the configuration record for every item, the statistics
