@@ -153,10 +153,12 @@ def test_operations_of_2_24_cycles_and_more(mc, speeds):
 
 
 @pytest.mark.parametrize("speeds", [[1, 2, 3], [8, 7, 6, 5, 4, 3, 2, 1], [64, 63, 61]])
-@pytest.mark.parametrize("members,bits_log2", [(1280, 18), (1281, 18), (4096, 10), (4097, 10), (8193, 13)])
+@pytest.mark.parametrize("members,bits_log2", [(1280, 18), (1281, 18), (4096, 10), (4097, 10), (8193, 13),
+                                               (3, 19), (2, 21), (1, 25)])
 def test_swarm_sizes(mc, speeds, members, bits_log2):
     """The largest swarm whose bit arrays are in LDS and the smallest in memory; the largest of
-    one member to a wavefront and the smallest of more."""
+    one member to a wavefront and the smallest of more; one member's array larger than a
+    quarter of a CU's LDS, and than all of it."""
     model = w.with_speeds(w.reduction_model(64, len(speeds), [1, 4], [1, 2], 9, 2), speeds)
     need = members * (80 + (1 << bits_log2) // 8) + (1 << 20)
     g = mc.Model(model, log2_slots=(need // 8).bit_length())
