@@ -866,6 +866,7 @@ int run_resume(mc_model* h, uint32_t T, mc_stats* st) {
 template <int W>
 int trace_w(mc_model* h, uint32_t cfg, uint32_t clock) {
   hipStream_t s = h->stream;
+  if (capturing(s)) return MC_E_DEVICE;
   uint32_t fields[kFields] = {0};
   fields[kFCfg] = cfg;
   fields[kFClock] = clock;
@@ -1502,6 +1503,7 @@ int mc_trace(mc_model* h, uint32_t* rows, size_t cap, size_t* len) {
 int mc_simulate(mc_model* h, uint64_t seed, uint32_t* t_end, uint32_t* cfg) {
   if (!h || !t_end || !cfg) return MC_E_INVAL;
   hipStream_t s = h->stream;
+  if (capturing(s)) return MC_E_DEVICE;
   const QueryArgs q = make_args(h, false, 0);
   HIPCHK(launch_simulate(s, q, seed));
   HIPCHK(hipMemcpyAsync(h->hpoll, &h->ctrl->sim_t, 8, hipMemcpyDeviceToHost, s));
@@ -1586,6 +1588,7 @@ int mc_swarm(mc_model* h, const mc_swarm_opts* o, mc_swarm_result* r) {
   const SwarmPlan p = swarm_plan(h, o->members, o->bits_log2);
   if (p.total > h->plan.table_bytes) return MC_E_NOMEM;
   hipStream_t s = h->stream;
+  if (capturing(s)) return MC_E_DEVICE;
   // the region is no longer a visited set
   HIPCHK(join_side(h));
   h->dirty_in = std::max<uint64_t>(h->dirty_in, std::min<uint64_t>(p.total, h->max_need));
@@ -1686,6 +1689,7 @@ int mc_swarm_trace(mc_model* h, uint32_t* rows, size_t cap, size_t* len) {
   if (!h || !len) return MC_E_INVAL;
   if (!h->swarm_best) return MC_E_STATE;
   hipStream_t s = h->stream;
+  if (capturing(s)) return MC_E_DEVICE;
   // the rows go after the last swarm's member records, over its bit arrays
   mc_swarm_opts o{};
   o.members = h->swarm_members;

@@ -514,6 +514,7 @@ int mc_batch_min_time(mc_batch* b, uint32_t* t_min, uint64_t* states, mc_stats* 
   if (!b) return MC_E_INVAL;
   const auto t0 = std::chrono::steady_clock::now();
   hipStream_t s = b->stream;
+  if (capturing(s)) return MC_E_DEVICE;  // (it waits for the stream)
   HIPCHK(hipEventRecord(b->ev[0], s));
   if (b->exec) {
     HIPCHK(hipGraphLaunch(b->exec, s));

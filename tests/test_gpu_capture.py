@@ -60,6 +60,10 @@ def test_model(mc, kind):
                 _refused(mc, g.mc_min_time)
                 _refused(mc, lambda: g.mc_min_time_bb(0))
                 _refused(mc, lambda: g.mc_check(5))
+                _refused(mc, lambda: g.mc_simulate(1))
+                _refused(mc, lambda: g.mc_tune_bisect(1))
+                _refused(mc, lambda: g.mc_swarm(4, 10, 100, 1))
+                _refused(mc, lambda: mc.mc_min_time_static(model, stream=stream))
             for k in range(2):
                 assert g.mc_min_time() == (r["t_min"], r["argmin"])
                 assert g.last_stats["states"] == r["reachable"]
@@ -69,6 +73,29 @@ def test_model(mc, kind):
         stream.synchronize()
         assert x.tolist() == [2.0] * 4
         g.close()
+
+
+def test_batch(mc):
+    import torch
+    models = [w.reduction_model(64, 3, [1, 2], [1, 2], 9, 2),
+              w.with_speeds(w.reduction_model(64, 3, [1, 2], [1, 2], 9, 2), [1, 2, 3])]
+    refs = [oracle.explore(m, trace=False) for m in models]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        b = mc.Batch(models)
+        x = torch.zeros(4, device="cuda:0")
+        stream.synchronize()
+        for before in range(2):
+            graph = torch.cuda.CUDAGraph()
+            with _capture(graph):
+                x.add_(1)
+                _refused(mc, b.mc_batch_min_time)
+            assert b.mc_batch_min_time() == ([r["t_min"] for r in refs],
+                                             [r["reachable"] for r in refs])
+            graph.replay()
+        stream.synchronize()
+        assert x.tolist() == [2.0] * 4
+        b.close()
 
 
 def test_engine_step(mc):
