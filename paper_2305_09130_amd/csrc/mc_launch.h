@@ -338,20 +338,19 @@ struct SwarmArgs {
 // Members per wavefront of a swarm.  A member's walks are one serial chain, and a wavefront takes
 // every branch that one of its members takes: 4,096 wavefronts (four per SIMD, as many as their
 // registers let share one) hold as few members each as that allows.  Fewer wavefronts leave SIMDs
-// waiting for one chain, more take turns (walks not counted by interval:
-// 16,384 members on eight units of eight speeds in 1,024 wavefronts 41 ms, in 4,096 27; 8,192
-// members on three units of a long period 73 and 56, in 8,192 wavefronts 43, but 65,536 on them
-// 96, 101 and 125).
+// waiting for one chain, more take turns (walks not counted by interval: 16,384 members on eight
+// units of eight speeds in 1,024 wavefronts 41 ms, in 4,096 27; 8,192 members on three units of a
+// long period 73 and 56, in 8,192 wavefronts 43, but 65,536 on them 96, 101 and 125).
 inline uint32_t swarm_lanes(uint32_t members) {
   const uint32_t n = members / 4096u + (members % 4096u ? 1u : 0u);
   return n < 64u ? n : 64u;
 }
 // Whether the members' bit arrays of 2^bits_log2 bits are held in LDS: where a wavefront's fit in
 // a quarter of a CU's 160 KiB, and those of the whole swarm in the chip's 256 CUs at once (else
-// SwarmArgs::bits is used, and cleared before the launch).  A lookup in memory is a 1-2 us link of a walk's chain, but wavefronts that
-// wait for LDS cost more: 16,384 members of 8 KiB on matmul32_cu4_s1123 5.7 ms in LDS, 3.5 in
-// memory, with a long period 121 and 67 ms; 4,096 of them 2.3 and 2.5, on units alike 1.8 and 2.0
-// (2,048 members).
+// SwarmArgs::bits is used, and cleared before the launch).  A lookup in memory is a 1-2 us link
+// of a walk's chain, but wavefronts that wait for LDS cost more: 16,384 members of 8 KiB on
+// matmul32_cu4_s1123 5.7 ms in LDS, 3.5 in memory, with a long period 121 and 67 ms; 4,096 of
+// them 2.3 and 2.5, on units alike 1.8 and 2.0 (2,048 members).
 inline bool swarm_in_lds(uint32_t members, uint32_t bits_log2) {
   const uint32_t log2_bytes = bits_log2 - 3u;
   return (unsigned long long)swarm_lanes(members) << log2_bytes <= 40u << 10 &&
